@@ -340,8 +340,8 @@ int moc_search_cuts(const moc_graph* g, int64_t B, int32_t* starts, int32_t* end
  * max_cuts steps as in moc_search_cuts, with the moves of moc_eval_cuts_keep.
  * Phase 2 (the paper's Phase 2 minimises the duration, Eq. (1), from a solution
  * within the budget): max_merges times, the merge moves of the candidate are
- * written out as candidates of their own, evaluated by moc_eval_batch, and the
- * best one is applied in place.  A merge move exists for every live copy c that
+ * scored with what moc_eval_batch would return for the edited candidate, and
+ * the best one is applied in place.  A merge move exists for every live copy c that
  * has a live copy of its node below it (lower copy index); it switches c off
  * and keeps the nearest such copy until the later of the two ends: the node is
  * computed once less and its output held across the gap.  Only the first K
@@ -352,12 +352,12 @@ int moc_search_cuts(const moc_graph* g, int64_t B, int32_t* starts, int32_t* end
  *   starts, ends, active   device, [B][T], edited in place
  *   K                      >= 1, merge moves per candidate and step
  *   work_best              device, moc_best_move [B], 8-byte aligned
- *   work_starts, work_ends device, int32 [B*K][T]      workspaces of Phase 2
- *   work_active            device, uint8 [B*K][T]      (may be NULL when
- *   work_list              device, int32 [B*K]          max_merges == 0)
- *   work_results           device, moc_result [B*K], 8-byte aligned
+ *   work_starts, work_ends, work_active, work_list (4-byte aligned),
+ *   work_results (8-byte aligned)
+ *                          asked for when max_merges > 0, neither read nor
+ *                          written: any device pointers of that alignment
  *   out_cuts, out_merges   device, int32 [B]: moves applied in each phase
- * Queues 2 * max_cuts + 4 * max_merges + 2 kernels and returns; allocates
+ * Queues 2 * max_cuts + 3 kernels and returns; allocates
  * nothing.  Limits as moc_eval_cuts; B * K <= 2^31 - 1.
  * Errors: MOC_EINVAL, MOC_EDEVICE, MOC_EOVERFLOW, MOC_EHIP.
  */

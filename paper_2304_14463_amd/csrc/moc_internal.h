@@ -93,6 +93,11 @@ int moc_eval_prepare(const moc_graph* g);
 // moc_eval_batch_noalloc; once per device.
 int moc_eval_static_setup(int device);
 
+// The second phase of moc_search_two_phase: queues the kernel that applies up to max_steps merges
+// to each of the B candidates (one workgroup each) and writes how many it applied to out_merges.
+int moc_queue_merges(const moc_graph* g, int64_t B, int32_t* starts, int32_t* ends, uint8_t* active, int max_steps,
+                     int K, int32_t* out_merges, hipStream_t stream);
+
 int moc_set_hip_error(hipError_t e);  // records e, returns MOC_EHIP
 
 #define MOC_HIP(call)                                  \

@@ -1,0 +1,381 @@
+// What the kernels that score moves of a base candidate share: packed copies, wave scans, and
+// the base staged in LDS (copies, memory profile of Eq. (4), maxima over any range of it).
+#pragma once
+
+#include "moc_internal.h"
+
+namespace {
+
+// ------------------------------------------------------------------ packed copies
+// s | e << 16; low half 0xFFFF: not live (no position x satisfies 0xFFFF < x).
+__device__ __forceinline__ bool live_of(uint32_t p) { return (p & 0xFFFFu) != 0xFFFFu; }
+__device__ __forceinline__ bool covers1(uint32_t pu, uint32_t x) { return (pu & 0xFFFFu) < x && (pu >> 16) >= x; }
+__device__ __forceinline__ uint32_t pack_copy(bool live, int s, int e) {
+  return live ? ((uint32_t)s | ((uint32_t)e << 16)) : MOC_DEAD;
+}
+__device__ __forceinline__ bool bit_at(const uint32_t* bits, int t) { return (bits[t >> 5] >> (t & 31)) & 1u; }
+
+// ------------------------------------------------------------------ wave scans
+// The value of the lane CTRL names (a lane shift of the vector ALU), 0 where that lane does not
+// exist or the row is not in ROWS.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int lane_shift(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, true); }
+
+// Inclusive scans over the 64 lanes: inside rows of 16 by shifts of 1, 2, 4, 8, then lane 15 of
+// rows 0 and 2 goes to rows 1 and 3, then lane 31 to rows 2 and 3.  Values of the maximum >= 0.
+__device__ __forceinline__ int scan_sum(int x) {
+  x += lane_shift<0x111, 0xF>(x);
+  x += lane_shift<0x112, 0xF>(x);
+  x += lane_shift<0x114, 0xF>(x);
+  x += lane_shift<0x118, 0xF>(x);
+  x += lane_shift<0x142, 0xA>(x);
+  x += lane_shift<0x143, 0xC>(x);
+  return x;
+}
+__device__ __forceinline__ int scan_max(int x) {
+  x = max(x, lane_shift<0x111, 0xF>(x));
+  x = max(x, lane_shift<0x112, 0xF>(x));
+  x = max(x, lane_shift<0x114, 0xF>(x));
+  x = max(x, lane_shift<0x118, 0xF>(x));
+  x = max(x, lane_shift<0x142, 0xA>(x));
+  x = max(x, lane_shift<0x143, 0xC>(x));
+  return x;
+}
+__device__ __forceinline__ int last_lane(int x) { return __builtin_amdgcn_readlane(x, kWave - 1); }
+
+// LDS written by some lanes of a wave is read by others of the same wave: LDS operations of a
+// wave complete in order, so the compiler must keep them in order, and that is all.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// ------------------------------------------------------------------ the base in LDS
+constexpr int kBlk = 8;   // positions per block of the profile's range maxima (two 16-byte reads)
+
+// Word offsets.  The profile begins at 0; `table` holds, at level l and index i, the maximum over
+// the blocks i .. i + 2^l - 1; pre[i] the maximum over the blocks before i, suf[i] over the
+// blocks from i on.
+struct MvLayout {
+  int blocks, levels, bit_words;
+  int table, pre, suf, packed, occ1, occ2, peak_bits, peak_before, scratch, extra;
+  int lists;   // adjacency lists in LDS, 0 if they are read from global memory
+  int bytes;
+};
+
+constexpr int kScratchWords = 160;
+
+// extra_words: what the kernel needs beyond the base.  with_lists: the adjacency lists too, if they fit.
+inline MvLayout mv_layout(int T, int n, int m, int extra_words, bool with_lists, int max_lds) {
+  MvLayout l;
+  l.blocks = (T + kBlk - 1) / kBlk;
+  l.levels = 1;
+  while ((2 << (l.levels - 1)) <= l.blocks) ++l.levels;
+  l.bit_words = 2 * ((T + 63) / 64);
+  l.table = l.blocks * kBlk;
+  l.pre = l.table + l.levels * l.blocks;
+  l.suf = l.pre + l.blocks + 1;
+  l.packed = (l.suf + l.blocks + 1 + 3) & ~3;
+  l.occ1 = l.packed + ((T + 3) & ~3);
+  l.occ2 = l.occ1 + l.bit_words;
+  l.peak_bits = l.occ2 + l.bit_words;
+  l.peak_before = l.peak_bits + l.bit_words;
+  l.scratch = l.peak_before + l.bit_words;
+  l.extra = (l.scratch + kScratchWords + 3) & ~3;
+  const int words = l.extra + extra_words;
+  l.lists = 0;
+  l.bytes = 4 * words;
+  // sizes and edge pairs as words, the rest in 16 bits (which is why m is bounded)
+  const int lists = n + m + (2 * (n + 1) + m + 1) / 2;
+  if (with_lists && m < 0xFFFF && 4 * (words + lists) <= max_lds) {
+    l.lists = words;
+    l.bytes = 4 * (words + lists);
+  }
+  return l;
+}
+
+// Adjacency of the graph: in-edges of v are [in_begin(v), in_begin(v + 1)) in the order of in_idx;
+// pair(x) = u*C | v*C << 16 of in-edge x; consumers of u are consumer(y), y in [out_begin(u),
+// out_begin(u + 1)).  In LDS (16-bit entries) or in global memory.
+template <bool LISTS>
+struct Lists;
+template <>
+struct Lists<true> {
+  const int32_t* sizes;
+  const uint32_t* pairs;
+  const uint16_t *in_ptr, *out_ptr, *out_idx;
+  __device__ __forceinline__ int in_begin(int v) const { return in_ptr[v]; }
+  __device__ __forceinline__ int out_begin(int v) const { return out_ptr[v]; }
+  __device__ __forceinline__ int consumer_copy(int y, int) const { return out_idx[y]; }   // w*C
+  __device__ __forceinline__ uint32_t pair(int x) const { return pairs[x]; }
+  __device__ __forceinline__ int size_of(int v) const { return sizes[v]; }
+  template <int NT>
+  __device__ __forceinline__ void load(const GraphView& g, uint32_t* at, int t) {
+    const int n = g.n, m = g.m, C = g.C;
+    int32_t* s = reinterpret_cast<int32_t*>(at);
+    uint32_t* p = at + n;
+    uint16_t* ip = reinterpret_cast<uint16_t*>(p + m);
+    uint16_t* op = ip + n + 1;
+    uint16_t* oi = op + n + 1;
+    for (int x = t; x < n; x += NT) s[x] = g.size_dur[x].x;
+    for (int x = t; x <= n; x += NT) { ip[x] = (uint16_t)g.in_ptr[x]; op[x] = (uint16_t)g.out_ptr[x]; }
+    for (int x = t; x < m; x += NT) { p[x] = g.edge_pair_c[x]; oi[x] = (uint16_t)(g.out_idx[x] * C); }
+    sizes = s; pairs = p; in_ptr = ip; out_ptr = op; out_idx = oi;
+  }
+};
+template <>
+struct Lists<false> {
+  GraphView g;
+  __device__ __forceinline__ int in_begin(int v) const { return g.in_ptr[v]; }
+  __device__ __forceinline__ int out_begin(int v) const { return g.out_ptr[v]; }
+  __device__ __forceinline__ int consumer_copy(int y, int C) const { return g.out_idx[y] * C; }
+  __device__ __forceinline__ uint32_t pair(int x) const { return g.edge_pair_c[x]; }
+  __device__ __forceinline__ int size_of(int v) const { return g.size_dur[v].x; }
+  template <int NT>
+  __device__ __forceinline__ void load(const GraphView& view, uint32_t*, int) { g = view; }
+};
+
+struct BaseLds {
+  int32_t *profile, *table, *pre, *suf, *peak_before, *scratch;
+  uint32_t *packed, *occ1, *occ2, *peak_bits, *extra;
+  __device__ __forceinline__ void carve(uint32_t* raw, const MvLayout& l) {
+    profile = reinterpret_cast<int32_t*>(raw);
+    table = profile + l.table;
+    pre = profile + l.pre;
+    suf = profile + l.suf;
+    packed = raw + l.packed;
+    occ1 = raw + l.occ1;
+    occ2 = raw + l.occ2;
+    peak_bits = raw + l.peak_bits;
+    peak_before = profile + l.peak_before;
+    scratch = profile + l.scratch;
+    extra = raw + l.extra;
+  }
+};
+
+// What one thread saw while staging; summed over the workgroup by the caller.
+struct StageSums {
+  int viol = 0;   // Eq. (2), (8), (7)
+  int live = 0;   // live copies
+  int dur = 0;    // Eq. (1)
+};
+
+// Stages a candidate: packed copies (an inactive copy is MOC_DEAD, an active one that is not well
+// formed MOC_DEAD | 1 << 16), deltas of Eq. (4) in the profile array, start bitmaps.  The first
+// loads go out before the arrays are cleared.  Starts with no barrier (the arrays must be free),
+// ends with one.
+template <int CT, int NT>
+__device__ __forceinline__ StageSums stage_copies(const GraphView& g, const BaseLds& L, const MvLayout& lay,
+                                                  const int32_t* s_row, const int32_t* e_row, const uint8_t* a_row, int t) {
+  constexpr int kAhead = 4;
+  const int T = g.T, C = CT ? CT : g.C;
+  int as[kAhead], ae[kAhead];
+  uint32_t aa[kAhead];
+  int2 asd[kAhead];
+#pragma unroll
+  for (int j = 0; j < kAhead; ++j) {   // lanes past the last copy read it again
+    const uint32_t k = (uint32_t)min(j * NT + t, T - 1);
+    as[j] = *reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(s_row) + 4u * k);
+    ae[j] = *reinterpret_cast<const int32_t*>(reinterpret_cast<const char*>(e_row) + 4u * k);
+    aa[j] = *reinterpret_cast<const uint8_t*>(a_row + k);
+    asd[j] = g.size_dur[k / (uint32_t)C];
+  }
+  for (int x = 4 * t; x < lay.blocks * kBlk; x += 4 * NT) *reinterpret_cast<int4*>(L.profile + x) = make_int4(0, 0, 0, 0);
+  for (int w = t; w < lay.bit_words; w += NT) { L.occ1[w] = 0; L.occ2[w] = 0; }
+  __syncthreads();
+  StageSums sums;
+  auto stage = [&](int k, int s, int e, uint32_t flag, int2 sd) {
+    const bool act = flag != 0, live = act && (uint32_t)s <= (uint32_t)e && (uint32_t)e < (uint32_t)T;
+    L.packed[k] = live ? (uint32_t)s | ((uint32_t)e << 16) : act ? MOC_DEAD | 0x10000u : MOC_DEAD;
+    if (k % C == 0 && !act) ++sums.viol;   // Eq. (7)
+    if (act) sums.dur += sd.y;
+    if (act && !live) ++sums.viol;         // Eq. (2)/(8)
+    if (live) {
+      ++sums.live;
+      atomicAdd(&L.profile[s], sd.x);
+      if (e + 1 < T) atomicSub(&L.profile[e + 1], sd.x);
+      const uint32_t bit = 1u << (s & 31);
+      const uint32_t old = atomicOr(&L.occ1[s >> 5], bit);
+      if (old & bit) atomicOr(&L.occ2[s >> 5], bit);
+    }
+  };
+#pragma unroll
+  for (int j = 0; j < kAhead; ++j) {
+    const int k = j * NT + t;
+    if (k < T) stage(k, as[j], ae[j], aa[j], asd[j]);
+  }
+  for (int k = kAhead * NT + t; k < T; k += NT) stage(k, s_row[k], e_row[k], a_row[k], g.size_dur[k / C]);
+  __syncthreads();
+  return sums;
+}
+
+// The violations of Eq. (3), (5) in the staged base, this thread's share of them.
+template <int CT, int NT, typename A>
+__device__ __forceinline__ int count_order_and_inputs(const GraphView& g, const A& lists, const uint32_t* __restrict__ packed,
+                                                      int t) {
+  const int C = CT ? CT : g.C;
+  int viol = 0;
+  for (int v = t; v < g.n; v += NT) {   // Eq. (3): each live copy against the next live copy of its node
+    int end = -1;
+    for (int i = 0; i < C; ++i) {
+      const uint32_t p = packed[v * C + i];
+      if (!live_of(p)) continue;
+      viol += end > (int)(p & 0xFFFFu) ? 1 : 0;
+      end = (int)(p >> 16);
+    }
+  }
+  for (int x = t; x < g.m; x += NT) {   // Eq. (5): one lane per edge
+    const uint32_t pair = lists.pair(x);
+    const uint32_t* const pu = packed + (pair & 0xFFFFu);
+    const uint32_t* const pv = packed + (pair >> 16);
+    for (int i = 0; i < C; ++i) {
+      const uint32_t at = pv[i] & 0xFFFFu;
+      bool held = at == 0xFFFFu;
+      for (int q = 0; q < C; ++q) held = held || covers1(pu[q], at);
+      viol += held ? 0 : 1;
+    }
+  }
+  return viol;
+}
+
+// profile <- running sums of the profile array (0 behind the last position), and level 0 of the
+// table.  A wave takes rows of 256 positions, four per lane.  Ends with a barrier.
+template <int NT>
+__device__ __forceinline__ void scan_profile(const BaseLds& L, const MvLayout& lay, int T, int t) {
+  constexpr int NW = NT / kWave;
+  const int lane = t & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(t / kWave);
+  const int words = lay.blocks * kBlk;
+  const int rows = (words + 4 * kWave - 1) / (4 * kWave), per_wave = (rows + NW - 1) / NW;
+  const int r0 = min(wave * per_wave, rows), r1 = min(r0 + per_wave, rows);
+  int sum = 0;
+  for (int r = r0; r < r1; ++r) {
+    const int x = (r * kWave + lane) * 4;
+    if (x < words) {
+      const int4 v = *reinterpret_cast<const int4*>(L.profile + x);
+      sum += v.x + v.y + v.z + v.w;
+    }
+  }
+  if constexpr (NW > 1) {
+    sum = scan_sum(sum);
+    if (lane == kWave - 1) L.scratch[wave] = sum;
+    __syncthreads();
+  }
+  int before = 0;
+  for (int w = 0; w < wave; ++w) before += L.scratch[w];
+  for (int r = r0; r < r1; ++r) {
+    const int x = (r * kWave + lane) * 4;
+    int4 v = make_int4(0, 0, 0, 0);
+    if (x < words) v = *reinterpret_cast<const int4*>(L.profile + x);
+    v.y += v.x; v.z += v.y; v.w += v.z;
+    const int incl = scan_sum(v.w);
+    const int base = before + incl - v.w;
+    before += last_lane(incl);
+    v.x = x < T ? v.x + base : 0;
+    v.y = x + 1 < T ? v.y + base : 0;
+    v.z = x + 2 < T ? v.z + base : 0;
+    v.w = x + 3 < T ? v.w + base : 0;
+    int top = max(max(v.x, v.y), max(v.z, v.w));
+    top = max(top, __builtin_amdgcn_update_dpp(0, top, 0xB1, 0xF, 0xF, true));   // quad_perm [1,0,3,2]: the block's other half
+    if (x < words) {
+      *reinterpret_cast<int4*>(L.profile + x) = v;
+      if ((lane & 1) == 0) L.table[x / kBlk] = top;
+    }
+  }
+  __syncthreads();
+}
+
+// The levels of the table above 0, and the maxima before and from every block: one wave each.
+// Ends with a barrier.
+template <int NT>
+__device__ __forceinline__ void build_maxima(const BaseLds& L, const MvLayout& lay, int t) {
+  constexpr int NW = NT / kWave;
+  const int lane = t & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(t / kWave);
+  const int blocks = lay.blocks;
+  if (wave == 0) {
+    for (int l = 1; l < lay.levels; ++l) {
+      const int half = 1 << (l - 1);
+      const int32_t* below = L.table + (l - 1) * blocks;
+      for (int x = lane; x + 2 * half <= blocks; x += kWave) L.table[l * blocks + x] = max(below[x], below[x + half]);
+      wave_lds_order();
+    }
+  }
+  if (wave == (NW > 1 ? 1 : 0)) {
+    int carry = 0;
+    for (int x0 = 0; x0 < blocks; x0 += kWave) {
+      const int x = x0 + lane;
+      const int incl = max(carry, scan_max(x < blocks ? L.table[x] : 0));
+      if (x < blocks) L.pre[x + 1] = incl;
+      carry = last_lane(incl);
+    }
+    if (lane == 0) { L.pre[0] = 0; L.suf[blocks] = 0; }
+  }
+  if (wave == (NW > 2 ? 2 : 0)) {
+    int carry = 0;
+    for (int x0 = 0; x0 < blocks; x0 += kWave) {
+      const int x = blocks - 1 - (x0 + lane);
+      const int incl = max(carry, scan_max(x >= 0 ? L.table[x] : 0));
+      if (x >= 0) L.suf[x] = incl;
+      carry = last_lane(incl);
+    }
+  }
+  __syncthreads();
+}
+
+// profile += change on [lo, hi], level 0 of the table with it.  Ends with a barrier.
+struct Range { int lo, hi, change; };
+template <int NT, typename R>
+__device__ __forceinline__ void add_ranges(const BaseLds& L, const MvLayout& lay, const R* ranges, int count, int t) {
+  for (int x0 = 0; x0 < lay.blocks * kBlk; x0 += 4 * NT) {   // whole waves
+    const int x = x0 + 4 * t;
+    int4 v = make_int4(0, 0, 0, 0);
+    if (x < lay.blocks * kBlk) v = *reinterpret_cast<const int4*>(L.profile + x);
+    for (int r = 0; r < count; ++r) {
+      const int lo = ranges[r].lo, hi = ranges[r].hi, d = ranges[r].change;
+      v.x += lo <= x && x <= hi ? d : 0;
+      v.y += lo <= x + 1 && x + 1 <= hi ? d : 0;
+      v.z += lo <= x + 2 && x + 2 <= hi ? d : 0;
+      v.w += lo <= x + 3 && x + 3 <= hi ? d : 0;
+    }
+    int top = max(max(v.x, v.y), max(v.z, v.w));
+    top = max(top, __builtin_amdgcn_update_dpp(0, top, 0xB1, 0xF, 0xF, true));
+    if (x < lay.blocks * kBlk) {
+      *reinterpret_cast<int4*>(L.profile + x) = v;
+      if ((t & 1) == 0) L.table[x / kBlk] = top;
+    }
+  }
+  __syncthreads();
+}
+
+// Maxima of the profile over [lo, hi], 0 <= lo <= hi < T, and over all other positions: whole
+// blocks from the tables, the two blocks at the ends position by position.
+struct InOut { int in, out; };
+template <bool OUTSIDE>
+__device__ __forceinline__ InOut range_maxima(const BaseLds& L, int blocks, int lo, int hi) {
+  const int bl = lo / kBlk, bh = hi / kBlk;
+  const int4* const fl = reinterpret_cast<const int4*>(L.profile + bl * kBlk);
+  const int4* const fh = reinterpret_cast<const int4*>(L.profile + bh * kBlk);
+  const int4 l0 = fl[0], l1 = fl[1], h0 = fh[0], h1 = fh[1];
+  const int first = bl + 1, count = bh - first;   // whole blocks between
+  InOut r{0, 0};
+  if (count > 0) {
+    const int level = 31 - __clz(count);
+    const int32_t* row = L.table + level * blocks;
+    r.in = max(row[first], row[bh - (1 << level)]);
+  }
+  if constexpr (OUTSIDE) r.out = max(L.pre[bl], L.suf[bh + 1]);
+  // bit j: position j of the block lies in the range
+  uint32_t ml = 0xFFu << (lo & (kBlk - 1)), mh = 0xFFu >> (kBlk - 1 - (hi & (kBlk - 1)));
+  if (bl == bh) { ml &= mh; mh = ml; }
+  auto take = [&](uint32_t m, int j, int v) {
+    const int on = (int)(m << (31 - j)) >> 31;   // all ones or zero
+    r.in = max(r.in, v & on);
+    if constexpr (OUTSIDE) r.out = max(r.out, v & ~on);
+  };
+  take(ml, 0, l0.x); take(ml, 1, l0.y); take(ml, 2, l0.z); take(ml, 3, l0.w);
+  take(ml, 4, l1.x); take(ml, 5, l1.y); take(ml, 6, l1.z); take(ml, 7, l1.w);
+  take(mh, 0, h0.x); take(mh, 1, h0.y); take(mh, 2, h0.z); take(mh, 3, h0.w);
+  take(mh, 4, h1.x); take(mh, 5, h1.y); take(mh, 6, h1.z); take(mh, 7, h1.w);
+  return r;
+}
+
+}  // namespace

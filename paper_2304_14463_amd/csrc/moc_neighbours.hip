@@ -1734,112 +1734,6 @@ int eval_cuts(const moc_graph* g, int64_t B, const int32_t* starts, const int32_
   return MOC_OK;
 }
 
-// ---- merges: the moves of the second phase, scored by the evaluation kernel itself
-constexpr int kMergeNT = 256;
-
-__device__ __forceinline__ bool copy_is_live(int s, int e, uint8_t a, int T) {
-  return a != 0 && (uint32_t)s <= (uint32_t)e && (uint32_t)e < (uint32_t)T;
-}
-
-// The nearest live copy of the same node below copy k (index within the row), -1 if none.
-__device__ __forceinline__ int live_copy_below(const int32_t* s, const int32_t* e, const uint8_t* a, int T, int C,
-                                               int k) {
-  const int first = k - k % C;
-  for (int c = k - 1; c >= first; --c)
-    if (copy_is_live(s[c], e[c], a[c], T)) return c;
-  return -1;
-}
-
-// One workgroup per walker: the first K copies, in index order, that are live and have a live
-// copy of their node below them, to list[walker][0..K); the rest of the list is -1.
-__global__ __launch_bounds__(kMergeNT) void list_merges_kernel(int64_t B, int T, int C, int K,
-                                                               const int32_t* __restrict__ starts,
-                                                               const int32_t* __restrict__ ends,
-                                                               const uint8_t* __restrict__ active,
-                                                               int32_t* __restrict__ list) {
-  __shared__ int wave_count[kMergeNT / kWave];
-  const int64_t b = blockIdx.x;
-  const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid / kWave;
-  const int32_t* s = starts + b * T;
-  const int32_t* e = ends + b * T;
-  const uint8_t* a = active + b * T;
-  int32_t* out = list + b * K;
-  for (int r = tid; r < K; r += kMergeNT) out[r] = -1;
-  int found = 0;   // entries written by earlier rounds
-  for (int k0 = 0; k0 < T && found < K; k0 += kMergeNT) {
-    const int k = k0 + tid;
-    const bool mergeable = k < T && copy_is_live(s[k], e[k], a[k], T) && live_copy_below(s, e, a, T, C, k) >= 0;
-    const uint64_t hits = __ballot(mergeable);
-    __syncthreads();   // the counts of the last round have been read; the -1s above are in place
-    if (lane == 0) wave_count[wave] = __popcll(hits);
-    __syncthreads();
-    int before = found, total = found;
-    for (int w = 0; w < kMergeNT / kWave; ++w) {
-      if (w < wave) before += wave_count[w];
-      total += wave_count[w];
-    }
-    const int r = before + __popcll(hits & ((1ull << lane) - 1));
-    if (mergeable && r < K) out[r] = k;
-    found = total;
-  }
-}
-
-// One workgroup per (walker, entry of its list): the walker's row with that merge applied (the
-// copy switched off, the live copy below it kept until the later of the two ends), or the row
-// as it is where the list has no entry.
-__global__ __launch_bounds__(kMergeNT) void write_merges_kernel(int T, int C, int K, const int32_t* __restrict__ starts,
-                                                                const int32_t* __restrict__ ends,
-                                                                const uint8_t* __restrict__ active,
-                                                                const int32_t* __restrict__ list,
-                                                                int32_t* __restrict__ ws, int32_t* __restrict__ we,
-                                                                uint8_t* __restrict__ wa) {
-  const int64_t idx = blockIdx.x, b = idx / K;
-  const int32_t* s = starts + b * T;
-  const int32_t* e = ends + b * T;
-  const uint8_t* a = active + b * T;
-  const int k = list[idx];
-  int below = -1, end = 0;
-  if (k >= 0) {
-    below = live_copy_below(s, e, a, T, C, k);
-    end = max(e[below], e[k]);
-  }
-  for (int x = threadIdx.x; x < T; x += kMergeNT) {
-    ws[idx * T + x] = s[x];
-    we[idx * T + x] = x == below ? end : e[x];
-    wa[idx * T + x] = x == k ? (uint8_t)0 : a[x];
-  }
-}
-
-// One lane per walker: among the scored merges of its list those whose result is feasible, the
-// one with the lowest duration, then the lowest peak, then the lowest copy index, applied in place.
-__global__ void select_merges_kernel(int64_t B, int T, int C, int K, int32_t* starts, int32_t* ends, uint8_t* active,
-                                     const int32_t* __restrict__ list, const moc_result* __restrict__ results,
-                                     int32_t* merges) {
-  const int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  int best = -1;
-  int64_t best_dur = 0, best_peak = 0;
-  for (int r = 0; r < K; ++r) {
-    const int k = list[b * K + r];
-    if (k < 0) break;
-    const moc_result res = results[b * K + r];
-    if (!res.feasible) continue;
-    if (best < 0 || res.duration < best_dur || (res.duration == best_dur && res.peak < best_peak)) {
-      best = k;
-      best_dur = res.duration;
-      best_peak = res.peak;
-    }
-  }
-  if (best < 0) return;
-  int32_t* s = starts + b * T;
-  int32_t* e = ends + b * T;
-  uint8_t* a = active + b * T;
-  const int below = live_copy_below(s, e, a, T, C, best);
-  e[below] = max(e[below], e[best]);
-  a[best] = 0;
-  merges[b] += 1;
-}
-
 }  // namespace
 
 extern "C" int moc_search_cuts(const moc_graph* g, int64_t B, int32_t* starts, int32_t* ends, uint8_t* active,
@@ -1894,22 +1788,14 @@ extern "C" int moc_search_two_phase(const moc_graph* g, int64_t B, int32_t* star
   if (const int rc = plan_cuts(g, B, true, &plan)) return rc;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const unsigned blocks = (unsigned)((B + 255) / 256);
-  const int T = g->view.T, C = g->view.C;
   hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks), dim3(256), 0, stream, out_cuts, B);
   hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks), dim3(256), 0, stream, out_merges, B);
   // Phase 1: towards the budget by cuts that keep the producer's inputs
   queue_cut_steps(g, plan, B, starts, ends, active, max_cuts, 1, work_best, out_cuts, stream);
   MOC_HIP(hipGetLastError());
   // Phase 2: undo recomputations while the candidate stays within the budget
-  for (int step = 0; step < max_merges; ++step) {
-    hipLaunchKernelGGL(list_merges_kernel, dim3((unsigned)B), dim3(kMergeNT), 0, stream, B, T, C, (int)K, starts, ends,
-                       active, work_list);
-    hipLaunchKernelGGL(write_merges_kernel, dim3((unsigned)(B * K)), dim3(kMergeNT), 0, stream, T, C, (int)K, starts,
-                       ends, active, work_list, work_starts, work_ends, work_active);
-    MOC_HIP(hipGetLastError());
-    if (const int rc = moc_eval_batch(g, B * K, work_starts, work_ends, work_active, work_results, hip_stream)) return rc;
-    hipLaunchKernelGGL(select_merges_kernel, dim3(blocks), dim3(256), 0, stream, B, T, C, (int)K, starts, ends, active,
-                       work_list, work_results, out_merges);
+  if (max_merges > 0) {
+    if (const int rc = moc_queue_merges(g, B, starts, ends, active, max_merges, K, out_merges, stream)) return rc;
   }
   MOC_HIP(hipGetLastError());
   return MOC_OK;

@@ -271,17 +271,12 @@ def moc_search_two_phase(g: Graph, starts, ends, active, max_cuts, max_merges, K
     dev = starts.device
     with _on(stream):
         work_best = torch.empty((B, BEST_MOVE_DTYPE.itemsize), dtype=torch.uint8, device=dev)
-        rows = B * K if max_merges > 0 else 0
-        ws = torch.empty((rows, g.T), dtype=torch.int32, device=dev)
-        we = torch.empty((rows, g.T), dtype=torch.int32, device=dev)
-        wa = torch.empty((rows, g.T), dtype=torch.uint8, device=dev)
-        wl = torch.empty((rows,), dtype=torch.int32, device=dev)
-        wr = torch.empty((rows, RESULT_DTYPE.itemsize), dtype=torch.uint8, device=dev)
         cuts = torch.empty((B,), dtype=torch.int32, device=dev)
         merges = torch.empty((B,), dtype=torch.int32, device=dev)
     P = lambda t: ctypes.c_void_p(t.data_ptr()) if t.numel() else None
-    code = lib().moc_search_two_phase(g._h, B, ps, pe, pa, int(max_cuts), int(max_merges), int(K), P(work_best), P(ws),
-                                      P(we), P(wa), P(wl), P(wr), P(cuts), P(merges), _stream_handle(stream))
+    unused = P(work_best)   # the call asks for the second phase's workspaces and does not use them
+    code = lib().moc_search_two_phase(g._h, B, ps, pe, pa, int(max_cuts), int(max_merges), int(K), P(work_best), unused,
+                                      unused, unused, unused, unused, P(cuts), P(merges), _stream_handle(stream))
     _check(code, "moc_search_two_phase")
     return cuts, merges
 
