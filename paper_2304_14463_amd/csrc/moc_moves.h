@@ -378,4 +378,24 @@ __device__ __forceinline__ InOut range_maxima(const BaseLds& L, int blocks, int 
   return r;
 }
 
+// Number of positions in [lo, hi] at which the profile reaches `bound`.  Blocks that stay below it
+// are passed over by the levels of the table, the largest run first.
+__device__ __forceinline__ int count_reaching(const BaseLds& L, const MvLayout& lay, int lo, int hi, int bound) {
+  int count = 0;
+  const int last = hi / kBlk;
+  for (int b = lo / kBlk; b <= last; ++b) {
+    for (int l = lay.levels - 1; l >= 0; --l)
+      if (b + (1 << l) <= last + 1 && L.table[l * lay.blocks + b] < bound) b += 1 << l;
+    if (b > last) break;
+    const int4* const at = reinterpret_cast<const int4*>(L.profile + b * kBlk);
+    const int4 x = at[0], y = at[1];
+    uint32_t m = (x.x >= bound ? 1u : 0u) | (x.y >= bound ? 2u : 0u) | (x.z >= bound ? 4u : 0u) | (x.w >= bound ? 8u : 0u) |
+                 (y.x >= bound ? 16u : 0u) | (y.y >= bound ? 32u : 0u) | (y.z >= bound ? 64u : 0u) | (y.w >= bound ? 128u : 0u);
+    if (b == lo / kBlk) m &= 0xFFu << (lo & (kBlk - 1));
+    if (b == last) m &= 0xFFu >> (kBlk - 1 - (hi & (kBlk - 1)));
+    count += __popc(m);
+  }
+  return count;
+}
+
 }  // namespace

@@ -1619,54 +1619,11 @@ extern "C" int moc_eval_toggles(const moc_graph* g, int64_t B, const int32_t* st
 
 namespace {
 
-constexpr int kApplyNT = 256;
+
 
 __global__ void fill_zero_kernel(int32_t* p, int64_t n) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0;
-}
-
-// Applies to each base the move its moc_best_move names (none if move < 0) and counts it.
-// One workgroup per base stages what find_cut reads -- packed copies and the start bitmap --
-// and one lane edits the three arrays in place.
-__global__ __launch_bounds__(kApplyNT) void apply_cuts_kernel(GraphView g, int64_t B, int32_t* starts, int32_t* ends,
-                                                              uint8_t* active, const moc_best_move* best,
-                                                              int32_t* steps, int mode) {
-  extern __shared__ uint32_t ap_raw[];
-  const int T = g.T, C = g.C, tid = threadIdx.x;
-  const int bit_words = (T + 31) / 32;
-  NbLds L{};
-  L.packed = ap_raw;
-  L.occ1 = ap_raw + T;
-  const int64_t b = blockIdx.x;
-  if (b >= B) return;
-  const int q = best[b].move;
-  if (q < 0) return;   // the same for every lane of the workgroup
-  const int64_t row = b * T;
-  for (int w = tid; w < bit_words; w += kApplyNT) L.occ1[w] = 0;
-  __syncthreads();
-  for (int k = tid; k < T; k += kApplyNT) {
-    const int s = starts[row + k], e = ends[row + k];
-    const bool live = active[row + k] != 0 && (uint32_t)s <= (uint32_t)e && (uint32_t)e < (uint32_t)T;
-    L.packed[k] = pack_copy(live, s, e);
-    if (live) atomicOr(&L.occ1[s >> 5], 1u << (s & 31));
-  }
-  __syncthreads();
-  if (tid == 0) {
-    const Adj A{g.in_ptr, g.in_idx, g.out_ptr, g.out_idx, reinterpret_cast<const int32_t*>(g.size_dur), 2};
-    const int x = q / C, i = q - x * C;
-    const int u = g.in_idx[x];
-    Cut cut;
-    if (find_cut(A, C, L, active + row, u, (int)(g.edge_pair_c[x] >> 16) + i, mode, &cut)) {
-      if (mode == 1)
-        for_each_kept_input(A, C, L.packed, u, cut.p, [&](int w, int q, int) { ends[row + w * C + q] = cut.p; });
-      ends[row + u * C + cut.k] = cut.last_use;
-      starts[row + u * C + cut.j] = cut.p;
-      ends[row + u * C + cut.j] = cut.ek;
-      active[row + u * C + cut.j] = 1;
-      steps[b] += 1;
-    }
-  }
 }
 
 }  // namespace
@@ -1679,10 +1636,9 @@ struct CutsPlan {
   void (*kern)(GraphView, int64_t, const int32_t*, const int32_t*, const uint8_t*, moc_toggle_score*, moc_best_move*,
                int, int, TgLayout);
   unsigned grid;
-  int apply_bytes;
 };
 
-int plan_cuts(const moc_graph* g, int64_t B, bool with_apply, CutsPlan* plan) {
+int plan_cuts(const moc_graph* g, int64_t B, CutsPlan* plan) {
   if (g->has_self_loop) return MOC_EINVAL;
   plan->lay = tg_layout(g->view.T, g->view.n, g->view.m, g->max_lds);
   if (plan->lay.bytes > g->max_lds) return MOC_EOVERFLOW;
@@ -1691,28 +1647,9 @@ int plan_cuts(const moc_graph* g, int64_t B, bool with_apply, CutsPlan* plan) {
   int per_cu = 0;
   if (const int rc = moc_kernel_occupancy(g, reinterpret_cast<const void*>(plan->kern), kNT, plan->lay.bytes, false, &per_cu))
     return rc;
-  plan->apply_bytes = 4 * (g->view.T + (g->view.T + 31) / 32);
-  if (with_apply) {
-    int apply_per_cu = 0;   // not used: the call is for the kernel's LDS limit
-    if (const int rc = moc_kernel_occupancy(g, reinterpret_cast<const void*>(apply_cuts_kernel), kApplyNT,
-                                            plan->apply_bytes, false, &apply_per_cu))
-      return rc;
-  }
   const int64_t resident = (int64_t)per_cu * g->num_cu;
   plan->grid = (unsigned)(B < resident ? B : resident);
   return MOC_OK;
-}
-
-// max_steps times: the best cut of every candidate that improves it, then its application.
-void queue_cut_steps(const moc_graph* g, const CutsPlan& plan, int64_t B, int32_t* starts, int32_t* ends,
-                     uint8_t* active, int max_steps, int mode, moc_best_move* work_best, int32_t* out_steps,
-                     hipStream_t stream) {
-  for (int step = 0; step < max_steps; ++step) {
-    hipLaunchKernelGGL(plan.kern, dim3(plan.grid), dim3(kNT), plan.lay.bytes, stream, g->view, B, starts, ends, active,
-                       static_cast<moc_toggle_score*>(nullptr), work_best, 1, mode, plan.lay);
-    hipLaunchKernelGGL(apply_cuts_kernel, dim3((unsigned)B), dim3(kApplyNT), plan.apply_bytes, stream, g->view, B,
-                       starts, ends, active, work_best, out_steps, mode);
-  }
 }
 
 int eval_cuts(const moc_graph* g, int64_t B, const int32_t* starts, const int32_t* ends, const uint8_t* active,
@@ -1727,7 +1664,7 @@ int eval_cuts(const moc_graph* g, int64_t B, const int32_t* starts, const int32_
   MOC_HIP(hipGetDevice(&dev));
   if (dev != g->device) return MOC_EDEVICE;
   CutsPlan plan;
-  if (const int rc = plan_cuts(g, B, false, &plan)) return rc;
+  if (const int rc = plan_cuts(g, B, &plan)) return rc;
   hipLaunchKernelGGL(plan.kern, dim3(plan.grid), dim3(kNT), plan.lay.bytes, static_cast<hipStream_t>(hip_stream), g->view,
                      B, starts, ends, active, out_moves, out_best, 0, mode, plan.lay);
   MOC_HIP(hipGetLastError());
@@ -1747,10 +1684,12 @@ extern "C" int moc_search_cuts(const moc_graph* g, int64_t B, int32_t* starts, i
   MOC_HIP(hipGetDevice(&dev));
   if (dev != g->device) return MOC_EDEVICE;
   CutsPlan plan;
-  if (const int rc = plan_cuts(g, B, true, &plan)) return rc;
+  if (const int rc = plan_cuts(g, B, &plan)) return rc;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, stream, out_steps, B);
-  queue_cut_steps(g, plan, B, starts, ends, active, max_steps, 0, work_best, out_steps, stream);
+  if (max_steps == 0)
+    hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, stream, out_steps, B);
+  else if (const int rc = moc_queue_cut_descent(g, B, starts, ends, active, max_steps, 0, work_best, out_steps, stream))
+    return rc;
   MOC_HIP(hipGetLastError());
   return MOC_OK;
 }
@@ -1785,18 +1724,20 @@ extern "C" int moc_search_two_phase(const moc_graph* g, int64_t B, int32_t* star
   MOC_HIP(hipGetDevice(&dev));
   if (dev != g->device) return MOC_EDEVICE;
   CutsPlan plan;
-  if (const int rc = plan_cuts(g, B, true, &plan)) return rc;
+  if (const int rc = plan_cuts(g, B, &plan)) return rc;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const unsigned blocks = (unsigned)((B + 255) / 256);
-  hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks), dim3(256), 0, stream, out_cuts, B);
-  hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks), dim3(256), 0, stream, out_merges, B);
   // Phase 1: towards the budget by cuts that keep the producer's inputs
-  queue_cut_steps(g, plan, B, starts, ends, active, max_cuts, 1, work_best, out_cuts, stream);
+  if (max_cuts == 0)
+    hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks), dim3(256), 0, stream, out_cuts, B);
+  else if (const int rc = moc_queue_cut_descent(g, B, starts, ends, active, max_cuts, 1, work_best, out_cuts, stream))
+    return rc;
   MOC_HIP(hipGetLastError());
   // Phase 2: undo recomputations while the candidate stays within the budget
-  if (max_merges > 0) {
-    if (const int rc = moc_queue_merges(g, B, starts, ends, active, max_merges, K, out_merges, stream)) return rc;
-  }
+  if (max_merges == 0)
+    hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks), dim3(256), 0, stream, out_merges, B);
+  else if (const int rc = moc_queue_merges(g, B, starts, ends, active, max_merges, K, out_merges, stream))
+    return rc;
   MOC_HIP(hipGetLastError());
   return MOC_OK;
 }

@@ -1,15 +1,164 @@
-// The second phase of moc_search_two_phase: merges that lower the duration of a candidate within
-// the budget, one workgroup per candidate from its first step to its last (gfx950).
+// The searches that change a candidate by cuts (moc_search_cuts, the first phase of
+// moc_search_two_phase) and by merges (its second phase), one workgroup per candidate from its
+// first step to its last (gfx950).
 //
-// A merge switches a live copy c off and keeps b, the nearest live copy of its node below it,
+// The base is staged once -- packed copies, profile with range maxima (moc_moves.h) -- and stays in
+// LDS: a step scores the moves, one lane each, chooses, edits the candidate's rows and the staged
+// base alike, and brings the maxima up to date.  Nothing is read from global memory between two
+// steps, and a candidate that has come to its end costs nothing more.
+//
+// Cuts: see moc_cut_moves.h.  A merge switches a live copy c off and keeps b, the nearest live copy of its node below it,
 // until the later of the two ends.  What changes is the node's own order (Eq. (3)), the start and
 // the inputs of c (Eq. (5), (6)), which copies serve the node's consumers (Eq. (5)), and the
-// profile on one stretch: +m between the two copies, or -m where they overlapped.  So the base is
-// staged once -- packed copies, profile with range maxima (moc_moves.h) -- and a merge is scored
-// by one lane from it, with the result moc_eval_batch has for the edited candidate.
-#include "moc_moves.h"
+// profile on one stretch: +m between the two copies, or -m where they overlapped.
+#include <algorithm>
+
+#include "moc_cut_moves.h"
 
 namespace {
+
+constexpr int kMaxRanges = kWave + 1;   // stretches of the profile that are changed together
+
+// Words of LDS beyond the base: a queue of 2 * kWave moves per wave, the stretches, the chosen move.
+constexpr int descend_words(int nt) { return (2 * nt + 3 * kMaxRanges + 1 + (int)(sizeof(Cut) / 4) + 1) & ~1; }
+
+// One workgroup per candidate: up to max_steps cuts, each the best of the candidate as it stands,
+// applied if it lowers (violations, max(peak, M)) or, above the budget with both unchanged, leaves
+// fewer positions at the peak.  Bound by the chain of instructions and LDS latencies of a step (a
+// lone wave issues one vector instruction in 8 clocks): 15 to 21 us, of which the sieve takes 5
+// and the scoring 3 (plain cuts) to 12 (cuts that keep inputs).  n = 442, 1024 walkers, up to 64
+// keeping cuts: 27 ms with two launches a step that staged and scored everything again, 0.7 ms now;
+// n = 1000, 32 walkers, 32 plain cuts: 1.31 -> 0.46 ms.
+template <int CT, int NT, bool LISTS>
+__global__ __launch_bounds__(NT) void descend_cuts_kernel(GraphView g, int32_t* __restrict__ starts, int32_t* __restrict__ ends,
+                                                          uint8_t* __restrict__ active, int max_steps, int mode,
+                                                          moc_best_move* __restrict__ last_move, int32_t* __restrict__ out_steps,
+                                                          int cap, MvLayout lay) {
+  extern __shared__ uint32_t lds_raw[];
+  constexpr int NW = NT / kWave;
+  const int t = threadIdx.x, lane = t & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(t / kWave);
+  const int T = g.T, C = CT ? CT : g.C;
+  BaseLds L;
+  L.carve(lds_raw, lay);
+  Lists<LISTS> lists;
+  lists.template load<NT>(g, lds_raw + lay.lists, t);
+  int32_t* const queue = reinterpret_cast<int32_t*>(L.extra);
+  Range* const ranges = reinterpret_cast<Range*>(queue + 2 * kWave * NW);
+  int32_t* const n_ranges = reinterpret_cast<int32_t*>(ranges + kMaxRanges);
+  Cut* const chosen_cut = reinterpret_cast<Cut*>(n_ranges + 1);
+  const SiftLds sift = carve_sift(L.extra + descend_words(NT), g.n, cap);
+  const int64_t row = (int64_t)blockIdx.x * T;
+
+  const StageSums sums = stage_copies<CT, NT>(g, L, lay, starts + row, ends + row, active + row, t);
+  int viol = sums.viol + sums.live + count_order_and_inputs<CT, NT>(g, lists, L.packed, t);
+  for (int w = t; w < lay.bit_words; w += NT) viol -= __popc(L.occ1[w]);   // Eq. (6): live copies - distinct starts
+  viol = last_lane(scan_sum(viol));
+  if (lane == 0) L.scratch[128 + wave] = viol;
+  scan_profile<NT>(L, lay, T, t);
+  build_maxima<NT>(L, lay, t);
+  int base_viol = 0, base_peak = L.pre[lay.blocks];
+#pragma unroll
+  for (int w = 0; w < NW; ++w) base_viol += L.scratch[128 + w];
+
+  int steps = 0;
+  moc_best_move chosen{-1, 0, 0};
+  for (; steps < max_steps; ++steps) {
+    chosen = moc_best_move{-1, 0, 0};
+    if (base_viol == 0 && (int64_t)base_peak <= g.budget) break;   // no move lowers anything a step looks at
+    const PeakCount at_peak = mark_peak<NT>(L, lay, T, base_peak, t);
+    BestCut best;
+    Cut cut{};
+    bool known = false;   // this lane holds the chosen move in `cut`
+    if (base_viol != 0 || !best_cut_of_clean_base<CT, NT>(g, lists, L, lay, queue, sift, mode, base_peak, at_peak, best, cut, known, t)) {
+      best = BestCut{};
+      known = false;
+      score_cuts<CT, NT>(g, lists, L, lay, queue, mode, base_viol, base_peak, at_peak, base_viol == 0, best, t,
+                         [](int, int, const CutScore*) {});
+      best_of_workgroup<NT>(best, L.scratch, t);
+      if (t == 0 && best.move() >= 0) {
+        const int x = best.move() / C;
+        const uint32_t pair = lists.pair(x);
+        known = find_cut(lists, C, L, (int)(pair & 0xFFFFu), (int)(L.packed[(pair >> 16) + best.move() - x * C] & 0xFFFFu), mode,
+                         base_viol == 0, cut);
+      }
+    }
+    const int q = best.move();
+    if (q < 0) break;
+    const int64_t now = max((int64_t)base_peak, g.budget), then = max((int64_t)best.peak(), g.budget);
+    if (!(best.viol() < base_viol ||
+          (best.viol() == base_viol &&
+           (then < now || (then == now && (int64_t)base_peak > g.budget && best.at() < at_peak.total)))))
+      break;
+    chosen = moc_best_move{q, best.viol(), (int64_t)best.peak()};
+
+    // ---- apply it: one wave edits the copies and lists the stretches of the profile that change
+    if (known) *chosen_cut = cut;
+    __syncthreads();
+    cut = *chosen_cut;
+    const int ub = (int)(lists.pair(q / C) & 0xFFFFu), u = ub / C;
+    const int y0 = lists.in_begin(u), y1 = lists.in_begin(u + 1);
+    const int rounds = mode == 1 ? max(1, (y1 - y0 + kWave - 1) / kWave) : 1;
+    for (int round = 0; round < rounds; ++round) {
+      __syncthreads();   // every wave has read what it needs of the copies, the stretches of the last round are added
+      if (wave == 0) {
+        int count = 0;
+        if (round == 0) {
+          if (lane == 0) ranges[0] = Range{cut.last_use + 1, cut.p - 1, -lists.size_of(u)};
+          count = 1;
+        }
+        int kept = -1, end = -1, w = 0;   // the copy of the lane's predecessor of u that is kept until p
+        if (mode == 1) {
+          const int y = y0 + round * kWave + lane;
+          if (y < y1) {
+            w = (int)(lists.pair(y) & 0xFFFFu);
+            int held = 0;
+            for (int c = 0; c < C; ++c) {
+              const uint32_t pw = L.packed[w + c];
+              held |= covers1(pw, (uint32_t)cut.p) ? 1 : 0;
+              if (live_of(pw) && (int)(pw >> 16) < cut.p && (int)(pw >> 16) >= end) {
+                kept = c;
+                end = (int)(pw >> 16);
+              }
+            }
+            if (held) kept = -1;
+            // listed before in this round (in an earlier one: it is held by now)
+            for (int z = y0 + round * kWave; z < y; ++z)
+              if ((int)(lists.pair(z) & 0xFFFFu) == w) kept = -1;
+          }
+          const uint64_t m = __ballot(kept >= 0);
+          wave_lds_order();   // all lanes have read the copies
+          if (kept >= 0) {
+            ranges[count + __popcll(m & ((1ull << lane) - 1))] = Range{end + 1, cut.p, lists.size_of(w / C)};
+            L.packed[w + kept] = (L.packed[w + kept] & 0xFFFFu) | (uint32_t)cut.p << 16;
+            ends[row + w + kept] = cut.p;
+          }
+          count += __popcll(m);
+        }
+        if (lane == 0) {
+          *n_ranges = count;
+          if (round == rounds - 1) {
+            L.packed[ub + cut.k] = (uint32_t)cut.sk | (uint32_t)cut.last_use << 16;
+            L.packed[ub + cut.j] = (uint32_t)cut.p | (uint32_t)cut.ek << 16;
+            L.occ1[cut.p >> 5] |= 1u << (cut.p & 31);
+            ends[row + ub + cut.k] = cut.last_use;
+            starts[row + ub + cut.j] = cut.p;
+            ends[row + ub + cut.j] = cut.ek;
+            active[row + ub + cut.j] = 1;
+          }
+        }
+      }
+      __syncthreads();
+      add_ranges<NT>(L, lay, ranges, *n_ranges, t);
+    }
+    build_maxima<NT>(L, lay, t);
+    base_viol = best.viol();
+    base_peak = best.peak();
+  }
+  if (t == 0) {
+    out_steps[blockIdx.x] = steps;
+    last_move[blockIdx.x] = chosen;
+  }
+}
 
 struct Merge { int c, below; };
 
@@ -195,6 +344,24 @@ __global__ __launch_bounds__(NT) void merge_kernel(GraphView g, int32_t* __restr
   if (t == 0) merges[blockIdx.x] = steps;
 }
 
+using DescendKernel = void (*)(GraphView, int32_t*, int32_t*, uint8_t*, int, int, moc_best_move*, int32_t*, int, MvLayout);
+
+template <int NT, bool LISTS>
+DescendKernel pick_descend(int C) {
+  switch (C) {
+    case 2: return descend_cuts_kernel<2, NT, LISTS>;
+    case 3: return descend_cuts_kernel<3, NT, LISTS>;
+    default: return descend_cuts_kernel<0, NT, LISTS>;
+  }
+}
+DescendKernel pick_descend(int C, int nt, bool lists) {
+  switch (nt) {
+    case 256: return lists ? pick_descend<256, true>(C) : pick_descend<256, false>(C);
+    case 512: return lists ? pick_descend<512, true>(C) : pick_descend<512, false>(C);
+    default: return lists ? pick_descend<1024, true>(C) : pick_descend<1024, false>(C);
+  }
+}
+
 using MergeKernel = void (*)(GraphView, int32_t*, int32_t*, uint8_t*, int, int, int32_t*, MvLayout);
 
 template <int NT, bool LISTS>
@@ -208,6 +375,32 @@ MergeKernel pick_merge(int C) {
 }
 
 }  // namespace
+
+int moc_queue_cut_descent(const moc_graph* g, int64_t B, int32_t* starts, int32_t* ends, uint8_t* active, int max_steps,
+                          int mode, moc_best_move* last_move, int32_t* out_steps, hipStream_t stream) {
+  const int n = g->view.n, m = g->view.m, T = g->view.T;
+  const auto layout = [&](int nt, int cap) { return mv_layout(T, n, m, descend_words(nt) + sift_words(n, cap), true, g->max_lds); };
+  // As many threads per candidate as the candidates that share a compute unit leave room for (a
+  // thread takes about 96 registers): a step is a chain of short phases, which more waves shorten,
+  // but a wave with nothing to do in a phase still takes its part of the barriers and the issue
+  // slots.  n = 442, 1024 walkers, keeping cuts: 1.0 ms with 256 threads, 1.3 with 512, 2.1 with
+  // 1024; n = 1000, 32 walkers: 0.63, 0.47, 0.46 ms.
+  const int64_t share = (B + g->num_cu - 1) / g->num_cu;
+  const int by_lds = g->max_lds / layout(256, 256).bytes;
+  const int nt = share <= 1 || by_lds <= 1 ? 1024 : share <= 2 || by_lds <= 2 ? 512 : 256;
+  // the lists of moves that pass the sieve: as long as costs no resident workgroup
+  const int want = (int)std::min<int64_t>({share, by_lds, 1024 / nt});
+  int cap = 2048;
+  while (cap > 256 && layout(nt, cap).bytes * std::max(want, 1) > g->max_lds) cap /= 2;
+  const MvLayout lay = layout(nt, cap);
+  if (lay.bytes > g->max_lds) return MOC_EOVERFLOW;
+  const DescendKernel kern = pick_descend(g->view.C, nt, lay.lists != 0);
+  int per_cu = 0;   // not used: the call is for the kernel's LDS limit
+  if (const int rc = moc_kernel_occupancy(g, reinterpret_cast<const void*>(kern), nt, lay.bytes, false, &per_cu)) return rc;
+  hipLaunchKernelGGL(kern, dim3((unsigned)B), dim3(nt), lay.bytes, stream, g->view, starts, ends, active, max_steps, mode,
+                     last_move, out_steps, cap, lay);
+  return MOC_OK;
+}
 
 int moc_queue_merges(const moc_graph* g, int64_t B, int32_t* starts, int32_t* ends, uint8_t* active, int max_steps, int K,
                      int32_t* out_merges, hipStream_t stream) {

@@ -77,3 +77,66 @@ def test_merges_follow_the_oracle(moc, n, C, K):
         assert (ga[b] == wa).all() and (gs[b] == ws).all() and (ge[b] == we).all(), b
     assert C == 1 or n < 4 or merges.max() > 0
     gh.free()
+
+
+@pytest.mark.parametrize("n,C,B,mode", [(2, 2, 6, 0), (9, 2, 6, 1), (63, 2, 9, 0), (64, 2, 9, 1), (65, 3, 9, 1), (129, 4, 6, 1), (50, 5, 6, 1),
+                                        (257, 2, 300, 1), (257, 2, 600, 0), (512, 3, 4, 1), (1100, 2, 3, 0)])
+def test_cuts_follow_the_oracle(moc, n, C, B, mode):
+    """The descent by cuts (mode 0) and by cuts that keep the inputs (mode 1): counts, rows and, for
+    mode 0, the last step's choice.  Bases with and without violations, batches on either side of
+    the lines between the workgroup sizes (the rows repeat beyond the first nine)."""
+    import torch
+    rng = np.random.default_rng(31 * n + C + mode)
+    g = random_graph(rng, n)
+    rows, steps = min(B, 9), 12 if n < 300 else 5
+    s, e, a = schedules(rng, g, C, rows, wild=True)
+    budget = int(0.8 * np.median(oracle.evaluate(g, 0, C, s, e, a)[::3, 0]))
+    pick = np.arange(B) % rows
+    gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, budget, C)
+    ds, de, da = to_dev(s[pick], e[pick], a[pick])
+    last = torch.full((B, 16), 0x55, dtype=torch.uint8, device="cuda")
+    if mode == 1:
+        count, merges = moc.moc_search_two_phase(gh, ds, de, da, steps, 0)
+        assert (merges.cpu().numpy() == 0).all()
+    else:
+        count = moc.moc_search_cuts(gh, ds, de, da, steps, work_best=last)
+    count, gs, ge, ga = count.cpu().numpy(), ds.cpu().numpy(), de.cpu().numpy(), da.cpu().numpy()
+    last = moc.results_to_numpy(last, moc.BEST_MOVE_DTYPE)
+    applied = 0
+    for r in range(rows):
+        k, ws, we, wa = oracle.search_cuts(g, budget, C, s[r], e[r], a[r], steps, mode=mode)
+        for b in range(r, B, rows):
+            assert count[b] == k, (b, count[b], k)
+            assert (ga[b] == wa).all() and (gs[b] == ws).all() and (ge[b] == we).all(), b
+            if mode == 0:   # a step that found nothing leaves no choice behind
+                assert (int(last[b]["move"]) < 0) == (k < steps), b
+        applied += k
+    assert applied > 0 or n < 60
+    gh.free()
+
+
+@pytest.mark.parametrize("mode", [0, 1])
+def test_cuts_with_more_moves_than_the_lists_hold(moc, mode):
+    """Chains of long edges across one peak: thousands of moves pass the sieve of a base without
+    violations, more than it has room for, and all of them are scored after all."""
+    from paper_2304_14463_amd.inputs import graph_from_edges
+    n, C = 900, 2
+    rng = np.random.default_rng(4)
+    half = n // 2
+    edges = sorted({(u, half + int(v)) for u in range(half) for v in rng.integers(0, n - half, 6)} | {(u, u + 1) for u in range(half)})
+    g = graph_from_edges(n, edges, rng.integers(1, 40, n), rng.integers(1, 9, n))
+    s = np.zeros((1, n * C), np.int32); e = s.copy(); a = np.zeros((1, n * C), np.uint8)
+    last = np.arange(n) * C
+    for u, v in edges:
+        last[u] = max(last[u], v * C)
+    s[0, ::C], e[0, ::C], a[0, ::C] = np.arange(n) * C, last, 1
+    gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, 1000, C)
+    ds, de, da = to_dev(s, e, a)
+    if mode == 1:
+        count, _ = moc.moc_search_two_phase(gh, ds, de, da, 3, 0)
+    else:
+        count = moc.moc_search_cuts(gh, ds, de, da, 3)
+    k, ws, we, wa = oracle.search_cuts(g, 1000, C, s[0], e[0], a[0], 3, mode=mode)
+    assert int(count[0]) == k and k > 0
+    assert (da[0].cpu().numpy() == wa).all() and (ds[0].cpu().numpy() == ws).all() and (de[0].cpu().numpy() == we).all()
+    gh.free()
