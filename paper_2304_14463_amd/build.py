@@ -27,10 +27,9 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-shared", "-fPIC",
 # Per source file.  The evaluation kernels are scheduled for instruction-level parallelism
 # rather than for occupancy (their workgroup sizes fix the waves per SIMD anyway): n = 5000,
 # C = 3 gains 1.7 points of HBM peak (64.4 -> 66.1 %; repeated on four machines), the other
-# evaluation workloads stay within what two runs differ by.  In the neighbourhood file the
-# toggles kernel gains 3 % and the cuts kernel under 1 % (both repeated), the neighbourhood
-# kernel itself does not move.  Decode and the staged evaluator stay within 1 % either way
-# and keep the default.
+# evaluation workloads stay within what two runs differ by.  The neighbourhood kernel does not
+# move; decode, the staged evaluator, toggles and cuts stay within 2 % either way and keep the
+# default.
 FILE_FLAGS = {"moc_eval.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
               "moc_neighbours.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
 

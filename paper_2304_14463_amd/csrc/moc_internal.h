@@ -93,16 +93,9 @@ int moc_eval_prepare(const moc_graph* g);
 // moc_eval_batch_noalloc; once per device.
 int moc_eval_static_setup(int device);
 
-// moc_search_cuts and the first phase of moc_search_two_phase: queues the kernel that applies up to
-// max_steps (>= 1) cuts to each of the B candidates (one workgroup each); mode as for the cuts
-// kernel; last_move receives the choice of a candidate's last step, out_steps the cuts applied.
-int moc_queue_cut_descent(const moc_graph* g, int64_t B, int32_t* starts, int32_t* ends, uint8_t* active, int max_steps,
-                          int mode, moc_best_move* last_move, int32_t* out_steps, hipStream_t stream);
-
-// The second phase of moc_search_two_phase: queues the kernel that applies up to max_steps merges
-// to each of the B candidates (one workgroup each) and writes how many it applied to out_merges.
-int moc_queue_merges(const moc_graph* g, int64_t B, int32_t* starts, int32_t* ends, uint8_t* active, int max_steps,
-                     int K, int32_t* out_merges, hipStream_t stream);
+// Whether the calls on cuts take this graph, with it as the current device's: MOC_OK, MOC_EDEVICE,
+// MOC_EINVAL (an edge (v,v)), MOC_EOVERFLOW.
+int moc_check_cuts(const moc_graph* g);
 
 int moc_set_hip_error(hipError_t e);  // records e, returns MOC_EHIP
 

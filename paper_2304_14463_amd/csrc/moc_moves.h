@@ -53,9 +53,10 @@ __device__ __forceinline__ void wave_lds_order() {
 // ------------------------------------------------------------------ the base in LDS
 constexpr int kBlk = 8;   // positions per block of the profile's range maxima (two 16-byte reads)
 
-// Word offsets.  The profile begins at 0; `table` holds, at level l and index i, the maximum over
-// the blocks i .. i + 2^l - 1; pre[i] the maximum over the blocks before i, suf[i] over the
-// blocks from i on.
+// Word offsets.  The profile begins at 0; `table` holds, at level l and index i <= blocks - 2^l, the
+// maximum over the blocks i .. i + 2^l - 1, level behind level (table_level); pre[i] the maximum
+// over the blocks before i, suf[i] over the blocks from i on.
+__host__ __device__ __forceinline__ int table_level(int level, int blocks) { return level * (blocks + 1) - (1 << level) + 1; }
 struct MvLayout {
   int blocks, levels, bit_words;
   int table, pre, suf, packed, occ1, occ2, peak_bits, peak_before, scratch, extra;
@@ -73,7 +74,7 @@ inline MvLayout mv_layout(int T, int n, int m, int extra_words, bool with_lists,
   while ((2 << (l.levels - 1)) <= l.blocks) ++l.levels;
   l.bit_words = 2 * ((T + 63) / 64);
   l.table = l.blocks * kBlk;
-  l.pre = l.table + l.levels * l.blocks;
+  l.pre = l.table + table_level(l.levels, l.blocks);
   l.suf = l.pre + l.blocks + 1;
   l.packed = (l.suf + l.blocks + 1 + 3) & ~3;
   l.occ1 = l.packed + ((T + 3) & ~3);
@@ -294,8 +295,9 @@ __device__ __forceinline__ void build_maxima(const BaseLds& L, const MvLayout& l
   if (wave == 0) {
     for (int l = 1; l < lay.levels; ++l) {
       const int half = 1 << (l - 1);
-      const int32_t* below = L.table + (l - 1) * blocks;
-      for (int x = lane; x + 2 * half <= blocks; x += kWave) L.table[l * blocks + x] = max(below[x], below[x + half]);
+      const int32_t* below = L.table + table_level(l - 1, blocks);
+      int32_t* here = L.table + table_level(l, blocks);
+      for (int x = lane; x + 2 * half <= blocks; x += kWave) here[x] = max(below[x], below[x + half]);
       wave_lds_order();
     }
   }
@@ -359,7 +361,7 @@ __device__ __forceinline__ InOut range_maxima(const BaseLds& L, int blocks, int 
   InOut r{0, 0};
   if (count > 0) {
     const int level = 31 - __clz(count);
-    const int32_t* row = L.table + level * blocks;
+    const int32_t* row = L.table + table_level(level, blocks);
     r.in = max(row[first], row[bh - (1 << level)]);
   }
   if constexpr (OUTSIDE) r.out = max(L.pre[bl], L.suf[bh + 1]);
@@ -385,7 +387,7 @@ __device__ __forceinline__ int count_reaching(const BaseLds& L, const MvLayout& 
   const int last = hi / kBlk;
   for (int b = lo / kBlk; b <= last; ++b) {
     for (int l = lay.levels - 1; l >= 0; --l)
-      if (b + (1 << l) <= last + 1 && L.table[l * lay.blocks + b] < bound) b += 1 << l;
+      if (b + (1 << l) <= last + 1 && L.table[table_level(l, lay.blocks) + b] < bound) b += 1 << l;
     if (b > last) break;
     const int4* const at = reinterpret_cast<const int4*>(L.profile + b * kBlk);
     const int4 x = at[0], y = at[1];

@@ -28,7 +28,7 @@
 // alone (fields that cannot win are left out), and with the table of scores (a
 // wave writes the rows of consecutive copies, the inactive ones filled in).
 // The adjacency lists are kept in LDS when that costs no resident workgroup.
-#include "moc_internal.h"
+#include "moc_moves.h"
 
 namespace {
 
@@ -86,13 +86,6 @@ struct NbLds {
   uint32_t* amask;      // bit k: copy k is active
   int32_t* scratch;   // 8 * kNW + 16
 };
-
-__device__ __forceinline__ bool live_of(uint32_t p) { return (p & 0xFFFFu) != 0xFFFFu; }
-__device__ __forceinline__ bool covers1(uint32_t pu, uint32_t x) { return (pu & 0xFFFFu) < x && (pu >> 16) >= x; }
-__device__ __forceinline__ uint32_t pack_copy(bool live, int s, int e) {
-  return live ? ((uint32_t)s | ((uint32_t)e << 16)) : MOC_DEAD;
-}
-__device__ __forceinline__ bool bit_at(const uint32_t* bits, int t) { return (bits[t >> 5] >> (t & 31)) & 1u; }
 
 struct AddOp { static __device__ int id() { return 0; } static __device__ int op(int a, int b) { return a + b; } };
 
@@ -841,705 +834,6 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
   }
 }
 
-
-
-// ---------------------------------------------------------------------------------------------
-// moc_eval_toggles: every candidate that differs from the base in one active flag.  The base
-// is staged as above (packed intervals, profile with prefix and suffix maxima, start bitmaps);
-// the maximum of the profile over a copy's whole interval comes from maxima over blocks of 32
-// positions.  One lane per copy: violations' = violations + f(copy with the flag flipped) -
-// f(copy as it is) + what Eq. (6) and Eq. (7) see of the flip, with f = node_part (see
-// toggle_delta); peak' from the interval the copy gives up or takes; duration' = duration -+ w_v.
-// f(copy with its active flag flipped) - f(copy as it is), f = node_part, in one walk over
-// the node's edges: the flip makes a well-formed copy leave or join the live copies of v
-// (an ill-formed one only starts or stops counting as such).
-__device__ __forceinline__ int toggle_delta(const Adj& g, int C, const uint32_t* __restrict__ packed, int v, int i,
-                                            bool was, bool well, int s, int e) {
-  if (!well) return was ? -1 : 1;   // Eq. (2)/(8)
-  const int sign = was ? -1 : 1;    // the copy leaves (-1) or joins (+1)
-  // Eq. (3) among the live copies of v, with and without copy i
-  int with = 0, without = 0, end_with = -1, end_without = -1;
-  for (int j = 0; j < C; ++j) {
-    const uint32_t p = j == i ? pack_copy(true, s, e) : packed[v * C + j];
-    if (!live_of(p)) continue;
-    const int start = (int)(p & 0xFFFFu), end = (int)(p >> 16);
-    with += end_with > start ? 1 : 0;
-    end_with = end;
-    if (j != i) {
-      without += end_without > start ? 1 : 0;
-      end_without = end;
-    }
-  }
-  int delta = sign * (with - without);
-  // Eq. (5), the copy as consumer: its inputs count while it is live
-  for (int q = g.in_ptr[v]; q < g.in_ptr[v + 1]; ++q) {
-    const int u = g.in_idx[q];
-    bool cov = false;
-    for (int j = 0; j < C; ++j) cov = cov || covers1(packed[u * C + j], (uint32_t)s);
-    delta += cov ? 0 : sign;
-  }
-  // Eq. (5), node v as provider: the consumer copies that only this copy covers
-  for (int q = g.out_ptr[v]; q < g.out_ptr[v + 1]; ++q) {
-    const int w = g.out_idx[q];
-    for (int jw = 0; jw < C; ++jw) {
-      const int x = (int)(packed[w * C + jw] & 0xFFFFu);
-      if (x == 0xFFFF || !(s < x && x <= e)) continue;
-      bool others = false;
-      for (int j = 0; j < C; ++j) others = others || (j != i && covers1(packed[v * C + j], (uint32_t)x));
-      delta -= others ? 0 : sign;
-    }
-  }
-  return delta;
-}
-
-// max(a[from..to]), from <= to; eight reads in flight at a time (re-reading the last element
-// changes no maximum).
-__device__ __forceinline__ int range_max8(const int32_t* a, int from, int to) {
-  int m = 0;
-  for (int t = from; t <= to; t += 8) {
-    int x[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) x[j] = a[min(t + j, to)];
-    m = max(max(max(m, x[0]), max(x[1], x[2])), max(max(x[3], x[4]), max(max(x[5], x[6]), x[7])));
-  }
-  return m;
-}
-
-// Maxima of the profile over blocks of 32 positions, as a table for range queries:
-// level l holds, at i, the maximum over the blocks i .. i + 2^l - 1 (level 0: the blocks).
-struct BlockMax {
-  const int32_t* level0;
-  int blocks;
-  __device__ __forceinline__ int over(int first, int last) const {   // blocks [first, last), first < last
-    const int l = 31 - __clz(last - first);
-    const int32_t* row = level0 + l * blocks;
-    return max(row[first], row[last - (1 << l)]);
-  }
-};
-
-// max(profile[s..e]), s <= e: whole blocks from the table, the rest position by position.
-__device__ __forceinline__ int interval_max(const int32_t* profile, const BlockMax& bm, int s, int e) {
-  if (e - s < 64) return range_max8(profile, s, e);
-  const int first_block = (s + 31) >> 5, last_block = (e + 1) >> 5;   // whole blocks [first, last): at least one
-  int top = bm.over(first_block, last_block);
-  if (s < 32 * first_block) top = max(top, range_max8(profile, s, 32 * first_block - 1));
-  if (32 * last_block <= e) top = max(top, range_max8(profile, 32 * last_block, e));
-  return top;
-}
-
-// Number of x in [s, e] with profile[x] >= bound.  Whole blocks whose maximum stays below the
-// bound are passed over: few blocks come near the peak, and the ranges are long.
-__device__ __forceinline__ int count_reaching(const int32_t* profile, const BlockMax& bm, int s, int e, int bound) {
-  int cnt = 0;
-  const int first_block = (s + 31) >> 5, last_block = (e + 1) >> 5;   // whole blocks [first, last)
-  if (first_block >= last_block) {
-    for (int x = s; x <= e; ++x) cnt += profile[x] >= bound ? 1 : 0;
-    return cnt;
-  }
-  for (int x = s; x < 32 * first_block; ++x) cnt += profile[x] >= bound ? 1 : 0;
-  for (int blk = first_block; blk < last_block; ++blk) {
-    if (bm.level0[blk] < bound) continue;
-    for (int x = 32 * blk; x < 32 * blk + 32; ++x) cnt += profile[x] >= bound ? 1 : 0;
-  }
-  for (int x = 32 * last_block; x <= e; ++x) cnt += profile[x] >= bound ? 1 : 0;
-  return cnt;
-}
-
-// Positions at which the base's profile reaches its peak, countable over any range.
-struct PeakCount {
-  const uint32_t* bits;
-  const int32_t* before;   // per word: such positions in the words below it
-  int total;
-  __device__ __forceinline__ int up_to(int x) const {   // in [0, x]
-    return before[x >> 5] + (int)__popc(bits[x >> 5] & (0xFFFFFFFFu >> (31 - (x & 31))));
-  }
-  __device__ __forceinline__ int within(int lo, int hi) const {   // in [lo, hi], 1 <= lo <= hi
-    return up_to(hi) - up_to(lo - 1);
-  }
-};
-
-// The cut-and-recompute move for the in-edge (u, v) and copy i of the consumer (see
-// moc_eval_cuts in moccasin.h): copy k of u, the last-starting live copy that covers the
-// consumer's start t, keeps [s_k, last use before p]; the lowest inactive copy j of u takes
-// [p, e_k], p the last position in (s_k, t) where no live copy starts and all inputs of u are
-// held.  Only Eq. (3) among the copies of u and Eq. (7) (when j is copy 0) can change: every
-// consumer that k covered is covered by one of the two pieces, since no live consumer starts
-// in (last use, p], and the new computation finds its inputs by the choice of p.  The profile
-// loses m_u on (last use, p).
-struct Cut {
-  int k, j;        // copy of u that is cut, copy of u that becomes active
-  int sk, ek;      // interval of copy k as it stands
-  int p;           // start of the recomputation
-  int last_use;    // new end of copy k
-};
-
-// Which copies and positions the move for producer u and the given consumer copy involves;
-// false if it is not applicable.  Reads the packed copies and the start bitmap of L.
-// Is node w held at position x (a live copy with s < x <= e)?
-__device__ __forceinline__ bool held_at(int C, const uint32_t* __restrict__ packed, int w, int x) {
-  bool held = false;
-  for (int q = 0; q < C; ++q) held = held || covers1(packed[w * C + q], (uint32_t)x);
-  return held;
-}
-
-// The live copy of w with the largest end below x, the highest index among equals; -1 if none.
-__device__ __forceinline__ int copy_to_keep(int C, const uint32_t* __restrict__ packed, int w, int x, int* end_out) {
-  int best = -1, best_end = -1;
-  for (int q = 0; q < C; ++q) {
-    const uint32_t pw = packed[w * C + q];
-    if (live_of(pw) && (int)(pw >> 16) < x && (int)(pw >> 16) >= best_end) {
-      best = q;
-      best_end = (int)(pw >> 16);
-    }
-  }
-  *end_out = best_end;
-  return best;
-}
-
-// Calls f(w, q, end) for every predecessor w of u that is not held at p: q is the copy of w that
-// the move keeps until p, `end` its end as it stands.  A predecessor listed several times is
-// visited once (after the first visit it is held).
-template <typename Fn>
-__device__ __forceinline__ void for_each_kept_input(const Adj& g, int C, const uint32_t* __restrict__ packed, int u,
-                                                    int p, Fn f) {
-  const int y0 = g.in_ptr[u], y1 = g.in_ptr[u + 1];
-  for (int y = y0; y < y1; ++y) {
-    const int w = g.in_idx[y];
-    if (held_at(C, packed, w, p)) continue;
-    bool seen = false;
-    for (int z = y0; z < y; ++z) seen = seen || g.in_idx[z] == w;
-    if (seen) continue;
-    int end;
-    const int q = copy_to_keep(C, packed, w, p, &end);
-    f(w, q, end);
-  }
-}
-
-// mode 0: the recomputation waits where all inputs of u are held.  mode 1: it goes to the last free
-// position at which every input is held or has an earlier copy that can be kept until there.
-__device__ __forceinline__ bool find_cut(const Adj& g, int C, const NbLds& L, const uint8_t* active_row, int u,
-                                         int consumer_copy, int mode, Cut* cut) {
-  const uint32_t mine = L.packed[consumer_copy];
-  if (!live_of(mine)) return false;
-  const uint32_t t = mine & 0xFFFFu;
-  int k = -1, j = -1, sk = -1, ek = 0;
-  for (int q = 0; q < C; ++q) {
-    const uint32_t pu = L.packed[u * C + q];
-    if (covers1(pu, t) && (int)(pu & 0xFFFFu) > sk) {
-      k = q;
-      sk = (int)(pu & 0xFFFFu);
-      ek = (int)(pu >> 16);
-    }
-    if (j < 0 && active_row[u * C + q] == 0) j = q;
-  }
-  if (k < 0 || j < 0) return false;
-  // the last position below t that is free (by words of the start bitmap) and at which every
-  // input of u is held; where an input is missing, the search resumes at the end of the
-  // nearest earlier copy of that input
-  int p = -1;
-  for (int hi = (int)t - 1; hi > sk;) {
-    int pos = -1;
-    for (int x = hi; x > sk;) {
-      const uint32_t free_bits = ~L.occ1[x >> 5] & (0xFFFFFFFFu >> (31 - (x & 31)));
-      if (free_bits) {
-        pos = (x & ~31) + 31 - __clz(free_bits);
-        break;
-      }
-      x = (x & ~31) - 1;
-    }
-    if (pos <= sk) return false;
-    if (mode == 1) {
-      bool ok = true;
-      for (int y = g.in_ptr[u]; y < g.in_ptr[u + 1] && ok; ++y) {
-        const int w = g.in_idx[y];
-        int end;
-        ok = held_at(C, L.packed, w, pos) || copy_to_keep(C, L.packed, w, pos, &end) >= 0;
-      }
-      if (ok) {
-        p = pos;
-        break;
-      }
-      hi = pos - 1;
-      continue;
-    }
-    int resume = pos;
-    for (int y = g.in_ptr[u]; y < g.in_ptr[u + 1]; ++y) {
-      const int w = g.in_idx[y];
-      bool held = false;
-      int below = -1;
-      for (int q = 0; q < C; ++q) {
-        const uint32_t pw = L.packed[w * C + q];
-        held = held || covers1(pw, (uint32_t)pos);
-        if (live_of(pw) && (int)(pw >> 16) < pos) below = max(below, (int)(pw >> 16));
-      }
-      if (!held) resume = min(resume, below);
-    }
-    if (resume == pos) {
-      p = pos;
-      break;
-    }
-    hi = resume;
-  }
-  if (p <= sk) return false;
-  int last_use = sk;
-  for (int y = g.out_ptr[u]; y < g.out_ptr[u + 1]; ++y) {
-    const int w = g.out_idx[y];
-    for (int q = 0; q < C; ++q) {
-      const int x = (int)(L.packed[w * C + q] & 0xFFFFu);   // 0xFFFF (not live) is above every p
-      if (x > sk && x < p) last_use = max(last_use, x);
-    }
-  }
-  *cut = Cut{k, j, sk, ek, p, last_use};
-  return true;
-}
-
-__device__ __forceinline__ bool score_cut(const Adj& g, int C, int T, const NbLds& L, const BlockMax& block_max,
-                                          const uint8_t* __restrict__ active_row, int u, int consumer_copy,
-                                          int base_viol, int base_peak, const PeakCount& at_peak, int mode,
-                                          int* viol_out, int* peak_out, int* at_peak_out) {
-  Cut cut;
-  if (!find_cut(g, C, L, active_row, u, consumer_copy, mode, &cut)) return false;
-  const int k = cut.k, j = cut.j, sk = cut.sk, ek = cut.ek, p = cut.p, last_use = cut.last_use;
-  int vv = base_viol;
-  // Eq. (3) among the live copies of u, before and after
-  int before = 0, after = 0, end_before = -1, end_after = -1;
-  for (int q = 0; q < C; ++q) {
-    const uint32_t pu = L.packed[u * C + q];
-    if (live_of(pu)) {
-      before += end_before > (int)(pu & 0xFFFFu) ? 1 : 0;
-      end_before = (int)(pu >> 16);
-    }
-    const uint32_t now = q == k ? pack_copy(true, sk, last_use) : q == j ? pack_copy(true, p, ek) : pu;
-    if (live_of(now)) {
-      after += end_after > (int)(now & 0xFFFFu) ? 1 : 0;
-      end_after = (int)(now >> 16);
-    }
-  }
-  vv += after - before;
-  // Eq. (5): the inputs of the new computation are held at p by the choice of p
-  if (j == 0) --vv;   // Eq. (7)
-  int pk = base_peak, at = at_peak.total;
-  // mode 1: the inputs that are kept until p.  lo = the lowest position whose memory changes.
-  // The first kKept of them are noted (end, size) for the walk below, which looks at each of them
-  // once per step: finding them again every time costs a pass over the in-edges of u with
-  // several reads per edge.
-  constexpr int kKept = 8;
-  int kept_end[kKept], kept_size[kKept];
-#pragma unroll
-  for (int s = 0; s < kKept; ++s) { kept_end[s] = 0; kept_size[s] = 0; }
-  int n_kept = 0, lo = last_use + 1;
-  if (mode == 1)
-    for_each_kept_input(g, C, L.packed, u, p, [&](int w, int q, int end) {
-      const int m_w = g.size_of(w);
-#pragma unroll
-      for (int s = 0; s < kKept; ++s)
-        if (s == n_kept) { kept_end[s] = end; kept_size[s] = m_w; }
-      ++n_kept;
-      lo = min(lo, end + 1);
-      // Eq. (3): the kept copy against the next live copy of its node
-      for (int c = q + 1; c < C; ++c) {
-        const uint32_t nx = L.packed[w * C + c];
-        if (live_of(nx)) {
-          const int sn = (int)(nx & 0xFFFFu);
-          vv += (p > sn ? 1 : 0) - (end > sn ? 1 : 0);
-          break;
-        }
-      }
-      // Eq. (5): consumers of w that start in (end, p] are covered now.  None of them was: a copy
-      // of w that covered a position in (end, p] would end at or after p and cover p as well
-      // (w would be held there), or end in (end, p), and `end` is the largest end below p.
-      for (int y = g.out_ptr[w]; y < g.out_ptr[w + 1]; ++y) {
-        const int x = g.out_idx[y];
-        for (int c = 0; c < C; ++c) {
-          const int sx = (int)(L.packed[x * C + c] & 0xFFFFu);   // 0xFFFF if not live: above every p
-          if (sx > end && sx <= p) --vv;
-        }
-      }
-    });
-  if (n_kept == 0) {
-    if (last_use + 1 <= p - 1) {
-      const int top = interval_max(L.profile, block_max, last_use + 1, p - 1);
-      const int sz = g.size_of(u);
-      pk = max(top - sz, max(L.pmax[last_use], L.smax[p]));
-      // positions still at the base's peak: those outside the range (all, if nothing is taken away)
-      at = pk < base_peak ? 0 : at - (sz > 0 ? at_peak.within(last_use + 1, p - 1) : 0);
-    }
-  } else {
-    // The memory changes on [lo, p]: -m_u on (last_use, p), +m_w on (end_w, p] for every kept
-    // input.  All these stretches end at p or just before it, so the change is a step function
-    // whose steps are at last_use + 1, at the end_w + 1 and at p: walk it step by step (the next
-    // step is found by a pass over the kept inputs; there are few of them).
-    const int sz = g.size_of(u);
-    int top = max(L.pmax[lo - 1], L.smax[p + 1]);
-    int still = at_peak.total - at_peak.within(max(lo, 1), p) - (lo == 0 && bit_at(at_peak.bits, 0) ? 1 : 0);
-    for (int from = lo; from <= p;) {
-      int next = p + 1, add = 0;   // the step after `from`, and the change on [from, next)
-      if (from < last_use + 1) next = min(next, last_use + 1);
-      if (from < p) next = min(next, p);
-      if (n_kept <= kKept) {
-#pragma unroll
-        for (int s = 0; s < kKept; ++s) {
-          if (s < n_kept) {
-            if (kept_end[s] + 1 > from) next = min(next, kept_end[s] + 1);
-            else add += kept_size[s];
-          }
-        }
-      } else {
-        for_each_kept_input(g, C, L.packed, u, p, [&](int w, int, int end) {
-          if (end + 1 > from) next = min(next, end + 1);
-          else add += g.size_of(w);
-        });
-      }
-      if (from >= last_use + 1 && from < p) add -= sz;
-      const int here = interval_max(L.profile, block_max, from, next - 1);
-      top = max(top, here + add);
-      // positions of [from, next) that reach the base's peak afterwards
-      if (add == 0) {
-        still += at_peak.within(max(from, 1), next - 1) + (from == 0 && bit_at(at_peak.bits, 0) ? 1 : 0);
-      } else if (add > 0 && here + add >= base_peak) {
-        still += count_reaching(L.profile, block_max, from, next - 1, base_peak - add);
-      }
-      from = next;
-    }
-    pk = top;
-    at = pk < base_peak ? 0 : still;
-  }
-  *viol_out = vv;
-  *peak_out = pk;
-  *at_peak_out = at;
-  return true;
-}
-
-struct TgLayout {
-  int T_pad, bit_words, blocks;
-  int levels;    // of the table of block maxima: 2^(levels - 1) <= blocks
-  int adj_off;   // word offset of the adjacency lists and sizes in LDS, 0 if they stay in global memory
-  int bytes;
-};
-
-TgLayout tg_layout(int T, int n, int m, int max_lds) {
-  TgLayout l;
-  l.T_pad = (T + 3) & ~3;
-  l.bit_words = (T + 31) / 32;
-  l.blocks = (T + 31) / 32;
-  l.levels = 1;
-  while ((2 << (l.levels - 1)) <= l.blocks) ++l.levels;
-  // profile, prefix max, suffix max (with sentinels), packed, block maxima, two start bitmaps, the
-  // bitmap of the positions at the peak with its running count per word, scratch, and a queue
-  // of 128 moves per wave
-  const int words = 4 * l.T_pad + 8 + l.levels * l.blocks + 4 * l.bit_words + 8 * kNW + 16 + 2 * kWave * kNW;
-  l.adj_off = 0;
-  l.bytes = 4 * words;
-  // A lane walks its node's edges one after the other: from LDS whenever the lists fit (the
-  // latency of global memory per edge costs more than the second workgroup per CU brings).
-  const int with_adj = 4 * (words + 2 * (n + 1) + 2 * m + n);
-  if (with_adj <= max_lds) {
-    l.adj_off = words;
-    l.bytes = with_adj;
-  }
-  return l;
-}
-
-template <bool ADJ_LDS, bool CUTS>
-__global__ __launch_bounds__(kNT) void toggles_kernel(GraphView g, int64_t B, const int32_t* __restrict__ starts,
-                                                      const int32_t* __restrict__ ends,
-                                                      const uint8_t* __restrict__ active,
-                                                      moc_toggle_score* __restrict__ out,
-                                                      moc_best_move* __restrict__ out_best, int improving,
-                                                      int mode, TgLayout lay) {
-  extern __shared__ uint32_t nb_raw[];
-  NbLds L{};
-  L.profile = reinterpret_cast<int32_t*>(nb_raw);
-  L.pmax = L.profile + lay.T_pad + 4;   // pmax[-1] = 0
-  L.smax = L.pmax + lay.T_pad;          // smax[T] = 0
-  L.packed = reinterpret_cast<uint32_t*>(L.smax + lay.T_pad + 4);
-  int32_t* const block_max = reinterpret_cast<int32_t*>(L.packed + lay.T_pad);
-  L.occ1 = reinterpret_cast<uint32_t*>(block_max + lay.levels * lay.blocks);
-  const BlockMax block_table{block_max, lay.blocks};
-  L.occ2 = L.occ1 + lay.bit_words;
-  uint32_t* const peak_bits = L.occ2 + lay.bit_words;        // bit t: the profile reaches the base's peak at t
-  int32_t* const peak_before = reinterpret_cast<int32_t*>(peak_bits + lay.bit_words);   // such positions in earlier words
-  L.scratch = reinterpret_cast<int32_t*>(peak_before + lay.bit_words);
-  int32_t* const counts = L.scratch + 8 * kNW;   // [0] base violations, [1] base duration
-  int32_t* const queue = counts + 16;            // 2 * kWave moves per wave (the descent's sieve)
-  const int tid = threadIdx.x;
-  const int T = g.T, C = g.C;
-  Adj A{g.in_ptr, g.in_idx, g.out_ptr, g.out_idx, reinterpret_cast<const int32_t*>(g.size_dur), 2};
-  if constexpr (ADJ_LDS) {
-    int32_t* a = reinterpret_cast<int32_t*>(nb_raw) + lay.adj_off;
-    int32_t* const sizes = a + 2 * (g.n + 1) + 2 * g.m;
-    for (int x = tid; x <= g.n; x += kNT) { a[x] = g.in_ptr[x]; a[g.n + 1 + g.m + x] = g.out_ptr[x]; }
-    for (int x = tid; x < g.m; x += kNT) { a[g.n + 1 + x] = g.in_idx[x]; a[2 * (g.n + 1) + g.m + x] = g.out_idx[x]; }
-    for (int x = tid; x < g.n; x += kNT) sizes[x] = g.size_dur[x].x;
-    A = Adj{a, a + g.n + 1, a + g.n + 1 + g.m, a + 2 * (g.n + 1) + g.m, sizes, 1};
-    __syncthreads();
-  }
-
-  for (int64_t b = blockIdx.x; b < B; b += gridDim.x) {
-    const int64_t row = b * T;
-    // ---- the base: copies, deltas, starts.  The first kAhead * kNT copies are asked for before
-    // the arrays are cleared, all at once and without conditions (as in the kernel above).
-    constexpr int kAhead = 4;
-    int ahead_s[kAhead], ahead_e[kAhead];
-    uint32_t ahead_a[kAhead];
-    int2 ahead_sd[kAhead];
-    {
-      const char* const s_row = reinterpret_cast<const char*>(starts + row);
-      const char* const e_row = reinterpret_cast<const char*>(ends + row);
-      const char* const a_row = reinterpret_cast<const char*>(active + row);
-      int t = tid;   // offsets formed here for every base, not kept in registers across the bases
-      asm volatile("" : "+v"(t));
-#pragma unroll
-      for (int j = 0; j < kAhead; ++j) {
-        const uint32_t k = (uint32_t)min(j * kNT + t, T - 1);
-        ahead_s[j] = *reinterpret_cast<const int32_t*>(s_row + 4u * k);
-        ahead_e[j] = *reinterpret_cast<const int32_t*>(e_row + 4u * k);
-        ahead_a[j] = *reinterpret_cast<const uint8_t*>(a_row + k);
-        ahead_sd[j] = g.size_dur[k / (uint32_t)C];
-      }
-    }
-    for (int t = tid; t < T; t += kNT) L.profile[t] = 0;
-    for (int w = tid; w < 2 * lay.bit_words; w += kNT) L.occ1[w] = 0;
-    if (tid < 2) counts[tid] = 0;
-    if (tid == 0) { L.pmax[-1] = 0; L.smax[T] = 0; }
-    __syncthreads();
-    int viol = 0, nlive = 0, dur = 0;
-    auto stage = [&](int k, int s, int e, uint32_t flag, int2 sd) {
-      const bool act = flag != 0;
-      const bool live = act && (uint32_t)s <= (uint32_t)e && (uint32_t)e < (uint32_t)T;
-      const int v = k / C;
-      L.packed[k] = pack_copy(live, s, e);
-      if (k == v * C && !act) ++viol;   // Eq. (7)
-      if (act) dur += sd.y;             // Eq. (1)
-      if (live) {
-        ++nlive;
-        const int sz = sd.x;
-        atomicAdd(&L.profile[s], sz);
-        if (e + 1 < T) atomicSub(&L.profile[e + 1], sz);
-        const uint32_t bit = 1u << (s & 31);
-        const uint32_t old = atomicOr(&L.occ1[s >> 5], bit);
-        if (old & bit) atomicOr(&L.occ2[s >> 5], bit);
-      }
-    };
-#pragma unroll
-    for (int j = 0; j < kAhead; ++j) {
-      const int k = j * kNT + tid;
-      if (k < T) stage(k, ahead_s[j], ahead_e[j], ahead_a[j], ahead_sd[j]);
-    }
-    for (int k = kAhead * kNT + tid; k < T; k += kNT)
-      stage(k, starts[row + k], ends[row + k], active[row + k], g.size_dur[k / C]);
-    __syncthreads();
-    block_scan<AddOp, false>(L.profile, L.profile, T, L.scratch, tid);   // Eq. (4) per position
-    block_max_both_ways(L.profile, L.pmax, L.smax, T, L.scratch, tid);
-    for (int x = tid; x < lay.blocks; x += kNT) {
-      int m = 0;
-      for (int t = 32 * x; t < min(32 * x + 32, T); ++t) m = max(m, L.profile[t]);
-      block_max[x] = m;
-    }
-    for (int l = 1; l < lay.levels; ++l) {
-      __syncthreads();
-      const int half = 1 << (l - 1);
-      const int32_t* below = block_max + (l - 1) * lay.blocks;
-      for (int x = tid; x + 2 * half <= lay.blocks; x += kNT) block_max[l * lay.blocks + x] = max(below[x], below[x + half]);
-    }
-    // ---- the violations of the base, each instance once (as pass 1 of the kernel above)
-    for (int k = tid; k < T; k += kNT) {
-      const uint32_t mine = L.packed[k];
-      if (!live_of(mine)) {
-        viol += active[row + k] != 0 ? 1 : 0;   // Eq. (2)/(8)
-        continue;
-      }
-      const int v = k / C, i = k - v * C;
-      const int s = (int)(mine & 0xFFFFu), e = (int)(mine >> 16);
-      for (int j = i + 1; j < C; ++j) {   // Eq. (3)
-        const uint32_t p = L.packed[v * C + j];
-        if (live_of(p)) {
-          viol += e > (int)(p & 0xFFFFu) ? 1 : 0;
-          break;
-        }
-      }
-      for (int q = A.in_ptr[v]; q < A.in_ptr[v + 1]; ++q) {   // Eq. (5)
-        const int u = A.in_idx[q];
-        bool cov = false;
-        for (int j = 0; j < C; ++j) cov = cov || covers1(L.packed[u * C + j], (uint32_t)s);
-        viol += cov ? 0 : 1;
-      }
-    }
-    int distinct = 0;
-    for (int w = tid; w < lay.bit_words; w += kNT) distinct += __popc(L.occ1[w]);
-    atomicAdd(&counts[0], viol + nlive - distinct);   // Eq. (6): live copies - distinct starts
-    atomicAdd(&counts[1], dur);
-    __syncthreads();
-    const int base_viol = counts[0], base_dur = counts[1], base_peak = L.pmax[T - 1];
-
-    if constexpr (CUTS) {
-      // ---- where the base is at its peak: a wave takes 64 positions at a time (two words of
-      // the bitmap by one ballot), then one wave turns the words' counts into running counts
-      {
-        const int lane = tid & (kWave - 1), wave = tid / kWave;
-        for (int t0 = wave * kWave; t0 < 32 * lay.bit_words; t0 += kNT) {
-          const int t = t0 + lane;
-          const uint64_t hit = __ballot(t < T && L.profile[t] == base_peak);
-          if (lane == 0) {
-            peak_bits[t0 >> 5] = (uint32_t)hit;
-            if ((t0 >> 5) + 1 < lay.bit_words) peak_bits[(t0 >> 5) + 1] = (uint32_t)(hit >> 32);
-          }
-        }
-        __syncthreads();
-        if (wave == 0) {
-          int carry = 0;
-          for (int w0 = 0; w0 < lay.bit_words; w0 += kWave) {
-            const int w = w0 + lane;
-            const int mine = w < lay.bit_words ? (int)__popc(peak_bits[w]) : 0;
-            int inc = mine;
-#pragma unroll
-            for (int off = 1; off < kWave; off <<= 1) {
-              const int o = __shfl_up(inc, off);
-              if (lane >= off) inc += o;
-            }
-            if (w < lay.bit_words) peak_before[w] = carry + inc - mine;
-            carry += __shfl(inc, kWave - 1);
-          }
-        }
-        __syncthreads();
-      }
-      const PeakCount at_peak{peak_bits, peak_before,
-                              peak_before[lay.bit_words - 1] + (int)__popc(peak_bits[lay.bit_words - 1])};
-      // ---- one lane per in-edge and copy of its consumer; the best move is the applicable one
-      // that minimises (violations, peak, positions left at the base's peak, index)
-      const int64_t out_row = b * ((int64_t)g.m * C);
-      uint32_t best_viol = 0xFFFFFFFFu, best_peak = 0xFFFFFFFFu;
-      int best_at = 0x7FFFFFFF, best_q = -1;
-      auto take = [&](uint32_t ov, uint32_t op, int oa, int oq) {
-        if (oq < 0) return;
-        if (best_q < 0 || ov < best_viol ||
-            (ov == best_viol &&
-             (op < best_peak || (op == best_peak && (oa < best_at || (oa == best_at && oq < best_q)))))) {
-          best_viol = ov;
-          best_peak = op;
-          best_at = oa;
-          best_q = oq;
-        }
-      };
-      auto score = [&](int q) {
-        const int x = q / C, i = q - x * C;
-        const int u = A.in_idx[x];
-        const int consumer_copy = (int)(g.edge_pair_c[x] >> 16) + i;
-        moc_toggle_score sc{-1, -1, 0};
-        int vv, pk, at;
-        if (score_cut(A, C, T, L, block_table, active + row, u, consumer_copy, base_viol, base_peak, at_peak, mode, &vv,
-                      &pk, &at)) {
-          sc.violations = vv;
-          sc.peak = pk;
-          sc.duration = (int64_t)base_dur + g.size_dur[u].y;
-          take((uint32_t)vv, (uint32_t)pk, at, q);
-        }
-        if (out) out[out_row + q] = sc;
-      };
-      const int n_moves = g.m * C;
-      {
-        // Most moves are not applicable (the consumer's copy is not live, or no copy of the
-        // producer covers it), and scoring is long: each wave sifts its moves by that test, keeps
-        // the survivors in a queue of its own and scores them 64 at a time; the others get their
-        // "not applicable" score at once.  A descent step from a candidate without violations
-        // can, beyond that, only take a move that lowers the peak or the number of positions
-        // reaching it: one with such a position inside (s_k, t), which contains the range the
-        // move frees; the sieve then lets only those through.
-        const bool sift_peak = improving && !out && base_viol == 0;
-        const int lane = tid & (kWave - 1), wave = tid / kWave;
-        int32_t* const mine_q = queue + wave * (2 * kWave);
-        int queued = 0;
-        for (int q0 = wave * kWave; q0 < n_moves; q0 += kNT) {
-          const int q = q0 + lane;
-          bool keep = false;
-          if (q < n_moves) {
-            const int x = q / C, i = q - x * C;
-            const int u = A.in_idx[x];
-            const uint32_t consumer = L.packed[(int)(g.edge_pair_c[x] >> 16) + i];
-            if (live_of(consumer)) {
-              const uint32_t t = consumer & 0xFFFFu;
-              int sk = -1;
-              for (int c = 0; c < C; ++c) {
-                const uint32_t pu = L.packed[u * C + c];
-                if (covers1(pu, t)) sk = max(sk, (int)(pu & 0xFFFFu));
-              }
-              keep = sk >= 0 && (!sift_peak || (sk + 1 <= (int)t - 1 && at_peak.within(sk + 1, (int)t - 1) > 0));
-            }
-            if (!keep && out) out[out_row + q] = moc_toggle_score{-1, -1, 0};
-          }
-          const uint64_t kept = __ballot(keep);
-          if (keep) mine_q[queued + __popcll(kept & ((1ull << lane) - 1))] = q;
-          queued += __popcll(kept);
-          __builtin_amdgcn_wave_barrier();
-          if (queued >= kWave) {
-            queued -= kWave;
-            score(mine_q[queued + lane]);
-            __builtin_amdgcn_wave_barrier();
-          }
-        }
-        if (lane < queued) score(mine_q[lane]);
-      }
-      if (out_best) {
-#pragma unroll
-        for (int off = kWave / 2; off > 0; off >>= 1)
-          take(__shfl_xor(best_viol, off), __shfl_xor(best_peak, off), __shfl_xor(best_at, off),
-               __shfl_xor(best_q, off));
-        __syncthreads();   // the scratch words below were last read by the scans of the staging
-        if ((tid & (kWave - 1)) == 0) {
-          L.scratch[4 * (tid / kWave)] = (int)best_viol;
-          L.scratch[4 * (tid / kWave) + 1] = (int)best_peak;
-          L.scratch[4 * (tid / kWave) + 2] = best_at;
-          L.scratch[4 * (tid / kWave) + 3] = best_q;
-        }
-        __syncthreads();
-        if (tid == 0) {
-          best_q = -1;
-          for (int w = 0; w < kNW; ++w)
-            take((uint32_t)L.scratch[4 * w], (uint32_t)L.scratch[4 * w + 1], L.scratch[4 * w + 2],
-                 L.scratch[4 * w + 3]);
-          // a descent step takes the move only if it lowers (violations, max(peak, M)) or, above
-          // the budget with both unchanged, leaves fewer positions at the peak
-          if (improving && best_q >= 0) {
-            const int64_t now = max((int64_t)base_peak, g.budget), then = max((int64_t)best_peak, g.budget);
-            const bool better = (int)best_viol < base_viol ||
-                                ((int)best_viol == base_viol &&
-                                 (then < now || (then == now && base_peak > g.budget && best_at < at_peak.total)));
-            if (!better) best_q = -1;
-          }
-          moc_best_move bm{best_q, best_q < 0 ? 0 : (int)best_viol, best_q < 0 ? 0 : (int64_t)best_peak};
-          out_best[b] = bm;
-        }
-      }
-      __syncthreads();
-      continue;
-    }
-    // ---- one lane per copy
-    for (int k = tid; k < T; k += kNT) {
-      const int v = k / C, i = k - v * C;
-      const int s = starts[row + k], e = ends[row + k];
-      const bool was = active[row + k] != 0;
-      const bool well = (uint32_t)s <= (uint32_t)e && (uint32_t)e < (uint32_t)T;
-      const bool live_old = was && well, live_new = !was && well;
-      int vv = base_viol + toggle_delta(A, C, L.packed, v, i, was, well, s, e);
-      if (live_old && bit_at(L.occ2, s)) --vv;   // Eq. (6): a shared start loses one of its copies
-      if (live_new && bit_at(L.occ1, s)) ++vv;   //          or a taken start gains one
-      if (i == 0) vv += was ? 1 : -1;            // Eq. (7)
-      int pk = base_peak;
-      if (well) {   // the copy's interval leaves or joins the profile
-        const int top = interval_max(L.profile, block_table, s, e);
-        const int sz = A.size_of(v);
-        pk = max(max(top + (was ? -sz : sz), 0), max(L.pmax[s - 1], L.smax[e + 1]));
-      }
-      moc_toggle_score sc;
-      sc.violations = vv;
-      sc.peak = pk;
-      sc.duration = (int64_t)base_dur + (was ? -g.size_dur[v].y : g.size_dur[v].y);
-      out[row + k] = sc;
-    }
-    __syncthreads();
-  }
-}
-
 using NbKernel = void (*)(GraphView, int64_t, const int32_t*, const int32_t*, const uint8_t*, int, moc_move_score*,
                           moc_best_move*, NbLayout);
 
@@ -1594,155 +888,12 @@ extern "C" int moc_eval_neighbours(const moc_graph* g, int64_t B, const int32_t*
   return MOC_OK;
 }
 
-extern "C" int moc_eval_toggles(const moc_graph* g, int64_t B, const int32_t* starts, const int32_t* ends,
-                                const uint8_t* active, moc_toggle_score* out, void* hip_stream) {
-  if (!g || B < 0) return MOC_EINVAL;
-  if (B == 0) return MOC_OK;
-  if (!starts || !ends || !active || !out) return MOC_EINVAL;
-  if ((((uintptr_t)starts | (uintptr_t)ends) & 3) || ((uintptr_t)out & 7)) return MOC_EINVAL;
-  int dev = -1;
-  MOC_HIP(hipGetDevice(&dev));
-  if (dev != g->device) return MOC_EDEVICE;
-  if (g->has_self_loop) return MOC_EINVAL;
-  const TgLayout lay = tg_layout(g->view.T, g->view.n, g->view.m, g->max_lds);
-  if (lay.bytes > g->max_lds) return MOC_EOVERFLOW;
-  auto kern = lay.adj_off ? toggles_kernel<true, false> : toggles_kernel<false, false>;
-  int per_cu = 0;
-  if (const int rc = moc_kernel_occupancy(g, reinterpret_cast<const void*>(kern), kNT, lay.bytes, false, &per_cu)) return rc;
-  const int64_t resident = (int64_t)per_cu * g->num_cu;
-  const unsigned grid = (unsigned)(B < resident ? B : resident);
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(kNT), lay.bytes, static_cast<hipStream_t>(hip_stream), g->view, B, starts,
-                     ends, active, out, static_cast<moc_best_move*>(nullptr), 0, 0, lay);
-  MOC_HIP(hipGetLastError());
-  return MOC_OK;
-}
-
 namespace {
-
-
 
 __global__ void fill_zero_kernel(int32_t* p, int64_t n) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0;
 }
-
-}  // namespace
-
-namespace {
-
-// What the launches of the cuts kernel need, worked out once per call.
-struct CutsPlan {
-  TgLayout lay;
-  void (*kern)(GraphView, int64_t, const int32_t*, const int32_t*, const uint8_t*, moc_toggle_score*, moc_best_move*,
-               int, int, TgLayout);
-  unsigned grid;
-};
-
-int plan_cuts(const moc_graph* g, int64_t B, CutsPlan* plan) {
-  if (g->has_self_loop) return MOC_EINVAL;
-  plan->lay = tg_layout(g->view.T, g->view.n, g->view.m, g->max_lds);
-  if (plan->lay.bytes > g->max_lds) return MOC_EOVERFLOW;
-  if ((int64_t)g->view.m * g->view.C > 0x7FFFFFFFll) return MOC_EOVERFLOW;
-  plan->kern = plan->lay.adj_off ? toggles_kernel<true, true> : toggles_kernel<false, true>;
-  int per_cu = 0;
-  if (const int rc = moc_kernel_occupancy(g, reinterpret_cast<const void*>(plan->kern), kNT, plan->lay.bytes, false, &per_cu))
-    return rc;
-  const int64_t resident = (int64_t)per_cu * g->num_cu;
-  plan->grid = (unsigned)(B < resident ? B : resident);
-  return MOC_OK;
-}
-
-int eval_cuts(const moc_graph* g, int64_t B, const int32_t* starts, const int32_t* ends, const uint8_t* active,
-              int mode, moc_cut_score* out_moves, moc_best_move* out_best, void* hip_stream) {
-  if (!g || B < 0) return MOC_EINVAL;
-  if (!out_moves && !out_best) return MOC_EINVAL;
-  if (B == 0) return MOC_OK;
-  if (!starts || !ends || !active) return MOC_EINVAL;
-  if ((((uintptr_t)starts | (uintptr_t)ends) & 3) || ((uintptr_t)out_moves & 7) || ((uintptr_t)out_best & 7))
-    return MOC_EINVAL;
-  int dev = -1;
-  MOC_HIP(hipGetDevice(&dev));
-  if (dev != g->device) return MOC_EDEVICE;
-  CutsPlan plan;
-  if (const int rc = plan_cuts(g, B, &plan)) return rc;
-  hipLaunchKernelGGL(plan.kern, dim3(plan.grid), dim3(kNT), plan.lay.bytes, static_cast<hipStream_t>(hip_stream), g->view,
-                     B, starts, ends, active, out_moves, out_best, 0, mode, plan.lay);
-  MOC_HIP(hipGetLastError());
-  return MOC_OK;
-}
-
-}  // namespace
-
-extern "C" int moc_search_cuts(const moc_graph* g, int64_t B, int32_t* starts, int32_t* ends, uint8_t* active,
-                               int32_t max_steps, moc_best_move* work_best, int32_t* out_steps, void* hip_stream) {
-  if (!g || B < 0 || max_steps < 0) return MOC_EINVAL;
-  if (B == 0) return MOC_OK;
-  if (!starts || !ends || !active || !work_best || !out_steps) return MOC_EINVAL;
-  if ((((uintptr_t)starts | (uintptr_t)ends | (uintptr_t)out_steps) & 3) || ((uintptr_t)work_best & 7)) return MOC_EINVAL;
-  if (B > 0x7FFFFFFFll) return MOC_EINVAL;
-  int dev = -1;
-  MOC_HIP(hipGetDevice(&dev));
-  if (dev != g->device) return MOC_EDEVICE;
-  CutsPlan plan;
-  if (const int rc = plan_cuts(g, B, &plan)) return rc;
-  hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  if (max_steps == 0)
-    hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, stream, out_steps, B);
-  else if (const int rc = moc_queue_cut_descent(g, B, starts, ends, active, max_steps, 0, work_best, out_steps, stream))
-    return rc;
-  MOC_HIP(hipGetLastError());
-  return MOC_OK;
-}
-
-extern "C" int moc_eval_cuts(const moc_graph* g, int64_t B, const int32_t* starts, const int32_t* ends,
-                             const uint8_t* active, moc_cut_score* out_moves, moc_best_move* out_best,
-                             void* hip_stream) {
-  return eval_cuts(g, B, starts, ends, active, 0, out_moves, out_best, hip_stream);
-}
-
-extern "C" int moc_eval_cuts_keep(const moc_graph* g, int64_t B, const int32_t* starts, const int32_t* ends,
-                                  const uint8_t* active, moc_cut_score* out_moves, moc_best_move* out_best,
-                                  void* hip_stream) {
-  return eval_cuts(g, B, starts, ends, active, 1, out_moves, out_best, hip_stream);
-}
-
-extern "C" int moc_search_two_phase(const moc_graph* g, int64_t B, int32_t* starts, int32_t* ends, uint8_t* active,
-                                    int32_t max_cuts, int32_t max_merges, int32_t K, moc_best_move* work_best,
-                                    int32_t* work_starts, int32_t* work_ends, uint8_t* work_active,
-                                    int32_t* work_list, moc_result* work_results, int32_t* out_cuts,
-                                    int32_t* out_merges, void* hip_stream) {
-  if (!g || B < 0 || max_cuts < 0 || max_merges < 0 || K < 1) return MOC_EINVAL;
-  if (B == 0) return MOC_OK;
-  if (!starts || !ends || !active || !work_best || !out_cuts || !out_merges) return MOC_EINVAL;
-  if (max_merges > 0 && (!work_starts || !work_ends || !work_active || !work_list || !work_results)) return MOC_EINVAL;
-  if ((((uintptr_t)starts | (uintptr_t)ends | (uintptr_t)out_cuts | (uintptr_t)out_merges | (uintptr_t)work_list) & 3) ||
-      (((uintptr_t)work_best | (uintptr_t)work_results) & 7))
-    return MOC_EINVAL;
-  if (((uintptr_t)work_starts | (uintptr_t)work_ends) & 3) return MOC_EINVAL;
-  if (B > 0x7FFFFFFFll || (int64_t)B * K > 0x7FFFFFFFll) return MOC_EINVAL;
-  int dev = -1;
-  MOC_HIP(hipGetDevice(&dev));
-  if (dev != g->device) return MOC_EDEVICE;
-  CutsPlan plan;
-  if (const int rc = plan_cuts(g, B, &plan)) return rc;
-  hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  const unsigned blocks = (unsigned)((B + 255) / 256);
-  // Phase 1: towards the budget by cuts that keep the producer's inputs
-  if (max_cuts == 0)
-    hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks), dim3(256), 0, stream, out_cuts, B);
-  else if (const int rc = moc_queue_cut_descent(g, B, starts, ends, active, max_cuts, 1, work_best, out_cuts, stream))
-    return rc;
-  MOC_HIP(hipGetLastError());
-  // Phase 2: undo recomputations while the candidate stays within the budget
-  if (max_merges == 0)
-    hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks), dim3(256), 0, stream, out_merges, B);
-  else if (const int rc = moc_queue_merges(g, B, starts, ends, active, max_merges, K, out_merges, stream))
-    return rc;
-  MOC_HIP(hipGetLastError());
-  return MOC_OK;
-}
-
-namespace {
 
 // Applies to each base the single-field move its moc_best_move names if that move lowers
 // (violations, max(peak, M), peak) against the base's own result, and counts it.

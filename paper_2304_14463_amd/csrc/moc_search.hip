@@ -29,9 +29,9 @@ constexpr int descend_words(int nt) { return (2 * nt + 3 * kMaxRanges + 1 + (int
 // and the scoring 3 (plain cuts) to 12 (cuts that keep inputs).  n = 442, 1024 walkers, up to 64
 // keeping cuts: 27 ms with two launches a step that staged and scored everything again, 0.7 ms now;
 // n = 1000, 32 walkers, 32 plain cuts: 1.31 -> 0.46 ms.
-template <int CT, int NT, bool LISTS>
+template <int CT, int NT, bool LISTS, int MODE>
 __global__ __launch_bounds__(NT) void descend_cuts_kernel(GraphView g, int32_t* __restrict__ starts, int32_t* __restrict__ ends,
-                                                          uint8_t* __restrict__ active, int max_steps, int mode,
+                                                          uint8_t* __restrict__ active, int max_steps,
                                                           moc_best_move* __restrict__ last_move, int32_t* __restrict__ out_steps,
                                                           int cap, MvLayout lay) {
   extern __shared__ uint32_t lds_raw[];
@@ -69,16 +69,16 @@ __global__ __launch_bounds__(NT) void descend_cuts_kernel(GraphView g, int32_t* 
     BestCut best;
     Cut cut{};
     bool known = false;   // this lane holds the chosen move in `cut`
-    if (base_viol != 0 || !best_cut_of_clean_base<CT, NT>(g, lists, L, lay, queue, sift, mode, base_peak, at_peak, best, cut, known, t)) {
+    if (base_viol != 0 || !best_cut_of_clean_base<CT, NT>(g, lists, L, lay, queue, sift, MODE, base_peak, at_peak, best, cut, known, t)) {
       best = BestCut{};
       known = false;
-      score_cuts<CT, NT>(g, lists, L, lay, queue, mode, base_viol, base_peak, at_peak, base_viol == 0, best, t,
+      score_cuts<CT, NT>(g, lists, L, lay, queue, MODE, base_viol, base_peak, at_peak, base_viol == 0, best, t,
                          [](int, int, const CutScore*) {});
       best_of_workgroup<NT>(best, L.scratch, t);
       if (t == 0 && best.move() >= 0) {
         const int x = best.move() / C;
         const uint32_t pair = lists.pair(x);
-        known = find_cut(lists, C, L, (int)(pair & 0xFFFFu), (int)(L.packed[(pair >> 16) + best.move() - x * C] & 0xFFFFu), mode,
+        known = find_cut(lists, C, L, (int)(pair & 0xFFFFu), (int)(L.packed[(pair >> 16) + best.move() - x * C] & 0xFFFFu), MODE,
                          base_viol == 0, cut);
       }
     }
@@ -97,7 +97,7 @@ __global__ __launch_bounds__(NT) void descend_cuts_kernel(GraphView g, int32_t* 
     cut = *chosen_cut;
     const int ub = (int)(lists.pair(q / C) & 0xFFFFu), u = ub / C;
     const int y0 = lists.in_begin(u), y1 = lists.in_begin(u + 1);
-    const int rounds = mode == 1 ? max(1, (y1 - y0 + kWave - 1) / kWave) : 1;
+    const int rounds = MODE == 1 ? max(1, (y1 - y0 + kWave - 1) / kWave) : 1;
     for (int round = 0; round < rounds; ++round) {
       __syncthreads();   // every wave has read what it needs of the copies, the stretches of the last round are added
       if (wave == 0) {
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(NT) void descend_cuts_kernel(GraphView g, int32_t* 
           count = 1;
         }
         int kept = -1, end = -1, w = 0;   // the copy of the lane's predecessor of u that is kept until p
-        if (mode == 1) {
+        if (MODE == 1) {
           const int y = y0 + round * kWave + lane;
           if (y < y1) {
             w = (int)(lists.pair(y) & 0xFFFFu);
@@ -344,22 +344,20 @@ __global__ __launch_bounds__(NT) void merge_kernel(GraphView g, int32_t* __restr
   if (t == 0) merges[blockIdx.x] = steps;
 }
 
-using DescendKernel = void (*)(GraphView, int32_t*, int32_t*, uint8_t*, int, int, moc_best_move*, int32_t*, int, MvLayout);
+using DescendKernel = void (*)(GraphView, int32_t*, int32_t*, uint8_t*, int, moc_best_move*, int32_t*, int, MvLayout);
 
-template <int NT, bool LISTS>
+template <int NT, bool LISTS, int MODE>
 DescendKernel pick_descend(int C) {
   switch (C) {
-    case 2: return descend_cuts_kernel<2, NT, LISTS>;
-    case 3: return descend_cuts_kernel<3, NT, LISTS>;
-    default: return descend_cuts_kernel<0, NT, LISTS>;
+    case 2: return descend_cuts_kernel<2, NT, LISTS, MODE>;
+    case 3: return descend_cuts_kernel<3, NT, LISTS, MODE>;
+    default: return descend_cuts_kernel<0, NT, LISTS, MODE>;
   }
 }
+template <int MODE>
 DescendKernel pick_descend(int C, int nt, bool lists) {
-  switch (nt) {
-    case 256: return lists ? pick_descend<256, true>(C) : pick_descend<256, false>(C);
-    case 512: return lists ? pick_descend<512, true>(C) : pick_descend<512, false>(C);
-    default: return lists ? pick_descend<1024, true>(C) : pick_descend<1024, false>(C);
-  }
+  if (!lists) return pick_descend<1024, false, MODE>(C);
+  return nt == 256 ? pick_descend<256, true, MODE>(C) : nt == 512 ? pick_descend<512, true, MODE>(C) : pick_descend<1024, true, MODE>(C);
 }
 
 using MergeKernel = void (*)(GraphView, int32_t*, int32_t*, uint8_t*, int, int, int32_t*, MvLayout);
@@ -374,9 +372,7 @@ MergeKernel pick_merge(int C) {
   }
 }
 
-}  // namespace
-
-int moc_queue_cut_descent(const moc_graph* g, int64_t B, int32_t* starts, int32_t* ends, uint8_t* active, int max_steps,
+int queue_cut_descent(const moc_graph* g, int64_t B, int32_t* starts, int32_t* ends, uint8_t* active, int max_steps,
                           int mode, moc_best_move* last_move, int32_t* out_steps, hipStream_t stream) {
   const int n = g->view.n, m = g->view.m, T = g->view.T;
   const auto layout = [&](int nt, int cap) { return mv_layout(T, n, m, descend_words(nt) + sift_words(n, cap), true, g->max_lds); };
@@ -387,22 +383,22 @@ int moc_queue_cut_descent(const moc_graph* g, int64_t B, int32_t* starts, int32_
   // 1024; n = 1000, 32 walkers: 0.63, 0.47, 0.46 ms.
   const int64_t share = (B + g->num_cu - 1) / g->num_cu;
   const int by_lds = g->max_lds / layout(256, 256).bytes;
-  const int nt = share <= 1 || by_lds <= 1 ? 1024 : share <= 2 || by_lds <= 2 ? 512 : 256;
+  const int nt = !layout(1024, 256).lists || share <= 1 || by_lds <= 1 ? 1024 : share <= 2 || by_lds <= 2 ? 512 : 256;
   // the lists of moves that pass the sieve: as long as costs no resident workgroup
   const int want = (int)std::min<int64_t>({share, by_lds, 1024 / nt});
   int cap = 2048;
   while (cap > 256 && layout(nt, cap).bytes * std::max(want, 1) > g->max_lds) cap /= 2;
   const MvLayout lay = layout(nt, cap);
   if (lay.bytes > g->max_lds) return MOC_EOVERFLOW;
-  const DescendKernel kern = pick_descend(g->view.C, nt, lay.lists != 0);
+  const DescendKernel kern = mode == 0 ? pick_descend<0>(g->view.C, nt, lay.lists != 0) : pick_descend<1>(g->view.C, nt, lay.lists != 0);
   int per_cu = 0;   // not used: the call is for the kernel's LDS limit
   if (const int rc = moc_kernel_occupancy(g, reinterpret_cast<const void*>(kern), nt, lay.bytes, false, &per_cu)) return rc;
-  hipLaunchKernelGGL(kern, dim3((unsigned)B), dim3(nt), lay.bytes, stream, g->view, starts, ends, active, max_steps, mode,
+  hipLaunchKernelGGL(kern, dim3((unsigned)B), dim3(nt), lay.bytes, stream, g->view, starts, ends, active, max_steps,
                      last_move, out_steps, cap, lay);
   return MOC_OK;
 }
 
-int moc_queue_merges(const moc_graph* g, int64_t B, int32_t* starts, int32_t* ends, uint8_t* active, int max_steps, int K,
+int queue_merges(const moc_graph* g, int64_t B, int32_t* starts, int32_t* ends, uint8_t* active, int max_steps, int K,
                      int32_t* out_merges, hipStream_t stream) {
   const int T = g->view.T;
   const MvLayout lay = mv_layout(T, g->view.n, g->view.m, (T + 1) / 2, true, g->max_lds);
@@ -413,5 +409,61 @@ int moc_queue_merges(const moc_graph* g, int64_t B, int32_t* starts, int32_t* en
   if (const int rc = moc_kernel_occupancy(g, reinterpret_cast<const void*>(kern), NT, lay.bytes, false, &per_cu)) return rc;
   hipLaunchKernelGGL(kern, dim3((unsigned)B), dim3(NT), lay.bytes, stream, g->view, starts, ends, active, K, max_steps,
                      out_merges, lay);
+  return MOC_OK;
+}
+
+__global__ void fill_zero_kernel(int32_t* p, int64_t n) {
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (i < n) p[i] = 0;
+}
+
+}  // namespace
+
+extern "C" int moc_search_cuts(const moc_graph* g, int64_t B, int32_t* starts, int32_t* ends, uint8_t* active,
+                               int32_t max_steps, moc_best_move* work_best, int32_t* out_steps, void* hip_stream) {
+  if (!g || B < 0 || max_steps < 0) return MOC_EINVAL;
+  if (B == 0) return MOC_OK;
+  if (!starts || !ends || !active || !work_best || !out_steps) return MOC_EINVAL;
+  if ((((uintptr_t)starts | (uintptr_t)ends | (uintptr_t)out_steps) & 3) || ((uintptr_t)work_best & 7)) return MOC_EINVAL;
+  if (B > 0x7FFFFFFFll) return MOC_EINVAL;
+  if (const int rc = moc_check_cuts(g)) return rc;
+  hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  if (max_steps == 0)
+    hipLaunchKernelGGL(fill_zero_kernel, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, stream, out_steps, B);
+  else if (const int rc = queue_cut_descent(g, B, starts, ends, active, max_steps, 0, work_best, out_steps, stream))
+    return rc;
+  MOC_HIP(hipGetLastError());
+  return MOC_OK;
+}
+
+extern "C" int moc_search_two_phase(const moc_graph* g, int64_t B, int32_t* starts, int32_t* ends, uint8_t* active,
+                                    int32_t max_cuts, int32_t max_merges, int32_t K, moc_best_move* work_best,
+                                    int32_t* work_starts, int32_t* work_ends, uint8_t* work_active,
+                                    int32_t* work_list, moc_result* work_results, int32_t* out_cuts,
+                                    int32_t* out_merges, void* hip_stream) {
+  if (!g || B < 0 || max_cuts < 0 || max_merges < 0 || K < 1) return MOC_EINVAL;
+  if (B == 0) return MOC_OK;
+  if (!starts || !ends || !active || !work_best || !out_cuts || !out_merges) return MOC_EINVAL;
+  if (max_merges > 0 && (!work_starts || !work_ends || !work_active || !work_list || !work_results)) return MOC_EINVAL;
+  if ((((uintptr_t)starts | (uintptr_t)ends | (uintptr_t)out_cuts | (uintptr_t)out_merges | (uintptr_t)work_list) & 3) ||
+      (((uintptr_t)work_best | (uintptr_t)work_results) & 7))
+    return MOC_EINVAL;
+  if (((uintptr_t)work_starts | (uintptr_t)work_ends) & 3) return MOC_EINVAL;
+  if (B > 0x7FFFFFFFll || (int64_t)B * K > 0x7FFFFFFFll) return MOC_EINVAL;
+  if (const int rc = moc_check_cuts(g)) return rc;
+  hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  const unsigned blocks = (unsigned)((B + 255) / 256);
+  // Phase 1: towards the budget by cuts that keep the producer's inputs
+  if (max_cuts == 0)
+    hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks), dim3(256), 0, stream, out_cuts, B);
+  else if (const int rc = queue_cut_descent(g, B, starts, ends, active, max_cuts, 1, work_best, out_cuts, stream))
+    return rc;
+  MOC_HIP(hipGetLastError());
+  // Phase 2: undo recomputations while the candidate stays within the budget
+  if (max_merges == 0)
+    hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks), dim3(256), 0, stream, out_merges, B);
+  else if (const int rc = queue_merges(g, B, starts, ends, active, max_merges, K, out_merges, stream))
+    return rc;
+  MOC_HIP(hipGetLastError());
   return MOC_OK;
 }

@@ -80,7 +80,7 @@ def test_merges_follow_the_oracle(moc, n, C, K):
 
 
 @pytest.mark.parametrize("n,C,B,mode", [(2, 2, 6, 0), (9, 2, 6, 1), (63, 2, 9, 0), (64, 2, 9, 1), (65, 3, 9, 1), (129, 4, 6, 1), (50, 5, 6, 1),
-                                        (257, 2, 300, 1), (257, 2, 600, 0), (512, 3, 4, 1), (1100, 2, 3, 0)])
+                                        (257, 2, 300, 1), (257, 2, 600, 0), (512, 3, 4, 1), (1100, 2, 3, 0), (2190, 4, 3, 0), (2190, 4, 3, 1)])
 def test_cuts_follow_the_oracle(moc, n, C, B, mode):
     """The descent by cuts (mode 0) and by cuts that keep the inputs (mode 1): counts, rows and, for
     mode 0, the last step's choice.  Bases with and without violations, batches on either side of
@@ -88,7 +88,7 @@ def test_cuts_follow_the_oracle(moc, n, C, B, mode):
     import torch
     rng = np.random.default_rng(31 * n + C + mode)
     g = random_graph(rng, n)
-    rows, steps = min(B, 9), 12 if n < 300 else 5
+    rows, steps = min(B, 9), 12 if n < 300 else 5 if n < 2000 else 1
     s, e, a = schedules(rng, g, C, rows, wild=True)
     budget = int(0.8 * np.median(oracle.evaluate(g, 0, C, s, e, a)[::3, 0]))
     pick = np.arange(B) % rows

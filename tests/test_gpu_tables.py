@@ -1,0 +1,85 @@
+"""GPU parity of the toggle and cut tables where their kernels can go wrong: edges of the blocks of 8
+positions, the rows of 64 and 256, one to five copies per node, workgroups of each size, graphs
+whose adjacency lists do not fit LDS, and the largest number of copies the calls take."""
+import numpy as np
+import pytest
+
+import oracle
+from test_gpu_cuts import assert_best, assert_same, schedules, to_dev
+from test_gpu_search_steps import random_graph
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def moc():
+    import torch
+    assert torch.cuda.is_available(), "these tests need the MI355X"
+    from paper_2304_14463_amd import moccasin
+    moccasin.lib()
+    return moccasin
+
+
+@pytest.mark.parametrize("n,C", [(1, 1), (1, 2), (7, 1), (8, 1), (9, 1), (4, 2), (31, 2), (32, 2), (33, 2), (21, 3), (64, 4), (13, 5), (129, 2),
+                                 (511, 2), (1025, 2), (700, 5)])
+def test_toggles(moc, n, C):
+    rng = np.random.default_rng(7 * n + C)
+    g = random_graph(rng, n)
+    B = 6 if n < 500 else 3
+    s, e, a = schedules(rng, g, C, B, wild=True)
+    gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, 100, C)
+    got = moc.results_to_numpy(moc.moc_eval_toggles(gh, *to_dev(s, e, a)), moc.TOGGLE_SCORE_DTYPE)
+    for b in range(B):
+        assert_same(got[b], oracle.toggles(g, 100, C, s[b], e[b], a[b]), f"n={n} C={C} row {b}")
+    gh.free()
+
+
+@pytest.mark.parametrize("n,C,mode", [(4, 2, 0), (32, 2, 1), (33, 2, 0), (21, 3, 1), (13, 5, 0), (129, 2, 1), (511, 2, 0), (900, 3, 1)])
+def test_cuts(moc, n, C, mode):
+    rng = np.random.default_rng(11 * n + C)
+    g = random_graph(rng, n)
+    B = 6 if n < 500 else 3
+    s, e, a = schedules(rng, g, C, B, wild=True)
+    gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, 100, C)
+    moves, best = moc.moc_eval_cuts(gh, *to_dev(s, e, a), want_best=True, keep_inputs=mode == 1)
+    moves, best = moc.results_to_numpy(moves, moc.TOGGLE_SCORE_DTYPE), moc.results_to_numpy(best, moc.BEST_MOVE_DTYPE)
+    for b in range(B):
+        want = oracle.cuts(g, 100, C, s[b], e[b], a[b], with_at_peak=True, mode=mode)
+        assert_same(moves[b], want, f"n={n} C={C} row {b}")
+        assert_best(best[b], want, f"n={n} C={C} row {b}")
+    gh.free()
+
+
+def test_largest_base(moc):
+    """T = 8790, a little below the limit: no adjacency lists in LDS, the deepest table of maxima.
+    One orderly base; every 40th toggle and cut against the evaluator."""
+    n, C = 4395, 2
+    T = n * C
+    rng = np.random.default_rng(3)
+    g = random_graph(rng, n)
+    s, e, a = schedules(rng, g, C, 1, wild=False)
+    gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, 100, C)
+    dev = to_dev(s, e, a)
+    got = moc.results_to_numpy(moc.moc_eval_toggles(gh, *dev), moc.TOGGLE_SCORE_DTYPE)[0]
+    pick = np.arange(0, T, 40)
+    flips = np.repeat(a, len(pick), 0)
+    flips[np.arange(len(pick)), pick] ^= 1
+    want = oracle.evaluate(g, 100, C, np.repeat(s, len(pick), 0), np.repeat(e, len(pick), 0), flips)
+    for i, name in ((2, "violations"), (0, "peak"), (1, "duration")):
+        assert (got[name][pick].astype(np.int64) == want[:, i]).all(), name
+    for mode in (0, 1):
+        moves, best = moc.moc_eval_cuts(gh, *dev, want_best=True, keep_inputs=mode == 1)
+        moves = moc.results_to_numpy(moves, moc.TOGGLE_SCORE_DTYPE)[0]
+        bm = moc.results_to_numpy(best, moc.BEST_MOVE_DTYPE)[0]
+        ok = np.flatnonzero(moves["violations"] >= 0)
+        assert ok.size > 0 and int(bm["violations"]) == moves["violations"][ok].min()
+        # one step of the search takes that move, and the edited candidate is worth its score
+        ws, we, wa = (x.clone() for x in dev)
+        if mode == 0:
+            count = moc.moc_search_cuts(gh, ws, we, wa, 1)
+        else:
+            count, _ = moc.moc_search_two_phase(gh, ws, we, wa, 1, 0)
+        if int(count[0]):
+            after = oracle.evaluate(g, 100, C, ws.cpu().numpy(), we.cpu().numpy(), wa.cpu().numpy())[0]
+            assert (after[2], after[0]) == (int(bm["violations"]), int(bm["peak"]))
+    gh.free()
