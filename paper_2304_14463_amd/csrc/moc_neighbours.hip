@@ -20,20 +20,21 @@
 // and peak' = max(prefix max before, suffix max after, shifted profile inside)
 // over the changed positions (at most R of them unless the copy was outside
 // the domain before the move).
-// The active copies are listed while the base is staged.  Pass 1 counts the
-// violations of the base and marks the copies that take part in one.  Pass 2
-// runs one lane per (active copy, field): it builds the 0/1 terms of f as bit
+// The live copies are listed while the base is staged, and behind them the
+// active copies that are not live.  Pass 1 counts the violations of the base
+// and marks the copies that take part in one.  Pass 2 runs one lane per (live
+// copy, field): it builds the 0/1 terms of f as bit
 // masks over the displacements, sums them in bit planes and walks outwards from
 // the old position (see build_field, walk_own).  Two kernels: for the best move
 // alone (fields that cannot win are left out), and with the table of scores (a
 // wave writes the rows of consecutive copies, the inactive ones filled in).
 // The adjacency lists are kept in LDS when that costs no resident workgroup.
+#include <algorithm>
+#include <type_traits>
+
 #include "moc_moves.h"
 
 namespace {
-
-constexpr int kNT = 1024;
-constexpr int kNW = kNT / kWave;
 
 struct NbLayout {
   int T_pad;      // T rounded up to 4
@@ -43,20 +44,23 @@ struct NbLayout {
   int bytes;
 };
 
-NbLayout nb_layout(int T, int n, int m, int max_lds) {
+NbLayout nb_layout(int T, int n, int m, int max_lds, int nt) {
   NbLayout l;
   l.T_pad = (T + 3) & ~3;
   l.bit_words = (T + 31) / 32;
   l.mask_words = 2 * ((T + 63) / 64);
   // profile, prefix max, suffix max, packed, the list of active copies (16 bits an entry) + bitmaps + scratch
-  const int words = 4 * l.T_pad + l.T_pad / 2 + 8 + 2 * l.bit_words + 2 * l.mask_words + 8 * kNW + 16;
+  const int words = 4 * l.T_pad + l.T_pad / 2 + 8 + 2 * l.bit_words + 2 * l.mask_words + 8 * (nt / kWave) + 16;
   l.adj_off = 0;
+  const int full = nt == 1024 ? 2 : 4;
   l.bytes = 4 * words;
-  // The CSR lists both ways and the sizes, which every move reads, if that costs no resident
-  // workgroup (two of 16 waves fit a CU).  (At T = 4000 it would: with them in LDS and one
-  // workgroup per CU the table of scores takes 4.2 ms instead of 3.6.)
-  const int with_adj = 4 * (words + 2 * (n + 1) + 2 * m + n);
-  if (with_adj <= max_lds && std::min(max_lds / with_adj, 2) >= std::min(max_lds / l.bytes, 2)) {
+  // The CSR lists both ways (16-bit entries) and the sizes, which every move reads, if that costs no
+  // resident workgroup beyond the fourth (the second of 16 waves).  At T = 4000 it would: with them
+  // in LDS and one workgroup of 16 waves per CU the table of scores takes 4.2 ms instead of 3.6; at
+  // T = 2000 four workgroups of 512 threads take 73 us (best move, 1024 bases), three with the lists
+  // in LDS 90; at T = 884 six workgroups of 256 with the lists 96 us, eight without 101.
+  const int with_adj = 4 * (words + n + (2 * (n + 1) + 2 * m + 1) / 2);
+  if (m < 0xFFFF && with_adj <= max_lds && std::min(max_lds / with_adj, full) >= std::min(max_lds / l.bytes, full)) {
     l.adj_off = words;
     l.bytes = with_adj;
   }
@@ -64,14 +68,15 @@ NbLayout nb_layout(int T, int n, int m, int max_lds) {
 }
 
 // The graph's adjacency, by in-edges and by out-edges (CSR), in LDS or in global memory.
+template <bool LDS>
 struct Adj {
-  const int32_t* in_ptr;
-  const int32_t* in_idx;
-  const int32_t* out_ptr;
-  const int32_t* out_idx;
+  using Entry = typename std::conditional<LDS, uint16_t, int32_t>::type;
+  const Entry* in_ptr;
+  const Entry* in_idx;
+  const Entry* out_ptr;
+  const Entry* out_idx;
   const int32_t* size;   // m_v, one word per node (LDS) or per two words (the graph's {m_v, w_v} pairs)
-  int size_stride;
-  __device__ __forceinline__ int size_of(int v) const { return size[v * size_stride]; }
+  __device__ __forceinline__ int size_of(int v) const { return size[LDS ? v : 2 * v]; }
 };
 
 struct NbLds {
@@ -84,13 +89,13 @@ struct NbLds {
   uint32_t* occ2;
   uint32_t* involved;   // bit k: copy k takes part in a violation of Eq. (3) or (5)
   uint32_t* amask;      // bit k: copy k is active
-  int32_t* scratch;   // 8 * kNW + 16
+  int32_t* scratch;   // 8 words per wave + 16
 };
 
 struct AddOp { static __device__ int id() { return 0; } static __device__ int op(int a, int b) { return a + b; } };
 
 // Inclusive scan of dst[idx(0..T-1)] <- src, in place allowed; REV scans from the top.
-template <typename Op, bool REV>
+template <typename Op, bool REV, int kNT>
 __device__ void block_scan(const int32_t* src, int32_t* dst, int T, int32_t* scratch, int tid) {
   const int lane = tid & (kWave - 1), wave = tid / kWave;
   const int L = (T + kNT - 1) / kNT;
@@ -118,8 +123,10 @@ __device__ void block_scan(const int32_t* src, int32_t* dst, int T, int32_t* scr
 }
 
 // dst_up[t] = max(src[0..t]) and dst_down[t] = max(src[t..T-1]) in one pass (src >= 0).
+template <int kNT>
 __device__ void block_max_both_ways(const int32_t* src, int32_t* dst_up, int32_t* dst_down, int T, int32_t* scratch,
                                     int tid) {
+  constexpr int kNW = kNT / kWave;
   const int lane = tid & (kWave - 1), wave = tid / kWave;
   const int L = (T + kNT - 1) / kNT;
   const int lo = tid * L, hi = min(lo + L, T);
@@ -167,7 +174,8 @@ __device__ void block_max_both_ways(const int32_t* src, int32_t* dst_up, int32_t
 //   order : Eq. (3) among the live copies of v
 //   cons  : in-edges of v not covered at the start of copy i
 //   prov  : (out-edge (v,w), live copy of w) pairs not covered by any live copy of v
-__device__ __forceinline__ int node_part(const Adj& g, int C, const uint32_t* __restrict__ packed, int v, int i,
+template <typename A>
+__device__ __forceinline__ int node_part(const A& g, int C, const uint32_t* __restrict__ packed, int v, int i,
                                          bool active, bool live, int s, int e) {
   const uint32_t mine = pack_copy(live, s, e);
   int count = (active && !live) ? 1 : 0;
@@ -208,7 +216,8 @@ __device__ __forceinline__ int node_part(const Adj& g, int C, const uint32_t* __
 // One move of a copy, from scratch: (violations, peak) of the candidate with that one field
 // at `moved`.  The general form; the kernel uses it for copies that are ill-formed before
 // the move, where the changed positions are a whole interval.
-__device__ __forceinline__ void score_move(const Adj& g, int C, int sz, const NbLds& L, int T, int v, int i,
+template <typename A>
+__device__ __forceinline__ void score_move(const A& g, int C, int sz, const NbLds& L, int T, int v, int i,
                                            int field, int s, int e, int moved, int base_rest, int base_peak,
                                            moc_move_score& sc) {   // base_rest: the base count without f(old copy)
   const int k = v * C + i;
@@ -305,8 +314,8 @@ struct FieldState {
 // bit per move (no room for the extra bit at R = 32); there the copy's present contribution
 // is computed edge by edge.  On a counter overflow in any lane the state is marked invalid
 // (the caller then scores the moves one by one).
-template <int CT, bool WIDE>
-__device__ __forceinline__ void build_field(const Adj& A, int C, int sz, const NbLds& L, int T, int R, int v, int i,
+template <int CT, bool WIDE, typename Lists_>
+__device__ __forceinline__ void build_field(const Lists_& A, int C, int sz, const NbLds& L, int T, int R, int v, int i,
                                             int field, uint32_t mine, int base_viol, int q0, FieldState<WIDE>& st) {
   using B = Bits<WIDE>;
   using M = typename B::M;
@@ -504,7 +513,7 @@ __device__ __forceinline__ void walk_own(const FieldState<WIDE>& st, const NbLds
   }
 }
 
-template <bool ADJ_LDS, int CT, bool WIDE, bool TABLE>
+template <int kNT, bool ADJ_LDS, int CT, bool WIDE, bool TABLE>
 __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) void neighbours_kernel(GraphView g, int64_t B, const int32_t* __restrict__ starts,
                                                          const int32_t* __restrict__ ends,
                                                          const uint8_t* __restrict__ active, int R,
@@ -532,17 +541,20 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
   const int pieces = four_r <= kWave ? 1 : 2;
   const int sub = four_r <= kWave ? lane / four_r : 0;
   const int rem = four_r <= kWave ? lane - sub * four_r : lane;
-  int32_t* const counts = L.scratch + 8 * kNW;   // [0] base violations, [1] active copies, [2] fewest violations of a move so far, [3] work drawn
+  int32_t* const counts = L.scratch + 8 * (kNT / kWave);   // [0] base violations, [1] live copies, [2] fewest violations of a move so far, [3] work drawn, [4] active copies that are not live, [5] work drawn from their moves
   const bool pairs = TABLE && (R & 1) == 0 && (reinterpret_cast<uintptr_t>(out_moves) & 15) == 0;   // scores stored two at a time
-  Adj A{g.in_ptr, g.in_idx, g.out_ptr, g.out_idx, reinterpret_cast<const int32_t*>(g.size_dur), 2};
+  constexpr int kNW = kNT / kWave;
+  Adj<ADJ_LDS> A;
   if constexpr (ADJ_LDS) {   // the adjacency lists and sizes are read by every move: keep them in LDS
-    int32_t* a = reinterpret_cast<int32_t*>(nb_raw) + lay.adj_off;
-    int32_t* const sizes = a + 2 * (g.n + 1) + 2 * g.m;
-    for (int x = tid; x <= g.n; x += kNT) { a[x] = g.in_ptr[x]; a[g.n + 1 + g.m + x] = g.out_ptr[x]; }
-    for (int x = tid; x < g.m; x += kNT) { a[g.n + 1 + x] = g.in_idx[x]; a[2 * (g.n + 1) + g.m + x] = g.out_idx[x]; }
+    int32_t* const sizes = reinterpret_cast<int32_t*>(nb_raw) + lay.adj_off;
+    uint16_t* const a = reinterpret_cast<uint16_t*>(sizes + g.n);
+    for (int x = tid; x <= g.n; x += kNT) { a[x] = (uint16_t)g.in_ptr[x]; a[g.n + 1 + g.m + x] = (uint16_t)g.out_ptr[x]; }
+    for (int x = tid; x < g.m; x += kNT) { a[g.n + 1 + x] = (uint16_t)g.in_idx[x]; a[2 * (g.n + 1) + g.m + x] = (uint16_t)g.out_idx[x]; }
     for (int x = tid; x < g.n; x += kNT) sizes[x] = g.size_dur[x].x;
-    A = Adj{a, a + g.n + 1, a + g.n + 1 + g.m, a + 2 * (g.n + 1) + g.m, sizes, 1};
+    A = Adj<ADJ_LDS>{a, a + g.n + 1, a + g.n + 1 + g.m, a + 2 * (g.n + 1) + g.m, sizes};
     __syncthreads();
+  } else {
+    A = Adj<ADJ_LDS>{g.in_ptr, g.in_idx, g.out_ptr, g.out_idx, reinterpret_cast<const int32_t*>(g.size_dur)};
   }
 
   for (int64_t b = blockIdx.x; b < B; b += gridDim.x) {
@@ -577,18 +589,18 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
       }
     }
     for (int t = t_; t < T; t += kNT) L.profile[t] = 0;
-    for (int w = t_; w < 2 * lay.bit_words + lay.mask_words; w += kNT) L.occ1[w] = 0;   // occ1, occ2, involved
-    if (t_ < 4) counts[t_] = t_ == 2 ? 0x7FFFFFFF : 0;
+    for (int w = t_; w < 2 * lay.bit_words; w += kNT) L.occ1[w] = 0;   // occ1, occ2
+    if (t_ < 6) counts[t_] = t_ == 2 ? 0x7FFFFFFF : 0;
     if (t_ == 0) { L.pmax[-1] = 0; L.smax[T] = 0; }
     __syncthreads();
     // whole waves, 64 consecutive copies each: a ballot gives the active flags of the 64
     int viol = 0, nlive = 0;
     auto stage = [&](int k0, int s, int e, uint32_t flag, int sz) {
       const int k = k0 + lane_;
-      bool act = false;
+      bool act = false, live = false;
       if (k < T) {
         act = flag != 0;
-        const bool live = act && (uint32_t)s <= (uint32_t)e && (uint32_t)e < (uint32_t)T;
+        live = act && (uint32_t)s <= (uint32_t)e && (uint32_t)e < (uint32_t)T;
         const int v = C == 1 ? k : (int)__umulhi((uint32_t)k, c_magic);
         L.packed[k] = pack_copy(live, s, e);
         if (k == v * C && !act) ++viol;   // Eq. (7)
@@ -601,11 +613,14 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
           if (old & bit) atomicOr(&L.occ2[s >> 5], bit);
         }
       }
-      const uint64_t am = __ballot(act);
+      const uint64_t am = __ballot(act), lm = __ballot(live);
       if (lane_ == 0) {
         L.amask[k0 >> 5] = (uint32_t)am;
         L.amask[(k0 >> 5) + 1] = (uint32_t)(am >> 32);
-        atomicAdd(&counts[1], __popcll(am));
+        L.involved[k0 >> 5] = (uint32_t)lm;   // the live copies, until pass 1 begins
+        L.involved[(k0 >> 5) + 1] = (uint32_t)(lm >> 32);
+        atomicAdd(&counts[1], __popcll(lm));
+        atomicAdd(&counts[4], __popcll(am & ~lm));
       }
     };
 #pragma unroll
@@ -618,28 +633,43 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
       stage(k0, starts[row + k], ends[row + k], active[row + k], A.size_of(C == 1 ? k : (int)__umulhi((uint32_t)k, c_magic)));
     }
     __syncthreads();
-    // the active copies in order: those of 64 copies go behind those of the copies before
-    for (int c = wave_; c < lay.mask_words / 2; c += kNW) {
-      int before = 0;
-      for (int x = lane_; x < c; x += kWave) before += __popc(L.amask[2 * x]) + __popc(L.amask[2 * x + 1]);
+    // the list: the live copies in order, those of 64 copies behind those of the copies before; then,
+    // in the same way, the active copies that are not live
+    auto chunk = [&](const uint32_t* bits, int c) { return (uint64_t)bits[2 * c] | ((uint64_t)bits[2 * c + 1] << 32); };
+    const int chunks = lay.mask_words / 2;
+    const int n_live = __builtin_amdgcn_readfirstlane(counts[1]), n_ill = __builtin_amdgcn_readfirstlane(counts[4]);
+    for (int c = wave_; c < chunks; c += kNW) {
+      int before = 0, before_ill = 0;
+      for (int x = lane_; x < c; x += kWave) {
+        const int live = __popcll(chunk(L.involved, x));
+        before += live;
+        before_ill += __popcll(chunk(L.amask, x)) - live;
+      }
 #pragma unroll
-      for (int off = kWave / 2; off > 0; off >>= 1) before += __shfl_xor(before, off);
-      const uint64_t am = (uint64_t)L.amask[2 * c] | ((uint64_t)L.amask[2 * c + 1] << 32);
-      if ((am >> lane_) & 1) L.list[before + __popcll(am & (((uint64_t)1 << lane_) - 1))] = (uint16_t)(c * kWave + lane_);
+      for (int off = kWave / 2; off > 0; off >>= 1) {
+        before += __shfl_xor(before, off);
+        before_ill += __shfl_xor(before_ill, off);
+      }
+      const uint64_t lm = chunk(L.involved, c), ill = chunk(L.amask, c) & ~lm, lower = ((uint64_t)1 << lane_) - 1;
+      if ((lm >> lane_) & 1) L.list[before + __popcll(lm & lower)] = (uint16_t)(c * kWave + lane_);
+      if ((ill >> lane_) & 1) L.list[n_live + before_ill + __popcll(ill & lower)] = (uint16_t)(c * kWave + lane_);
     }
-    block_scan<AddOp, false>(L.profile, L.profile, T, L.scratch, t_);   // Eq. (4) per position
-    block_max_both_ways(L.profile, L.pmax, L.smax, T, L.scratch, t_);
+    block_scan<AddOp, false, kNT>(L.profile, L.profile, T, L.scratch, t_);   // Eq. (4) per position
+    block_max_both_ways<kNT>(L.profile, L.pmax, L.smax, T, L.scratch, t_);
 
+    // For the best move alone the rest looks at the live copies only; the rows of the table are filled
+    // by active flags.
+    for (int w = t_; w < lay.mask_words; w += kNT) {
+      if constexpr (!TABLE) L.amask[w] = L.involved[w];
+      L.involved[w] = 0;
+    }
+    __syncthreads();
     // ---- pass 1: the violations of the base, each instance once: per active copy its form,
     // the order pair it opens and its inputs
-    const int n_active = __builtin_amdgcn_readfirstlane(counts[1]);
-    for (int j = t_; j < n_active; j += kNT) {
+    if (t_ == 0) viol += n_ill;   // Eq. (2)/(8)
+    for (int j = t_; j < n_live; j += kNT) {
       const int k = L.list[j];
       const uint32_t mine = L.packed[k];
-      if (!live_of(mine)) {   // Eq. (2)/(8)
-        ++viol;
-        continue;
-      }
       const int v = C == 1 ? k : (int)__umulhi((uint32_t)k, c_magic), i = k - v * C;
       const int s = (int)(mine & 0xFFFFu), e = (int)(mine >> 16);
       auto mark = [&](int copy) { atomicOr(&L.involved[copy >> 5], 1u << (copy & 31)); };
@@ -675,10 +705,8 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     // For the best move alone the list is built again, the copies that take part in a violation
     // first: their moves are the ones that can lower the count, and once one has, the others
     // are left out wave_ by wave_ (see below).
-    int n_first = n_active;   // entries of the list's first part
+    int n_first = n_live;   // entries of the list's first part
     if constexpr (!TABLE) {
-      auto chunk = [&](const uint32_t* bits, int c) { return (uint64_t)bits[2 * c] | ((uint64_t)bits[2 * c + 1] << 32); };
-      const int chunks = lay.mask_words / 2;
       int all_first = 0;
       for (int x = lane_; x < chunks; x += kWave) all_first += __popcll(chunk(L.amask, x) & chunk(L.involved, x));
 #pragma unroll
@@ -717,7 +745,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     // instead of 3.0.)
     const bool table = TABLE && out_moves != nullptr;
     const int draw = table ? kWave / 2 : kWave;
-    const int total = table ? max(n_active, 1) : 2 * n_active;
+    const int total = table ? max(n_live, 1) : 2 * n_live;
     for (;;) {
       int u0 = 0;
       if (lane == 0) u0 = atomicAdd(&counts[3], draw);
@@ -729,11 +757,11 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
         field = lane >> 5;
       } else {   // both fields of the first part of the list, then both of the rest
         const int u = u0 + lane, part = u >= 2 * n_first ? 1 : 0;
-        const int in_part = u - part * 2 * n_first, size = part ? n_active - n_first : n_first;
+        const int in_part = u - part * 2 * n_first, size = part ? n_live - n_first : n_first;
         field = in_part >= size ? 1 : 0;
         entry = part * n_first + in_part - field * size;
       }
-      const bool has_unit = entry < n_active;
+      const bool has_unit = entry < n_live;
       const int k = has_unit ? L.list[entry] : 0;
       const int v = C == 1 ? k : (int)__umulhi((uint32_t)k, c_magic), i = k - v * C;
       const int q0 = (2 * k + field) * two_r;
@@ -745,7 +773,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
       // is computed for it: a copy that takes part in no violation now (not marked in pass 1,
       // its start not shared) cannot get below the base's count.  After the masks are built:
       // no move has fewer violations than the terms that do not depend on the displacement.
-      bool build = has_unit && live_of(L.packed[k]), left_out = false;
+      bool build = has_unit, left_out = false;
       [[maybe_unused]] int least = 0x7FFFFFFF;
       if constexpr (!TABLE) {
         least = *const_cast<volatile int32_t*>(&counts[2]);
@@ -770,9 +798,9 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
           }
         }
       }
-      if (has_unit && st.field < 0 && !left_out) {   // active and ill formed, or a node with very many edges (rare): move by move, from scratch
+      if (has_unit && st.field < 0 && !left_out) {   // a node with very many edges (rare): move by move, from scratch
         const int s = starts[row + k], e = ends[row + k];
-        const int base_rest = base_viol - node_part(A, C, L.packed, v, i, true, live_of(L.packed[k]), s, e);
+        const int base_rest = base_viol - node_part(A, C, L.packed, v, i, true, true, s, e);
         for (int d = 0; d < two_r; ++d) {
           const int moved = (field == 0 ? s : e) + (d < R ? d - R : d - R + 1);
           moc_move_score sc{-1, -1};
@@ -786,7 +814,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
       }
       if (table) {   // the moves of the inactive copies from this block's first copy to the next block's are not applicable
         const int k_lo = u0 == 0 ? 0 : (int)L.list[u0];
-        const int k_hi = u0 + draw < n_active ? (int)L.list[u0 + draw] : T;
+        const int k_hi = u0 + draw < n_live ? (int)L.list[u0 + draw] : T;
         for (int kk0 = k_lo; kk0 < k_hi; kk0 += per_wave) {
           const int kk = kk0 + sub;
           const bool fill = sub < per_wave && kk < k_hi && !((L.amask[kk >> 5] >> (kk & 31)) & 1u);
@@ -795,6 +823,35 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
             if (fill && in_copy < four_r) store_score(row0, (uint32_t)(kk * four_r + in_copy), moc_move_score{-1, -1});
           }
         }
+      }
+    }
+    // ---- the moves of the active copies that are not live, one lane per move: most leave the copy as
+    // it is, the others make it live (its whole interval joins the profile).  One lane for all 2R
+    // moves of a field cost every wave with one such copy 2R times the walk over the node's edges.
+    for (;;) {
+      int m0 = 0;
+      if (lane == 0) m0 = atomicAdd(&counts[5], kWave);
+      m0 = __builtin_amdgcn_readfirstlane(m0);
+      if (m0 >= n_ill * four_r) break;
+      const int at = m0 + lane;
+      if (at < n_ill * four_r) {
+        const int j = at / four_r, in_copy = at - j * four_r;
+        const int k = L.list[n_live + j], field = in_copy >= two_r ? 1 : 0, d = in_copy - field * two_r;
+        const int v = C == 1 ? k : (int)__umulhi((uint32_t)k, c_magic), i = k - v * C;
+        const int s = starts[row + k], e = ends[row + k];
+        const int moved = (field == 0 ? s : e) + (d < R ? d - R : d - R + 1);
+        const int s2 = field == 0 ? moved : s, e2 = field == 0 ? e : moved;
+        moc_move_score sc{-1, -1};
+        if (moved >= 0 && moved < T) {
+          sc = moc_move_score{base_viol, base_peak};
+          if ((uint32_t)s2 <= (uint32_t)e2 && (uint32_t)e2 < (uint32_t)T) {
+            const int base_rest = base_viol - node_part(A, C, L.packed, v, i, true, false, s, e);
+            score_move(A, C, A.size_of(v), L, T, v, i, field, s, e, moved, base_rest, base_peak, sc);
+          }
+          const Best cand{sc.violations, sc.peak, k * four_r + in_copy};
+          if (better(cand, best)) best = cand;
+        }
+        if (row0) store_score(row0, (uint32_t)(k * four_r + in_copy), sc);
       }
     }
     // ---- best move of the candidate
@@ -837,26 +894,44 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
 using NbKernel = void (*)(GraphView, int64_t, const int32_t*, const int32_t*, const uint8_t*, int, moc_move_score*,
                           moc_best_move*, NbLayout);
 
-template <bool ADJ_LDS, bool WIDE, bool TABLE>
+template <int NT, bool ADJ_LDS, bool WIDE, bool TABLE>
 NbKernel pick_copies(int C) {
+  if constexpr (NT == 1024) {
+    if (C == 1) return neighbours_kernel<NT, ADJ_LDS, 1, WIDE, TABLE>;
+    if (C == 4) return neighbours_kernel<NT, ADJ_LDS, 4, WIDE, TABLE>;
+  }
   switch (C) {
-    case 1: return neighbours_kernel<ADJ_LDS, 1, WIDE, TABLE>;
-    case 2: return neighbours_kernel<ADJ_LDS, 2, WIDE, TABLE>;
-    case 3: return neighbours_kernel<ADJ_LDS, 3, WIDE, TABLE>;
-    case 4: return neighbours_kernel<ADJ_LDS, 4, WIDE, TABLE>;
-    default: return neighbours_kernel<ADJ_LDS, 0, WIDE, TABLE>;   // C read at run time
+    case 2: return neighbours_kernel<NT, ADJ_LDS, 2, WIDE, TABLE>;
+    case 3: return neighbours_kernel<NT, ADJ_LDS, 3, WIDE, TABLE>;
+    default: return neighbours_kernel<NT, ADJ_LDS, 0, WIDE, TABLE>;   // C read at run time
   }
 }
 
-template <bool ADJ_LDS, bool WIDE>
-NbKernel pick_table(int C, bool table) {
-  return table ? pick_copies<ADJ_LDS, WIDE, true>(C) : pick_copies<ADJ_LDS, WIDE, false>(C);
+template <int NT, bool ADJ_LDS>
+NbKernel pick_kernel(int C, int R, bool table) {
+  if (2 * R > 31) return table ? pick_copies<NT, ADJ_LDS, true, true>(C) : pick_copies<NT, ADJ_LDS, true, false>(C);   // 64-bit displacement masks
+  return table ? pick_copies<NT, ADJ_LDS, false, true>(C) : pick_copies<NT, ADJ_LDS, false, false>(C);
 }
 
-NbKernel pick_kernel(bool adj_lds, int C, int R, bool table) {
-  const bool wide = 2 * R > 31;   // 64-bit displacement masks
-  if (adj_lds) return wide ? pick_table<true, true>(C, table) : pick_table<true, false>(C, table);
-  return wide ? pick_table<false, true>(C, table) : pick_table<false, false>(C, table);
+NbKernel pick_kernel(int nt, bool adj_lds, int C, int R, bool table) {
+  switch (nt) {
+    case 256: return adj_lds ? pick_kernel<256, true>(C, R, table) : pick_kernel<256, false>(C, R, table);
+    case 512: return adj_lds ? pick_kernel<512, true>(C, R, table) : pick_kernel<512, false>(C, R, table);
+    default: return adj_lds ? pick_kernel<1024, true>(C, R, table) : pick_kernel<1024, false>(C, R, table);
+  }
+}
+
+// Threads per base.  A wave scores 64 (copy, field) pairs at a time, and the staging is a chain of
+// short passes over T positions: a small base does not feed 16 waves, and several bases on a compute
+// unit hide each other's latencies, as long as the batch has several per unit.  Best move alone, R = 8,
+// C = 2, by 256 / 512 / 1024 threads: n = 120, 2048 bases 33 / 47 / 90 us; n = 442, 1024 bases
+// 46 / 47 / 67, 16 bases 41 / 26 / 26; n = 1000, 1024 bases 85 / 73 / 87; n = 2000, 512 bases
+// 174 / 96 / 77.
+int nb_threads(int T, int64_t B, int num_cu) {
+  const int64_t per_cu = (B + num_cu - 1) / num_cu;
+  if (T <= 1024 && per_cu >= 4) return 256;
+  if (T <= 2560 && per_cu >= 2) return 512;
+  return 1024;
 }
 
 }  // namespace
@@ -874,15 +949,16 @@ extern "C" int moc_eval_neighbours(const moc_graph* g, int64_t B, const int32_t*
   MOC_HIP(hipGetDevice(&dev));
   if (dev != g->device) return MOC_EDEVICE;
   if (g->has_self_loop) return MOC_EINVAL;
-  const NbLayout lay = nb_layout(g->view.T, g->view.n, g->view.m, g->max_lds);
+  const int nt = nb_threads(g->view.T, B, g->num_cu);
+  const NbLayout lay = nb_layout(g->view.T, g->view.n, g->view.m, g->max_lds, nt);
   if (lay.bytes > g->max_lds) return MOC_EOVERFLOW;
   if ((int64_t)g->view.T * 4 * R * 8 > 0xFFFFFFFFll) return MOC_EOVERFLOW;   // byte offsets in a candidate's table are 32 bits
-  auto kern = pick_kernel(lay.adj_off != 0, g->view.C, R, out_moves != nullptr);
+  const NbKernel kern = pick_kernel(nt, lay.adj_off != 0, g->view.C, R, out_moves != nullptr);
   int per_cu = 0;
-  if (const int rc = moc_kernel_occupancy(g, reinterpret_cast<const void*>(kern), kNT, lay.bytes, false, &per_cu)) return rc;
+  if (const int rc = moc_kernel_occupancy(g, reinterpret_cast<const void*>(kern), nt, lay.bytes, false, &per_cu)) return rc;
   const int64_t resident = (int64_t)per_cu * g->num_cu;
   const unsigned grid = (unsigned)(B < resident ? B : resident);
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(kNT), lay.bytes, static_cast<hipStream_t>(hip_stream), g->view, B,
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(nt), lay.bytes, static_cast<hipStream_t>(hip_stream), g->view, B,
                      starts, ends, active, R, out_moves, out_best, lay);
   MOC_HIP(hipGetLastError());
   return MOC_OK;
@@ -928,7 +1004,7 @@ extern "C" int moc_search_moves(const moc_graph* g, int64_t B, int32_t* starts, 
   MOC_HIP(hipGetDevice(&dev));
   if (dev != g->device) return MOC_EDEVICE;
   if (g->has_self_loop) return MOC_EINVAL;
-  const NbLayout lay = nb_layout(g->view.T, g->view.n, g->view.m, g->max_lds);
+  const NbLayout lay = nb_layout(g->view.T, g->view.n, g->view.m, g->max_lds, 1024);
   if (lay.bytes > g->max_lds) return MOC_EOVERFLOW;
   if ((int64_t)g->view.T * 4 * R * 8 > 0xFFFFFFFFll) return MOC_EOVERFLOW;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);

@@ -83,3 +83,30 @@ def test_largest_base(moc):
             after = oracle.evaluate(g, 100, C, ws.cpu().numpy(), we.cpu().numpy(), wa.cpu().numpy())[0]
             assert (after[2], after[0]) == (int(bm["violations"]), int(bm["peak"]))
     gh.free()
+
+
+@pytest.mark.parametrize("n,C,B,R", [(5, 2, 3, 2), (64, 2, 1100, 3), (130, 2, 1100, 4), (300, 3, 600, 3), (33, 5, 1100, 2), (600, 2, 520, 2),
+                                     (64, 2, 3, 16), (130, 4, 1100, 16)])
+def test_neighbours_with_ill_formed_copies(moc, n, C, B, R):
+    """Bases in which many active copies are not live (start behind end, outside the domain) and some
+    have no live copy at all, on either side of the lines between the workgroup sizes; the rows
+    repeat.  Table, best move with it and best move alone."""
+    rng = np.random.default_rng(13 * n + C + R)
+    g = random_graph(rng, n)
+    rows, T = 3, n * C
+    s, e, a = schedules(rng, g, C, rows, wild=True)
+    flip = rng.random(T) < 0.3                       # row 0: a schedule with some of its intervals turned round
+    s[0], e[0] = np.where(flip, e[0] + 1, s[0]), np.where(flip, s[0], e[0])
+    s[1], e[1], a[1] = rng.integers(1, T + 3, T), 0, 1   # row 1: no live copy
+    pick = np.arange(B) % rows
+    gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, 100, C)
+    dev = to_dev(s[pick], e[pick], a[pick])
+    moves, best = (moc.results_to_numpy(x, d) for x, d in zip(moc.moc_eval_neighbours(gh, *dev, R), (moc.MOVE_SCORE_DTYPE, moc.BEST_MOVE_DTYPE)))
+    alone = moc.results_to_numpy(moc.moc_eval_neighbours(gh, *dev, R, want_moves=False)[1], moc.BEST_MOVE_DTYPE)
+    assert (alone == best).all()
+    for r in range(rows):
+        assert (moves[r::rows] == moves[r]).all() and (best[r::rows] == best[r]).all(), r
+        scores, bm = oracle.neighbours(g, 100, C, s[r], e[r], a[r], R)
+        assert (moves[r]["violations"] == scores[:, 0]).all() and (moves[r]["peak"] == scores[:, 1]).all(), r
+        assert (int(best[r]["move"]), int(best[r]["violations"]), int(best[r]["peak"])) == bm, r
+    gh.free()
