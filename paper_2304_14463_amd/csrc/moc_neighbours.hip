@@ -639,31 +639,26 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     const int chunks = lay.mask_words / 2;
     const int n_live = __builtin_amdgcn_readfirstlane(counts[1]), n_ill = __builtin_amdgcn_readfirstlane(counts[4]);
     for (int c = wave_; c < chunks; c += kNW) {
-      int before = 0, before_ill = 0;
+      int both = 0;   // live copies before these 64, and (from bit 16 on) active copies that are not live
       for (int x = lane_; x < c; x += kWave) {
         const int live = __popcll(chunk(L.involved, x));
-        before += live;
-        before_ill += __popcll(chunk(L.amask, x)) - live;
+        both += live + ((__popcll(chunk(L.amask, x)) - live) << 16);
       }
-#pragma unroll
-      for (int off = kWave / 2; off > 0; off >>= 1) {
-        before += __shfl_xor(before, off);
-        before_ill += __shfl_xor(before_ill, off);
-      }
+      both = last_lane(scan_sum(both));
+      const int before = both & 0xFFFF, before_ill = both >> 16;
       const uint64_t lm = chunk(L.involved, c), ill = chunk(L.amask, c) & ~lm, lower = ((uint64_t)1 << lane_) - 1;
       if ((lm >> lane_) & 1) L.list[before + __popcll(lm & lower)] = (uint16_t)(c * kWave + lane_);
       if ((ill >> lane_) & 1) L.list[n_live + before_ill + __popcll(ill & lower)] = (uint16_t)(c * kWave + lane_);
     }
     block_scan<AddOp, false, kNT>(L.profile, L.profile, T, L.scratch, t_);   // Eq. (4) per position
-    block_max_both_ways<kNT>(L.profile, L.pmax, L.smax, T, L.scratch, t_);
-
     // For the best move alone the rest looks at the live copies only; the rows of the table are filled
     // by active flags.
     for (int w = t_; w < lay.mask_words; w += kNT) {
       if constexpr (!TABLE) L.amask[w] = L.involved[w];
       L.involved[w] = 0;
     }
-    __syncthreads();
+    block_max_both_ways<kNT>(L.profile, L.pmax, L.smax, T, L.scratch, t_);
+
     // ---- pass 1: the violations of the base, each instance once: per active copy its form,
     // the order pair it opens and its inputs
     if (t_ == 0) viol += n_ill;   // Eq. (2)/(8)
@@ -713,17 +708,13 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
       for (int off = kWave / 2; off > 0; off >>= 1) all_first += __shfl_xor(all_first, off);
       n_first = __builtin_amdgcn_readfirstlane(all_first);
       for (int c = wave_; c < chunks; c += kNW) {
-        int before_first = 0, before_rest = 0;
+        int both = 0;
         for (int x = lane_; x < c; x += kWave) {
           const uint64_t am = chunk(L.amask, x), inv = chunk(L.involved, x);
-          before_first += __popcll(am & inv);
-          before_rest += __popcll(am & ~inv);
+          both += __popcll(am & inv) + (__popcll(am & ~inv) << 16);
         }
-#pragma unroll
-        for (int off = kWave / 2; off > 0; off >>= 1) {
-          before_first += __shfl_xor(before_first, off);
-          before_rest += __shfl_xor(before_rest, off);
-        }
+        both = last_lane(scan_sum(both));
+        const int before_first = both & 0xFFFF, before_rest = both >> 16;
         const uint64_t am = chunk(L.amask, c), inv = chunk(L.involved, c), lower = ((uint64_t)1 << lane_) - 1;
         if ((am & inv) >> lane_ & 1) L.list[before_first + __popcll(am & inv & lower)] = (uint16_t)(c * kWave + lane_);
         if ((am & ~inv) >> lane_ & 1) L.list[n_first + before_rest + __popcll(am & ~inv & lower)] = (uint16_t)(c * kWave + lane_);
@@ -926,7 +917,7 @@ NbKernel pick_kernel(int nt, bool adj_lds, int C, int R, bool table) {
 // unit hide each other's latencies, as long as the batch has several per unit.  Best move alone, R = 8,
 // C = 2, by 256 / 512 / 1024 threads: n = 120, 2048 bases 33 / 47 / 90 us; n = 442, 1024 bases
 // 46 / 47 / 67, 16 bases 41 / 26 / 26; n = 1000, 1024 bases 85 / 73 / 87; n = 2000, 512 bases
-// 174 / 96 / 77.
+// 174 / 96 / 77 (with lists built by packed counts the chosen ones take 43, 67 and 70).
 int nb_threads(int T, int64_t B, int num_cu) {
   const int64_t per_cu = (B + num_cu - 1) / num_cu;
   if (T <= 1024 && per_cu >= 4) return 256;
