@@ -2,7 +2,7 @@
 // the base staged in LDS (copies, memory profile of Eq. (4), maxima over any range of it).
 #pragma once
 
-#include "moc_internal.h"
+#include "moc_wave.h"
 
 namespace {
 
@@ -14,34 +14,6 @@ __device__ __forceinline__ uint32_t pack_copy(bool live, int s, int e) {
   return live ? ((uint32_t)s | ((uint32_t)e << 16)) : MOC_DEAD;
 }
 __device__ __forceinline__ bool bit_at(const uint32_t* bits, int t) { return (bits[t >> 5] >> (t & 31)) & 1u; }
-
-// ------------------------------------------------------------------ wave scans
-// The value of the lane CTRL names (a lane shift of the vector ALU), 0 where that lane does not
-// exist or the row is not in ROWS.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ int lane_shift(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, true); }
-
-// Inclusive scans over the 64 lanes: inside rows of 16 by shifts of 1, 2, 4, 8, then lane 15 of
-// rows 0 and 2 goes to rows 1 and 3, then lane 31 to rows 2 and 3.  Values of the maximum >= 0.
-__device__ __forceinline__ int scan_sum(int x) {
-  x += lane_shift<0x111, 0xF>(x);
-  x += lane_shift<0x112, 0xF>(x);
-  x += lane_shift<0x114, 0xF>(x);
-  x += lane_shift<0x118, 0xF>(x);
-  x += lane_shift<0x142, 0xA>(x);
-  x += lane_shift<0x143, 0xC>(x);
-  return x;
-}
-__device__ __forceinline__ int scan_max(int x) {
-  x = max(x, lane_shift<0x111, 0xF>(x));
-  x = max(x, lane_shift<0x112, 0xF>(x));
-  x = max(x, lane_shift<0x114, 0xF>(x));
-  x = max(x, lane_shift<0x118, 0xF>(x));
-  x = max(x, lane_shift<0x142, 0xA>(x));
-  x = max(x, lane_shift<0x143, 0xC>(x));
-  return x;
-}
-__device__ __forceinline__ int last_lane(int x) { return __builtin_amdgcn_readlane(x, kWave - 1); }
 
 // LDS written by some lanes of a wave is read by others of the same wave: LDS operations of a
 // wave complete in order, so the compiler must keep them in order, and that is all.

@@ -22,7 +22,8 @@
 // hold the few nodes recomputed in a stage, and the stage's own node).
 //
 // One workgroup per candidate at a time, one lane per node, all in LDS.
-#include "moc_internal.h"
+#include "moc_cover.h"
+#include "moc_wave.h"
 
 namespace {
 
@@ -71,17 +72,12 @@ __device__ __forceinline__ int wave_sum_i(int v) {
   return v;
 }
 
-// CT = C when C <= 4 (the copies of a node are then read into registers, for this candidate at
-// the top of its turn and for the workgroup's next candidate as soon as they are used), else 0
-// (any C, read where needed); U = nodes per lane, ceil(n / kNT), when CT > 0.
-template <int CT, int U>
-// 64 registers (four workgroups per CU) where the copies of a lane's nodes are few enough to fit
-// beside the rest; otherwise as many as they take.
-__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu((CT == 0 ? 1 : CT) * U <= 4 && U <= 2 && CT <= 3 ? 8 : 4, 8))) void eval_staged_kernel(GraphView g, const int32_t* __restrict__ place, int64_t B,
-                                                          const int32_t* __restrict__ starts,
-                                                          const int32_t* __restrict__ ends,
-                                                          const uint8_t* __restrict__ active,
-                                                          moc_result* __restrict__ out, StLayout lay) {
+// Any C: the copies are read where needed, several passes over them in LDS.
+__global__ __launch_bounds__(kNT) void eval_staged_general_kernel(GraphView g, const int32_t* __restrict__ place, int64_t B,
+                                                                  const int32_t* __restrict__ starts,
+                                                                  const int32_t* __restrict__ ends,
+                                                                  const uint8_t* __restrict__ active,
+                                                                  moc_result* __restrict__ out, StLayout lay) {
   extern __shared__ uint32_t st_raw[];
   int32_t* const cur = reinterpret_cast<int32_t*>(st_raw + lay.cur_off);
   uint16_t* const bucket = reinterpret_cast<uint16_t*>(st_raw + lay.bucket_off);
@@ -94,56 +90,6 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu((CT == 0 ? 
   const uint32_t D = (uint32_t)n * (uint32_t)(n + 1) / 2u;   // positions of the domain
 
   for (int i = tid; i < kNT * lay.chunk; i += kNT) delta[i] = 0;
-
-  // registers for the copies of the lane's nodes (CT > 0)
-  constexpr int RU = CT > 0 ? U : 1, RC = CT > 0 ? CT : 1;
-  [[maybe_unused]] int rs[RU][RC], re[RU][RC];
-  // a node's flags as they lie in memory, in one register, taken apart where they are used:
-  // bytes put together in a register as they arrive make each load wait where it is issued
-  struct Flags { uint8_t a[RC]; };
-  static_assert(sizeof(Flags) <= 4, "the flags of a node fit a register");
-  [[maybe_unused]] uint32_t ra[RU];
-  // The candidate's rows are the same for all lanes (scalar registers); a lane adds a 32-bit
-  // offset that is formed here from the thread index each time.  Whole addresses per lane, kept
-  // across the loop over the candidates, would be spilled, and fetching them back here makes
-  // every load of the request wait for the one before.
-  struct alignas(4) Ints { int32_t x[RC]; };
-  [[maybe_unused]] auto request = [&](int64_t cand) {
-    if constexpr (CT > 0) {
-      const char* const s_row = reinterpret_cast<const char*>(starts + cand * T);
-      const char* const e_row = reinterpret_cast<const char*>(ends + cand * T);
-      const char* const a_row = reinterpret_cast<const char*>(active + cand * T);
-      int t = tid;
-      asm volatile("" : "+v"(t));
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const uint32_t off = (uint32_t)min(u * kNT + t, n - 1) * CT;   // lanes past the last node re-read it
-        const Ints sv = *reinterpret_cast<const Ints*>(s_row + off * 4u);
-        const Ints ev = *reinterpret_cast<const Ints*>(e_row + off * 4u);
-        const Flags f = *reinterpret_cast<const Flags*>(a_row + off);
-#pragma unroll
-        for (int i = 0; i < CT; ++i) {
-          rs[u][i] = sv.x[i];
-          re[u][i] = ev.x[i];
-        }
-        uint32_t w = 0;
-        __builtin_memcpy(&w, &f, sizeof(Flags));
-        ra[u] = w;
-      }
-    }
-  };
-  if ((int64_t)blockIdx.x < B) request(blockIdx.x);
-  // place, m_v, w_v of the lane's nodes: the same for every candidate
-  [[maybe_unused]] int rk[RU];
-  [[maybe_unused]] int2 rsd[RU];
-  if constexpr (CT > 0) {
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int v = min(u * kNT + tid, n - 1);
-      rk[u] = place[v];
-      rsd[u] = g.size_dur[v];
-    }
-  }
 
   for (int64_t b = blockIdx.x; b < B; b += gridDim.x) {
     const int64_t row = b * T;
@@ -180,50 +126,11 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu((CT == 0 ? 
       pj[c] = live ? code : -2;   // -2 >> 1 = -1: no stage
       pe[c] = e;
     };
-    if constexpr (CT > 0) {
-      // the same per copy, on registers: the start's register takes the copy's code (stage << 1 |
-      // first at its position, -2 if not usable), which the next two phases read
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int v = u * kNT + tid;
-        if (v < n) {
-          const int k = rk[u], w = rsd[u].y;
-          int prev_end = -1;
-#pragma unroll
-          for (int i = 0; i < CT; ++i) {
-            const int s = rs[u][i], e = re[u][i];
-            const bool act = ((ra[u] >> (8 * i)) & 0xFFu) != 0;
-            bool live = act && (uint32_t)s <= (uint32_t)e && (uint32_t)e < D;
-            int j = -1;
-            if (live) {
-              j = stage_of((uint32_t)s);
-              live = (uint32_t)s - stage_start(j) == (uint32_t)k && (i > 0 || j == k);
-            }
-            viol += (act && !live) ? 1 : 0;
-            if (i == 0) viol += act ? 0 : 1;
-            dur += act ? w : 0;
-            int code = -2;
-            if (live) {
-              viol += prev_end > s ? 1 : 0;   // Eq. (3), on the positions as given
-              prev_end = e;
-              bool first_here = true;         // Eq. (6), see above
-#pragma unroll
-              for (int q = 0; q < i; ++q) first_here = first_here && rs[u][q] >> 1 != j;
-              if (first_here) atomicAdd(&cur[j], 1);
-              else viol += 1;
-              code = j << 1 | (first_here ? 1 : 0);
-            }
-            rs[u][i] = code;
-          }
-        }
-      }
-    } else {
-      for (int v = tid; v < n; v += kNT) {
-        const int k = place[v], w = g.size_dur[v].y;
-        int prev_end = -1;
-        for (int i = 0; i < C; ++i)
-          copy_step(v, k, w, i, starts[row + v * C + i], ends[row + v * C + i], active[row + v * C + i] != 0, prev_end);
-      }
+    for (int v = tid; v < n; v += kNT) {
+      const int k = place[v], w = g.size_dur[v].y;
+      int prev_end = -1;
+      for (int i = 0; i < C; ++i)
+        copy_step(v, k, w, i, starts[row + v * C + i], ends[row + v * C + i], active[row + v * C + i] != 0, prev_end);
     }
     __syncthreads();
 
@@ -253,64 +160,16 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu((CT == 0 ? 
     __syncthreads();
 
     // ---- buckets: the place of every node that has a first-at-its-position start in the stage
-    if constexpr (CT > 0) {
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (u * kNT + tid >= n) continue;
-#pragma unroll
-        for (int i = 0; i < CT; ++i) {
-          const int code = rs[u][i];
-          if (code >= 0 && (code & 1)) bucket[atomicAdd(&cur[code >> 1], 1)] = (uint16_t)rk[u];
-        }
-      }
-    } else {
-      for (int v = tid; v < n; v += kNT) {
-        const int k = place[v];
-        for (int i = 0; i < C; ++i) {
-          const int code = pj[v * C + i];
-          if (code >= 0 && (code & 1)) bucket[atomicAdd(&cur[code >> 1], 1)] = (uint16_t)k;
-        }
+    for (int v = tid; v < n; v += kNT) {
+      const int k = place[v];
+      for (int i = 0; i < C; ++i) {
+        const int code = pj[v * C + i];
+        if (code >= 0 && (code & 1)) bucket[atomicAdd(&cur[code >> 1], 1)] = (uint16_t)k;
       }
     }
     __syncthreads();   // now cur[j] = end of stage j's bucket = start of stage j + 1's
 
     // ---- renumber, stage the records, scatter Eq. (4)
-    // Entries of stage j's bucket below `key` (or up to it), on top of the bucket's offset.  A
-    // bucket holds the stage's own node and the few nodes recomputed in the stage: the first two
-    // entries are read at once, a loop takes the rest.
-    [[maybe_unused]] auto rank_in_stage = [&](int j, uint32_t key, bool up_to) -> int {
-      const int lo = j ? cur[j - 1] : 0, hi = cur[j];
-      const uint32_t b0 = lo < hi ? bucket[lo] : 0xFFFFu, b1 = lo + 1 < hi ? bucket[lo + 1] : 0xFFFFu;   // places stay below 0xFFFF
-      const uint32_t bound = key + (up_to ? 1u : 0u);
-      int r = lo + (b0 < bound ? 1 : 0) + (b1 < bound ? 1 : 0);
-      for (int x = lo + 2; x < hi; ++x) r += bucket[x] < bound ? 1 : 0;
-      return r;
-    };
-    if constexpr (CT > 0) {
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int v = u * kNT + tid;
-        if (v >= n) continue;
-#pragma unroll
-        for (int i = 0; i < CT; ++i) {
-          const int code = rs[u][i];
-          uint32_t rec = MOC_DEAD;
-          if (code >= 0) {
-            const int cs = rank_in_stage(code >> 1, (uint32_t)rk[u], false);
-            // the last start position not after the end: all starts of earlier stages, and those of
-            // the end's stage at slots up to the end's
-            const uint32_t e = (uint32_t)re[u][i];
-            const int je = stage_of(e);
-            const int ce = rank_in_stage(je, e - stage_start(je), true) - 1;
-            rec = (uint32_t)cs | (uint32_t)ce << 16;
-            atomicAdd(&delta[cs], rsd[u].x);
-            atomicSub(&delta[ce + 1], rsd[u].x);
-          }
-          pj[v * CT + i] = (int32_t)rec;
-        }
-      }
-      if (b + gridDim.x < B) request(b + gridDim.x);   // the rest of this turn works from LDS
-    } else
     for (int v = tid; v < n; v += kNT) {
       const int2 sd = g.size_dur[v];
       const int k = place[v];
@@ -404,6 +263,320 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu((CT == 0 ? 
   }
 }
 
+// C <= 4: the copies of a lane's nodes are held in registers, the workgroup's next candidate is asked
+// for as soon as they are used.  U = nodes per lane, ceil(n / kNT).  What the renumbering needs for a
+// node's first copy follows from its place k alone: its start can only be slot k of stage k, the
+// highest slot of that stage, so that its rank is the last of the stage's; only the copies beyond
+// the first, which are few, are put into buckets and searched for.  An end at the last slot of its
+// stage (where the first copy of a consumer starts) takes the stage's last rank, any other the
+// stage's recomputed nodes up to its slot.  cur[j] holds, in the high bits, first the number of
+// distinct recomputed starts of stage j, then the offset of its bucket, then the end of the bucket;
+// bit 0 says whether the stage's own node starts there (it comes behind the bucket).
+// Bound by the vector ALU.  n = 1000, C = 2, 16384 candidates: 208 us with every copy put into a
+// bucket and searched for, correctly rounded square roots and the whole delta array scanned; 131 us
+// without these; 103 us with the wave scans and sums by lane shifts instead of the LDS crossbar.
+__device__ __forceinline__ int stage_and_slot(uint32_t p, uint32_t* slot) {   // stage_of(p) and the slot in it
+  int j = (int)(__builtin_amdgcn_sqrtf(8.0f * (float)p + 1.0f) * 0.5f - 0.5f);   // off by one at most: as in stage_of, with one more ulp (2^-7 at most) in the root
+  int at = (int)(p - stage_start(j));
+  if (at < 0) {
+    at += j;
+    --j;
+  } else if (at > j) {
+    ++j;
+    at -= j;
+  }
+  *slot = (uint32_t)at;
+  return j;
+}
+
+template <int CT, int U, int EDGES>
+__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(CT * U <= 4 && U <= 2 && CT <= 3 ? 8 : 4, 8)))
+void eval_staged_kernel(GraphView g, const int32_t* __restrict__ place, int64_t B, const int32_t* __restrict__ starts,
+                        const int32_t* __restrict__ ends, const uint8_t* __restrict__ active,
+                        moc_result* __restrict__ out, StLayout lay) {
+  extern __shared__ uint32_t st_raw[];
+  int32_t* const cur = reinterpret_cast<int32_t*>(st_raw + lay.cur_off);
+  uint16_t* const bucket = reinterpret_cast<uint16_t*>(st_raw + lay.bucket_off);
+  uint32_t* const rec = st_raw + lay.pj_off;   // records of the copies; one more node that is never live
+  int32_t* const delta = reinterpret_cast<int32_t*>(st_raw + lay.delta_off);
+  int32_t* const red = reinterpret_cast<int32_t*>(st_raw + lay.red_off);
+  const int tid = threadIdx.x;
+  const int n = g.n, T = g.T, m = g.m;
+  const uint32_t D = (uint32_t)n * (uint32_t)(n + 1) / 2u;   // positions of the domain
+
+  for (int i = tid; i < kNT * lay.chunk; i += kNT) delta[i] = 0;
+  for (int j = tid; j < n; j += kNT) cur[j] = 0;
+  if (tid < CT) rec[T + tid] = MOC_DEAD;
+
+  int rs[U][CT], re[U][CT];
+  // a node's flags as they lie in memory, in one register, taken apart where they are used:
+  // bytes put together in a register as they arrive make each load wait where it is issued
+  struct Flags { uint8_t a[CT]; };
+  static_assert(sizeof(Flags) <= 4, "the flags of a node fit a register");
+  uint32_t ra[U];
+  // The candidate's rows are the same for all lanes (scalar registers); a lane adds a 32-bit
+  // offset that is formed here from the thread index each time.  Whole addresses per lane, kept
+  // across the loop over the candidates, would be spilled, and fetching them back here makes
+  // every load of the request wait for the one before.
+  struct alignas(4) Ints { int32_t x[CT]; };
+  auto request = [&](int64_t cand) {
+    const char* const s_row = reinterpret_cast<const char*>(starts + cand * T);
+    const char* const e_row = reinterpret_cast<const char*>(ends + cand * T);
+    const char* const a_row = reinterpret_cast<const char*>(active + cand * T);
+    int t = tid;
+    asm volatile("" : "+v"(t));
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t off = (uint32_t)min(u * kNT + t, n - 1) * CT;   // lanes past the last node re-read it
+      const Ints sv = *reinterpret_cast<const Ints*>(s_row + off * 4u);
+      const Ints ev = *reinterpret_cast<const Ints*>(e_row + off * 4u);
+      const Flags f = *reinterpret_cast<const Flags*>(a_row + off);
+#pragma unroll
+      for (int i = 0; i < CT; ++i) {
+        rs[u][i] = sv.x[i];
+        re[u][i] = ev.x[i];
+      }
+      uint32_t w = 0;
+      __builtin_memcpy(&w, &f, sizeof(Flags));
+      ra[u] = w;
+    }
+  };
+  if ((int64_t)blockIdx.x < B) request(blockIdx.x);
+  // place, m_v, w_v of the lane's nodes and its edges: the same for every candidate
+  int rk[U];
+  int2 rsd[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int v = min(u * kNT + tid, n - 1);
+    rk[u] = place[v];
+    rsd[u] = g.size_dur[v];
+  }
+  const uint32_t no_edge = (uint32_t)T | (uint32_t)T << 16;   // beyond the list: the node that is never live
+  uint32_t edge[EDGES > 0 ? EDGES : 1];
+#pragma unroll
+  for (int x = 0; x < EDGES; ++x) {
+    const int at = x * kNT + tid;
+    edge[x] = at < m ? g.edge_pair_c[at] : no_edge;
+  }
+  __syncthreads();
+
+  for (int64_t b = blockIdx.x; b < B; b += gridDim.x) {
+    int t_ = tid;   // what derives from the thread index is formed again for every candidate
+    asm volatile("" : "+v"(t_));
+    const int lane = t_ & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(t_ / kWave);
+    // ---- per node: Eq. (1), (2), (3), (7), (8) and the domain of the starts; count the distinct
+    //      usable starts per stage.  A start's register takes the copy's code: stage << 1 | first at
+    //      its position, -2 if not usable.
+    int viol = 0, dur = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int v = u * kNT + t_;
+      if (v < n) {
+        const int k = rk[u], w = rsd[u].y;
+        const uint32_t flags = ra[u];
+        const int e0 = re[u][0];
+        const bool act0 = (flags & 0xFFu) != 0;
+        const bool live0 = act0 && (uint32_t)rs[u][0] == stage_start(k) + (uint32_t)k && (uint32_t)rs[u][0] <= (uint32_t)e0 && (uint32_t)e0 < D;
+        viol += live0 ? 0 : 1;   // Eq. (2), (8) if it is active, Eq. (7) if it is not
+        dur += act0 ? w : 0;
+        rs[u][0] = live0 ? k << 1 | 1 : -2;
+        if (live0) atomicAdd(&cur[k], 1);
+        if constexpr (CT > 1) {
+          int prev_end = live0 ? e0 : -1;   // end of the node's latest usable copy so far
+#pragma unroll
+          for (int i = 1; i < CT; ++i) {
+            const int s = rs[u][i], e = re[u][i];
+            int code = -2;
+            if ((flags >> (8 * i)) & 0xFFu) {
+              dur += w;
+              bool live = (uint32_t)s <= (uint32_t)e && (uint32_t)e < D;
+              uint32_t slot = 0;
+              const int j = stage_and_slot(live ? (uint32_t)s : 0u, &slot);
+              live = live && slot == (uint32_t)k;
+              if (live) {
+                viol += prev_end > s ? 1 : 0;   // Eq. (3), on the positions as given
+                prev_end = e;
+                // Eq. (6): a usable start shares its position only with copies of its own node, which
+                // sit in the same stage; the first of them stands for the position
+                bool first_here = true;
+#pragma unroll
+                for (int q = 0; q < i; ++q) first_here = first_here && rs[u][q] >> 1 != j;
+                if (first_here) atomicAdd(&cur[j], 2);
+                else viol += 1;
+                code = j << 1 | (first_here ? 1 : 0);
+              } else {
+                viol += 1;   // Eq. (2), (8)
+              }
+            }
+            rs[u][i] = code;
+          }
+        }
+      }
+    }
+    __syncthreads();
+
+    // ---- cur[j] <- offset of the stage's bucket, by a running sum of the starts in the stages before
+    int total = 0;   // distinct usable starts
+    {
+      constexpr int per = U;
+      const int j0 = t_ * per;
+      int c[per], sum = 0;
+#pragma unroll
+      for (int d = 0; d < per; ++d) {
+        c[d] = j0 + d < n ? cur[j0 + d] : 0;
+        sum += (c[d] >> 1) + (c[d] & 1);
+      }
+      const int incl = scan_sum(sum);
+      if (lane == kWave - 1) red[wave] = incl;
+      __syncthreads();
+      int before = incl - sum;
+#pragma unroll
+      for (int w = 0; w < kNW; ++w) {
+        const int x = red[w];
+        before += w < wave ? x : 0;
+        total += x;
+      }
+#pragma unroll
+      for (int d = 0; d < per; ++d) {
+        if (j0 + d < n) cur[j0 + d] = before << 1 | (c[d] & 1);
+        before += (c[d] >> 1) + (c[d] & 1);
+      }
+      total = __builtin_amdgcn_readfirstlane(total);
+    }
+    __syncthreads();
+
+    // ---- buckets: the place of every node that is computed again in the stage
+    if constexpr (CT > 1) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        if (u * kNT + t_ >= n) continue;
+#pragma unroll
+        for (int i = 1; i < CT; ++i) {
+          const int code = rs[u][i];
+          if (code >= 0 && (code & 1)) bucket[atomicAdd(&cur[code >> 1], 2) >> 1] = (uint16_t)rk[u];
+        }
+      }
+      __syncthreads();
+    }
+
+    // ---- renumber, stage the records, scatter Eq. (4)
+    // recomputed nodes of stage j with a place below `bound`, on top of the rank of the stage's first start
+    auto rank_in_stage = [&](int j, uint32_t bound) -> int {
+      const int before = j ? cur[j - 1] : 0, hi = cur[j] >> 1;
+      const int lo = (before >> 1) + (before & 1);
+      int r = lo;
+      for (int x = lo; x < hi; ++x) r += bucket[x] < bound ? 1 : 0;
+      return r;
+    };
+    auto rank_of_end = [&](uint32_t e) -> int {   // of the last start not after position e
+      uint32_t slot;
+      const int j = stage_and_slot(e, &slot);
+      if (slot == (uint32_t)j) {
+        const int c = cur[j];
+        return (c >> 1) + (c & 1) - 1;
+      }
+      return rank_in_stage(j, slot + 1) - 1;
+    };
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int v = u * kNT + t_;
+      if (v >= n) continue;
+      uint32_t r[CT];
+#pragma unroll
+      for (int i = 0; i < CT; ++i) {
+        const int code = rs[u][i];
+        r[i] = MOC_DEAD;
+        if (code >= 0) {
+          const int cs = i == 0 ? cur[rk[u]] >> 1 : rank_in_stage(code >> 1, (uint32_t)rk[u]);
+          const int ce = rank_of_end((uint32_t)re[u][i]);
+          r[i] = (uint32_t)cs | (uint32_t)ce << 16;
+          atomicAdd(&delta[cs], rsd[u].x);
+          atomicSub(&delta[ce + 1], rsd[u].x);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < CT; ++i) rec[v * CT + i] = r[i];
+    }
+    if (b + gridDim.x < B) request(b + gridDim.x);   // the rest of this turn works from LDS
+    __syncthreads();
+
+    // ---- Eq. (4): peak of the running sum over the renumbered positions (the releases behind the
+    // last of them change no maximum but are cleared)
+    int S = 0, P = 0;
+    {
+      const int chunk = ((total + 1 + kNT - 1) / kNT) | 1;   // <= lay.chunk
+      int own = t_;
+      asm volatile("" : "+v"(own));
+      int32_t* d = delta + own * chunk;
+      for (int x = 0; x < chunk; ++x) {
+        const int y = d[x];
+        d[x] = 0;
+        S += y;
+        P = max(P, S);
+      }
+      combine_segments(S, P);
+    }
+    for (int j = t_; j < n; j += kNT) cur[j] = 0;   // for the next candidate
+    // ---- Eq. (5): one lane per edge, every usable copy of the consumer
+    auto check = [&](uint32_t pair) {
+      Record<CT> pu, pv;
+#pragma unroll
+      for (int q = 0; q < CT; ++q) {
+        pu.w[q] = rec[(pair & 0xFFFFu) + q];
+        pv.w[q] = rec[(pair >> 16) + q];
+      }
+#pragma unroll
+      for (int i = 0; i < CT; ++i) count_live_uncovered<CT>(viol, pu, pv.w[i]);
+    };
+    if constexpr (EDGES > 0) {
+#pragma unroll
+      for (int x = 0; x < EDGES; ++x) check(edge[x]);
+    } else {
+      for (int x0 = 0; x0 < m; x0 += kNT) {   // every lane the same number of rounds
+        const uint32_t pair = g.edge_pair_c[min(x0 + t_, m - 1)];
+        check(x0 + t_ < m ? pair : no_edge);
+      }
+    }
+    viol = scan_sum(viol);
+    dur = scan_sum(dur);
+    if (lane == kWave - 1) {   // the lane that holds the wave's totals
+      int32_t* r = red + 8 + wave * 4;
+      r[0] = S; r[1] = P; r[2] = viol; r[3] = dur;
+    }
+    __syncthreads();
+    // (no barrier behind this: the words read here are written again behind several)
+    if (t_ == 0) {
+      int S0 = 0, P0 = 0, V = 0, W = 0;
+      for (int w = 0; w < kNW; ++w) {
+        const int32_t* r = red + 8 + w * 4;
+        P0 = max(P0, S0 + r[1]);
+        S0 += r[0];
+        V += r[2];
+        W += r[3];
+      }
+      moc_result res;
+      res.peak = P0;
+      res.duration = W;
+      res.violations = V;
+      res.feasible = (V == 0 && (int64_t)P0 <= g.budget) ? 1 : 0;
+      out[b] = res;
+    }
+  }
+}
+
+using StagedKernel = void (*)(GraphView, const int32_t*, int64_t, const int32_t*, const int32_t*, const uint8_t*, moc_result*, StLayout);
+
+// The edges of a lane stay in registers where there are at most kEdges of them.
+constexpr int kEdges = 6;
+template <int CT, int U>
+StagedKernel pick_edges(int per_lane) {
+  if constexpr (U <= 2) {
+    if (per_lane <= 3) return eval_staged_kernel<CT, U, 3>;
+    if (per_lane <= kEdges) return eval_staged_kernel<CT, U, kEdges>;
+  }
+  return eval_staged_kernel<CT, U, 0>;
+}
+
 }  // namespace
 
 extern "C" int moc_eval_batch_staged(const moc_graph* g, int64_t B, const int32_t* starts, const int32_t* ends,
@@ -419,24 +592,25 @@ extern "C" int moc_eval_batch_staged(const moc_graph* g, int64_t B, const int32_
   const StLayout lay = st_layout(g->view.n, g->view.C);
   if (lay.bytes > g->max_lds || g->view.T >= 0xFFFF) return MOC_EOVERFLOW;
   const int per_lane = (g->view.n + kNT - 1) / kNT, C = g->view.C;
-  auto kern = eval_staged_kernel<0, 1>;
+  const int edges = (g->view.m + kNT - 1) / kNT;
+  StagedKernel kern = eval_staged_general_kernel;
   if (C <= 4 && per_lane * C <= 16) {   // the copies of a lane's nodes fit its registers
     const int u = per_lane <= 1 ? 1 : per_lane <= 2 ? 2 : per_lane <= 4 ? 4 : 8;
     switch (C * 16 + u) {
-      case 1 * 16 + 1: kern = eval_staged_kernel<1, 1>; break;
-      case 1 * 16 + 2: kern = eval_staged_kernel<1, 2>; break;
-      case 1 * 16 + 4: kern = eval_staged_kernel<1, 4>; break;
-      case 1 * 16 + 8: kern = eval_staged_kernel<1, 8>; break;
-      case 2 * 16 + 1: kern = eval_staged_kernel<2, 1>; break;
-      case 2 * 16 + 2: kern = eval_staged_kernel<2, 2>; break;
-      case 2 * 16 + 4: kern = eval_staged_kernel<2, 4>; break;
-      case 2 * 16 + 8: kern = eval_staged_kernel<2, 8>; break;
-      case 3 * 16 + 1: kern = eval_staged_kernel<3, 1>; break;
-      case 3 * 16 + 2: kern = eval_staged_kernel<3, 2>; break;
-      case 3 * 16 + 4: kern = eval_staged_kernel<3, 4>; break;
-      case 4 * 16 + 1: kern = eval_staged_kernel<4, 1>; break;
-      case 4 * 16 + 2: kern = eval_staged_kernel<4, 2>; break;
-      case 4 * 16 + 4: kern = eval_staged_kernel<4, 4>; break;
+      case 1 * 16 + 1: kern = pick_edges<1, 1>(edges); break;
+      case 1 * 16 + 2: kern = pick_edges<1, 2>(edges); break;
+      case 1 * 16 + 4: kern = pick_edges<1, 4>(edges); break;
+      case 1 * 16 + 8: kern = pick_edges<1, 8>(edges); break;
+      case 2 * 16 + 1: kern = pick_edges<2, 1>(edges); break;
+      case 2 * 16 + 2: kern = pick_edges<2, 2>(edges); break;
+      case 2 * 16 + 4: kern = pick_edges<2, 4>(edges); break;
+      case 2 * 16 + 8: kern = pick_edges<2, 8>(edges); break;
+      case 3 * 16 + 1: kern = pick_edges<3, 1>(edges); break;
+      case 3 * 16 + 2: kern = pick_edges<3, 2>(edges); break;
+      case 3 * 16 + 4: kern = pick_edges<3, 4>(edges); break;
+      case 4 * 16 + 1: kern = pick_edges<4, 1>(edges); break;
+      case 4 * 16 + 2: kern = pick_edges<4, 2>(edges); break;
+      case 4 * 16 + 4: kern = pick_edges<4, 4>(edges); break;
       default: break;
     }
   }

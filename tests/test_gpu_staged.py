@@ -183,3 +183,43 @@ def test_staged_argument_errors(moc):
         moc.moc_eval_batch_staged(gh, z, z, torch.zeros((1, 2 * n), dtype=torch.uint8, device="cuda"))
     assert err.value.code == -2
     gh.free()
+
+
+@pytest.mark.parametrize("n,C,degree,B", [(100, 2, 2, 2600), (1, 2, 0, 9), (511, 4, 3, 60), (512, 2, 9, 40), (513, 2, 4, 40), (600, 1, 1, 40),
+                                          (1100, 3, 2, 12), (1030, 4, 6, 6), (2100, 2, 2, 6), (2100, 1, 5, 6)])
+def test_staged_recomputed_starts_and_ends(moc, n, C, degree, B):
+    """Every instantiation by nodes and edges per lane.  Further copies at their node's slot of any
+    stage (its own among them, with the first copy there or not, and twice in one stage), ends at
+    slots of their stage from the first to the last, several candidates per workgroup."""
+    from paper_2304_14463_amd.inputs import graph_from_edges
+    rng = np.random.default_rng(1000 * n + 10 * C + degree)
+    edges = sorted({(int(u), v) for v in range(1, n) for u in rng.integers(max(0, v - 40), v, size=degree)})
+    g = graph_from_edges(n, edges, rng.integers(0, 60, n), rng.integers(0, 9, n))
+    order = list(range(n))
+    D = n * (n + 1) // 2
+    place = np.arange(n)
+    rows = min(B, 40)
+    s = np.zeros((rows, n, C), np.int64)
+    e = np.zeros((rows, n, C), np.int64)
+    a = (rng.random((rows, n, C)) < 0.5).astype(np.uint8)
+    a[:, :, 0] = rng.random((rows, n)) < 0.9
+    s[:, :, 0] = slot_position(place, place)
+    for i in range(1, C):
+        j = np.minimum(place + (rng.random((rows, n)) * (n - place) * rng.integers(0, 2, (rows, n))).astype(int) + rng.integers(0, 2, (rows, n)), n - 1)
+        s[:, :, i] = slot_position(j, place)
+    s = np.where(rng.random(s.shape) < 0.02, np.clip(s + rng.integers(-2, 3, s.shape), -1, D), s)     # off the slot
+    stage = np.floor((np.sqrt(8.0 * np.maximum(s, 0) + 1) - 1) / 2).astype(np.int64)
+    je = np.minimum(stage + rng.integers(0, 6, s.shape), n - 1)
+    kind = rng.integers(0, 3, s.shape)
+    e = np.where(kind == 0, slot_position(je, je), np.where(kind == 1, slot_position(je, 0), slot_position(je, (rng.random(s.shape) * (je + 1)).astype(int))))
+    e = np.where(rng.random(e.shape) < 0.02, rng.integers(-3, D + 3, e.shape), e)
+    s, e, a = s.reshape(rows, -1).astype(np.int32), e.reshape(rows, -1).astype(np.int32), a.reshape(rows, -1)
+    budget = int(g.size.sum()) // 2
+    gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, budget, C)
+    moc.moc_graph_set_order(gh, order)
+    pick = np.arange(B) % rows
+    gpu = moc.results_to_numpy(moc.moc_eval_batch_staged(gh, *to_dev(s[pick], e[pick], a[pick])))
+    ref = oracle_staged_parallel(g, budget, C, place.astype(np.int32), s, e, a)
+    assert_results_equal(gpu, ref[pick], f"n={n} C={C}")
+    assert len(np.unique(ref[:, F["violations"]])) > 1 or n == 1
+    gh.free()
