@@ -15,6 +15,7 @@ import numpy as np
 _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libmoccasin_hip.so")
 _lib = None
+_torch = None
 
 MOC_MAX_T = 19455
 
@@ -95,11 +96,22 @@ def _host(arr, n):
     return a
 
 
+def _tc():
+    """torch, imported on first use (device memory and streams)."""
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    return _torch
+
+
 def _stream_handle(stream):
-    import torch
+    # The raw handle of the current device's current stream, without a Stream object in between:
+    # small calls are bound by what happens on the host before their launch.
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream)
+        torch = _tc()
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _on(stream):
@@ -107,8 +119,7 @@ def _on(stream):
     allocates and drops while kernels queued on `stream` still use it must belong to that
     stream for torch's allocator, or it could be handed to work on another stream too early."""
     import contextlib
-    import torch
-    return torch.cuda.stream(stream) if stream is not None else contextlib.nullcontext()
+    return _tc().cuda.stream(stream) if stream is not None else contextlib.nullcontext()
 
 
 class Graph:
@@ -143,22 +154,24 @@ def moc_graph_upload(n, in_ptr, in_idx, size, dur, budget, C) -> Graph:
 
 
 def _cand_ptrs(g, B, starts, ends, active):
-    import torch
-    for t, dt in ((starts, torch.int32), (ends, torch.int32), (active, torch.uint8)):
-        if not t.is_cuda or t.dtype != dt or not t.is_contiguous() or t.numel() != B * g.T:
-            raise ValueError("candidate arrays must be contiguous CUDA tensors [B][T]: int32, int32, uint8")
-    return ctypes.c_void_p(starts.data_ptr()), ctypes.c_void_p(ends.data_ptr()), ctypes.c_void_p(active.data_ptr())
+    torch = _tc()
+    n = B * g.T
+    if not (starts.is_cuda and ends.is_cuda and active.is_cuda and starts.dtype is torch.int32 and ends.dtype is torch.int32
+            and active.dtype is torch.uint8 and starts.is_contiguous() and ends.is_contiguous() and active.is_contiguous()
+            and starts.numel() == n and ends.numel() == n and active.numel() == n):
+        raise ValueError("candidate arrays must be contiguous CUDA tensors [B][T]: int32, int32, uint8")
+    return starts.data_ptr(), ends.data_ptr(), active.data_ptr()
 
 
 def moc_eval_batch(g: Graph, starts, ends, active, out=None, stream=None):
     """Evaluate B candidates; returns a uint8 CUDA tensor [B][24] holding moc_result records
     (see results_to_numpy).  Asynchronous on `stream` (default: torch's current stream)."""
-    import torch
+    torch = _tc()
     B = starts.numel() // g.T if g.T else 0
     ps, pe, pa = _cand_ptrs(g, B, starts, ends, active)
     if out is None:
         out = torch.empty((B, RESULT_DTYPE.itemsize), dtype=torch.uint8, device=starts.device)
-    code = lib().moc_eval_batch(g._h, B, ps, pe, pa, ctypes.c_void_p(out.data_ptr()), _stream_handle(stream))
+    code = lib().moc_eval_batch(g._h, B, ps, pe, pa, out.data_ptr(), _stream_handle(stream))
     _check(code, "moc_eval_batch")
     return out
 
@@ -170,7 +183,7 @@ def moc_eval_batch_noalloc(g: Graph, starts, ends, active, out, stream=None):
     ps, pe, pa = _cand_ptrs(g, B, starts, ends, active)
     if not (out.is_cuda and out.is_contiguous() and out.numel() * out.element_size() >= B * RESULT_DTYPE.itemsize):
         raise ValueError("out must be a contiguous CUDA tensor of at least B * 24 bytes")
-    code = lib().moc_eval_batch_noalloc(g._h, B, ps, pe, pa, ctypes.c_void_p(out.data_ptr()), _stream_handle(stream))
+    code = lib().moc_eval_batch_noalloc(g._h, B, ps, pe, pa, out.data_ptr(), _stream_handle(stream))
     _check(code, "moc_eval_batch_noalloc")
     return out
 
@@ -184,12 +197,12 @@ def moc_graph_set_order(g: Graph, order):
 def moc_eval_batch_staged(g: Graph, starts, ends, active, out=None, stream=None):
     """Evaluate B candidates in the stage-restricted domain; returns a uint8 CUDA tensor [B][24]
     of moc_result records."""
-    import torch
+    torch = _tc()
     B = starts.numel() // g.T if g.T else 0
     ps, pe, pa = _cand_ptrs(g, B, starts, ends, active)
     if out is None:
         out = torch.empty((B, RESULT_DTYPE.itemsize), dtype=torch.uint8, device=starts.device)
-    code = lib().moc_eval_batch_staged(g._h, B, ps, pe, pa, ctypes.c_void_p(out.data_ptr()), _stream_handle(stream))
+    code = lib().moc_eval_batch_staged(g._h, B, ps, pe, pa, out.data_ptr(), _stream_handle(stream))
     _check(code, "moc_eval_batch_staged")
     return out
 
@@ -198,7 +211,7 @@ def moc_eval_neighbours(g: Graph, starts, ends, active, R, want_moves=True, want
                         out_best=None, stream=None):
     """Score all single-field moves of B candidates.  Returns (moves, best): uint8 CUDA tensors
     [B][T*4R][8] (moc_move_score) and [B][16] (moc_best_move), or None where not requested."""
-    import torch
+    torch = _tc()
     B = starts.numel() // g.T if g.T else 0
     ps, pe, pa = _cand_ptrs(g, B, starts, ends, active)
     if want_moves and out_moves is None:
@@ -207,8 +220,8 @@ def moc_eval_neighbours(g: Graph, starts, ends, active, R, want_moves=True, want
         out_best = torch.empty((B, BEST_MOVE_DTYPE.itemsize), dtype=torch.uint8, device=starts.device)
     code = lib().moc_eval_neighbours(
         g._h, B, ps, pe, pa, int(R),
-        ctypes.c_void_p(out_moves.data_ptr()) if out_moves is not None else None,
-        ctypes.c_void_p(out_best.data_ptr()) if out_best is not None else None, _stream_handle(stream))
+        out_moves.data_ptr() if out_moves is not None else None,
+        out_best.data_ptr() if out_best is not None else None, _stream_handle(stream))
     _check(code, "moc_eval_neighbours")
     return out_moves, out_best
 
@@ -216,12 +229,12 @@ def moc_eval_neighbours(g: Graph, starts, ends, active, R, want_moves=True, want
 def moc_eval_toggles(g: Graph, starts, ends, active, out=None, stream=None):
     """Score the B x T candidates that differ from a base in one active flag.  Returns a uint8
     CUDA tensor [B][T][16] (moc_toggle_score)."""
-    import torch
+    torch = _tc()
     B = starts.numel() // g.T if g.T else 0
     ps, pe, pa = _cand_ptrs(g, B, starts, ends, active)
     if out is None:
         out = torch.empty((B, g.T, TOGGLE_SCORE_DTYPE.itemsize), dtype=torch.uint8, device=starts.device)
-    code = lib().moc_eval_toggles(g._h, B, ps, pe, pa, ctypes.c_void_p(out.data_ptr()), _stream_handle(stream))
+    code = lib().moc_eval_toggles(g._h, B, ps, pe, pa, out.data_ptr(), _stream_handle(stream))
     _check(code, "moc_eval_toggles")
     return out
 
@@ -230,7 +243,7 @@ def moc_eval_cuts(g: Graph, starts, ends, active, want_moves=True, want_best=Fal
                   stream=None, keep_inputs=False):
     """Score the B x m*C cut-and-recompute moves.  Returns (uint8 CUDA tensor [B][m*C][16] of
     moc_cut_score or None, uint8 CUDA tensor [B][16] of moc_best_move or None)."""
-    import torch
+    torch = _tc()
     B = starts.numel() // g.T if g.T else 0
     ps, pe, pa = _cand_ptrs(g, B, starts, ends, active)
     if out_moves is None and want_moves:
@@ -239,8 +252,8 @@ def moc_eval_cuts(g: Graph, starts, ends, active, want_moves=True, want_best=Fal
         out_best = torch.empty((B, BEST_MOVE_DTYPE.itemsize), dtype=torch.uint8, device=starts.device)
     call = lib().moc_eval_cuts_keep if keep_inputs else lib().moc_eval_cuts
     code = call(
-        g._h, B, ps, pe, pa, ctypes.c_void_p(out_moves.data_ptr()) if out_moves is not None else None,
-        ctypes.c_void_p(out_best.data_ptr()) if out_best is not None else None, _stream_handle(stream))
+        g._h, B, ps, pe, pa, out_moves.data_ptr() if out_moves is not None else None,
+        out_best.data_ptr() if out_best is not None else None, _stream_handle(stream))
     _check(code, "moc_eval_cuts")
     return out_moves, out_best
 
@@ -248,7 +261,7 @@ def moc_eval_cuts(g: Graph, starts, ends, active, want_moves=True, want_best=Fal
 def moc_search_cuts(g: Graph, starts, ends, active, max_steps, work_best=None, out_steps=None, stream=None):
     """Greedy descent by cut-and-recompute moves, in place.  Returns the int32 CUDA tensor [B] of
     moves applied per candidate."""
-    import torch
+    torch = _tc()
     B = starts.numel() // g.T if g.T else 0
     ps, pe, pa = _cand_ptrs(g, B, starts, ends, active)
     with _on(stream):
@@ -256,8 +269,8 @@ def moc_search_cuts(g: Graph, starts, ends, active, max_steps, work_best=None, o
             work_best = torch.empty((B, BEST_MOVE_DTYPE.itemsize), dtype=torch.uint8, device=starts.device)
         if out_steps is None:
             out_steps = torch.empty((B,), dtype=torch.int32, device=starts.device)
-    code = lib().moc_search_cuts(g._h, B, ps, pe, pa, int(max_steps), ctypes.c_void_p(work_best.data_ptr()),
-                                 ctypes.c_void_p(out_steps.data_ptr()), _stream_handle(stream))
+    code = lib().moc_search_cuts(g._h, B, ps, pe, pa, int(max_steps), work_best.data_ptr(),
+                                 out_steps.data_ptr(), _stream_handle(stream))
     _check(code, "moc_search_cuts")
     return out_steps
 
@@ -265,7 +278,7 @@ def moc_search_cuts(g: Graph, starts, ends, active, max_steps, work_best=None, o
 def moc_search_two_phase(g: Graph, starts, ends, active, max_cuts, max_merges, K=64, stream=None):
     """Two-phase local search in place (cuts that keep the inputs towards the budget, then merges
     that lower the duration).  Returns (cuts, merges): int32 CUDA tensors [B] of moves applied."""
-    import torch
+    torch = _tc()
     B = starts.numel() // g.T if g.T else 0
     ps, pe, pa = _cand_ptrs(g, B, starts, ends, active)
     dev = starts.device
@@ -273,7 +286,7 @@ def moc_search_two_phase(g: Graph, starts, ends, active, max_cuts, max_merges, K
         work_best = torch.empty((B, BEST_MOVE_DTYPE.itemsize), dtype=torch.uint8, device=dev)
         cuts = torch.empty((B,), dtype=torch.int32, device=dev)
         merges = torch.empty((B,), dtype=torch.int32, device=dev)
-    P = lambda t: ctypes.c_void_p(t.data_ptr()) if t.numel() else None
+    P = lambda t: t.data_ptr() if t.numel() else None
     unused = P(work_best)   # the call asks for the second phase's workspaces and does not use them
     code = lib().moc_search_two_phase(g._h, B, ps, pe, pa, int(max_cuts), int(max_merges), int(K), P(work_best), unused,
                                       unused, unused, unused, unused, P(cuts), P(merges), _stream_handle(stream))
@@ -284,7 +297,7 @@ def moc_search_two_phase(g: Graph, starts, ends, active, max_cuts, max_merges, K
 def moc_search_moves(g: Graph, starts, ends, active, R, max_steps, out_steps=None, stream=None):
     """Greedy descent by single-field start/end moves of radius R, in place.  Returns the int32
     CUDA tensor [B] of moves applied per candidate."""
-    import torch
+    torch = _tc()
     B = starts.numel() // g.T if g.T else 0
     ps, pe, pa = _cand_ptrs(g, B, starts, ends, active)
     with _on(stream):
@@ -293,8 +306,8 @@ def moc_search_moves(g: Graph, starts, ends, active, R, max_steps, out_steps=Non
         if out_steps is None:
             out_steps = torch.empty((B,), dtype=torch.int32, device=starts.device)
     code = lib().moc_search_moves(g._h, B, ps, pe, pa, int(R), int(max_steps),
-                                  ctypes.c_void_p(work_results.data_ptr()), ctypes.c_void_p(work_best.data_ptr()),
-                                  ctypes.c_void_p(out_steps.data_ptr()), _stream_handle(stream))
+                                  work_results.data_ptr(), work_best.data_ptr(),
+                                  out_steps.data_ptr(), _stream_handle(stream))
     _check(code, "moc_search_moves")
     return out_steps
 
@@ -302,7 +315,7 @@ def moc_search_moves(g: Graph, starts, ends, active, R, max_steps, out_steps=Non
 def moc_decode_batch(g: Graph, starts, active, want_seq=True, out=None, out_seq=None, stream=None):
     """Decode B candidates to their sequences.  Returns (uint8 CUDA tensor [B][24] of
     moc_decode_result, int32 CUDA tensor [B][T] of sequences or None)."""
-    import torch
+    torch = _tc()
     B = starts.numel() // g.T if g.T else 0
     for t, dt in ((starts, torch.int32), (active, torch.uint8)):
         if not (t.is_cuda and t.is_contiguous() and t.dtype == dt and t.numel() == B * g.T):
@@ -312,8 +325,8 @@ def moc_decode_batch(g: Graph, starts, active, want_seq=True, out=None, out_seq=
     if out_seq is None and want_seq:
         out_seq = torch.empty((B, g.T), dtype=torch.int32, device=starts.device)
     code = lib().moc_decode_batch(
-        g._h, B, ctypes.c_void_p(starts.data_ptr()), ctypes.c_void_p(active.data_ptr()),
-        ctypes.c_void_p(out.data_ptr()), ctypes.c_void_p(out_seq.data_ptr()) if out_seq is not None else None,
+        g._h, B, starts.data_ptr(), active.data_ptr(),
+        out.data_ptr(), out_seq.data_ptr() if out_seq is not None else None,
         _stream_handle(stream))
     _check(code, "moc_decode_batch")
     return out, out_seq
