@@ -269,6 +269,14 @@ struct Bits<true> {
 constexpr int kPlanes = 6;           // per-move counters of up to 63 as bit planes; beyond that the slow path
 constexpr int kNoCopy = 0x3FFFFFFF;  // start of a copy that does not exist
 
+// A step of moc_search_moves: what the kernel does beyond finding the best move (all null in a plain call).
+struct NbSearch {
+  int32_t* starts;    // the candidates again, to be edited
+  int32_t* ends;
+  int32_t* steps;     // per candidate: moves applied
+  int32_t* stopped;   // per candidate: its best move does not improve it, and never will
+};
+
 struct Best {
   int viol, peak, move;   // move < 0: none
 };
@@ -518,7 +526,8 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
                                                          const int32_t* __restrict__ ends,
                                                          const uint8_t* __restrict__ active, int R,
                                                          moc_move_score* __restrict__ out_moves,
-                                                         moc_best_move* __restrict__ out_best, NbLayout lay) {
+                                                         moc_best_move* __restrict__ out_best, NbSearch search,
+                                                         NbLayout lay) {
   extern __shared__ uint32_t nb_raw[];
   NbLds L;
   L.profile = reinterpret_cast<int32_t*>(nb_raw);
@@ -558,6 +567,9 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
   }
 
   for (int64_t b = blockIdx.x; b < B; b += gridDim.x) {
+    if constexpr (!TABLE) {
+      if (search.stopped && search.stopped[b]) continue;   // the same for the whole workgroup
+    }
     // what the staging below derives from the thread index is computed again for every base:
     // kept across bases it would sit in registers that the scoring needs, or be spilled
     int t_ = tid;
@@ -876,6 +888,22 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
         r.violations = all.move < 0 ? 0 : all.viol;
         r.peak = all.move < 0 ? 0 : all.peak;
         out_best[b] = r;
+        if constexpr (!TABLE) {
+          if (search.stopped) {
+            // the move is applied if it lowers (violations, max(peak, M), peak); the candidate's rows are
+            // read by this workgroup only, and not again in this launch
+            const int64_t m1 = max(r.peak, g.budget), m0 = max((int64_t)base_peak, g.budget);
+            const bool better_than_now = r.move >= 0 && (r.violations < base_viol || (r.violations == base_viol &&
+                                                         (m1 < m0 || (m1 == m0 && r.peak < base_peak))));
+            if (better_than_now) {
+              const int d = r.move % two_r, field = (r.move / two_r) & 1, k = r.move / four_r;
+              (field == 0 ? search.starts : search.ends)[row + k] += d < R ? d - R : d - R + 1;
+              search.steps[b] += 1;
+            } else {
+              search.stopped[b] = 1;
+            }
+          }
+        }
       }
     }
     __syncthreads();
@@ -883,7 +911,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
 }
 
 using NbKernel = void (*)(GraphView, int64_t, const int32_t*, const int32_t*, const uint8_t*, int, moc_move_score*,
-                          moc_best_move*, NbLayout);
+                          moc_best_move*, NbSearch, NbLayout);
 
 template <int NT, bool ADJ_LDS, bool WIDE, bool TABLE>
 NbKernel pick_copies(int C) {
@@ -927,6 +955,37 @@ int nb_threads(int T, int64_t B, int num_cu) {
 
 }  // namespace
 
+namespace {
+
+// One launch over B bases: scores and best moves, or (search) a step of the descent by single-field moves.
+int queue_neighbours(const moc_graph* g, int64_t B, const int32_t* starts, const int32_t* ends, const uint8_t* active,
+                     int32_t R, moc_move_score* out_moves, moc_best_move* out_best, const NbSearch& search,
+                     hipStream_t stream) {
+  const int nt = nb_threads(g->view.T, B, g->num_cu);
+  const NbLayout lay = nb_layout(g->view.T, g->view.n, g->view.m, g->max_lds, nt);
+  const NbKernel kern = pick_kernel(nt, lay.adj_off != 0, g->view.C, R, out_moves != nullptr);
+  int per_cu = 0;
+  if (const int rc = moc_kernel_occupancy(g, reinterpret_cast<const void*>(kern), nt, lay.bytes, false, &per_cu)) return rc;
+  const int64_t resident = (int64_t)per_cu * g->num_cu;
+  const unsigned grid = (unsigned)(B < resident ? B : resident);
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(nt), lay.bytes, stream, g->view, B, starts, ends, active, R, out_moves,
+                     out_best, search, lay);
+  return MOC_OK;
+}
+
+// What both calls refuse about the graph: another device, an edge (v,v), a T too large for LDS or for 32-bit offsets.
+int check_neighbours(const moc_graph* g, int32_t R) {
+  int dev = -1;
+  MOC_HIP(hipGetDevice(&dev));
+  if (dev != g->device) return MOC_EDEVICE;
+  if (g->has_self_loop) return MOC_EINVAL;
+  if (nb_layout(g->view.T, g->view.n, g->view.m, g->max_lds, 1024).bytes > g->max_lds) return MOC_EOVERFLOW;
+  if ((int64_t)g->view.T * 4 * R * 8 > 0xFFFFFFFFll) return MOC_EOVERFLOW;   // byte offsets in a candidate's table are 32 bits
+  return MOC_OK;
+}
+
+}  // namespace
+
 extern "C" int moc_eval_neighbours(const moc_graph* g, int64_t B, const int32_t* starts, const int32_t* ends,
                                    const uint8_t* active, int32_t R, moc_move_score* out_moves,
                                    moc_best_move* out_best, void* hip_stream) {
@@ -936,47 +995,20 @@ extern "C" int moc_eval_neighbours(const moc_graph* g, int64_t B, const int32_t*
   if (!starts || !ends || !active) return MOC_EINVAL;
   if (((uintptr_t)starts | (uintptr_t)ends) & 3) return MOC_EINVAL;
   if (((uintptr_t)out_moves & 7) || ((uintptr_t)out_best & 7)) return MOC_EINVAL;
-  int dev = -1;
-  MOC_HIP(hipGetDevice(&dev));
-  if (dev != g->device) return MOC_EDEVICE;
-  if (g->has_self_loop) return MOC_EINVAL;
-  const int nt = nb_threads(g->view.T, B, g->num_cu);
-  const NbLayout lay = nb_layout(g->view.T, g->view.n, g->view.m, g->max_lds, nt);
-  if (lay.bytes > g->max_lds) return MOC_EOVERFLOW;
-  if ((int64_t)g->view.T * 4 * R * 8 > 0xFFFFFFFFll) return MOC_EOVERFLOW;   // byte offsets in a candidate's table are 32 bits
-  const NbKernel kern = pick_kernel(nt, lay.adj_off != 0, g->view.C, R, out_moves != nullptr);
-  int per_cu = 0;
-  if (const int rc = moc_kernel_occupancy(g, reinterpret_cast<const void*>(kern), nt, lay.bytes, false, &per_cu)) return rc;
-  const int64_t resident = (int64_t)per_cu * g->num_cu;
-  const unsigned grid = (unsigned)(B < resident ? B : resident);
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(nt), lay.bytes, static_cast<hipStream_t>(hip_stream), g->view, B,
-                     starts, ends, active, R, out_moves, out_best, lay);
+  if (const int rc = check_neighbours(g, R)) return rc;
+  if (const int rc = queue_neighbours(g, B, starts, ends, active, R, out_moves, out_best, NbSearch{}, static_cast<hipStream_t>(hip_stream)))
+    return rc;
   MOC_HIP(hipGetLastError());
   return MOC_OK;
 }
 
 namespace {
 
-__global__ void fill_zero_kernel(int32_t* p, int64_t n) {
+__global__ void start_moves_kernel(int32_t* steps, int32_t* stopped, int64_t n) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0;
-}
-
-// Applies to each base the single-field move its moc_best_move names if that move lowers
-// (violations, max(peak, M), peak) against the base's own result, and counts it.
-__global__ void apply_moves_kernel(int64_t B, int T, int R, int64_t budget, int32_t* starts, int32_t* ends,
-                                   const moc_best_move* best, const moc_result* base, int32_t* steps) {
-  const int64_t b = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (b >= B) return;
-  const int q = best[b].move;
-  if (q < 0) return;
-  const int64_t v1 = best[b].violations, p1 = best[b].peak, v0 = base[b].violations, p0 = base[b].peak;
-  const int64_t m1 = max(p1, budget), m0 = max(p0, budget);
-  if (!(v1 < v0 || (v1 == v0 && (m1 < m0 || (m1 == m0 && p1 < p0))))) return;
-  const int d = q % (2 * R), field = (q / (2 * R)) & 1, k = q / (4 * R);
-  const int delta = d < R ? d - R : d - R + 1;
-  (field == 0 ? starts : ends)[b * T + k] += delta;
-  steps[b] += 1;
+  if (i >= n) return;
+  steps[i] = 0;
+  stopped[i] = 0;
 }
 
 }  // namespace
@@ -991,24 +1023,16 @@ extern "C" int moc_search_moves(const moc_graph* g, int64_t B, int32_t* starts, 
       (((uintptr_t)work_best | (uintptr_t)work_results) & 7))
     return MOC_EINVAL;
   if (B > 0x7FFFFFFFll) return MOC_EINVAL;
-  int dev = -1;
-  MOC_HIP(hipGetDevice(&dev));
-  if (dev != g->device) return MOC_EDEVICE;
-  if (g->has_self_loop) return MOC_EINVAL;
-  const NbLayout lay = nb_layout(g->view.T, g->view.n, g->view.m, g->max_lds, 1024);
-  if (lay.bytes > g->max_lds) return MOC_EOVERFLOW;
-  if ((int64_t)g->view.T * 4 * R * 8 > 0xFFFFFFFFll) return MOC_EOVERFLOW;
+  if (const int rc = check_neighbours(g, R)) return rc;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  const unsigned blocks = (unsigned)((B + 255) / 256);
-  hipLaunchKernelGGL(fill_zero_kernel, dim3(blocks), dim3(256), 0, stream, out_steps, B);
-  for (int step = 0; step < max_steps; ++step) {
-    int rc = moc_eval_batch(g, B, starts, ends, active, work_results, hip_stream);
-    if (rc != MOC_OK) return rc;
-    rc = moc_eval_neighbours(g, B, starts, ends, active, R, nullptr, work_best, hip_stream);
-    if (rc != MOC_OK) return rc;
-    hipLaunchKernelGGL(apply_moves_kernel, dim3(blocks), dim3(256), 0, stream, B, g->view.T, (int)R, g->view.budget,
-                       starts, ends, work_best, work_results, out_steps);
-  }
+  // One launch a step: the best-move kernel has the base's own violations and peak, applies the move
+  // by itself, and passes over the candidates that have come to their end.  (Before: an evaluation,
+  // the best move and an application per step, for every candidate: n = 442, 256 walkers, 16 steps 542 us,
+  // now 268; n = 1000, 32 walkers, 8 steps 294 us, now 111.)
+  const NbSearch search{starts, ends, out_steps, reinterpret_cast<int32_t*>(work_results)};
+  hipLaunchKernelGGL(start_moves_kernel, dim3((unsigned)((B + 255) / 256)), dim3(256), 0, stream, out_steps, search.stopped, B);
+  for (int step = 0; step < max_steps; ++step)
+    if (const int rc = queue_neighbours(g, B, starts, ends, active, R, nullptr, work_best, search, stream)) return rc;
   MOC_HIP(hipGetLastError());
   return MOC_OK;
 }

@@ -140,3 +140,27 @@ def test_cuts_with_more_moves_than_the_lists_hold(moc, mode):
     assert int(count[0]) == k and k > 0
     assert (da[0].cpu().numpy() == wa).all() and (ds[0].cpu().numpy() == ws).all() and (de[0].cpu().numpy() == we).all()
     gh.free()
+
+
+@pytest.mark.parametrize("n,C,B,R,steps", [(1, 1, 3, 1, 2), (20, 2, 6, 3, 9), (64, 2, 1200, 2, 5), (65, 3, 600, 2, 4), (40, 5, 9, 16, 4),
+                                           (300, 4, 3, 4, 3), (700, 2, 520, 2, 2)])
+def test_moves_follow_the_oracle(moc, n, C, B, R, steps):
+    """The descent by single-field moves: some candidates stop at once, some run out of steps; the
+    rows repeat beyond the first nine."""
+    rng = np.random.default_rng(17 * n + C + R)
+    g = random_graph(rng, n)
+    rows = min(B, 9 if n < 100 else 3)
+    s, e, a = schedules(rng, g, C, rows, wild=True)
+    budget = int(0.9 * oracle.evaluate(g, 0, C, s, e, a)[0, 0])
+    pick = np.arange(B) % rows
+    gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, budget, C)
+    ds, de, da = to_dev(s[pick], e[pick], a[pick])
+    count = moc.moc_search_moves(gh, ds, de, da, R, steps).cpu().numpy()
+    gs, ge = ds.cpu().numpy(), de.cpu().numpy()
+    assert (da.cpu().numpy() == a[pick]).all()
+    for r in range(rows):
+        k, ws, we = oracle.search_moves(g, budget, C, s[r], e[r], a[r], R, steps)
+        for b in range(r, B, rows):
+            assert count[b] == k, (b, count[b], k)
+            assert (gs[b] == ws).all() and (ge[b] == we).all(), b
+    gh.free()
