@@ -327,7 +327,7 @@ int moc_eval_cuts_keep(const moc_graph* g, int64_t B, const int32_t* starts, con
  *   work_best              device, moc_best_move [B], 8-byte aligned: workspace
  *                          (holds the last step's choice on return)
  *   out_steps              device, int32 [B]: number of moves applied
- * Queues one kernel on the stream and returns; allocates
+ * Queues one kernel (per 2^21 candidates) on the stream and returns; allocates
  * nothing.  Limits as moc_eval_cuts; B <= 2^31 - 1.
  * Errors: MOC_EINVAL, MOC_EDEVICE, MOC_EOVERFLOW, MOC_EHIP.
  */
@@ -357,7 +357,7 @@ int moc_search_cuts(const moc_graph* g, int64_t B, int32_t* starts, int32_t* end
  *                          asked for when max_merges > 0, neither read nor
  *                          written: any device pointers of that alignment
  *   out_cuts, out_merges   device, int32 [B]: moves applied in each phase
- * Queues two kernels and returns; allocates
+ * Queues two kernels (per 2^21 candidates) and returns; allocates
  * nothing.  Limits as moc_eval_cuts; B * K <= 2^31 - 1.
  * Errors: MOC_EINVAL, MOC_EDEVICE, MOC_EOVERFLOW, MOC_EHIP.
  */

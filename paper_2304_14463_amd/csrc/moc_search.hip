@@ -27,8 +27,8 @@ constexpr int descend_words(int nt) { return (2 * nt + 3 * kMaxRanges + 1 + (int
 // fewer positions at the peak.  Bound by the chain of instructions and LDS latencies of a step (a
 // lone wave issues one vector instruction in 8 clocks): 15 to 21 us, of which the sieve takes 5
 // and the scoring 3 (plain cuts) to 12 (cuts that keep inputs).  n = 442, 1024 walkers, up to 64
-// keeping cuts: 27 ms with two launches a step that staged and scored everything again, 0.7 ms now;
-// n = 1000, 32 walkers, 32 plain cuts: 1.31 -> 0.46 ms.
+// keeping cuts: 27 ms with two launches a step that staged and scored everything again, 0.76 ms now;
+// n = 1000, 32 walkers, 32 plain cuts: 1.31 -> 0.42 ms.
 template <int CT, int NT, bool LISTS, int MODE>
 __global__ __launch_bounds__(NT) void descend_cuts_kernel(GraphView g, int32_t* __restrict__ starts, int32_t* __restrict__ ends,
                                                           uint8_t* __restrict__ active, int max_steps,
@@ -372,6 +372,8 @@ MergeKernel pick_merge(int C) {
   }
 }
 
+constexpr int64_t kMaxLaunch = (int64_t)1 << 21;   // candidates per launch: a grid has fewer than 2^32 threads
+
 int queue_cut_descent(const moc_graph* g, int64_t B, int32_t* starts, int32_t* ends, uint8_t* active, int max_steps,
                           int mode, moc_best_move* last_move, int32_t* out_steps, hipStream_t stream) {
   const int n = g->view.n, m = g->view.m, T = g->view.T;
@@ -393,8 +395,9 @@ int queue_cut_descent(const moc_graph* g, int64_t B, int32_t* starts, int32_t* e
   const DescendKernel kern = mode == 0 ? pick_descend<0>(g->view.C, nt, lay.lists != 0) : pick_descend<1>(g->view.C, nt, lay.lists != 0);
   int per_cu = 0;   // not used: the call is for the kernel's LDS limit
   if (const int rc = moc_kernel_occupancy(g, reinterpret_cast<const void*>(kern), nt, lay.bytes, false, &per_cu)) return rc;
-  hipLaunchKernelGGL(kern, dim3((unsigned)B), dim3(nt), lay.bytes, stream, g->view, starts, ends, active, max_steps,
-                     last_move, out_steps, cap, lay);
+  for (int64_t at = 0; at < B; at += kMaxLaunch)
+    hipLaunchKernelGGL(kern, dim3((unsigned)std::min(B - at, kMaxLaunch)), dim3(nt), lay.bytes, stream, g->view, starts + at * T,
+                       ends + at * T, active + at * T, max_steps, last_move + at, out_steps + at, cap, lay);
   return MOC_OK;
 }
 
@@ -407,8 +410,9 @@ int queue_merges(const moc_graph* g, int64_t B, int32_t* starts, int32_t* ends, 
   const MergeKernel kern = lay.lists ? pick_merge<NT, true>(g->view.C) : pick_merge<NT, false>(g->view.C);
   int per_cu = 0;   // not used: the call is for the kernel's LDS limit
   if (const int rc = moc_kernel_occupancy(g, reinterpret_cast<const void*>(kern), NT, lay.bytes, false, &per_cu)) return rc;
-  hipLaunchKernelGGL(kern, dim3((unsigned)B), dim3(NT), lay.bytes, stream, g->view, starts, ends, active, K, max_steps,
-                     out_merges, lay);
+  for (int64_t at = 0; at < B; at += kMaxLaunch)
+    hipLaunchKernelGGL(kern, dim3((unsigned)std::min(B - at, kMaxLaunch)), dim3(NT), lay.bytes, stream, g->view, starts + at * T,
+                       ends + at * T, active + at * T, K, max_steps, out_merges + at, lay);
   return MOC_OK;
 }
 
