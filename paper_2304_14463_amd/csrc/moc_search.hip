@@ -121,7 +121,7 @@ __global__ __launch_bounds__(NT) void descend_cuts_kernel(GraphView g, int32_t* 
               }
             }
             if (held) kept = -1;
-            // listed before in this round (in an earlier one: it is held by now)
+            // listed before among these 64 (among earlier ones: it is held by now)
             for (int z = y0 + round * kWave; z < y; ++z)
               if ((int)(lists.pair(z) & 0xFFFFu) == w) kept = -1;
           }
