@@ -302,6 +302,11 @@ CutsKernel pick_cuts(int C, int nt, bool lists) {
   return nt == 256 ? pick_cuts<256, true, MODE>(C) : nt == 512 ? pick_cuts<512, true, MODE>(C) : pick_cuts<1024, true, MODE>(C);
 }
 
+// Workgroups that share a compute unit: what LDS holds, or what the batch has for each unit.
+int bases_together(const moc_graph* g, int64_t B, int bytes) {
+  return (int)std::min<int64_t>(g->max_lds / bytes, (B + g->num_cu - 1) / g->num_cu);
+}
+
 template <typename K>
 int resident_grid(const moc_graph* g, K kern, int nt, int bytes, int64_t B, unsigned* grid) {
   int per_cu = 0;
@@ -335,12 +340,14 @@ int eval_cuts(const moc_graph* g, int64_t B, const int32_t* starts, const int32_
   if (const int rc = moc_check_cuts(g)) return rc;
   const GraphView& v = g->view;
   const auto layout = [&](int nt) { return mv_layout(v.T, v.n, v.m, 2 * nt, true, g->max_lds); };
-  // As many threads as fill the compute unit with the workgroups its LDS holds.  Plain cuts, C = 2, by
+  // As many threads as fill the compute unit with the workgroups its LDS holds and the batch has for it
+  // (87 keeping bases of n = 558, one per unit: 613 us before, about 630 by the LDS rule alone, 343 now).
+  // Plain cuts, C = 2, by
   // 256 / 512 / 1024 threads: n = 442 (six fit), 2048 bases 68 / 74 / 132 us; n = 1000 (three),
   // 2048 bases 116 / 90 / 149 us; n = 2000 (one), 1024 bases 463 / 269 / 200 us.  Without the lists
   // in LDS one workgroup fits anyway.
-  const int by_lds = g->max_lds / layout(256).bytes;
-  const int nt = !layout(1024).lists || by_lds <= 1 ? 1024 : by_lds <= 3 ? 512 : 256;
+  const int together = bases_together(g, B, layout(256).bytes);
+  const int nt = !layout(1024).lists || together <= 1 ? 1024 : together <= 3 ? 512 : 256;
   const MvLayout lay = layout(nt);
   if (lay.bytes > g->max_lds) return MOC_EOVERFLOW;
   const CutsKernel kern = mode == 0 ? pick_cuts<0>(v.C, nt, lay.lists != 0) : pick_cuts<1>(v.C, nt, lay.lists != 0);
@@ -372,8 +379,8 @@ extern "C" int moc_eval_toggles(const moc_graph* g, int64_t B, const int32_t* st
   if (lay.bytes > g->max_lds) return MOC_EOVERFLOW;
   // Threads as above; the kernel is held to 64 registers where that lets two workgroups of 1024 in.
   // n = 2000, C = 2 (two fit), 2048 bases: 165 us with 256 threads, 122 with 512, 112 with 1024.
-  const int by_lds = g->max_lds / lay.bytes;
-  const int nt = by_lds <= 2 ? 1024 : by_lds <= 4 ? 512 : 256;
+  const int together = bases_together(g, B, lay.bytes);
+  const int nt = together <= 2 ? 1024 : together <= 4 ? 512 : 256;
   const TogglesKernel kern = nt == 1024 ? pick_toggles<1024>(v.C) : nt == 512 ? pick_toggles<512>(v.C) : pick_toggles<256>(v.C);
   unsigned grid = 0;
   if (const int rc = resident_grid(g, kern, nt, lay.bytes, B, &grid)) return rc;

@@ -20,30 +20,35 @@ def moc():
     return moccasin
 
 
-@pytest.mark.parametrize("n,C", [(1, 1), (1, 2), (7, 1), (8, 1), (9, 1), (4, 2), (31, 2), (32, 2), (33, 2), (21, 3), (64, 4), (13, 5), (129, 2),
-                                 (511, 2), (1025, 2), (700, 5)])
-def test_toggles(moc, n, C):
+@pytest.mark.parametrize("n,C,B", [(1, 1, 6), (1, 2, 6), (7, 1, 6), (8, 1, 6), (9, 1, 1500), (4, 2, 6), (31, 2, 900), (32, 2, 1500), (33, 2, 6),
+                                   (21, 3, 1500), (64, 4, 900), (13, 5, 1500), (129, 2, 6), (511, 2, 900), (1025, 2, 3), (700, 5, 3)])
+def test_toggles(moc, n, C, B):
     rng = np.random.default_rng(7 * n + C)
     g = random_graph(rng, n)
-    B = 6 if n < 500 else 3
-    s, e, a = schedules(rng, g, C, B, wild=True)
+    rows = 6 if n < 500 else 3           # repeated beyond that: batches of every workgroup size
+    s, e, a = schedules(rng, g, C, rows, wild=True)
+    pick = np.arange(B) % rows
     gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, 100, C)
-    got = moc.results_to_numpy(moc.moc_eval_toggles(gh, *to_dev(s, e, a)), moc.TOGGLE_SCORE_DTYPE)
-    for b in range(B):
+    got = moc.results_to_numpy(moc.moc_eval_toggles(gh, *to_dev(s[pick], e[pick], a[pick])), moc.TOGGLE_SCORE_DTYPE)
+    assert (got == got[pick]).all()
+    for b in range(rows):
         assert_same(got[b], oracle.toggles(g, 100, C, s[b], e[b], a[b]), f"n={n} C={C} row {b}")
     gh.free()
 
 
-@pytest.mark.parametrize("n,C,mode", [(4, 2, 0), (32, 2, 1), (33, 2, 0), (21, 3, 1), (13, 5, 0), (129, 2, 1), (511, 2, 0), (900, 3, 1)])
-def test_cuts(moc, n, C, mode):
+@pytest.mark.parametrize("n,C,mode,B", [(4, 2, 0, 6), (32, 2, 1, 1500), (33, 2, 0, 600), (21, 3, 1, 1500), (13, 5, 0, 1500), (129, 2, 1, 600),
+                                        (511, 2, 0, 600), (129, 2, 0, 6), (900, 3, 1, 3)])
+def test_cuts(moc, n, C, mode, B):
     rng = np.random.default_rng(11 * n + C)
     g = random_graph(rng, n)
-    B = 6 if n < 500 else 3
-    s, e, a = schedules(rng, g, C, B, wild=True)
+    rows = 6 if n < 500 else 3           # repeated beyond that: batches of every workgroup size
+    s, e, a = schedules(rng, g, C, rows, wild=True)
+    pick = np.arange(B) % rows
     gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, 100, C)
-    moves, best = moc.moc_eval_cuts(gh, *to_dev(s, e, a), want_best=True, keep_inputs=mode == 1)
+    moves, best = moc.moc_eval_cuts(gh, *to_dev(s[pick], e[pick], a[pick]), want_best=True, keep_inputs=mode == 1)
     moves, best = moc.results_to_numpy(moves, moc.TOGGLE_SCORE_DTYPE), moc.results_to_numpy(best, moc.BEST_MOVE_DTYPE)
-    for b in range(B):
+    assert (moves == moves[pick]).all() and (best == best[pick]).all()
+    for b in range(rows):
         want = oracle.cuts(g, 100, C, s[b], e[b], a[b], with_at_peak=True, mode=mode)
         assert_same(moves[b], want, f"n={n} C={C} row {b}")
         assert_best(best[b], want, f"n={n} C={C} row {b}")
