@@ -23,11 +23,12 @@
 //
 // One workgroup per candidate at a time, one lane per node, all in LDS.
 #include "moc_cover.h"
+#include "moc_shapes.h"
 #include "moc_wave.h"
 
 namespace {
 
-constexpr int kNT = 512;
+constexpr int kNT = kStagedThreads;
 constexpr int kNW = kNT / kWave;
 
 struct StLayout {
@@ -264,7 +265,7 @@ __global__ __launch_bounds__(kNT) void eval_staged_general_kernel(GraphView g, c
 }
 
 // C <= 4: the copies of a lane's nodes are held in registers, the workgroup's next candidate is asked
-// for as soon as they are used.  U = nodes per lane, ceil(n / kNT).  What the renumbering needs for a
+// for as soon as they are used.  U = nodes per lane, at least n / kNT (staged_nodes_per_lane).  What the renumbering needs for a
 // node's first copy follows from its place k alone: its start can only be slot k of stage k, the
 // highest slot of that stage, so that its rank is the last of the stage's; only the copies beyond
 // the first, which are few, are put into buckets and searched for.  An end at the last slot of its
@@ -591,28 +592,24 @@ extern "C" int moc_eval_batch_staged(const moc_graph* g, int64_t B, const int32_
   if (dev != g->device) return MOC_EDEVICE;
   const StLayout lay = st_layout(g->view.n, g->view.C);
   if (lay.bytes > g->max_lds || g->view.T >= 0xFFFF) return MOC_EOVERFLOW;
-  const int per_lane = (g->view.n + kNT - 1) / kNT, C = g->view.C;
   const int edges = (g->view.m + kNT - 1) / kNT;
   StagedKernel kern = eval_staged_general_kernel;
-  if (C <= 4 && per_lane * C <= 16) {   // the copies of a lane's nodes fit its registers
-    const int u = per_lane <= 1 ? 1 : per_lane <= 2 ? 2 : per_lane <= 4 ? 4 : 8;
-    switch (C * 16 + u) {
-      case 1 * 16 + 1: kern = pick_edges<1, 1>(edges); break;
-      case 1 * 16 + 2: kern = pick_edges<1, 2>(edges); break;
-      case 1 * 16 + 4: kern = pick_edges<1, 4>(edges); break;
-      case 1 * 16 + 8: kern = pick_edges<1, 8>(edges); break;
-      case 2 * 16 + 1: kern = pick_edges<2, 1>(edges); break;
-      case 2 * 16 + 2: kern = pick_edges<2, 2>(edges); break;
-      case 2 * 16 + 4: kern = pick_edges<2, 4>(edges); break;
-      case 2 * 16 + 8: kern = pick_edges<2, 8>(edges); break;
-      case 3 * 16 + 1: kern = pick_edges<3, 1>(edges); break;
-      case 3 * 16 + 2: kern = pick_edges<3, 2>(edges); break;
-      case 3 * 16 + 4: kern = pick_edges<3, 4>(edges); break;
-      case 4 * 16 + 1: kern = pick_edges<4, 1>(edges); break;
-      case 4 * 16 + 2: kern = pick_edges<4, 2>(edges); break;
-      case 4 * 16 + 4: kern = pick_edges<4, 4>(edges); break;
-      default: break;
-    }
+  switch (g->view.C * 16 + staged_nodes_per_lane(g->view.n, g->view.C)) {
+    case 1 * 16 + 1: kern = pick_edges<1, 1>(edges); break;
+    case 1 * 16 + 2: kern = pick_edges<1, 2>(edges); break;
+    case 1 * 16 + 4: kern = pick_edges<1, 4>(edges); break;
+    case 1 * 16 + 8: kern = pick_edges<1, 8>(edges); break;
+    case 2 * 16 + 1: kern = pick_edges<2, 1>(edges); break;
+    case 2 * 16 + 2: kern = pick_edges<2, 2>(edges); break;
+    case 2 * 16 + 4: kern = pick_edges<2, 4>(edges); break;
+    case 2 * 16 + 8: kern = pick_edges<2, 8>(edges); break;
+    case 3 * 16 + 1: kern = pick_edges<3, 1>(edges); break;
+    case 3 * 16 + 2: kern = pick_edges<3, 2>(edges); break;
+    case 3 * 16 + 4: kern = pick_edges<3, 4>(edges); break;
+    case 4 * 16 + 1: kern = pick_edges<4, 1>(edges); break;
+    case 4 * 16 + 2: kern = pick_edges<4, 2>(edges); break;
+    case 4 * 16 + 4: kern = pick_edges<4, 4>(edges); break;
+    default: break;
   }
   int per_cu = 0;
   if (const int rc = moc_kernel_occupancy(g, reinterpret_cast<const void*>(kern), kNT, lay.bytes, false, &per_cu)) return rc;

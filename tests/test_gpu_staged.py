@@ -223,3 +223,30 @@ def test_staged_recomputed_starts_and_ends(moc, n, C, degree, B):
     assert_results_equal(gpu, ref[pick], f"n={n} C={C}")
     assert len(np.unique(ref[:, F["violations"]])) > 1 or n == 1
     gh.free()
+
+
+@pytest.mark.parametrize("n", [4096, 4097, 5000, 8192, 8193])
+def test_staged_one_copy_many_nodes(moc, n):
+    """One copy per node, on either side of the largest graph whose nodes the lanes hold in registers,
+    in an order that is not that of the ids.  Short intervals (the oracle goes over every position of
+    one), some copies inactive, some off their slot, some ends on the last slot of a stage."""
+    from paper_2304_14463_amd.inputs import graph_from_edges
+    rng = np.random.default_rng(n)
+    order = rng.permutation(n)
+    edges = sorted({(int(order[j]), int(order[k])) for k in range(1, n) for j in rng.integers(max(0, k - 30), k, size=2)})
+    g = graph_from_edges(n, edges, rng.integers(0, 60, n), rng.integers(0, 9, n))
+    place = np.empty(n, np.int32)
+    place[order] = np.arange(n)
+    rows, D = 4, n * (n + 1) // 2
+    s = np.tile(slot_position(place, place).astype(np.int64), (rows, 1))
+    last = np.minimum(place + rng.integers(0, 4, (rows, n)), n - 1)
+    e = np.where(rng.random((rows, n)) < 0.3, slot_position(last, last), np.minimum(s + rng.integers(0, 3 * n, (rows, n)), D - 1))
+    s = np.where(rng.random((rows, n)) < 0.01, s - 1, s)
+    a = (rng.random((rows, n)) < 0.97).astype(np.uint8)
+    s, e = s.astype(np.int32), e.astype(np.int32)
+    budget = int(g.size.sum()) // 100
+    gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, budget, 1)
+    moc.moc_graph_set_order(gh, order)
+    gpu = moc.results_to_numpy(moc.moc_eval_batch_staged(gh, *to_dev(s, e, a)))
+    assert_results_equal(gpu, oracle_staged_parallel(g, budget, 1, place, s, e, a), f"n={n}")
+    gh.free()
