@@ -277,6 +277,14 @@ struct NbSearch {
   int32_t* stopped;   // per candidate: its best move does not improve it, and never will
 };
 
+// The starts and ends as the kernel reads them.  A step of the descent edits them in the same launch
+// (through NbSearch, without the table), so only the instantiations with the table may say that
+// nothing else writes them.
+template <bool TABLE>
+struct Rows { using Ptr = const int32_t* __restrict__; };
+template <>
+struct Rows<false> { using Ptr = const int32_t*; };
+
 struct Best {
   int viol, peak, move;   // move < 0: none
 };
@@ -522,8 +530,8 @@ __device__ __forceinline__ void walk_own(const FieldState<WIDE>& st, const NbLds
 }
 
 template <int kNT, bool ADJ_LDS, int CT, bool WIDE, bool TABLE>
-__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) void neighbours_kernel(GraphView g, int64_t B, const int32_t* __restrict__ starts,
-                                                         const int32_t* __restrict__ ends,
+__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) void neighbours_kernel(GraphView g, int64_t B, typename Rows<TABLE>::Ptr starts,
+                                                         typename Rows<TABLE>::Ptr ends,
                                                          const uint8_t* __restrict__ active, int R,
                                                          moc_move_score* __restrict__ out_moves,
                                                          moc_best_move* __restrict__ out_best, NbSearch search,
