@@ -77,6 +77,12 @@ extern "C" {
 #define MOC_EHIP      (-4)  /* a HIP runtime call failed; see moc_last_hip_error() */
 #define MOC_EDEVICE   (-5)  /* the graph's device is not the current device */
 
+/* Version of this interface.  From 2 on, moc_search_two_phase neither reads nor
+ * writes its second phase's workspaces; version 1 (a library without
+ * moc_abi_version) writes B*K rows to them.  A program that hands over less
+ * than that checks moc_abi_version() first. */
+#define MOC_ABI_VERSION 2
+
 /* Largest T = n*C an uploaded graph may have: the per-candidate working set
  * (memory-delta array, one record of packed intervals per node, start bitmap)
  * lives in the 160 KB LDS of one compute unit.  The bound is reached with
@@ -355,7 +361,8 @@ int moc_search_cuts(const moc_graph* g, int64_t B, int32_t* starts, int32_t* end
  *   work_starts, work_ends, work_active, work_list (4-byte aligned),
  *   work_results (8-byte aligned)
  *                          asked for when max_merges > 0, neither read nor
- *                          written: any device pointers of that alignment
+ *                          written (MOC_ABI_VERSION >= 2): any device pointers
+ *                          of that alignment
  *   out_cuts, out_merges   device, int32 [B]: moves applied in each phase
  * Queues two kernels (per 2^21 candidates) and returns; allocates
  * nothing.  Limits as moc_eval_cuts; B * K <= 2^31 - 1.
@@ -415,6 +422,9 @@ int moc_decode_batch(const moc_graph* g, int64_t B, const int32_t* starts, const
 
 /* Release a graph (synchronises its device first).  NULL is a no-op. */
 void moc_graph_free(moc_graph* g);
+
+/* The MOC_ABI_VERSION that the library was built with. */
+int moc_abi_version(void);
 
 /* Static description of an error code. */
 const char* moc_strerror(int code);

@@ -306,6 +306,8 @@ void moc_graph_free(moc_graph* g) {
   delete g;
 }
 
+int moc_abi_version(void) { return MOC_ABI_VERSION; }
+
 const char* moc_strerror(int code) {
   switch (code) {
     case MOC_OK: return "ok";

@@ -18,6 +18,7 @@ _lib = None
 _torch = None
 
 MOC_MAX_T = 19455
+MOC_ABI_VERSION = 2
 
 # numpy views of the result structs of include/moccasin.h
 RESULT_DTYPE = np.dtype([("peak", "<i8"), ("duration", "<i8"), ("violations", "<i4"), ("feasible", "<i4")])
@@ -27,7 +28,7 @@ TOGGLE_SCORE_DTYPE = np.dtype([("violations", "<i4"), ("peak", "<i4"), ("duratio
 DECODE_RESULT_DTYPE = np.dtype([("status", "<i4"), ("length", "<i4"), ("peak", "<i8"), ("duration", "<i8")])
 
 EXPORTS = ("moc_graph_upload", "moc_graph_info", "moc_eval_batch", "moc_eval_batch_noalloc", "moc_graph_set_order", "moc_eval_batch_staged", "moc_eval_neighbours", "moc_eval_toggles",
-           "moc_eval_cuts", "moc_eval_cuts_keep", "moc_search_cuts", "moc_search_two_phase", "moc_search_moves", "moc_decode_batch", "moc_graph_free", "moc_strerror", "moc_last_hip_error")
+           "moc_eval_cuts", "moc_eval_cuts_keep", "moc_search_cuts", "moc_search_two_phase", "moc_search_moves", "moc_decode_batch", "moc_graph_free", "moc_abi_version", "moc_strerror", "moc_last_hip_error")
 
 
 class MoccasinError(RuntimeError):
@@ -45,6 +46,12 @@ def lib():
         if not os.path.exists(LIB_PATH):
             raise FileNotFoundError(f"{LIB_PATH} is not built; run python -m paper_2304_14463_amd.build")
         L = ctypes.CDLL(LIB_PATH)
+        # A library of another version may write where this binding gives it no room
+        # (moc_search_two_phase's workspaces): it is refused before any call.
+        version = L.moc_abi_version() if hasattr(L, "moc_abi_version") else 1
+        if version != MOC_ABI_VERSION:
+            raise RuntimeError(f"{LIB_PATH} has interface version {version}, this binding needs {MOC_ABI_VERSION}; "
+                               "run python -m paper_2304_14463_amd.build")
         P, I32, I64, VP = ctypes.POINTER, ctypes.c_int32, ctypes.c_int64, ctypes.c_void_p
         L.moc_graph_upload.argtypes = [I32, VP, VP, VP, VP, I64, I32, P(VP)]
         L.moc_graph_upload.restype = ctypes.c_int

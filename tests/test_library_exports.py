@@ -3,6 +3,9 @@ symbol that include/moccasin.h declares (no compute calls here)."""
 import ctypes
 import os
 import re
+import subprocess
+
+import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -51,3 +54,24 @@ def test_device_generator_library_loads():
     from paper_2304_14463_amd.inputs import device
     assert os.path.exists(device.LIB_PATH)
     assert hasattr(ctypes.CDLL(device.LIB_PATH), "mocgen_candidates")
+
+
+@pytest.mark.parametrize("version", [None, 1, 3])
+def test_library_of_another_version_is_refused(version, tmp_path, monkeypatch):
+    """The binding hands moc_search_two_phase no workspaces of its own any more; a library that still
+    writes to them, or one it does not know, must not be called."""
+    from paper_2304_14463_amd import moccasin
+    text = open(os.path.join(ROOT, "include", "moccasin.h")).read()
+    assert re.search(r"#define MOC_ABI_VERSION (\d+)", text).group(1) == str(moccasin.MOC_ABI_VERSION)
+    names = [x for x in moccasin.EXPORTS if x != "moc_abi_version"]
+    code = "".join(f"int {x}(void) {{ return 0; }}\n" for x in names)
+    if version is not None:
+        code += f"int moc_abi_version(void) {{ return {version}; }}\n"
+    src, out = tmp_path / "other.c", tmp_path / "libother.so"
+    src.write_text(code)
+    subprocess.run(["gcc", "-shared", "-fPIC", "-o", str(out), str(src)], check=True)
+    monkeypatch.setattr(moccasin, "LIB_PATH", str(out))
+    monkeypatch.setattr(moccasin, "_lib", None)
+    with pytest.raises(RuntimeError, match="interface version"):
+        moccasin.lib()
+    assert moccasin._lib is None
