@@ -288,6 +288,8 @@ def moc_search_two_phase(g: Graph, starts, ends, active, max_cuts, max_merges, K
     torch = _tc()
     B = starts.numel() // g.T if g.T else 0
     ps, pe, pa = _cand_ptrs(g, B, starts, ends, active)
+    if B > 0 and max_merges > 0 and not 1 <= K <= 0x7FFFFFFF // B:   # the call's limit, before K becomes an int32
+        raise MoccasinError(-1, "moc_search_two_phase")
     dev = starts.device
     with _on(stream):
         work_best = torch.empty((B, BEST_MOVE_DTYPE.itemsize), dtype=torch.uint8, device=dev)

@@ -162,3 +162,18 @@ def test_two_phase_rejects_bad_arguments(moc):
     torch.cuda.synchronize()
     assert (c1.cpu().numpy() == 0).all() and (c2.cpu().numpy() == 0).all()
     gh.free()
+
+
+@pytest.mark.parametrize("K", [0, -1, 2**31, 2**32 + 64, -2**32 + 64])
+def test_two_phase_refuses_what_is_no_count(moc, K):
+    """Numbers of merges outside 1 .. 2^31 - 1 are refused, also where their low 32 bits would pass."""
+    import torch
+    from paper_2304_14463_amd.inputs import graph_from_edges
+    g = graph_from_edges(3, [(0, 1), (1, 2)], [1, 1, 1], [1, 1, 1])
+    gh = moc.moc_graph_upload(3, g.in_ptr, g.in_idx, g.size, g.dur, 9, 2)
+    z = torch.zeros((1, 6), dtype=torch.int32, device="cuda")
+    a = torch.zeros((1, 6), dtype=torch.uint8, device="cuda")
+    with pytest.raises(moc.MoccasinError) as err:
+        moc.moc_search_two_phase(gh, z, z.clone(), a, 0, 1, K)
+    assert err.value.code == -1
+    gh.free()
