@@ -429,8 +429,6 @@ __device__ __forceinline__ void score_cuts(const GraphView& g, const A& lists, c
 // bounds, the ones with the lowest bounds are scored first -- as many as fill a wave -- and of the
 // others only those whose bound does not exceed the peak reached.  At n = 442 some 200 moves pass
 // the sieve and 5 to 50 have to be scored, on the training graph of 1000 nodes 2 of 1000.
-constexpr int kBuckets = kWave;
-
 struct SiftLds {
   uint32_t* moves;       // [cap] the moves that passed
   uint32_t* where;       // [cap] u*C << 16 | start of the consumer's copy
@@ -442,7 +440,7 @@ struct SiftLds {
   int cap;
 };
 
-inline int sift_words(int n, int cap) { return 3 * cap + cap / 2 + 2 * ((n + 63) / 64) + kBuckets + 4 + 2; }
+static_assert(kBuckets == kWave, "one lane per bucket");
 __device__ __forceinline__ SiftLds carve_sift(uint32_t* at, int n, int cap) {   // `at`: 8-byte aligned
   SiftLds s;
   s.node_bits = reinterpret_cast<uint64_t*>(at);

@@ -2,6 +2,7 @@
 // the base staged in LDS (copies, memory profile of Eq. (4), maxima over any range of it).
 #pragma once
 
+#include "moc_shapes.h"
 #include "moc_wave.h"
 
 namespace {
@@ -22,51 +23,7 @@ __device__ __forceinline__ void wave_lds_order() {
   __builtin_amdgcn_wave_barrier();
 }
 
-// ------------------------------------------------------------------ the base in LDS
-constexpr int kBlk = 8;   // positions per block of the profile's range maxima (two 16-byte reads)
-
-// Word offsets.  The profile begins at 0; `table` holds, at level l and index i <= blocks - 2^l, the
-// maximum over the blocks i .. i + 2^l - 1, level behind level (table_level); pre[i] the maximum
-// over the blocks before i, suf[i] over the blocks from i on.
-__host__ __device__ __forceinline__ int table_level(int level, int blocks) { return level * (blocks + 1) - (1 << level) + 1; }
-struct MvLayout {
-  int blocks, levels, bit_words;
-  int table, pre, suf, packed, occ1, occ2, peak_bits, peak_before, scratch, extra;
-  int lists;   // adjacency lists in LDS, 0 if they are read from global memory
-  int bytes;
-};
-
-constexpr int kScratchWords = 160;
-
-// extra_words: what the kernel needs beyond the base.  with_lists: the adjacency lists too, if they fit.
-inline MvLayout mv_layout(int T, int n, int m, int extra_words, bool with_lists, int max_lds) {
-  MvLayout l;
-  l.blocks = (T + kBlk - 1) / kBlk;
-  l.levels = 1;
-  while ((2 << (l.levels - 1)) <= l.blocks) ++l.levels;
-  l.bit_words = 2 * ((T + 63) / 64);
-  l.table = l.blocks * kBlk;
-  l.pre = l.table + table_level(l.levels, l.blocks);
-  l.suf = l.pre + l.blocks + 1;
-  l.packed = (l.suf + l.blocks + 1 + 3) & ~3;
-  l.occ1 = l.packed + ((T + 3) & ~3);
-  l.occ2 = l.occ1 + l.bit_words;
-  l.peak_bits = l.occ2 + l.bit_words;
-  l.peak_before = l.peak_bits + l.bit_words;
-  l.scratch = l.peak_before + l.bit_words;
-  l.extra = (l.scratch + kScratchWords + 3) & ~3;
-  const int words = l.extra + extra_words;
-  l.lists = 0;
-  l.bytes = 4 * words;
-  // sizes and edge pairs as words, the rest in 16 bits (which is why m is bounded)
-  const int lists = n + m + (2 * (n + 1) + m + 1) / 2;
-  if (with_lists && m < 0xFFFF && 4 * (words + lists) <= max_lds) {
-    l.lists = words;
-    l.bytes = 4 * (words + lists);
-  }
-  return l;
-}
-
+// ------------------------------------------------------------------ the base in LDS (MvLayout: moc_shapes.h)
 // Adjacency of the graph: in-edges of v are [in_begin(v), in_begin(v + 1)) in the order of in_idx;
 // pair(x) = u*C | v*C << 16 of in-edge x; consumers of u are consumer(y), y in [out_begin(u),
 // out_begin(u + 1)).  In LDS (16-bit entries) or in global memory.

@@ -17,10 +17,7 @@
 
 namespace {
 
-constexpr int kMaxRanges = kWave + 1;   // stretches of the profile that are changed together
-
-// Words of LDS beyond the base: a queue of 2 * kWave moves per wave, the stretches, the chosen move.
-constexpr int descend_words(int nt) { return (2 * nt + 3 * kMaxRanges + 1 + (int)(sizeof(Cut) / 4) + 1) & ~1; }
+static_assert(kMaxRanges == kWave + 1 && kCutWords == (int)(sizeof(Cut) / 4), "descend_words");
 
 // One workgroup per candidate: up to max_steps cuts, each the best of the candidate as it stands,
 // applied if it lowers (violations, max(peak, M)) or, above the budget with both unchanged, leaves
@@ -376,21 +373,10 @@ constexpr int64_t kMaxLaunch = (int64_t)1 << 21;   // candidates per launch: a g
 
 int queue_cut_descent(const moc_graph* g, int64_t B, int32_t* starts, int32_t* ends, uint8_t* active, int max_steps,
                           int mode, moc_best_move* last_move, int32_t* out_steps, hipStream_t stream) {
-  const int n = g->view.n, m = g->view.m, T = g->view.T;
-  const auto layout = [&](int nt, int cap) { return mv_layout(T, n, m, descend_words(nt) + sift_words(n, cap), true, g->max_lds); };
-  // As many threads per candidate as the candidates that share a compute unit leave room for (a
-  // thread takes about 96 registers): a step is a chain of short phases, which more waves shorten,
-  // but a wave with nothing to do in a phase still takes its part of the barriers and the issue
-  // slots.  n = 442, 1024 walkers, keeping cuts: 1.0 ms with 256 threads, 1.3 with 512, 2.1 with
-  // 1024; n = 1000, 32 walkers: 0.63, 0.47, 0.46 ms.
-  const int64_t share = (B + g->num_cu - 1) / g->num_cu;
-  const int by_lds = g->max_lds / layout(256, 256).bytes;
-  const int nt = !layout(1024, 256).lists || share <= 1 || by_lds <= 1 ? 1024 : share <= 2 || by_lds <= 2 ? 512 : 256;
-  // the lists of moves that pass the sieve: as long as costs no resident workgroup
-  const int want = (int)std::min<int64_t>({share, by_lds, 1024 / nt});
-  int cap = 2048;
-  while (cap > 256 && layout(nt, cap).bytes * std::max(want, 1) > g->max_lds) cap /= 2;
-  const MvLayout lay = layout(nt, cap);
+  const int T = g->view.T;
+  const DescendShape shape = descend_shape(T, g->view.n, g->view.m, B, g->num_cu, g->max_lds);
+  const int nt = shape.nt, cap = shape.cap;
+  const MvLayout lay = shape.lay;
   if (lay.bytes > g->max_lds) return MOC_EOVERFLOW;
   const DescendKernel kern = mode == 0 ? pick_descend<0>(g->view.C, nt, lay.lists != 0) : pick_descend<1>(g->view.C, nt, lay.lists != 0);
   int per_cu = 0;   // not used: the call is for the kernel's LDS limit

@@ -2,6 +2,10 @@
 // be checked over all sizes without a GPU.
 #pragma once
 
+#include <stdint.h>
+
+#include <algorithm>
+
 // ------------------------------------------------------------------ moc_eval_batch_staged
 constexpr int kStagedThreads = 512;
 
@@ -12,4 +16,98 @@ constexpr int staged_nodes_per_lane(int n, int C) {
   int u = 1;
   while (u * kStagedThreads < n) u *= 2;
   return C <= 4 && u <= 8 && u * C <= 16 ? u : 0;
+}
+
+// ------------------------------------------------------------------ a base in LDS (moc_moves.h)
+constexpr int kBlk = 8;   // positions per block of the profile's range maxima (two 16-byte reads)
+
+// Word offsets.  The profile begins at 0; `table` holds, at level l and index i <= blocks - 2^l, the
+// maximum over the blocks i .. i + 2^l - 1, level behind level (table_level); pre[i] the maximum
+// over the blocks before i, suf[i] over the blocks from i on.
+constexpr int table_level(int level, int blocks) { return level * (blocks + 1) - (1 << level) + 1; }
+struct MvLayout {
+  int blocks, levels, bit_words;
+  int table, pre, suf, packed, occ1, occ2, peak_bits, peak_before, scratch, extra;
+  int lists;   // adjacency lists in LDS, 0 if they are read from global memory
+  int bytes;
+};
+
+constexpr int kScratchWords = 160;
+
+// extra_words: what the kernel needs beyond the base.  with_lists: the adjacency lists too, if they fit.
+inline MvLayout mv_layout(int T, int n, int m, int extra_words, bool with_lists, int max_lds) {
+  MvLayout l;
+  l.blocks = (T + kBlk - 1) / kBlk;
+  l.levels = 1;
+  while ((2 << (l.levels - 1)) <= l.blocks) ++l.levels;
+  l.bit_words = 2 * ((T + 63) / 64);
+  l.table = l.blocks * kBlk;
+  l.pre = l.table + table_level(l.levels, l.blocks);
+  l.suf = l.pre + l.blocks + 1;
+  l.packed = (l.suf + l.blocks + 1 + 3) & ~3;
+  l.occ1 = l.packed + ((T + 3) & ~3);
+  l.occ2 = l.occ1 + l.bit_words;
+  l.peak_bits = l.occ2 + l.bit_words;
+  l.peak_before = l.peak_bits + l.bit_words;
+  l.scratch = l.peak_before + l.bit_words;
+  l.extra = (l.scratch + kScratchWords + 3) & ~3;
+  const int words = l.extra + extra_words;
+  l.lists = 0;
+  l.bytes = 4 * words;
+  // sizes and edge pairs as words, the rest in 16 bits (which is why m is bounded)
+  const int lists = n + m + (2 * (n + 1) + m + 1) / 2;
+  if (with_lists && m < 0xFFFF && 4 * (words + lists) <= max_lds) {
+    l.lists = words;
+    l.bytes = 4 * (words + lists);
+  }
+  return l;
+}
+
+// The largest T the calls on moves take: as many words per copy as their first kernels kept in LDS
+// (4.4 per copy, 4 per 32 copies, and what a workgroup of 16 waves needs).
+inline bool moves_fit(int T, int max_lds) {
+  const int blocks = (T + 31) / 32;
+  int levels = 1;
+  while ((2 << (levels - 1)) <= blocks) ++levels;
+  const int words = 4 * ((T + 3) & ~3) + 8 + levels * blocks + 4 * blocks + 8 * 16 + 16 + 2 * 64 * 16;
+  return 4 * words <= max_lds;
+}
+
+// ------------------------------------------------------------------ the descent by cuts (moc_search.hip)
+constexpr int kMaxRanges = 65;   // stretches of the profile that are changed together: one per lane and the producer's
+constexpr int kCutWords = 6;     // of the chosen move
+constexpr int kBuckets = 64;     // of the sieve's histogram of bounds
+
+// Words of LDS beyond the base: a queue of two moves per lane, the stretches, the chosen move.
+constexpr int descend_words(int nt) { return (2 * nt + 3 * kMaxRanges + 1 + kCutWords + 1) & ~1; }
+// ... and the lists of `cap` moves that pass the sieve.
+inline int sift_words(int n, int cap) { return 3 * cap + cap / 2 + 2 * ((n + 63) / 64) + kBuckets + 4 + 2; }
+
+struct DescendShape {
+  int nt;    // threads per candidate
+  int cap;   // moves that pass the sieve, at most
+  MvLayout lay;
+};
+
+// As many threads per candidate as the candidates that share a compute unit leave room for (a
+// thread takes about 96 registers): a step is a chain of short phases, which more waves shorten,
+// but a wave with nothing to do in a phase still takes its part of the barriers and the issue
+// slots.  n = 442, 1024 walkers, keeping cuts: 1.0 ms with 256 threads, 1.3 with 512, 2.1 with
+// 1024; n = 1000, 32 walkers: 0.63, 0.47, 0.46 ms.  Without the adjacency lists in LDS: 1024.
+inline DescendShape descend_shape(int T, int n, int m, int64_t B, int num_cu, int max_lds) {
+  const auto layout = [&](int nt, int cap) { return mv_layout(T, n, m, descend_words(nt) + sift_words(n, cap), true, max_lds); };
+  const int64_t share = (B + num_cu - 1) / num_cu;
+  const int by_lds = max_lds / layout(256, 256).bytes;
+  const int nt = !layout(1024, 256).lists || share <= 1 || by_lds <= 1 ? 1024 : share <= 2 || by_lds <= 2 ? 512 : 256;
+  // The lists of moves that pass the sieve: as long as costs neither a resident workgroup nor, down to
+  // 512, the adjacency lists their place in LDS (32 walkers, 32 plain cuts, with 2048 and without the
+  // adjacency lists / with them and what then fits: n = 2500, C = 2 781 / 739 us, n = 3000, training
+  // graph 1106 / 1012; with them and 256, which overflows, n = 2790 784 / 811).  A list that overflows
+  // costs the scoring of every move, a resident workgroup mostly more: 1024 walkers, 32 plain cuts,
+  // C = 2, 256 and one more workgroup / 512: n = 590 980 / 1374 us, n = 1320 1609 / 2460, n = 850
+  // 1625 / 1492, n = 1400, where most steps overflow, 2719 / 2455.
+  const int want = (int)std::min<int64_t>({share, by_lds, 1024 / nt});
+  int cap = 2048;
+  while (cap > 256 && (layout(nt, cap).bytes * std::max(want, 1) > max_lds || (!layout(nt, cap).lists && layout(nt, 512).lists))) cap /= 2;
+  return DescendShape{nt, cap, layout(nt, cap)};
 }

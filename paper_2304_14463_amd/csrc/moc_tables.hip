@@ -264,16 +264,6 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 1024 ?
 }
 
 // ------------------------------------------------------------------ host side
-// The largest T the calls on moves take: as many words per copy as their first kernels kept in LDS
-// (4.4 per copy, 4 per 32 copies, and what a workgroup of 16 waves needs).
-bool moves_fit(const moc_graph* g) {
-  const int T = g->view.T, blocks = (T + 31) / 32;
-  int levels = 1;
-  while ((2 << (levels - 1)) <= blocks) ++levels;
-  const int words = 4 * ((T + 3) & ~3) + 8 + levels * blocks + 4 * blocks + 8 * 16 + 16 + 2 * kWave * 16;
-  return 4 * words <= g->max_lds;
-}
-
 using TogglesKernel = void (*)(GraphView, int64_t, const int32_t*, const int32_t*, const uint8_t*, moc_toggle_score*, MvLayout);
 using CutsKernel = void (*)(GraphView, int64_t, const int32_t*, const int32_t*, const uint8_t*, moc_cut_score*, moc_best_move*,
                             MvLayout);
@@ -326,7 +316,7 @@ int check_graph(const moc_graph* g) {
   MOC_HIP(hipGetDevice(&dev));
   if (dev != g->device) return MOC_EDEVICE;
   if (g->has_self_loop) return MOC_EINVAL;
-  if (!moves_fit(g)) return MOC_EOVERFLOW;
+  if (!moves_fit(g->view.T, g->max_lds)) return MOC_EOVERFLOW;
   return MOC_OK;
 }
 

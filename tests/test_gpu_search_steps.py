@@ -80,7 +80,8 @@ def test_merges_follow_the_oracle(moc, n, C, K):
 
 
 @pytest.mark.parametrize("n,C,B,mode", [(2, 2, 6, 0), (9, 2, 6, 1), (63, 2, 9, 0), (64, 2, 9, 1), (65, 3, 9, 1), (129, 4, 6, 1), (50, 5, 6, 1),
-                                        (257, 2, 300, 1), (257, 2, 600, 0), (512, 3, 4, 1), (1100, 2, 3, 0), (2190, 4, 3, 0), (2190, 4, 3, 1)])
+                                        (257, 2, 300, 1), (257, 2, 600, 0), (512, 3, 4, 1), (1100, 2, 3, 0), (2190, 4, 3, 0), (2190, 4, 3, 1),
+                                        (2900, 2, 3, 0)])
 def test_cuts_follow_the_oracle(moc, n, C, B, mode):
     """The descent by cuts (mode 0) and by cuts that keep the inputs (mode 1): counts, rows and, for
     mode 0, the last step's choice.  Bases with and without violations, batches on either side of

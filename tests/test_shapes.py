@@ -10,12 +10,24 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 
 PROGRAM = r"""
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include "moc_shapes.h"
+constexpr int kMaxLds = 160 * 1024;
 int main(int argc, char** argv) {
   if (argc == 2 && !strcmp(argv[1], "staged"))
     for (int C = 1; C <= 8; ++C)
       for (int n = 1; n * C <= 19455; ++n) printf("%d %d %d\n", C, n, staged_nodes_per_lane(n, C));
+  if (argc == 5 && !strcmp(argv[1], "descend")) {   // C, edges per node, candidates
+    const int C = atoi(argv[2]);
+    const int64_t B = atoll(argv[4]);
+    for (int n = 1; moves_fit(n * C, kMaxLds); ++n) {
+      const int T = n * C, m = (int)(atof(argv[3]) * n);
+      const DescendShape s = descend_shape(T, n, m, B, 256, kMaxLds);
+      const MvLayout least = mv_layout(T, n, m, descend_words(s.nt) + sift_words(n, 512), true, kMaxLds);
+      printf("%d %d %d %d %d %d\n", n, s.nt, s.cap, s.lay.bytes, s.lay.lists != 0, least.lists != 0);
+    }
+  }
   return 0;
 }
 """
@@ -43,3 +55,18 @@ def test_staged_kernel_holds_every_node(shapes):
     # and it is taken wherever an instantiation covers them
     largest = np.array([0, 8, 8, 4, 4, 0, 0, 0, 0])[C] * 512
     assert (taken == (n <= largest)).all()
+
+
+@pytest.mark.parametrize("C", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("edges,B", [(3, 1), (3, 32), (3, 300), (2.25, 600), (3, 1024), (6, 1024), (0, 100000)])
+def test_descent_keeps_the_adjacency_lists(shapes, C, edges, B):
+    """The sieve's lists push the graph's adjacency lists out of LDS only where they would have to be
+    shorter than 512, workgroups of fewer than 1024 threads always have the adjacency lists (they are
+    not built without), and every size the call takes fits."""
+    n, nt, cap, bytes_, lists, lists_with_512 = shapes("descend", C, edges, B).T
+    assert n.size * C > 8700
+    assert (bytes_ <= 160 * 1024).all()
+    assert (lists[nt < 1024] == 1).all() and np.isin(nt, (256, 512, 1024)).all()
+    assert np.isin(cap, (256, 512, 1024, 2048)).all()
+    lost = n[lists < lists_with_512]
+    assert lost.size == 0, f"n = {lost.min()} .. {lost.max()}"
