@@ -42,8 +42,11 @@ int moc_kernel_occupancy(const moc_graph* g, const void* kern, int nt, int lds_b
   // first use of this kernel on this device, by any handle
   static std::mutex prepared_mu;
   static std::vector<std::pair<const void*, int>> prepared;
+  // Neither list grows after the upload, which is where running out of memory is caught: a kernel
+  // that finds its list full is asked for again by the next call.
   {
     std::lock_guard<std::mutex> plock(prepared_mu);
+    if (prepared.capacity() == 0) prepared.reserve(1024);   // the first upload of the process
     const std::pair<const void*, int> key(kern, g->device);
     if (std::find(prepared.begin(), prepared.end(), key) == prepared.end()) {
       if (no_static_lds) {
@@ -52,13 +55,13 @@ int moc_kernel_occupancy(const moc_graph* g, const void* kern, int nt, int lds_b
         if (attr.sharedSizeBytes != 0) return MOC_EINVAL;
       }
       MOC_HIP(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, g->max_lds));
-      prepared.push_back(key);
+      if (prepared.size() < prepared.capacity()) prepared.push_back(key);
     }
   }
   int blocks = 0;
   MOC_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, kern, nt, (size_t)lds_bytes));
   if (blocks < 1) blocks = 1;
-  g->occupancy.push_back(moc_graph::Occupancy{kern, nt, lds_bytes, blocks});
+  if (g->occupancy.size() < g->occupancy.capacity()) g->occupancy.push_back(moc_graph::Occupancy{kern, nt, lds_bytes, blocks});
   *per_cu = blocks;
   return MOC_OK;
 }
@@ -237,7 +240,7 @@ int moc_graph_upload(int32_t n, const int32_t* in_ptr, const int32_t* in_idx, co
       g->tickets = const_cast<uint32_t*>(dev);
     }
     if (rc == MOC_OK) {
-      g->occupancy.reserve(16);
+      g->occupancy.reserve(64);   // a graph takes some 40 kernels and shapes in all
       rc = moc_eval_prepare(g);
     }
     if (rc == MOC_OK) rc = moc_eval_static_setup(g->device);
