@@ -116,15 +116,34 @@ def test_cuts_follow_the_oracle(moc, n, C, B, mode):
     gh.free()
 
 
+def moves_through_the_peak(g, C, s, e, a):
+    """How many (in-edge, consumer copy) moves have a position at the candidate's peak between the
+    start of the producer's copy and the consumer's, and a copy of the producer to spare."""
+    _, memory = oracle.profile(g, 0, C, s, e, a)
+    before = np.concatenate([[0], np.cumsum(memory == memory.max())])
+    live = (a != 0) & (s >= 0) & (s <= e) & (e < g.n * C)
+    count = 0
+    for v in range(g.n):
+        for u in g.in_idx[g.in_ptr[v]:g.in_ptr[v + 1]]:
+            copies = np.arange(u * C, u * C + C)
+            for k in range(v * C, v * C + C):
+                covering = copies[live[copies] & (s[copies] < s[k]) & (e[copies] >= s[k])]
+                if live[k] and covering.size and (a[copies] == 0).any():
+                    count += int(before[s[k]] > before[s[covering].max() + 1])
+    return count
+
+
 @pytest.mark.parametrize("mode", [0, 1])
-def test_cuts_with_more_moves_than_the_lists_hold(moc, mode):
-    """Chains of long edges across one peak: thousands of moves pass the sieve of a base without
-    violations, more than it has room for, and all of them are scored after all."""
+@pytest.mark.parametrize("n,degree,B", [(900, 6, 1), (800, 7, 300), (800, 7, 1024)])
+def test_cuts_with_more_moves_than_the_lists_hold(moc, mode, n, degree, B):
+    """Chains of long edges across one peak: more moves pass the sieve of a base without violations
+    than the longest lists hold (2048), and all of them are scored after all.  Workgroups of 1024, 512
+    and 256 threads."""
     from paper_2304_14463_amd.inputs import graph_from_edges
-    n, C = 900, 2
+    C = 2
     rng = np.random.default_rng(4)
     half = n // 2
-    edges = sorted({(u, half + int(v)) for u in range(half) for v in rng.integers(0, n - half, 6)} | {(u, u + 1) for u in range(half)})
+    edges = sorted({(u, half + int(v)) for u in range(half) for v in rng.integers(0, n - half, degree)} | {(u, u + 1) for u in range(half)})
     g = graph_from_edges(n, edges, rng.integers(1, 40, n), rng.integers(1, 9, n))
     s = np.zeros((1, n * C), np.int32); e = s.copy(); a = np.zeros((1, n * C), np.uint8)
     last = np.arange(n) * C
@@ -132,14 +151,45 @@ def test_cuts_with_more_moves_than_the_lists_hold(moc, mode):
         last[u] = max(last[u], v * C)
     s[0, ::C], e[0, ::C], a[0, ::C] = np.arange(n) * C, last, 1
     gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, 1000, C)
-    ds, de, da = to_dev(s, e, a)
+    ds, de, da = to_dev(*(np.repeat(x, B, 0) for x in (s, e, a)))
     if mode == 1:
         count, _ = moc.moc_search_two_phase(gh, ds, de, da, 3, 0)
     else:
         count = moc.moc_search_cuts(gh, ds, de, da, 3)
     k, ws, we, wa = oracle.search_cuts(g, 1000, C, s[0], e[0], a[0], 3, mode=mode)
-    assert int(count[0]) == k and k > 0
-    assert (da[0].cpu().numpy() == wa).all() and (ds[0].cpu().numpy() == ws).all() and (de[0].cpu().numpy() == we).all()
+    assert (count.cpu().numpy() == k).all() and k == 3
+    assert min(moves_through_the_peak(g, C, s[0], e[0], a[0]), moves_through_the_peak(g, C, ws, we, wa)) > 2048
+    assert (da.cpu().numpy() == wa).all() and (ds.cpu().numpy() == ws).all() and (de.cpu().numpy() == we).all()
+    gh.free()
+
+
+@pytest.mark.parametrize("call", ["cuts", "two_phase"])
+def test_more_candidates_than_a_launch_takes(moc, call):
+    """2^21 candidates go into a launch of a descent: a batch that needs a second one, whose
+    candidates, counts and choices begin where the first one's end."""
+    import torch
+    rng = np.random.default_rng(21)
+    n, C, B = 8, 2, (1 << 21) + 301
+    g = random_graph(rng, n)
+    rows = 9
+    s, e, a = recomputed(rng, g, C, rows)
+    budget = int(0.8 * np.median(oracle.evaluate(g, 0, C, s, e, a)[:, 0]))
+    gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, budget, C)
+    pick = torch.arange(B, device="cuda") % rows
+    ds, de, da = (x[pick].contiguous() for x in to_dev(s, e, a))
+    if call == "cuts":
+        last = torch.full((B, 16), 0x55, dtype=torch.uint8, device="cuda")
+        counts = [moc.moc_search_cuts(gh, ds, de, da, 3, work_best=last)]
+        assert (last == last[:rows][pick]).all()
+        want = [oracle.search_cuts(g, budget, C, s[r], e[r], a[r], 3) for r in range(rows)]
+    else:
+        counts = list(moc.moc_search_two_phase(gh, ds, de, da, 3, 3, 8))
+        want = [oracle.search_two_phase(g, budget, C, s[r], e[r], a[r], 3, 3, 8) for r in range(rows)]
+    assert all(max(w[i] for w in want) > 0 for i in range(len(counts)))
+    for got, i in zip((ds, de, da), (-3, -2, -1)):
+        assert (got == torch.from_numpy(np.stack([w[i] for w in want])).cuda()[pick]).all(), i
+    for i, got in enumerate(counts):
+        assert (got == torch.tensor([w[i] for w in want], dtype=torch.int32, device="cuda")[pick]).all(), i
     gh.free()
 
 
@@ -164,4 +214,62 @@ def test_moves_follow_the_oracle(moc, n, C, B, R, steps):
         for b in range(r, B, rows):
             assert count[b] == k, (b, count[b], k)
             assert (gs[b] == ws).all() and (ge[b] == we).all(), b
+    gh.free()
+
+
+def wide_producers(rng):
+    """Two large outputs, each made from more than 130 small ones that nothing else needs later and
+    consumed far behind the peak: a keeping cut of one keeps all of its inputs.  The inputs are listed
+    in no order and some of them twice or three times, next to each other and far apart."""
+    from paper_2304_14463_amd.inputs import graph_from_edges
+    n, u1, u2 = 260, 150, 155
+    edges = [(w, u1) for w in range(140)] + [(w, u2) for w in range(10, 150)]
+    edges += [(v - 1, v) for v in range(156, n)] + [(v, 259) for v in range(160, 200, 3)]
+    edges += [(u1, 156), (u1, 230), (u2, 157), (u2, 236), (3, 225), (70, 228)]
+    size = rng.integers(1, 4, n)
+    size[[u1, u2]], size[160:200] = (2000, 1700), rng.integers(20, 60, 40)
+    g = graph_from_edges(n, edges, size, rng.integers(1, 9, n))
+    ptr, idx = list(g.in_ptr), list(g.in_idx)
+    for u in (u1, u2):
+        listed = idx[ptr[u]:ptr[u + 1]]
+        listed = [listed[i] for i in rng.permutation(len(listed))]
+        listed = listed[:63] + [listed[62]] * 2 + listed[63:100] + listed[5:9] + listed[100:] + [listed[70], listed[2]]
+        more = len(listed) - (ptr[u + 1] - ptr[u])
+        idx[ptr[u]:ptr[u + 1]] = listed
+        ptr[u + 1:] = [x + more for x in ptr[u + 1:]]
+    g.in_ptr, g.in_idx = np.asarray(ptr, np.int32), np.asarray(idx, np.int32)
+    assert g.in_ptr[-1] == len(idx)
+    return g, (u1, u2)
+
+
+@pytest.mark.parametrize("C,B", [(2, 1), (2, 300), (2, 600), (2, 1500), (3, 4), (5, 4)])
+def test_keeping_cut_of_a_producer_with_many_inputs(moc, C, B):
+    """The edit of a keeping cut takes the producer's inputs 64 at a time: three rounds, with inputs
+    listed again in the same round and in a later one.  One step keeps over 130 inputs; after it the
+    staged profile, maxima and counts have to be those of the edited candidate, or the next steps go
+    another way than the oracle's.  Workgroups of each size."""
+    g, producers = wide_producers(np.random.default_rng(C))
+    n, T = g.n, g.n * C
+    s, e, a = np.zeros((1, T), np.int32), np.zeros((1, T), np.int32), np.zeros((1, T), np.uint8)
+    pos, last = np.arange(n) * C, np.arange(n) * C
+    for v in range(n):
+        for u in g.in_idx[g.in_ptr[v]:g.in_ptr[v + 1]]:
+            last[u] = max(last[u], pos[v])
+    s[0, ::C], e[0, ::C], a[0, ::C] = pos, last, 1
+    s, e, a = (np.repeat(x, min(B, 2), 0) for x in (s, e, a))
+    if B > 1:                              # the second row: a base with violations (every move scored)
+        a[1, 240 * C] = 0
+    gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, 100, C)
+    pick = np.arange(B) % len(s)
+    for steps in (1, 6):
+        ds, de, da = to_dev(s[pick], e[pick], a[pick])
+        count, _ = moc.moc_search_two_phase(gh, ds, de, da, steps, 0)
+        count, gs, ge, ga = count.cpu().numpy(), ds.cpu().numpy(), de.cpu().numpy(), da.cpu().numpy()
+        for r in range(len(s)):
+            k, ws, we, wa = oracle.search_cuts(g, 100, C, s[r], e[r], a[r], steps, mode=1)
+            if r == 0:                     # what the test is about did happen
+                assert k >= min(steps, 3) and any(wa[u * C + 1] for u in producers) and (we[::C] != e[0, ::C]).sum() > 130
+            assert (count[r::len(s)] == k).all()
+            for got, want in ((gs, ws), (ge, we), (ga, wa)):
+                assert (got[r::len(s)] == want).all(), (steps, r)
     gh.free()
