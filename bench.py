@@ -28,8 +28,8 @@ HBM_PEAK_GBS = 8000.0
 # (profiles/eval_batch_kernel_n5000_C3_B262144.md): KiB per dispatch and the factors that the same
 # counters need to reproduce a 1 GiB device copy.  Valid for the kernel sources they were taken with.
 TRAFFIC = {"workload": 4, "B": 262144, "fetch_kib": 17328000.0, "fetch_scale": 2.0, "write_kib": 20497.0,
-           "write_scale": 1.0, "sources_sha256": "5d1d1510baa791cd38b37da9541ea2454c30ee77fedb60fe32d8e6a0109c3c10"}
-KERNEL_SOURCES = ("csrc/moc_eval.hip", "csrc/moc_cover.h", "csrc/moc_internal.h", "build.py")   # the kernel and how it is compiled
+           "write_scale": 1.0, "sources_sha256": "67d2f0bee54ddc36ef0a6456680041814a8f2a41b170ebb42fd75fd2f976de27"}
+KERNEL_SOURCES = ("csrc/moc_eval.hip", "csrc/moc_cover.h", "csrc/moc_wave.h", "csrc/moc_internal.h", "build.py")   # the kernel and how it is compiled
 
 
 def kernel_sources_sha256():

@@ -57,8 +57,8 @@
  * code.  Arguments are checked before anything is queued: with MOC_EINVAL,
  * MOC_EDEVICE or MOC_EOVERFLOW nothing has been queued on the stream.  MOC_EHIP
  * reports a failed HIP runtime call; from the calls that queue several kernels
- * (moc_search_two_phase, moc_search_moves) the kernels queued before the failing
- * one still run.  Contents of a candidate are never an error: bad values are
+ * (moc_search_two_phase, moc_search_moves, and moc_search_cuts above 2^21
+ * candidates) the kernels queued before the failing one still run.  Contents of a candidate are never an error: bad values are
  * violations.
  */
 #ifndef MOCCASIN_H

@@ -14,7 +14,7 @@
 // the occupied positions; the footprint is computed over positions rather than steps -- an
 // empty position holds a subset of what the next step holds -- by the same difference array
 // and running sum as Eq. (4).
-#include "moc_internal.h"
+#include "moc_wave.h"
 
 namespace {
 
@@ -36,40 +36,6 @@ DcLayout dc_layout(int n, int C) {
   const int words = 2 * l.T_pad + l.st_words + 2 * kNW + 16;
   l.bytes = words * 4;
   return l;
-}
-
-// The value of the lane CTRL names (a lane shift of the vector ALU), 0 where that lane does not
-// exist or the row is not in ROWS.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ int from_lane(int x) { return __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, true); }
-
-// Inclusive wave scan of one value per lane: inside rows of 16 lanes by shifts of 1, 2, 4, 8,
-// then lane 15 of rows 0 and 2 is added to rows 1 and 3, then lane 31 to rows 2 and 3.
-__device__ __forceinline__ int wave_scan_add(int x, int /*lane*/) {
-  x += from_lane<0x111, 0xF>(x);   // row_shr:1
-  x += from_lane<0x112, 0xF>(x);   // row_shr:2
-  x += from_lane<0x114, 0xF>(x);   // row_shr:4
-  x += from_lane<0x118, 0xF>(x);   // row_shr:8
-  x += from_lane<0x142, 0xA>(x);   // row_bcast:15
-  x += from_lane<0x143, 0xC>(x);   // row_bcast:31
-  return x;
-}
-
-// (sum, max prefix >= 0) of consecutive segments, one per lane, combined in lane order: the
-// last lane ends with the whole wave.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ void absorb_earlier(int& S, int& P) {
-  const int Se = from_lane<CTRL, ROWS>(S), Pe = from_lane<CTRL, ROWS>(P);
-  P = max(Pe, Se + P);
-  S = Se + S;
-}
-__device__ __forceinline__ void wave_combine_ordered(int& S, int& P) {
-  absorb_earlier<0x111, 0xF>(S, P);
-  absorb_earlier<0x112, 0xF>(S, P);
-  absorb_earlier<0x114, 0xF>(S, P);
-  absorb_earlier<0x118, 0xF>(S, P);
-  absorb_earlier<0x142, 0xA>(S, P);
-  absorb_earlier<0x143, 0xC>(S, P);
 }
 
 // Both scans below walk the array in rows of 64 consecutive positions, one lane per position
@@ -114,7 +80,7 @@ __device__ int block_peak_of_running_sum(const int32_t* a, int T, int32_t* scrat
   int carry = 0, top = INT32_MIN;   // sum and highest running sum of this wave's rows, from the wave's first position
   for (int r = r0; r < r1; ++r) {
     const int x = r * kWave + lane;
-    const int inc = wave_scan_add(x < T ? a[x] : 0, lane);
+    const int inc = scan_sum(x < T ? a[x] : 0);
     top = max(top, carry + inc);
     carry += __builtin_amdgcn_readlane(inc, kWave - 1);
   }
@@ -342,7 +308,7 @@ __device__ int block_peak_and_clear(int32_t* a, int words, int32_t* scratch, int
     S += v.y; P = max(P, S);
     S += v.z; P = max(P, S);
     S += v.w; P = max(P, S);
-    wave_combine_ordered(S, P);
+    combine_segments(S, P);
     top = max(top, carry + P);
     carry += S;
   }
@@ -501,7 +467,7 @@ void decode_fixed_kernel(GraphView G, int64_t B, const int32_t* __restrict__ sta
         mine += (who.x != 0) + (who.y != 0) + (who.z != 0) + (who.w != 0);
       }
     }
-    mine = __builtin_amdgcn_readlane(wave_scan_add(mine, lane_), kWave - 1);
+    mine = last_lane(scan_sum(mine));
     if (lane_ == 0) scratch[wave_] = mine;
     __syncthreads();
     int before = 0, length = 0;
@@ -515,7 +481,7 @@ void decode_fixed_kernel(GraphView G, int64_t B, const int32_t* __restrict__ sta
       int4 who = make_int4(0, 0, 0, 0);
       if (x < lay.T_pad) who = *reinterpret_cast<const int4*>(a + x);
       const int cnt = (who.x != 0) + (who.y != 0) + (who.z != 0) + (who.w != 0);
-      const int incl = wave_scan_add(cnt, lane_);
+      const int incl = scan_sum(cnt);
       if (cnt) {
         int at = before + incl - cnt;
         if (seq_row) {

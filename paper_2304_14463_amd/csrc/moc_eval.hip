@@ -50,6 +50,7 @@
 #include <type_traits>
 
 #include "moc_cover.h"
+#include "moc_wave.h"
 
 namespace {
 
@@ -165,34 +166,18 @@ __device__ __forceinline__ Lds carve(uint32_t* base, const LdsLayout& lay) {
 }
 
 // ------------------------------------------------------------------ wave helpers
-template <int CTRL>
-__device__ __forceinline__ int dpp_move(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, CTRL, 0xF, 0xF, true);
-}
-
 // Sum over the 64 lanes, returned in every lane (wave-uniform).
 __device__ __forceinline__ int wave_sum(int v) {
-  v += dpp_move<0xB1>(v);    // quad_perm [1,0,3,2]
-  v += dpp_move<0x4E>(v);    // quad_perm [2,3,0,1]
-  v += dpp_move<0x141>(v);   // row_half_mirror
-  v += dpp_move<0x140>(v);   // row_mirror: every lane of a row of 16 holds the row's sum
+  v += lane_shift<0xB1, 0xF>(v);    // quad_perm [1,0,3,2]
+  v += lane_shift<0x4E, 0xF>(v);    // quad_perm [2,3,0,1]
+  v += lane_shift<0x141, 0xF>(v);   // row_half_mirror
+  v += lane_shift<0x140, 0xF>(v);   // row_mirror: every lane of a row of 16 holds the row's sum
   return __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) + __builtin_amdgcn_readlane(v, 32) +
          __builtin_amdgcn_readlane(v, 48);
 }
 
-// (sum, max prefix) of consecutive segments, one per lane (max prefix >= 0 and >= sum, as a
-// running maximum that starts at 0 gives it), combined in lane order; the last lane ends with
-// the whole wave (the result stays in a vector register: scalar registers are scarce where this
-// is called).  Each lane takes in the lanes before it: inside rows of 16 by shifts of 1, 2, 4,
-// 8 (a lane with no source gets (0, 0), which changes nothing), then lane 15 of rows 0 and 2
-// goes to rows 1 and 3, then lane 31 to rows 2 and 3; lane 63 ends with the whole wave.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ void absorb_earlier(int& S, int& P) {
-  const int Se = __builtin_amdgcn_update_dpp(0, S, CTRL, ROWS, 0xF, true);
-  const int Pe = __builtin_amdgcn_update_dpp(0, P, CTRL, ROWS, 0xF, true);
-  P = max(Pe, Se + P);
-  S = Se + S;
-}
+// (sum, max prefix) of consecutive segments, one per lane, combined in lane order (combine_segments);
+// the result stays in a vector register: scalar registers are scarce where this is called.
 // IN_ALU: with the lane shifts of the vector ALU itself, else through the LDS crossbar, which
 // takes longer but leaves the vector ALU to the other waves.  Measured: the first is faster with
 // workgroups of up to 512 threads (n = 442: 43.9 -> 45.4 % of HBM peak, n = 1000: 57.4 -> 60.0 %),
@@ -201,12 +186,7 @@ __device__ __forceinline__ void absorb_earlier(int& S, int& P) {
 template <bool IN_ALU>
 __device__ __forceinline__ void wave_combine_ordered(int lane, int& S, int& P) {
   if constexpr (IN_ALU) {
-    absorb_earlier<0x111, 0xF>(S, P);   // row_shr:1
-    absorb_earlier<0x112, 0xF>(S, P);   // row_shr:2
-    absorb_earlier<0x114, 0xF>(S, P);   // row_shr:4
-    absorb_earlier<0x118, 0xF>(S, P);   // row_shr:8
-    absorb_earlier<0x142, 0xA>(S, P);   // row_bcast:15 into rows 1 and 3
-    absorb_earlier<0x143, 0xC>(S, P);   // row_bcast:31 into rows 2 and 3
+    combine_segments(S, P);
   } else {
 #pragma unroll
     for (int off = 1; off < kWave; off <<= 1) {   // lane l takes in lanes l-2*off+1 .. l-off

@@ -92,32 +92,29 @@ struct NbLds {
   int32_t* scratch;   // 8 words per wave + 16
 };
 
-struct AddOp { static __device__ int id() { return 0; } static __device__ int op(int a, int b) { return a + b; } };
-
-// Inclusive scan of dst[idx(0..T-1)] <- src, in place allowed; REV scans from the top.
-template <typename Op, bool REV, int kNT>
-__device__ void block_scan(const int32_t* src, int32_t* dst, int T, int32_t* scratch, int tid) {
+// a[x] <- a[0] + ... + a[x].
+template <int kNT>
+__device__ void block_running_sum(int32_t* a, int T, int32_t* scratch, int tid) {
   const int lane = tid & (kWave - 1), wave = tid / kWave;
   const int L = (T + kNT - 1) / kNT;
   const int lo = tid * L, hi = min(lo + L, T);
-  auto at = [&](int i) { return REV ? T - 1 - i : i; };
-  int acc = Op::id();
-  for (int i = lo; i < hi; ++i) acc = Op::op(acc, src[at(i)]);
+  int acc = 0;
+  for (int i = lo; i < hi; ++i) acc += a[i];
   int inc = acc;
 #pragma unroll
   for (int off = 1; off < kWave; off <<= 1) {
     const int o = __shfl_up(inc, off);
-    if (lane >= off) inc = Op::op(inc, o);
+    if (lane >= off) inc += o;
   }
   if (lane == kWave - 1) scratch[wave] = inc;
   __syncthreads();
-  int before = Op::id();
-  for (int w = 0; w < wave; ++w) before = Op::op(before, scratch[w]);
+  int before = 0;
+  for (int w = 0; w < wave; ++w) before += scratch[w];
   const int prev = __shfl_up(inc, 1);
-  int run = Op::op(before, lane == 0 ? Op::id() : prev);
+  int run = before + (lane == 0 ? 0 : prev);
   for (int i = lo; i < hi; ++i) {
-    run = Op::op(run, src[at(i)]);
-    dst[at(i)] = run;
+    run += a[i];
+    a[i] = run;
   }
   __syncthreads();
 }
@@ -670,7 +667,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
       if ((lm >> lane_) & 1) L.list[before + __popcll(lm & lower)] = (uint16_t)(c * kWave + lane_);
       if ((ill >> lane_) & 1) L.list[n_live + before_ill + __popcll(ill & lower)] = (uint16_t)(c * kWave + lane_);
     }
-    block_scan<AddOp, false, kNT>(L.profile, L.profile, T, L.scratch, t_);   // Eq. (4) per position
+    block_running_sum<kNT>(L.profile, T, L.scratch, t_);   // Eq. (4) per position
     // For the best move alone the rest looks at the live copies only; the rows of the table are filled
     // by active flags.
     for (int w = t_; w < lay.mask_words; w += kNT) {

@@ -305,7 +305,7 @@ int resident_grid(const moc_graph* g, K kern, int nt, int bytes, int64_t B, unsi
   return MOC_OK;
 }
 
-int check_bases(const moc_graph* g, int64_t B, const int32_t* starts, const int32_t* ends, const uint8_t* active) {
+int check_bases(const int32_t* starts, const int32_t* ends, const uint8_t* active) {
   if (!starts || !ends || !active) return MOC_EINVAL;
   if (((uintptr_t)starts | (uintptr_t)ends) & 3) return MOC_EINVAL;
   return MOC_OK;
@@ -325,7 +325,7 @@ int eval_cuts(const moc_graph* g, int64_t B, const int32_t* starts, const int32_
   if (!g || B < 0) return MOC_EINVAL;
   if (!out_moves && !out_best) return MOC_EINVAL;
   if (B == 0) return MOC_OK;
-  if (const int rc = check_bases(g, B, starts, ends, active)) return rc;
+  if (const int rc = check_bases(starts, ends, active)) return rc;
   if (((uintptr_t)out_moves & 7) || ((uintptr_t)out_best & 7)) return MOC_EINVAL;
   if (const int rc = moc_check_cuts(g)) return rc;
   const GraphView& v = g->view;
@@ -362,7 +362,7 @@ extern "C" int moc_eval_toggles(const moc_graph* g, int64_t B, const int32_t* st
   if (!g || B < 0) return MOC_EINVAL;
   if (B == 0) return MOC_OK;
   if (!out || ((uintptr_t)out & 7)) return MOC_EINVAL;
-  if (const int rc = check_bases(g, B, starts, ends, active)) return rc;
+  if (const int rc = check_bases(starts, ends, active)) return rc;
   if (const int rc = check_graph(g)) return rc;
   const GraphView& v = g->view;
   const MvLayout lay = mv_layout(v.T, v.n, v.m, v.T, false, g->max_lds);

@@ -13,12 +13,12 @@ __device__ __forceinline__ int lane_shift(int x) { return __builtin_amdgcn_updat
 // Inclusive scans over the 64 lanes: inside rows of 16 by shifts of 1, 2, 4, 8, then lane 15 of
 // rows 0 and 2 goes to rows 1 and 3, then lane 31 to rows 2 and 3.  Values of the maximum >= 0.
 __device__ __forceinline__ int scan_sum(int x) {
-  x += lane_shift<0x111, 0xF>(x);
-  x += lane_shift<0x112, 0xF>(x);
-  x += lane_shift<0x114, 0xF>(x);
-  x += lane_shift<0x118, 0xF>(x);
-  x += lane_shift<0x142, 0xA>(x);
-  x += lane_shift<0x143, 0xC>(x);
+  x += lane_shift<0x111, 0xF>(x);   // row_shr:1
+  x += lane_shift<0x112, 0xF>(x);   // row_shr:2
+  x += lane_shift<0x114, 0xF>(x);   // row_shr:4
+  x += lane_shift<0x118, 0xF>(x);   // row_shr:8
+  x += lane_shift<0x142, 0xA>(x);   // row_bcast:15 into rows 1 and 3
+  x += lane_shift<0x143, 0xC>(x);   // row_bcast:31 into rows 2 and 3
   return x;
 }
 __device__ __forceinline__ int scan_max(int x) {
@@ -32,8 +32,9 @@ __device__ __forceinline__ int scan_max(int x) {
 }
 __device__ __forceinline__ int last_lane(int x) { return __builtin_amdgcn_readlane(x, kWave - 1); }
 
-// (sum, max prefix >= 0) of consecutive segments, one per lane, combined in lane order: the last lane
-// ends with the whole wave.
+// (sum, max prefix >= 0) of consecutive segments, one per lane, combined in lane order: each lane takes
+// in the lanes before it (a lane with no source gets (0, 0), which changes nothing), the last lane ends
+// with the whole wave.
 template <int CTRL, int ROWS>
 __device__ __forceinline__ void combine_earlier(int& S, int& P) {
   const int Se = lane_shift<CTRL, ROWS>(S), Pe = lane_shift<CTRL, ROWS>(P);
