@@ -28,7 +28,7 @@ HBM_PEAK_GBS = 8000.0
 # (profiles/eval_batch_kernel_n5000_C3_B262144.md): KiB per dispatch and the factors that the same
 # counters need to reproduce a 1 GiB device copy.  Valid for the kernel sources they were taken with.
 TRAFFIC = {"workload": 4, "B": 262144, "fetch_kib": 17328000.0, "fetch_scale": 2.0, "write_kib": 20497.0,
-           "write_scale": 1.0, "sources_sha256": "67d2f0bee54ddc36ef0a6456680041814a8f2a41b170ebb42fd75fd2f976de27"}
+           "write_scale": 1.0, "sources_sha256": "e4348f9225713a6667754eb9bae6657d945a59085454340b15827f6bda4cae11"}
 KERNEL_SOURCES = ("csrc/moc_eval.hip", "csrc/moc_cover.h", "csrc/moc_wave.h", "csrc/moc_internal.h", "build.py")   # the kernel and how it is compiled
 
 
@@ -410,7 +410,8 @@ def measure_staged(moc, steps, warmup, with_cpu_baseline=True):
 
 
 def measure_two_phase(moc, cfg, walkers, max_cuts, max_merges, K):
-    """moc_search_two_phase from the violation-free candidates of a workload: how many walkers
+    """moc_search_two_phase from the violation-free candidates of a workload (one call; the process's
+    first also loads the kernels, which takes about 2 ms): how many walkers
     end within the budget, at what increase of the total duration over the plain schedule (the
     paper's TDI %), and whether every result decodes to a valid sequence of that cost."""
     import numpy as np

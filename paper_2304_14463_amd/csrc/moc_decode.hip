@@ -456,7 +456,7 @@ void decode_fixed_kernel(GraphView G, int64_t B, const int32_t* __restrict__ sta
       other[0] = 0; other[1] = 0; other[2] = 0;
     }
 
-    // ---- the sequence: occupied positions in order.  A wave_ owns rows of 256 positions, four per lane_.
+    // ---- the sequence: occupied positions in order.  A wave owns rows of 256 positions, four per lane.
     const int rows = (lay.T_pad + 4 * kWave - 1) / (4 * kWave), rows_per_wave = (rows + kNW - 1) / kNW;
     const int r0 = min(wave_ * rows_per_wave, rows), r1 = min(r0 + rows_per_wave, rows);
     int mine = 0;
@@ -497,7 +497,7 @@ void decode_fixed_kernel(GraphView G, int64_t B, const int32_t* __restrict__ sta
     if (seq_row)
       for (int x = length + t_; x < T; x += kNT) seq_row[x] = -1;
 
-    // ---- one lane_ per edge (u, v): each computation of v is served by the latest computation of u before it
+    // ---- one lane per edge (u, v): each computation of v is served by the latest computation of u before it
     bool unserved = false;
     auto serve = [&](const NodeStarts<CT>& su, const NodeStarts<CT>& sv) {
 #pragma unroll

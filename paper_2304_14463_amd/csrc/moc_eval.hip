@@ -624,8 +624,8 @@ __global__ __launch_bounds__(NT) void eval_batch_kernel(GraphView g, int64_t B, 
         default: __builtin_amdgcn_s_setprio(3); break;
       }
     }
-    int viol = wave == 0 ? n : 0;   // per wave (the same in every lane_, counted on lane_ masks); see phase 1
-    int dur = 0;               // per lane_
+    int viol = wave == 0 ? n : 0;   // per wave (the same in every lane, counted on lane masks); see phase 1
+    int dur = 0;               // per lane
     if (t_ == 0) drawn = groups ? atomicAdd(counter, 1u) : next + 1;
     // The workgroup's next candidate; the last one re-reads itself so that the loads below
     // need no condition.  Slot `it` is requested as soon as phase 1 has consumed the
@@ -641,7 +641,7 @@ __global__ __launch_bounds__(NT) void eval_batch_kernel(GraphView g, int64_t B, 
       asm volatile("" : "+v"(v));               // as for the edges: keep derived addresses out of registers
       if (it * NT + wave * kWave < n) {   // else: whole wave past the last node
         const NodeIn<CT>& r = in[it];
-        // Eq. (2), (7), (8), (3) on lane_ masks; Eq. (1) per lane_
+        // Eq. (2), (7), (8), (3) on lane masks; Eq. (1) per lane
         const lanemask isn = u_lt_k((uint32_t)v, (uint32_t)n);
         lanemask act[CT], live[CT];
         Record<CT> rec;
@@ -686,7 +686,7 @@ __global__ __launch_bounds__(NT) void eval_batch_kernel(GraphView g, int64_t B, 
           }
         }
         if (lanes(live[0])) scatter(r.s[0], r.e[0], sd[it].x);
-        // The other copies are rarely live: in round k every lane_ brings the k-th of its
+        // The other copies are rarely live: in round k every lane brings the k-th of its
         // live ones, so that a wave runs as many rounds as its busiest node has such copies
         // rather than one per copy.
         lanemask left[CT];
@@ -697,7 +697,7 @@ __global__ __launch_bounds__(NT) void eval_batch_kernel(GraphView g, int64_t B, 
           if (others == 0) break;
           int sx = r.s[CT - 1], ex = r.e[CT - 1];
 #pragma unroll
-          for (int i = CT - 2; i >= round; --i) {   // the first of the lane_'s copies that are left
+          for (int i = CT - 2; i >= round; --i) {   // the first of the lane's copies that are left
             sx = (int)pick(left[i], (uint32_t)r.s[i], (uint32_t)sx);
             ex = (int)pick(left[i], (uint32_t)r.e[i], (uint32_t)ex);
           }
@@ -744,7 +744,7 @@ __global__ __launch_bounds__(NT) void eval_batch_kernel(GraphView g, int64_t B, 
       wave_combine_ordered<(NT < 1024)>(lane_, S, P);
     }
     const int distinct = count_distinct_starts<NT>(L, lay, t_);
-    // (c) edges, three per slice of the prefetch; their violations are counted per lane_
+    // (c) edges, three per slice of the prefetch; their violations are counted per lane
     int queued = 0, eviol = 0;
 #pragma unroll
     for (int it = 0; it < ITERS; ++it) {
@@ -767,8 +767,8 @@ __global__ __launch_bounds__(NT) void eval_batch_kernel(GraphView g, int64_t B, 
             for (int i = 0; i < CT; ++i) count_live_uncovered<CT>(eviol, pu[j], pv[j].w[i]);
           }
         };
-        // The lane_'s last slice may hold edges in its first one or two entries only (padding in
-        // every lane_ beyond): blocks of their own, each one straight run of reads, then tests.
+        // The lane's last slice may hold edges in its first one or two entries only (padding in
+        // every lane beyond): blocks of their own, each one straight run of reads, then tests.
         const int here = lay.edge_slots - it * kEdgesPerNode;   // > 0
         if (it == ITERS - 1 && here == 1) edges_of_slice(std::integral_constant<int, 1>{});
         else if (it == ITERS - 1 && here == 2) edges_of_slice(std::integral_constant<int, 2>{});
@@ -787,7 +787,7 @@ __global__ __launch_bounds__(NT) void eval_batch_kernel(GraphView g, int64_t B, 
 #pragma unroll
         for (int j = 0; j < kEdgesPerNode; ++j) {
           const lanemask more = check_first_copies(eviol, pu[j], pv[j]);
-          const uint32_t tail = queue_addr + 4u * (uint32_t)queued;   // the same in every lane_: scalar arithmetic
+          const uint32_t tail = queue_addr + 4u * (uint32_t)queued;   // the same in every lane: scalar arithmetic
           lds_write_lanes(more, tail + 4u * rank_in(more, 0u), edge[it * kEdgesPerNode + j]);
           queued += count(more);
         }

@@ -49,7 +49,7 @@ NbLayout nb_layout(int T, int n, int m, int max_lds, int nt) {
   l.T_pad = (T + 3) & ~3;
   l.bit_words = (T + 31) / 32;
   l.mask_words = 2 * ((T + 63) / 64);
-  // profile, prefix max, suffix max, packed, the list of active copies (16 bits an entry) + bitmaps + scratch
+  // profile, prefix max, suffix max, packed, the list of copies (16 bits an entry) + bitmaps + scratch
   const int words = 4 * l.T_pad + l.T_pad / 2 + 8 + 2 * l.bit_words + 2 * l.mask_words + 8 * (nt / kWave) + 16;
   l.adj_off = 0;
   const int full = nt == 1024 ? 2 : 4;
@@ -84,7 +84,7 @@ struct NbLds {
   int32_t* pmax;
   int32_t* smax;
   uint32_t* packed;
-  uint16_t* list;   // the active copies, in order
+  uint16_t* list;   // the live copies, in order, and behind them the active copies that are not live
   uint32_t* occ1;
   uint32_t* occ2;
   uint32_t* involved;   // bit k: copy k takes part in a violation of Eq. (3) or (5)
@@ -676,8 +676,8 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     }
     block_max_both_ways<kNT>(L.profile, L.pmax, L.smax, T, L.scratch, t_);
 
-    // ---- pass 1: the violations of the base, each instance once: per active copy its form,
-    // the order pair it opens and its inputs
+    // ---- pass 1: the violations of the base, each instance once: the copies that are not well formed by
+    // their number, per live copy the order pair it opens and its inputs
     if (t_ == 0) viol += n_ill;   // Eq. (2)/(8)
     for (int j = t_; j < n_live; j += kNT) {
       const int k = L.list[j];
@@ -712,11 +712,11 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     for (int w = t_; w < lay.bit_words; w += kNT) distinct += __popc(L.occ1[w]);
     atomicAdd(&counts[0], viol + nlive - distinct);   // Eq. (6): live copies - distinct starts
     __syncthreads();
-    const int base_viol = __builtin_amdgcn_readfirstlane(counts[0]);   // the same in every lane_: scalar registers
+    const int base_viol = __builtin_amdgcn_readfirstlane(counts[0]);   // the same in every lane: scalar registers
     const int base_peak = __builtin_amdgcn_readfirstlane(L.pmax[T - 1]);
     // For the best move alone the list is built again, the copies that take part in a violation
     // first: their moves are the ones that can lower the count, and once one has, the others
-    // are left out wave_ by wave_ (see below).
+    // are left out wave by wave (see below).
     int n_first = n_live;   // entries of the list's first part
     if constexpr (!TABLE) {
       int all_first = 0;
@@ -739,9 +739,9 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
       __syncthreads();
     }
 
-    // ---- pass 2: one lane per (active copy, field); the waves draw 64 of these at a time.
+    // ---- pass 2: one lane per (live copy, field); the waves draw 64 of these at a time.
     // For the best move alone: start moves first, so that all lanes of a wave run the same
-    // field's code.  With the table of scores: both fields of 32 consecutive active copies, and
+    // field's code.  With the table of scores: both fields of 32 consecutive live copies, and
     // the same wave then fills the rows of the inactive copies between them, so that it
     // writes one contiguous stretch of the table (HBM takes long runs much faster than
     // scattered 128-byte rows).
@@ -918,6 +918,9 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
 using NbKernel = void (*)(GraphView, int64_t, const int32_t*, const int32_t*, const uint8_t*, int, moc_move_score*,
                           moc_best_move*, NbSearch, NbLayout);
 
+// C = 1 and C = 4 have a kernel of their own with 1024 threads only.  Where fewer are taken, C read at
+// run time costs less than the threads save (best move, 1024 bases, run time with fewer threads / 1024
+// and C fixed: n = 240, C = 1 30 / 51 us, C = 4 54 / 68), but for C = 4 close to T = 2560 (n = 600 109 / 92).
 template <int NT, bool ADJ_LDS, bool WIDE, bool TABLE>
 NbKernel pick_copies(int C) {
   if constexpr (NT == 1024) {
@@ -948,9 +951,10 @@ NbKernel pick_kernel(int nt, bool adj_lds, int C, int R, bool table) {
 // Threads per base.  A wave scores 64 (copy, field) pairs at a time, and the staging is a chain of
 // short passes over T positions: a small base does not feed 16 waves, and several bases on a compute
 // unit hide each other's latencies, as long as the batch has several per unit.  Best move alone, R = 8,
-// C = 2, by 256 / 512 / 1024 threads: n = 120, 2048 bases 33 / 47 / 90 us; n = 442, 1024 bases
-// 46 / 47 / 67, 16 bases 41 / 26 / 26; n = 1000, 1024 bases 85 / 73 / 87; n = 2000, 512 bases
-// 174 / 96 / 77 (with lists built by packed counts the chosen ones take 43, 67 and 70).
+// C = 2, microseconds by 256 / 512 / 1024 threads: n = 120, 2048 bases 35 / 52 / 97; n = 442, 1024 bases
+// 43 / 45 / 66, 600 bases 42 / 36 / 49, 16 bases 39 / 25 / 26; n = 1000, 1024 bases 91 / 73 / 92, 300
+// bases 84 / 48 / 45; n = 1280, 600 bases 104 / 68 / 73; n = 2000, 512 bases 164 / 89 / 71.  With the
+// table, 1024 bases: n = 442 90 / 99 / 112, n = 1000 191 / 178 / 208, n = 2000 577 / 376 / 346.
 int nb_threads(int T, int64_t B, int num_cu) {
   const int64_t per_cu = (B + num_cu - 1) / num_cu;
   if (T <= 1024 && per_cu >= 4) return 256;

@@ -23,9 +23,10 @@ static_assert(kMaxRanges == kWave + 1 && kCutWords == (int)(sizeof(Cut) / 4), "d
 // applied if it lowers (violations, max(peak, M)) or, above the budget with both unchanged, leaves
 // fewer positions at the peak.  Bound by the chain of instructions and LDS latencies of a step (a
 // lone wave issues one vector instruction in 8 clocks): 15 to 21 us, of which the sieve takes 5
-// and the scoring 3 (plain cuts) to 12 (cuts that keep inputs).  n = 442, 1024 walkers, up to 64
-// keeping cuts: 27 ms with two launches a step that staged and scored everything again, 0.76 ms now;
-// n = 1000, 32 walkers, 32 plain cuts: 1.31 -> 0.42 ms.
+// and the scoring 3 (plain cuts) to 12 (cuts that keep inputs).  The walkers are all resident, so the
+// launch lasts as long as those with the most steps: n = 442, 1024 walkers, up to 64 keeping cuts 0.76,
+// 1.36 and 1.41 ms for three sets of inputs (27 ms for the first with two launches a step that staged
+// and scored everything again); n = 1000, 32 walkers, 32 plain cuts: 1.31 -> 0.42 ms.
 template <int CT, int NT, bool LISTS, int MODE>
 __global__ __launch_bounds__(NT) void descend_cuts_kernel(GraphView g, int32_t* __restrict__ starts, int32_t* __restrict__ ends,
                                                           uint8_t* __restrict__ active, int max_steps,
@@ -180,9 +181,12 @@ __device__ __forceinline__ Range merged_range(uint32_t pc, uint32_t pb, int size
 // index order, as many as K; one lane per entry scores it; the feasible one of lowest duration,
 // then peak, then index is applied to the staged base and to the candidate's rows.  What bounds a
 // step is a chain of LDS latencies (list, walk over the node's edges, range maxima, tables), so
-// the workgroup is small and several share a compute unit.  1024 walkers at n = 442, C = 2, up to
-// 48 steps of K = 64: 0.25 ms.  (Every merge written out as a row of its own and evaluated by
-// moc_eval_batch, four launches a step: 19 ms, of which 9.8 the writing and 7.9 the evaluation.)
+// the workgroup is small and several share a compute unit: 256 threads for every size (n = 442, C = 2,
+// up to 32 steps of K = 64 by 256 / 512 / 1024 threads: 1024 walkers 251 / 386 / 840 us, 32 walkers
+// 217 / 213 / 239; where no step is found, staging alone, n = 2000, 256 walkers 32 / 25 / 20).  1024
+// walkers at n = 442, up to 48 steps of K = 64: 0.25 to 0.29 ms on three sets of inputs.  (Every merge
+// written out as a row of its own and evaluated by moc_eval_batch, four launches a step: 19 ms on the
+// first of them, 9.8 the writing and 7.9 the evaluation.)
 template <int CT, int NT, bool LISTS>
 __global__ __launch_bounds__(NT) void merge_kernel(GraphView g, int32_t* __restrict__ starts, int32_t* __restrict__ ends,
                                                    uint8_t* __restrict__ active, int K, int max_steps,

@@ -204,9 +204,7 @@ __global__ __launch_bounds__(kNT) void eval_staged_general_kernel(GraphView g, c
     // ---- Eq. (4): peak of the running sum over the renumbered positions
     int S = 0, P = 0;
     {
-      int own = tid;   // formed here: kept from the top of the kernel it is spilled, and the reload would
-      asm volatile("" : "+v"(own));   // wait for the next candidate's loads, which are in flight by now
-      int32_t* d = delta + own * lay.chunk;
+      int32_t* d = delta + tid * lay.chunk;
       for (int x = 0; x < lay.chunk; ++x) {
         const int y = d[x];
         d[x] = 0;

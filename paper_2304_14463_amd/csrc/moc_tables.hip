@@ -24,9 +24,10 @@ namespace {
 // A staged copy that is well formed and not active carries bit 15 on top of its start (positions
 // stay below 2^15: LDS bounds T), which keeps it from covering anything.
 //
-// Bound by the vector ALU and LDS latency.  n = 2000, C = 2, 2048 bases: 484 us with a walk per copy
-// over adjacency lists kept in LDS (one workgroup per compute unit), 112 us
-// now, of which the edges take 20 and the maxima of the copies' intervals 34.
+// Bound by the vector ALU and LDS latency.  n = 2000, C = 2, 2048 bases: 475 us with a walk per copy
+// over adjacency lists kept in LDS (one workgroup per compute unit), 112 us now, of which the edges take
+// 20 and the maxima of the copies' intervals 34 (calls on the same bases one behind the other; 118 on
+// bases that are new to the caches).
 constexpr uint32_t kOff = 0x8000u;
 
 template <int CT, int NT>
@@ -198,7 +199,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 512 ? 
 // instruction issue and LDS latency: scoring a move is some hundred instructions in a chain of reads.
 // n = 1000, C = 2, 2048 bases, plain cuts, table and best move: 303 us with one workgroup of 16 waves
 // per compute unit (adjacency lists of 32-bit words, prefix and suffix maxima per position), 90 us
-// now; 126 us with the mode read at run time, whose registers cost a workgroup per compute unit.
+// now (on the same bases again and again; 96 on new ones); 126 us with the mode read at run time, whose
+// registers cost a workgroup per compute unit.
 template <int CT, int NT, bool LISTS, int MODE>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 1024 ? 4 : 6))) void cuts_kernel(GraphView g, int64_t B, const int32_t* __restrict__ starts,
                                                   const int32_t* __restrict__ ends, const uint8_t* __restrict__ active,
