@@ -92,8 +92,9 @@ struct DescendShape {
 // As many threads per candidate as the candidates that share a compute unit leave room for (a
 // thread takes about 96 registers): a step is a chain of short phases, which more waves shorten,
 // but a wave with nothing to do in a phase still takes its part of the barriers and the issue
-// slots.  n = 442, 1024 walkers, keeping cuts: 1.0 ms with 256 threads, 1.3 with 512, 2.1 with
-// 1024; n = 1000, 32 walkers: 0.63, 0.47, 0.46 ms.  Without the adjacency lists in LDS: 1024.
+// slots.  C = 2, microseconds with 256 / 512 / 1024 threads: n = 442, 1024 walkers, keeping cuts 763 /
+// 1078 / 1877, plain cuts 512 walkers 554 / 538 / 1072, 256 walkers 507 / 474 / 545; n = 1000, 1024
+// walkers 1640 / 1386 / 2409, 32 walkers 598 / 450 / 427.  Without the adjacency lists in LDS: 1024.
 inline DescendShape descend_shape(int T, int n, int m, int64_t B, int num_cu, int max_lds) {
   const auto layout = [&](int nt, int cap) { return mv_layout(T, n, m, descend_words(nt) + sift_words(n, cap), true, max_lds); };
   const int64_t share = (B + num_cu - 1) / num_cu;
