@@ -106,11 +106,14 @@ def test_cuts_follow_the_oracle(moc, n, C, B, mode):
     applied = 0
     for r in range(rows):
         k, ws, we, wa = oracle.search_cuts(g, budget, C, s[r], e[r], a[r], steps, mode=mode)
+        left = oracle.evaluate(g, budget, C, ws, we, wa)[0]
+        after = (int(left[2]), int(left[0]))   # violations, peak
         for b in range(r, B, rows):
             assert count[b] == k, (b, count[b], k)
             assert (ga[b] == wa).all() and (gs[b] == ws).all() and (ge[b] == we).all(), b
-            if mode == 0:   # a step that found nothing leaves no choice behind
+            if mode == 0:   # the last step's choice and its score; a step that found nothing leaves none behind
                 assert (int(last[b]["move"]) < 0) == (k < steps), b
+                assert (int(last[b]["violations"]), int(last[b]["peak"])) == (after if k == steps else (0, 0)), b
         applied += k
     assert applied > 0 or n < 60
     gh.free()

@@ -186,7 +186,10 @@ def test_staged_argument_errors(moc):
 
 
 @pytest.mark.parametrize("n,C,degree,B", [(100, 2, 2, 2600), (1, 2, 0, 9), (511, 4, 3, 60), (512, 2, 9, 40), (513, 2, 4, 40), (600, 1, 1, 40),
-                                          (1100, 3, 2, 12), (1030, 4, 6, 6), (2100, 2, 2, 6), (2100, 1, 5, 6)])
+                                          (1100, 3, 2, 12), (1030, 4, 6, 6), (2100, 2, 2, 6), (2100, 1, 5, 6)] +
+                         # one and two nodes per lane with at most 3, 6 and more edges per lane; four; eight
+                         [(n, C, degree, 12) for C in (1, 2, 3, 4) for n, degree in ((400, 2), (400, 6), (400, 12), (900, 1), (900, 3), (900, 6), (1800, 2))] +
+                         [(3000, C, 2, 4) for C in (1, 2)])
 def test_staged_recomputed_starts_and_ends(moc, n, C, degree, B):
     """Every instantiation by nodes and edges per lane.  Further copies at their node's slot of any
     stage (its own among them, with the first copy there or not, and twice in one stage), ends at
