@@ -14,6 +14,10 @@
 // the occupied positions; the footprint is computed over positions rather than steps -- an
 // empty position holds a subset of what the next step holds -- by the same difference array
 // and running sum as Eq. (4).
+#include <algorithm>
+
+#include "moc_masks.h"
+#include "moc_slices.h"
 #include "moc_wave.h"
 
 namespace {
@@ -247,12 +251,24 @@ void decode_kernel(GraphView G, int64_t B, const int32_t* __restrict__ starts, c
   }
 }
 
-
-// ---- the same for C <= 4, with fewer passes (five barriers per candidate instead of twelve).
-// The copies of a node are adjacent, so a node's starts are one or two LDS words; the position
-// array holds the node computed at each position (v + 1) instead of a flag, so that the pass
-// that ranks the occupied positions can write the sequence out itself, in order, and clear the
-// array on its way; the running-sum scan at the end clears the difference array as it reads it.
+// ---- the same for C <= 4, in three passes with a barrier behind each.
+//
+// 1. One lane per node: its starts go to an entry of the node (16 bits each, counted from 1, 0: not
+//    computed) and the copy's name to the position it starts at, without atomics: two copies on one
+//    position show as fewer occupied positions than active copies (Eq. (6)).
+// 2. The occupied positions are counted, eight to a thread in one 16-byte read.  One lane per node walks
+//    the node's consumers (moc_slices.h) and keeps, for every computation of the node in order, the last
+//    start that falls between it and the next one: that is how long its output is held, known to one
+//    lane, without atomics or an array to meet in.  Two starts at a time in 16-bit halves of a register.
+//    Memory rises at the computation and falls behind the last use (Eq. (4) by events).
+// 3. The running sum's maximum; the names in order of position, from where the sequence is written out
+//    in 16-byte stores.
+//
+// Bound by HBM (295 MB read and written, 61 us at the rate of a copy), with the vector ALU at 60 % and LDS
+// at 45 % beside it.  n = 2000, C = 2, 8192 candidates: 124 us with one lane per edge, the last use of a
+// computation collected by atomic maxima (five passes, 824 vector and 114 LDS instructions per wave and
+// candidate); 82 us now (480 and 64).  Without pass 2's walk the kernel takes 61 us, without storing the
+// sequence 67, without anything else it does as long as with it.
 
 // The copies of a node as they lie in a candidate's row: aligned as their elements are, no more
 // (the global loads of this chip take several words at any word boundary).
@@ -260,339 +276,519 @@ template <int CT>
 struct alignas(4) CopyStarts {
   int32_t s[CT];
 };
-template <int CT>
-struct CopyFlags {
-  uint8_t a[CT];
+template <typename I>
+struct __attribute__((packed)) FlagBytes {
+  I x;
+};
+typedef int Words2 __attribute__((ext_vector_type(2)));
+typedef int Words4 __attribute__((ext_vector_type(4)));
+constexpr int kRawBuffer = 0x00020000;   // word 3 of a buffer descriptor: plain bytes, offsets checked against the size
+constexpr int kDropped = 0x40000000;     // an offset beyond any buffer here
+static_assert(sizeof(moc_decode_result) == 24, "stored as six words; peak and duration stay below 2^31");
+
+constexpr int node_slots(int C) { return C <= 2 ? 4 : 2; }   // nodes of a lane (with more copies a lane's positions set the limit)
+constexpr int kRows = 2;                                     // of a slice that stay in registers
+
+struct DfLayout {
+  int T_pad;                       // > T + 1, a multiple of 8
+  int pos_off, list_off, a_off;    // byte offsets; the starts lie at 0
+  int told_off;                    // what the waves tell each other
+  int bytes;
 };
 
+DfLayout df_layout(int n, int C, int nt) {
+  const int T = n * C;
+  DfLayout l;
+  l.T_pad = (T + 9) & ~7;
+  l.pos_off = (2 * starts_stride(C) * (n + 1) + 15) & ~15;
+  l.list_off = l.pos_off + 2 * l.T_pad;
+  l.a_off = l.list_off + 2 * l.T_pad;
+  l.told_off = l.a_off + 4 * l.T_pad;
+  l.bytes = l.told_off + (nt / kWave) * (16 + 2 * 8);
+  return l;
+}
+
+// Two 16-bit numbers in a register.
+typedef short Halves __attribute__((ext_vector_type(2)));
+typedef unsigned short UHalves __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ Halves halves(uint32_t w) { return __builtin_bit_cast(Halves, w); }
+__device__ __forceinline__ uint32_t word(Halves h) { return __builtin_bit_cast(uint32_t, h); }
+__device__ __forceinline__ uint32_t min_halves(uint32_t a, uint32_t b) {   // unsigned (written out: the compiler makes compares of some)
+  uint32_t r;
+  asm("v_pk_min_u16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ uint32_t max_halves(uint32_t a, uint32_t b) {
+  uint32_t r;
+  asm("v_pk_max_u16 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ uint32_t lower_half(uint32_t w) {   // the smaller of the two
+  uint32_t r;
+  asm("v_min_u32_sdwa %0, %1, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_0 src1_sel:WORD_1" : "=v"(r) : "v"(w));
+  return r;
+}
+__device__ __forceinline__ uint32_t upper_half(uint32_t w) {   // the larger
+  uint32_t r;
+  asm("v_max_u32_sdwa %0, %1, %1 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:WORD_0 src1_sel:WORD_1" : "=v"(r) : "v"(w));
+  return r;
+}
+
+// A node's starts as they lie in LDS, two to a word.
 template <int CT>
 struct NodeStarts {
-  uint32_t s[CT];   // kNoStart if the copy is not computed
+  static constexpr int kWords = CT <= 2 ? 1 : 2;
+  uint32_t w[kWords];
 };
-
-constexpr int starts_stride(int C) { return C == 3 ? 4 : C; }   // 16-bit entries per node
-
 template <int CT>
-__device__ __forceinline__ NodeStarts<CT> read_starts(const uint16_t* st, int v) {
+__device__ __forceinline__ NodeStarts<CT> read_starts(uint32_t addr) {
   NodeStarts<CT> r;
   if constexpr (CT == 1) {
-    r.s[0] = st[v];
+    r.w[0] = lds_read_u16(addr);
   } else if constexpr (CT == 2) {
-    const uint32_t w = *reinterpret_cast<const uint32_t*>(st + 2 * v);
-    r.s[0] = w & 0xFFFFu; r.s[1] = w >> 16;
+    r.w[0] = lds_read(addr);
   } else {
-    const uint2 w = *reinterpret_cast<const uint2*>(st + 4 * v);
-    r.s[0] = w.x & 0xFFFFu; r.s[1] = w.x >> 16; r.s[2] = w.y & 0xFFFFu;
-    if constexpr (CT == 4) r.s[3] = w.y >> 16;
+    const uint2 x = lds_read2(addr);
+    r.w[0] = x.x;
+    r.w[1] = x.y;
   }
   return r;
 }
 
-// max over x in [0, T] of a[0] + ... + a[x] (at least 0); every a[x] is left at zero.  The entry
-// at T only ever holds releases (values <= 0), so it cannot raise the maximum.  A wave takes
-// rows of 256 positions, four per lane in one 16-byte read; `words` (a multiple of 4, > T) is
-// the length of the array.
-__device__ int block_peak_and_clear(int32_t* a, int words, int32_t* scratch, int tid) {
-  const int lane = tid & (kWave - 1), wave = tid / kWave;
-  const int rows = (words + 4 * kWave - 1) / (4 * kWave), rows_per_wave = (rows + kNW - 1) / kNW;
-  const int r0 = min(wave * rows_per_wave, rows), r1 = min(r0 + rows_per_wave, rows);
-  int carry = 0, top = 0;   // last lane: sum and highest running sum of this wave's rows, from the wave's first position
-  for (int r = r0; r < r1; ++r) {
-    const int x = (r * kWave + lane) * 4;
-    int4 v = make_int4(0, 0, 0, 0);
-    if (x < words) {
-      v = *reinterpret_cast<int4*>(a + x);
-      *reinterpret_cast<int4*>(a + x) = make_int4(0, 0, 0, 0);
+// Adds to or takes from a word of LDS that several waves meet in.
+__device__ __forceinline__ void raise(int32_t* at, int x) { __hip_atomic_fetch_add(at, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+__device__ __forceinline__ void lower(int32_t* at, int x) { __hip_atomic_fetch_sub(at, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+
+constexpr int kNoUse = 0xFFFF;          // first use of an output that is not used
+constexpr uint32_t kNever = 0x7FFFu;   // start of a computation that does not happen: above every position
+
+// What the starts of its consumers say about a node.
+template <int CT>
+struct Uses {
+  uint32_t at[CT];     // the node's starts in rising order, kNever for those that are not computed
+  uint32_t last[CT];   // last use of each, in two halves that are joined at the end
+  uint32_t least;      // first use of any (0-based), in two halves
+  __device__ __forceinline__ void begin(const NodeStarts<CT>& su) {
+    uint32_t w[NodeStarts<CT>::kWords];
+#pragma unroll
+    for (int k = 0; k < NodeStarts<CT>::kWords; ++k)   // 0 -> kNever: 0 - 1 wraps to the highest number
+      w[k] = word(halves(min_halves(word(halves(su.w[k]) - Halves{1, 1}), 0x7FFE7FFEu)) + Halves{1, 1});
+    if constexpr (CT == 1) {
+      at[0] = w[0] & 0xFFFFu;
+    } else if constexpr (CT == 2) {
+      at[0] = lower_half(w[0]);
+      at[1] = upper_half(w[0]);
+    } else {
+      const uint32_t l0 = lower_half(w[0]), h0 = upper_half(w[0]), l1 = lower_half(w[1]), h1 = upper_half(w[1]);
+      const uint32_t x = max(l0, l1), y = min(h0, h1);
+      at[0] = min(l0, l1);
+      at[1] = min(x, y);
+      at[2] = max(x, y);
+      if constexpr (CT == 4) at[3] = max(h0, h1);
     }
-    int S = v.x, P = max(S, 0);
-    S += v.y; P = max(P, S);
-    S += v.z; P = max(P, S);
-    S += v.w; P = max(P, S);
-    combine_segments(S, P);
-    top = max(top, carry + P);
-    carry += S;
+#pragma unroll
+    for (int i = 0; i < CT; ++i) last[i] = at[i];
+    least = 0xFFFFFFFFu;
   }
-  if (lane == kWave - 1) {   // the lane that holds the rows' combined values
-    scratch[wave] = carry;
-    scratch[kNW + wave] = top;
+  __device__ __forceinline__ void use(const NodeStarts<CT>& sv) {   // 0: no use
+#pragma unroll
+    for (int k = 0; k < NodeStarts<CT>::kWords; ++k) {
+      uint32_t rest = sv.w[k];
+      least = min_halves(least, word(halves(rest) - Halves{1, 1}));
+#pragma unroll
+      for (int i = CT - 1; i > 0; --i) {   // the latest computation takes the uses behind it, the others go on
+        uint32_t behind;
+        asm("v_pk_sub_i16 %0, %1, %2 op_sel_hi:[0,1]" : "=v"(behind) : "v"(at[i]), "v"(sv.w[k]));
+        behind = word(halves(behind) >> 15);
+        last[i] = max_halves(last[i], rest & behind);
+        rest &= ~behind;
+      }
+      last[0] = max_halves(last[0], rest);
+    }
   }
-  __syncthreads();
-  int best = 0, before = 0;
-  for (int w = 0; w < kNW; ++w) {
-    best = max(best, before + scratch[kNW + w]);
-    before += scratch[w];
-  }
-  // No barrier here: the caller's next write to `scratch` lies behind its next barrier, and the
-  // array is clear for every wave since the barrier above.
-  return best;
-}
+};
 
-// SMALL: the graph has at most kUnroll * kNT nodes, a lane's nodes are the same for every
-// candidate: their sizes and durations stay in registers, and the starts and flags of the
-// workgroup's next candidate are asked for while this one is still being worked on (after the
-// edge pass, whose own loads would otherwise queue behind them), so that its first phase does
-// not begin with a wait for HBM.
-template <int CT, bool SMALL>
-__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8)))
-void decode_fixed_kernel(GraphView G, int64_t B, const int32_t* __restrict__ starts, const uint8_t* __restrict__ active,
-                         moc_decode_result* __restrict__ out, int32_t* __restrict__ out_seq, DcLayout lay) {
+// LOOP: more nodes than node_slots a lane or more positions than eight: the workgroup goes over them in
+// rounds and reads the graph again for every candidate.  Otherwise what a lane needs of the graph stays in
+// registers, and the starts and flags of the workgroup's next candidate are asked for while this one is
+// still being worked on.
+template <int CT, int NT, bool LOOP>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(8, 8)))
+void decode_fixed_kernel(GraphView G, const uint32_t* __restrict__ slices, int64_t B, const int32_t* __restrict__ starts,
+                         const uint8_t* __restrict__ active, moc_decode_result* __restrict__ out,
+                         int32_t* __restrict__ out_seq, DfLayout lay) {
   extern __shared__ int32_t lds[];
-  constexpr int SS = starts_stride(CT);
-  int32_t* a = lds;                 // node computed at each position (v + 1), then memory differences
-  int32_t* b = a + lay.T_pad;       // the last position each computation serves
-  uint16_t* st = reinterpret_cast<uint16_t*>(b + lay.T_pad);   // [n][SS] start of each copy, kNoStart if not computed
-  int32_t* scratch = reinterpret_cast<int32_t*>(st) + lay.st_words;
-  int32_t* flag_words = scratch + 2 * kNW;   // two sets of [0] not decodable, [1] not a valid sequence, [2] duration
+  constexpr int SS = starts_stride(CT), NW = NT / kWave, R = LOOP ? 2 : 1, kSlots = node_slots(CT);
+  char* const raw = reinterpret_cast<char*>(lds);   // at LDS address 0: [n + 1][SS] starts
+  uint16_t* const pos = reinterpret_cast<uint16_t*>(raw + lay.pos_off);     // copy (+ 1) that starts at a position, 0: none
+  uint16_t* const list = reinterpret_cast<uint16_t*>(raw + lay.list_off);   // the sequence, copies (+ 1), 0 behind its end
+  int32_t* const a = reinterpret_cast<int32_t*>(raw + lay.a_off);           // memory differences
+  int4* const told = reinterpret_cast<int4*>(raw + lay.told_off);           // per wave: copies computed, positions taken, duration, what is wrong
+  int2* const sums = reinterpret_cast<int2*>(told + NW);                    // per round and wave: sum and highest running sum
   const int tid = threadIdx.x;
-  const int T = G.T, n = G.n, m = G.m;
+  const int T = G.T, n = G.n;
 
-  for (int x = tid; x < lay.T_pad; x += kNT) a[x] = 0;
-  if (tid < 8) flag_words[tid] = 0;
-  if (tid < SS) st[n * SS + tid] = (uint16_t)kNoStart;   // node n: behind the last node, never computed; padding edges lead there
+  for (int x = 8 * tid; x < lay.T_pad; x += 8 * NT) {
+    const int4 zero = make_int4(0, 0, 0, 0);
+    *reinterpret_cast<int4*>(pos + x) = zero;
+    *reinterpret_cast<int4*>(list + x) = zero;
+    *reinterpret_cast<int4*>(a + x) = zero;
+    *reinterpret_cast<int4*>(a + x + 4) = zero;
+  }
+  if (tid < SS) reinterpret_cast<uint16_t*>(lds)[n * SS + tid] = 0;   // node n is never computed
+
   // The loads of a round of nodes are issued without conditions (lanes past the last node read
-  // it again and drop what they get) and all of them before the first is looked at; the flags
-  // take a register each.  Loads under a condition, or flags packed into the bytes of one
-  // register, end up one behind the other, each waiting for the one before.
+  // it again and drop what they get) and all of them before the first is looked at; a node's flags
+  // stay as they arrive, in one register (three copies: two).  Loads under a condition, or flags put
+  // together from several loads, end up one behind the other, each waiting for the one before.
   struct Round {
-    int32_t s[kUnroll][CT];
-    uint32_t on[kUnroll][CT];
+    int32_t s[kSlots][CT];
+    uint32_t on[kSlots][CT == 3 ? 2 : 1];
+    __device__ __forceinline__ lanemask active(int u, int i) const {
+      return CT == 3 && i == 2 ? byte_ne_k(on[u][CT == 3 ? 1 : 0], 0, 0u) : byte_ne_k(on[u][0], i, 0u);
+    }
   };
   // (the candidate's rows are scalar base addresses, a lane adds a 32-bit offset)
   auto request = [&](int64_t c, int round, int t, Round& r) {
     const char* const s_row = reinterpret_cast<const char*>(starts + c * T);
     const char* const a_row = reinterpret_cast<const char*>(active + c * T);
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-      const uint32_t off = (uint32_t)min(round + u * kNT + t, n - 1) * CT;
+    for (int u = 0; u < kSlots; ++u) {
+      const uint32_t off = (uint32_t)min(round + u * NT + t, n - 1) * CT;
       const CopyStarts<CT> sv = *reinterpret_cast<const CopyStarts<CT>*>(s_row + off * 4u);
-      const CopyFlags<CT> av = *reinterpret_cast<const CopyFlags<CT>*>(a_row + off);
 #pragma unroll
-      for (int i = 0; i < CT; ++i) {
-        r.s[u][i] = sv.s[i];
-        r.on[u][i] = av.a[i];
-      }
+      for (int i = 0; i < CT; ++i) r.s[u][i] = sv.s[i];
+      if constexpr (CT == 1) r.on[u][0] = *reinterpret_cast<const uint8_t*>(a_row + off);
+      else if constexpr (CT == 4) r.on[u][0] = reinterpret_cast<const FlagBytes<uint32_t>*>(a_row + off)->x;
+      else r.on[u][0] = reinterpret_cast<const FlagBytes<uint16_t>*>(a_row + off)->x;
+      if constexpr (CT == 3) r.on[u][1] = *reinterpret_cast<const uint8_t*>(a_row + off + 2);
     }
   };
-  [[maybe_unused]] Round ahead;            // SMALL: the workgroup's next candidate
-  [[maybe_unused]] int2 my_sd[kUnroll];    // SMALL: m_v, w_v of the lane's nodes
-  if constexpr (SMALL) {
-#pragma unroll
-    for (int u = 0; u < kUnroll; ++u) my_sd[u] = G.size_dur[min(u * kNT + tid, n - 1)];
+  // A slice: where its rows of consumers begin and how many there are; the lane's node with its m_v, w_v.
+  const int n_slices = (int)slices[0], n_apart = (int)slices[1];
+  struct Slice {
+    uint32_t rows;
+    int count;
+    uint32_t node;
+    int size, dur;
+  };
+  auto open_slice = [&](int i, int lane) {
+    Slice s;
+    const uint32_t at = slices[2 + i];
+    s.rows = at + kWave;
+    s.count = (int)((slices[3 + i] - at) / kWave) - 1;
+    s.node = slices[at + lane];
+    const int2 sd = G.size_dur[min((int)s.node, n - 1)];
+    s.size = sd.x;
+    s.dur = sd.y;
+    return s;
+  };
+  // The slices of a wave: the long ones come first, so every second round is dealt in reverse.
+  auto slice_of = [](int u, int wave) { return u * NW + (u & 1 ? NW - 1 - wave : wave); };
+  [[maybe_unused]] Round ahead;            // the workgroup's next candidate
+  [[maybe_unused]] Slice mine[kSlots];
+  [[maybe_unused]] uint32_t my_rows[kSlots][kRows];
+  if constexpr (!LOOP) {
     request(blockIdx.x, 0, tid, ahead);   // the grid is not larger than the batch
+    const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+#pragma unroll
+    for (int u = 0; u < kSlots; ++u) {
+      const int i = slice_of(u, wave);
+      mine[u] = Slice{0u, -1, 0u, 0, 0};
+      if (i < n_slices) mine[u] = open_slice(i, lane);
+#pragma unroll
+      for (int r = 0; r < kRows; ++r) {
+        my_rows[u][r] = 0;
+        if (r < mine[u].count) my_rows[u][r] = slices[mine[u].rows + r * kWave + lane];
+      }
+    }
   }
+  // Nothing is on its way into the loop: what it waits for is counted from its own operations alone.
+  __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
   __syncthreads();
 
-  int turn = 0;
-  for (int64_t cand = blockIdx.x; cand < B; cand += gridDim.x, turn ^= 1) {
+  for (int64_t cand = blockIdx.x; cand < B; cand += gridDim.x) {
     // What derives from the thread index (row bounds, LDS addresses) is formed again for every
     // candidate: kept across candidates it takes registers that the next candidate's copies need.
     int t_ = tid;
     asm volatile("" : "+v"(t_));
     const int lane_ = t_ & (kWave - 1);
     const int wave_ = __builtin_amdgcn_readfirstlane(t_ / kWave);
-    int32_t* seq_row = out_seq ? out_seq + cand * T : nullptr;
-    int32_t* flags = flag_words + 4 * turn;
-    const int64_t after = cand + gridDim.x < B ? cand + gridDim.x : cand;   // SMALL: whose loads go out next (the last candidate asks for itself again)
+    int32_t* const seq_row = out_seq ? out_seq + cand * T : nullptr;
 
-    // ---- who is computed where; every computation serves at least its own step
-    // What makes the candidate undecodable is collected and reported once per round: the
-    // compare-and-swaps of a round are all under way before the first answer is looked at.
+    // ---- 1. who is computed where.  Predicates are lane masks; those of lanes past the last node are 0.
+    int n_active = 0;                      // copies computed
+    lanemask outside = 0, missing = 0;     // a start outside [0, T), Eq. (8); a node that is not computed
+    auto lanes_in = [&](int round, int u) -> lanemask {   // the lanes that have a node in this slot
+      const int left = n - (round + u * NT + wave_ * kWave);
+      return left <= 0 ? 0 : left >= kWave ? ~(lanemask)0 : ((lanemask)1 << left) - 1;
+    };
     auto place = [&](int round, const Round& r) {
-      uint32_t taken = 0;    // != 0: a position was taken already, Eq. (6)
-      bool outside = false;  // a start outside [0, T), Eq. (8)
 #pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
-        const int v = round + u * kNT + t_;
-        if (v >= n) continue;
-        uint32_t where[SS];   // the node's entry of `st`, written in one piece
+      for (int u = 0; u < kSlots; ++u) {
+        const lanemask in = lanes_in(round, u);
+        if (in == 0) continue;
+        const uint32_t v = (uint32_t)(round + u * NT + t_), name = v * CT + 1u;
+        lanemask any = 0;
+        uint32_t where[SS];   // the node's entry of the starts, written in one piece
 #pragma unroll
-        for (int i = 0; i < SS; ++i) where[i] = kNoStart;
+        for (int i = 0; i < SS; ++i) where[i] = 0;
 #pragma unroll
         for (int i = 0; i < CT; ++i) {
-          if (r.on[u][i]) {
-            if (r.s[u][i] < 0 || r.s[u][i] >= T) {
-              outside = true;
-            } else {
-              const uint32_t sk = (uint32_t)r.s[u][i];
-              where[i] = sk;
-              taken |= (uint32_t)atomicCAS(&a[sk], 0, v + 1);   // the node there before, + 1
-              b[sk] = (int)sk;
-            }
-          }
+          const uint32_t at = (uint32_t)r.s[u][i];
+          const lanemask on = r.active(u, i) & in, well = u_lt_k(at, (uint32_t)T), ok = on & well;
+          n_active += count(on);
+          any |= on;
+          outside |= on & ~well;
+          where[i] = pick(ok, at + 1u);
+          lds_write16_lanes<0>(ok, (uint32_t)lay.pos_off + 2u * at, name + i);
         }
-        if constexpr (SS == 1) st[v] = (uint16_t)where[0];
-        else if constexpr (SS == 2) *reinterpret_cast<uint32_t*>(st + 2 * v) = where[0] | where[1] << 16;
-        else *reinterpret_cast<uint2*>(st + 4 * v) = make_uint2(where[0] | where[1] << 16, where[2] | where[3] << 16);
+        missing |= in & ~any;
+        if constexpr (SS == 1) lds_write16_lanes<0>(in, v * 2u, where[0]);
+        else if constexpr (SS == 2) lds_write_lanes(in, v * 4u, where[0] | where[1] << 16);
+        else if (lanes(in)) *reinterpret_cast<uint2*>(raw + v * 8u) = make_uint2(where[0] | where[1] << 16, where[2] | where[3] << 16);
       }
-      if (outside || taken != 0) flags[0] = 1;
     };
-    if constexpr (SMALL) {
+    [[maybe_unused]] uint32_t more_rows[kRows];   // of the first slice, the longest; asked for before there is anything to wait for
+    if constexpr (!LOOP) {
+#pragma unroll
+      for (int k = 0; k < kRows; ++k)
+        more_rows[k] = slices[mine[0].rows + (uint32_t)(max(min(kRows + k, mine[0].count - 1), 0) * kWave + lane_)];
       place(0, ahead);
     } else {
-      for (int round = 0; round < n; round += kUnroll * kNT) {
+      for (int round = 0; round < n; round += kSlots * NT) {
         Round now;
         request(cand, round, t_, now);
         __builtin_amdgcn_sched_barrier(0);
         place(round, now);
       }
     }
+    wait_for_lds_writes();
     __syncthreads();
-    if (flags[0]) {
-      if constexpr (SMALL) request(after, 0, t_, ahead);
-      if (seq_row)
-        for (int x = t_; x < T; x += kNT) seq_row[x] = -1;
-      for (int x = t_; x <= T; x += kNT) a[x] = 0;
-      __syncthreads();
-      if (t_ == 0) {
-        out[cand] = moc_decode_result{-1, 0, 0, 0};
-        flags[0] = 0;
-      }
-      __syncthreads();
-      turn ^= 1;   // the same set of flags serves the next candidate (it is clear again)
-      continue;
-    }
-    if (t_ == 0) {   // the other set, for the workgroup's next candidate
-      int32_t* other = flag_words + 4 * (turn ^ 1);
-      other[0] = 0; other[1] = 0; other[2] = 0;
-    }
 
-    // ---- the sequence: occupied positions in order.  A wave owns rows of 256 positions, four per lane.
-    const int rows = (lay.T_pad + 4 * kWave - 1) / (4 * kWave), rows_per_wave = (rows + kNW - 1) / kNW;
-    const int r0 = min(wave_ * rows_per_wave, rows), r1 = min(r0 + rows_per_wave, rows);
-    int mine = 0;
-    for (int r = r0; r < r1; ++r) {
-      const int x = (r * kWave + lane_) * 4;
+    // ---- 2. how many positions are taken; eight of them per thread and round
+    int4 who[R];
+    int taken = 0;   // those of the second round in the upper half
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int x = (r * NT + t_) * 8;
+      who[r] = make_int4(0, 0, 0, 0);
       if (x < lay.T_pad) {
-        const int4 who = *reinterpret_cast<const int4*>(a + x);
-        mine += (who.x != 0) + (who.y != 0) + (who.z != 0) + (who.w != 0);
+        who[r] = *reinterpret_cast<const int4*>(pos + x);
+        *reinterpret_cast<int4*>(pos + x) = make_int4(0, 0, 0, 0);
+      }
+      const auto ones = [](int w) { return min_halves((uint32_t)w, 0x00010001u); };   // 1 in each half that is not 0
+      const uint32_t c = ones(who[r].x) + ones(who[r].y) + ones(who[r].z) + ones(who[r].w);
+      taken += (int)((c & 0xFFFFu) + (c >> 16)) << (16 * r);
+    }
+    const int upto = scan_sum(taken);
+    // ---- and how long every output is held
+    lanemask unserved = 0;
+    int dur = 0;   // Eq. (1), this lane's nodes
+    auto hold = [&](const Uses<CT>& uses, int size, int w) {
+#pragma unroll
+      for (int i = 0; i < CT; ++i)
+        if (lanes(u_lt_k(uses.at[i], kNever))) {   // computed
+          raise(&a[uses.at[i]], size);
+          lower(&a[upper_half(uses.last[i]) + 1u], size);
+          dur += w;
+        }
+    };
+    auto two_uses = [&](Uses<CT>& uses, uint32_t row) {
+      uint32_t lo, hi;   // taken apart here: moved out of the loop over the candidates the halves would take registers of their own
+      asm volatile("v_and_b32 %0, 0xffff, %1" : "=v"(lo) : "v"(row));
+      asm volatile("v_lshrrev_b32 %0, 16, %1" : "=v"(hi) : "v"(row));
+      const NodeStarts<CT> x = read_starts<CT>(lo), y = read_starts<CT>(hi);
+      uses.use(x);
+      uses.use(y);
+    };
+    auto walk = [&](const Slice& s, const uint32_t* first_rows, const uint32_t* next_rows) {   // the first kRows, the kRows behind them, or null
+      Uses<CT> uses;
+      uses.begin(read_starts<CT>(s.node * (2u * SS)));
+      int count = s.count, r = 0;
+      asm volatile("" : "+s"(count));   // (compared here, not kept as a condition across the candidates)
+      if (first_rows) {
+#pragma unroll
+        for (int k = 0; k < kRows; ++k)
+          if (k < count) two_uses(uses, first_rows[k]);
+        r = kRows;
+      }
+      if (next_rows) {
+#pragma unroll
+        for (int k = 0; k < kRows; ++k)
+          if (kRows + k < count) two_uses(uses, next_rows[k]);
+        r = 2 * kRows;
+      }
+      for (; r < count; r += kRows) {
+        uint32_t row[kRows];
+#pragma unroll
+        for (int k = 0; k < kRows; ++k) row[k] = slices[s.rows + (uint32_t)(min(r + k, count - 1) * kWave + lane_)];
+#pragma unroll
+        for (int k = 0; k < kRows; ++k)
+          if (k == 0 || r + k < count) two_uses(uses, row[k]);
+      }
+      unserved |= u_lt(lower_half(uses.least), uses.at[0]);
+      hold(uses, s.size, s.dur);
+    };
+    if constexpr (!LOOP) {
+#pragma unroll
+      for (int u = 0; u < kSlots; ++u)
+        if (mine[u].count >= 0) walk(mine[u], my_rows[u], u == 0 ? more_rows : nullptr);
+    } else {
+      for (int u = 0; u * NW < n_slices; ++u) {
+        const int i = slice_of(u, wave_);
+        if (i < n_slices) walk(open_slice(i, lane_), nullptr, nullptr);
       }
     }
-    mine = last_lane(scan_sum(mine));
-    if (lane_ == 0) scratch[wave_] = mine;
-    __syncthreads();
-    int before = 0, length = 0;
-    for (int w = 0; w < kNW; ++w) {
-      const int t = scratch[w];
-      if (w < wave_) before += t;
-      length += t;
+    for (int i = wave_; i < n_apart; i += NW) {   // a node with very many consumers: all lanes of a wave
+      const int v = (int)slices[3 + n_slices + i];
+      Uses<CT> uses;
+      uses.begin(read_starts<CT>((uint32_t)v * (2u * SS)));
+      const int y1 = G.out_ptr[v + 1];
+      for (int y = G.out_ptr[v]; y < y1; y += kWave)
+        uses.use(read_starts<CT>((uint32_t)(y + lane_ < y1 ? G.out_idx[y + lane_] : n) * (2u * SS)));
+      const int first = kNoUse - last_lane(scan_max(kNoUse - (int)lower_half(uses.least)));
+      unserved |= (uint32_t)first < (uint32_t)__builtin_amdgcn_readfirstlane((int)uses.at[0]) ? 1 : 0;
+#pragma unroll
+      for (int k = 0; k < CT; ++k) uses.last[k] = (uint32_t)last_lane(scan_max((int)upper_half(uses.last[k])));
+      if (lane_ == 0) {
+        const int2 sd = G.size_dur[v];
+#pragma unroll
+        for (int k = 0; k < CT; ++k)
+          if (uses.at[k] < kNever) {
+            raise(&a[uses.at[k]], sd.x);
+            lower(&a[uses.last[k] + 1u], sd.x);
+            dur += sd.y;
+          }
+      }
     }
-    for (int r = r0; r < r1; ++r) {
-      const int x = (r * kWave + lane_) * 4;
-      int4 who = make_int4(0, 0, 0, 0);
-      if (x < lay.T_pad) who = *reinterpret_cast<const int4*>(a + x);
-      const int cnt = (who.x != 0) + (who.y != 0) + (who.z != 0) + (who.w != 0);
-      const int incl = scan_sum(cnt);
-      if (cnt) {
-        int at = before + incl - cnt;
-        if (seq_row) {
-          if (who.x) seq_row[at++] = who.x - 1;
-          if (who.y) seq_row[at++] = who.y - 1;
-          if (who.z) seq_row[at++] = who.z - 1;
-          if (who.w) seq_row[at++] = who.w - 1;
-        }
+    if constexpr (!LOOP) request(cand + gridDim.x < B ? cand + gridDim.x : cand, 0, t_, ahead);   // (the last candidate asks for itself again)
+    dur = scan_sum(dur);
+    if (lane_ == kWave - 1)
+      told[wave_] = make_int4(n_active, upto, dur, (outside ? 1 : 0) | (missing ? 2 : 0) | (unserved ? 4 : 0));
+    __syncthreads();
+
+    // ---- 3. what the waves know together: lanes 0 .. NW - 1 hold one wave each
+    int4 all = make_int4(0, 0, 0, 0);
+    if (lane_ < NW) all = told[lane_];
+    const auto scan_row = [](int x) {
+      x += lane_shift<0x111, 0xF>(x);
+      x += lane_shift<0x112, 0xF>(x);
+      x += lane_shift<0x114, 0xF>(x);
+      x += lane_shift<0x118, 0xF>(x);
+      return x;
+    };
+    const int pairs = scan_row(all.y);
+    const int total_active = __builtin_amdgcn_readlane(scan_row(all.x), NW - 1);
+    const int total_taken = __builtin_amdgcn_readlane(pairs, NW - 1);
+    const int total_dur = __builtin_amdgcn_readlane(scan_row(all.z), NW - 1);
+    const int taken_before = NW > 1 && wave_ > 0 ? __builtin_amdgcn_readlane(pairs, max(wave_ - 1, 0)) : 0;
+    const int length = (total_taken & 0xFFFF) + (total_taken >> 16);
+    // a start outside the domain, or two copies on one position: no order
+    const bool decodable = __ballot(all.w & 1) == 0 && total_active == length;
+    const bool valid = decodable && __ballot(all.w & 6) == 0;
+    // the names in order
+    if (seq_row && decodable) {
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int before = (taken_before + upto - taken) >> (16 * r) & 0xFFFF;
+        uint32_t at = (uint32_t)(before + (r ? total_taken & 0xFFFF : 0));
+        const auto put_two = [&](uint32_t w) {
+          const lanemask lo = low_ne_k(w, 0u), hi = high_ne_k(w, 0u);
+          lds_write16_lanes<0>(lo, (uint32_t)lay.list_off + 2u * at, w);
+          at = add_lanes(lo, at);
+          lds_write16_lanes<1>(hi, (uint32_t)lay.list_off + 2u * at, w);
+          at = add_lanes(hi, at);
+        };
+        put_two((uint32_t)who[r].x);
+        put_two((uint32_t)who[r].y);
+        put_two((uint32_t)who[r].z);
+        put_two((uint32_t)who[r].w);
+      }
+    }
+    // peak of the running sum, eight positions per thread and round; the differences are left at zero
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+      const int x = (r * NT + t_) * 8;
+      int S = 0, P = 0;
+      if (x < lay.T_pad) {
+        const int4 lo = *reinterpret_cast<const int4*>(a + x), hi = *reinterpret_cast<const int4*>(a + x + 4);
         *reinterpret_cast<int4*>(a + x) = make_int4(0, 0, 0, 0);
+        *reinterpret_cast<int4*>(a + x + 4) = make_int4(0, 0, 0, 0);
+        S = lo.x; P = max(S, 0);
+        S += lo.y; P = max(P, S);
+        S += lo.z; P = max(P, S);
+        S += lo.w; P = max(P, S);
+        S += hi.x; P = max(P, S);
+        S += hi.y; P = max(P, S);
+        S += hi.z; P = max(P, S);
+        S += hi.w; P = max(P, S);
       }
-      before += __builtin_amdgcn_readlane(incl, kWave - 1);
+      combine_segments(S, P);
+      if (lane_ == kWave - 1) sums[r * NW + wave_] = make_int2(S, P);   // the lane that holds the wave's
     }
-    if (seq_row)
-      for (int x = length + t_; x < T; x += kNT) seq_row[x] = -1;
-
-    // ---- one lane per edge (u, v): each computation of v is served by the latest computation of u before it
-    bool unserved = false;
-    auto serve = [&](const NodeStarts<CT>& su, const NodeStarts<CT>& sv) {
-#pragma unroll
-      for (int i = 0; i < CT; ++i) {
-        const uint32_t p = sv.s[i];
-        int q = -1;
-#pragma unroll
-        for (int j = 0; j < CT; ++j)
-          if (su.s[j] < p) q = max(q, (int)su.s[j]);    // kNoStart is above every position
-        const bool computed = p != kNoStart;
-        if (computed && q >= 0) atomicMax(&b[q], (int)p);
-        unserved = unserved || (computed && q < 0);
-      }
-    };
-    // The same for two copies per node on the entries of `st` as they are, both copies of the
-    // consumer at once in 16-bit halves of a register.  As signed 16-bit numbers kNoStart is -1
-    // and every position is far below 2^15 (LDS bounds T), so "the latest start of the producer
-    // before p, or -1" is max over the producer's copies of (s < p ? s : -1) = s | ((p - 1 - s) >> 15),
-    // and a consumer copy that is not computed (p = -1) gets -1 by itself.
-    [[maybe_unused]] uint32_t unserved2 = 0;   // sign bits of the halves: computed and not served
-    [[maybe_unused]] auto serve2 = [&](uint32_t su, uint32_t sv) {
-      typedef short Halves __attribute__((ext_vector_type(2)));
-      const auto halves = [](uint32_t x) { return __builtin_bit_cast(Halves, x); };
-      const auto word = [](Halves x) { return __builtin_bit_cast(uint32_t, x); };
-      const Halves before = halves(sv) - Halves{1, 1};                 // p - 1, per copy of the consumer
-      const uint32_t s0 = __builtin_amdgcn_perm(su, su, 0x01000100u);   // the producer's first start in both halves
-      const uint32_t s1 = __builtin_amdgcn_perm(su, su, 0x03020302u);   // its second
-      const uint32_t c0 = s0 | word((before - halves(s0)) >> 15);
-      const uint32_t c1 = s1 | word((before - halves(s1)) >> 15);
-      const Halves q = __builtin_elementwise_max(halves(c0), halves(c1));
-      unserved2 |= word(q) & ~sv;
-      const int q0 = q.x, q1 = q.y;
-      if (q0 >= 0) atomicMax(&b[q0], (int)(sv & 0xFFFFu));
-      if (q1 >= 0) atomicMax(&b[q1], (int)(sv >> 16));
-    };
-    for (int round = 0; round < m; round += kUnroll * kNT) {
-      const int base = round + t_;
-      uint32_t pair[kUnroll];
-#pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
-        const uint32_t got = G.edge_pair_c[min(base + u * kNT, m - 1)];
-        pair[u] = base + u * kNT < m ? got : (uint32_t)T << 16;   // beyond the list: an edge into node n
-      }
-#pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
-        if constexpr (CT == 2) serve2(*reinterpret_cast<const uint32_t*>(st + (pair[u] & 0xFFFFu)), *reinterpret_cast<const uint32_t*>(st + (pair[u] >> 16)));
-        else serve(read_starts<CT>(st, (int)(pair[u] & 0xFFFFu) / CT), read_starts<CT>(st, (int)(pair[u] >> 16) / CT));
-      }
-    }
-    if (unserved || (unserved2 & 0x80008000u)) flags[1] = 1;
-    if constexpr (SMALL) request(after, 0, t_, ahead);
+    wait_for_lds_writes();
     __syncthreads();
 
-    // ---- per node: does it occur, what does it add to the duration; its outputs are held from p through b[p]
-    int my_dur = 0;
-    for (int round = 0; round < n; round += kUnroll * kNT) {
-      const int base = round + t_;
-      int2 sd[kUnroll];
+    // The sequence and the result.  Every wave issues the same stores, with lanes that have nothing to write
+    // out of the buffer's range (such a store is dropped): a wave waits for its loads by the number of
+    // memory operations behind them, and the loads that are on their way for the next candidate would
+    // otherwise be waited for together with stores that may or may not have been issued.
+    const auto rows = __builtin_amdgcn_make_buffer_rsrc(seq_row, 0, seq_row ? 4 * T : 0, kRawBuffer);
 #pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
-        if constexpr (SMALL) sd[u] = my_sd[u];
-        else sd[u] = G.size_dur[min(base + u * kNT, n - 1)];
+    for (int r = 0; r < R; ++r) {
+      const int x = (r * NT + t_) * 8;
+      int4 e = make_int4(0, 0, 0, 0);   // entries behind the sequence are 0 and become -1; so do all if there is none
+      if (seq_row && decodable && x < length) {
+        e = *reinterpret_cast<const int4*>(list + x);
+        *reinterpret_cast<int4*>(list + x) = make_int4(0, 0, 0, 0);
       }
+      const auto node_of = [](uint32_t name) -> int {
+        if constexpr (CT == 3) return (int)((name + 2u) / 3u) - 1;
+        else return ((int)name - 1) >> (CT / 2);
+      };
+      const uint32_t w[4] = {(uint32_t)e.x, (uint32_t)e.y, (uint32_t)e.z, (uint32_t)e.w};
+      Words4 four[2];
 #pragma unroll
-      for (int u = 0; u < kUnroll; ++u) {
-        const int v = base + u * kNT;
-        if (v >= n) continue;
-        const NodeStarts<CT> sv = read_starts<CT>(st, v);
-        int times = 0;
+      for (int j = 0; j < 4; ++j) {
+        four[j / 2][2 * (j & 1)] = node_of(w[j] & 0xFFFFu);
+        four[j / 2][2 * (j & 1) + 1] = node_of(w[j] >> 16);
+      }
+      const int off = x + 8 <= T ? 4 * x : kDropped;
+      __builtin_amdgcn_raw_buffer_store_b128(four[0], rows, off, 0, 0);
+      __builtin_amdgcn_raw_buffer_store_b128(four[1], rows, off, 16, 0);
+      if ((T & 7) != 0 && seq_row) {   // the last thread of a row that is not a multiple of eight
 #pragma unroll
-        for (int i = 0; i < CT; ++i) {
-          const uint32_t p = sv.s[i];
-          if (p == kNoStart) continue;
-          ++times;
-          atomicAdd(&a[p], sd[u].x);
-          atomicAdd(&a[b[p] + 1], -sd[u].x);
-        }
-        if (times == 0) flags[1] = 1;
-        my_dur += times * sd[u].y;
+        for (int j = 0; j < 7; ++j)
+          if (x + 8 > T && x + j < T) seq_row[x + j] = four[j / 4][j & 3];
       }
     }
-    if (my_dur) atomicAdd(&flags[2], my_dur);
-    __syncthreads();
-    const int peak = block_peak_and_clear(a, lay.T_pad, scratch, t_);
-
-    if (t_ == 0) {
-      const bool valid = flags[1] == 0;
-      out[cand] = moc_decode_result{valid ? 1 : 0, length, valid ? (int64_t)peak : 0, valid ? (int64_t)flags[2] : 0};
+    // No barrier behind this: what is read here is written again behind the next candidate's second.
+    int2 segment = make_int2(0, 0);
+    if (wave_ == 0) {
+      if (lane_ < R * NW) segment = sums[lane_];
+      combine_segments(segment.x, segment.y);
     }
+    const auto result = __builtin_amdgcn_make_buffer_rsrc(out + cand, 0, (int)sizeof(moc_decode_result), kRawBuffer);
+    const int off = wave_ == 0 && lane_ == kWave - 1 ? 0 : kDropped;
+    __builtin_amdgcn_raw_buffer_store_b128(Words4{decodable ? (valid ? 1 : 0) : -1, decodable ? length : 0, valid ? segment.y : 0, 0},
+                                           result, off, 0, 0);
+    __builtin_amdgcn_raw_buffer_store_b64(Words2{valid ? total_dur : 0, 0}, result, off, 16, 0);
   }
 }
 
+using DfKernel = void (*)(GraphView, const uint32_t*, int64_t, const int32_t*, const uint8_t*, moc_decode_result*, int32_t*, DfLayout);
+
 template <int CT>
-auto fixed_kernel_for(int n) {
-  return n <= kUnroll * kNT ? decode_fixed_kernel<CT, true> : decode_fixed_kernel<CT, false>;
+DfKernel pick_fixed(int nt, bool loop) {
+  if (loop) return decode_fixed_kernel<CT, 1024, true>;
+  switch (nt) {
+    case 64: return decode_fixed_kernel<CT, 64, false>;
+    case 128: return decode_fixed_kernel<CT, 128, false>;
+    case 256: return decode_fixed_kernel<CT, 256, false>;
+    case 512: return decode_fixed_kernel<CT, 512, false>;
+    default: return decode_fixed_kernel<CT, 1024, false>;
+  }
 }
 
 }  // namespace
@@ -606,22 +802,47 @@ extern "C" int moc_decode_batch(const moc_graph* g, int64_t B, const int32_t* st
   int dev = -1;
   MOC_HIP(hipGetDevice(&dev));
   if (dev != g->device) return MOC_EDEVICE;
-  const DcLayout lay = dc_layout(g->view.n, g->view.C);
-  if (lay.bytes > g->max_lds) return MOC_EOVERFLOW;
-  auto kern = decode_kernel;
-  switch (g->view.C) {
-    case 1: kern = fixed_kernel_for<1>(g->view.n); break;
-    case 2: kern = fixed_kernel_for<2>(g->view.n); break;
-    case 3: kern = fixed_kernel_for<3>(g->view.n); break;
-    case 4: kern = fixed_kernel_for<4>(g->view.n); break;
-    default: break;
+  const GraphView& v = g->view;
+  hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  const DcLayout any = dc_layout(v.n, v.C);
+  if (any.bytes > g->max_lds) return MOC_EOVERFLOW;
+  const auto resident = [&](const void* kern, int nt, int bytes, bool no_static_lds, unsigned* grid) -> int {
+    int per_cu = 0;
+    if (const int rc = moc_kernel_occupancy(g, kern, nt, bytes, no_static_lds, &per_cu)) return rc;
+    *grid = (unsigned)std::min<int64_t>(B, (int64_t)per_cu * g->num_cu);
+    return MOC_OK;
+  };
+  if (g->slices) {   // C <= 4
+    // As few threads as hold the candidate: a workgroup's waves meet at three barriers per candidate, and
+    // lanes without a node still take their part of every pass.  By 64 / 128 / 256 / 512 / 1024 threads
+    // (before: 512 for every size): n = 100, C = 2, 16384 candidates 17.6 / 24.3 / 39.8 / 71.4 / 137 us
+    // (before 72.1); n = 442, 4096 candidates - / 14.5 / 17.7 / 26.5 / 46.2 (29.8); n = 1000, 4096
+    // candidates - / - / 24.9 / 31.0 / 49.6 (44.1).  With batches that leave compute units idle (n = 442, 16
+    // candidates; n = 2000, 128) every choice takes as long as the launch.  n = 2500, 2000 candidates: 1024
+    // threads 35.0 (44.1).
+    int nt = 64;
+    const auto holds = [&](int t) { return v.n <= node_slots(v.C) * t && df_layout(v.n, v.C, t).T_pad <= 8 * t; };
+    while (nt < 1024 && !holds(nt)) nt *= 2;
+    const bool loop = !holds(nt);
+    const DfLayout lay = df_layout(v.n, v.C, nt);
+    if (lay.bytes <= g->max_lds && lay.T_pad <= 16 * 1024) {
+      DfKernel kern = nullptr;
+      switch (v.C) {
+        case 1: kern = pick_fixed<1>(nt, loop); break;
+        case 2: kern = pick_fixed<2>(nt, loop); break;
+        case 3: kern = pick_fixed<3>(nt, loop); break;
+        default: kern = pick_fixed<4>(nt, loop); break;
+      }
+      unsigned grid = 0;
+      if (const int rc = resident(reinterpret_cast<const void*>(kern), nt, lay.bytes, true, &grid)) return rc;
+      hipLaunchKernelGGL(kern, dim3(grid), dim3(nt), lay.bytes, stream, v, g->slices, B, starts, active, out, out_seq, lay);
+      MOC_HIP(hipGetLastError());
+      return MOC_OK;
+    }
   }
-  int per_cu = 0;
-  if (const int rc = moc_kernel_occupancy(g, reinterpret_cast<const void*>(kern), kNT, lay.bytes, false, &per_cu)) return rc;
-  const int64_t resident = (int64_t)per_cu * g->num_cu;
-  const unsigned grid = (unsigned)(B < resident ? B : resident);
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(kNT), lay.bytes, static_cast<hipStream_t>(hip_stream), g->view, B,
-                     starts, active, out, out_seq, lay);
+  unsigned grid = 0;
+  if (const int rc = resident(reinterpret_cast<const void*>(decode_kernel), kNT, any.bytes, false, &grid)) return rc;
+  hipLaunchKernelGGL(decode_kernel, dim3(grid), dim3(kNT), any.bytes, stream, v, B, starts, active, out, out_seq, any);
   MOC_HIP(hipGetLastError());
   return MOC_OK;
 }

@@ -50,6 +50,7 @@
 #include <type_traits>
 
 #include "moc_cover.h"
+#include "moc_masks.h"
 #include "moc_wave.h"
 
 namespace {
@@ -324,19 +325,6 @@ __device__ __forceinline__ void load_node(const int32_t* __restrict__ s_row, con
   }
 }
 
-// ------------------------------------------------------------------ LDS by byte address
-// The dynamic LDS segment starts at address 0 (the kernels declare no static LDS, which the
-// host verifies before the first launch) and the node records are its first array: the LDS
-// address of a record is its word index times 4 and needs no base register.
-typedef __attribute__((address_space(3))) uint32_t lds_u32;
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-typedef __attribute__((address_space(3))) u32x2 lds_u32x2;
-__device__ __forceinline__ uint32_t lds_read(uint32_t addr) { return *(const lds_u32*)(uintptr_t)addr; }
-__device__ __forceinline__ uint2 lds_read2(uint32_t addr) {
-  const u32x2 v = *(const lds_u32x2*)(uintptr_t)addr;
-  return make_uint2(v.x, v.y);
-}
-
 // 4 * (low / high half of p): the LDS address of the record whose word index is packed in p.
 // Written out so that the half is picked by the shift itself, and kept where it is used: the
 // operand never changes, and the optimiser would otherwise hold every such address in a
@@ -354,8 +342,6 @@ __device__ __forceinline__ uint32_t addr_hi16(uint32_t p) {
   return r;
 }
 
-typedef __attribute__((address_space(3))) uint16_t lds_u16;
-__device__ __forceinline__ uint32_t lds_read_u16(uint32_t addr) { return *(const lds_u16*)(uintptr_t)addr; }
 // 2 * (high half of p): the LDS address of a 16-bit entry
 __device__ __forceinline__ uint32_t addr_hi16_half(uint32_t p) {
   uint32_t r;
@@ -373,67 +359,6 @@ __device__ __forceinline__ int delta_at(int t) {
   if constexpr (CH == 32) asm("v_lshrrev_b32 %0, 5, %1\n\tv_lshl_add_u32 %0, %0, 2, %1" : "=&v"(idx) : "v"(t));
   else asm("v_lshrrev_b32 %0, 4, %1\n\tv_lshl_add_u32 %0, %0, 2, %1" : "=&v"(idx) : "v"(t));
   return idx;
-}
-
-// Lane masks.  A predicate over the wave is one 64-bit scalar: a vector compare writes it
-// directly, the scalar unit combines and counts them, and nothing per lane is spent on
-// booleans.  The compares that pick a 16-bit half or a byte of their operand are written out
-// (sub-dword operand selects) since the compiler would first extract the field into a register.
-// Lanes that are switched off read as 0.  Use in wave-uniform control flow only.
-#define MOC_MASK_CMP(name, text, breg)                                             \
-  __device__ __forceinline__ lanemask name(uint32_t a, uint32_t b) {               \
-    lanemask m;                                                                    \
-    asm(text : "=s"(m) : "v"(a), breg(b));                                         \
-    return m;                                                                      \
-  }
-MOC_MASK_CMP(u_le, "v_cmp_le_u32_e64 %0, %1, %2", "v")
-MOC_MASK_CMP(i_gt, "v_cmp_gt_i32_e64 %0, %1, %2", "v")
-// b the same in every lane (a scalar register)
-MOC_MASK_CMP(u_lt_k, "v_cmp_lt_u32_e64 %0, %1, %2", "s")
-#undef MOC_MASK_CMP
-#define MOC_BYTE_CMP(name, sel)                                                                   \
-  template <typename F>                                                                           \
-  __device__ __forceinline__ lanemask name(F a, uint32_t b) {                                     \
-    lanemask m;                                                                                   \
-    asm("v_cmp_ne_u32_sdwa %0, %1, %2 src0_sel:" sel " src1_sel:DWORD" : "=s"(m) : "v"(a), "s"(b)); \
-    return m;                                                                                     \
-  }
-MOC_BYTE_CMP(byte0_ne_k, "BYTE_0")
-MOC_BYTE_CMP(byte1_ne_k, "BYTE_1")
-MOC_BYTE_CMP(byte2_ne_k, "BYTE_2")
-MOC_BYTE_CMP(byte3_ne_k, "BYTE_3")
-#undef MOC_BYTE_CMP
-template <typename F>
-__device__ __forceinline__ lanemask byte_ne_k(F a, int i, uint32_t b) {
-  return i == 0 ? byte0_ne_k(a, b) : i == 1 ? byte1_ne_k(a, b) : i == 2 ? byte2_ne_k(a, b) : byte3_ne_k(a, b);
-}
-// per lane: m ? yes : no
-__device__ __forceinline__ uint32_t pick(lanemask m, uint32_t yes, uint32_t no) {
-  uint32_t r;
-  asm("v_cndmask_b32_e64 %0, %1, %2, %3" : "=v"(r) : "v"(no), "v"(yes), "s"(m));
-  return r;
-}
-// per lane: m ? yes : 0
-__device__ __forceinline__ uint32_t pick(lanemask m, uint32_t yes) {
-  uint32_t r;
-  asm("v_cndmask_b32_e64 %0, 0, %1, %2" : "=v"(r) : "v"(yes), "s"(m));
-  return r;
-}
-__device__ __forceinline__ int count(lanemask m) { return __builtin_popcountll(m); }
-// true in exactly the lanes of m: `if (lanes(m))` runs its body with those lanes switched on
-__device__ __forceinline__ bool lanes(lanemask m) { return __builtin_amdgcn_inverse_ballot_w64(m); }
-// number of lanes of m below the calling lane, plus base
-__device__ __forceinline__ uint32_t rank_in(lanemask m, uint32_t base) {
-  return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, base));
-}
-// LDS[addr] = val in the lanes of m, without a branch: a branch would end the basic block, and
-// 16-bit values that live across blocks are widened again where they are used.  LDS
-// operations of a wave complete in order, so later reads see the write; the wave's count of
-// outstanding LDS operations is only ever higher than the compiler assumes, never lower.
-__device__ __forceinline__ void lds_write_lanes(lanemask m, uint32_t addr, uint32_t val) {
-  lanemask saved;
-  asm volatile("s_and_saveexec_b64 %0, %1\n\tds_write_b32 %2, %3\n\ts_mov_b64 exec, %0"
-               : "=&s"(saved) : "s"(m), "v"(addr), "v"(val) : "memory", "scc");
 }
 
 // C <= 2: the records of the two nodes of an edge held in a register as pair = u*C | v*C << 16

@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "moc_internal.h"
+#include "moc_slices.h"
 
 static thread_local int g_last_hip_error = 0;
 
@@ -204,6 +205,7 @@ int moc_graph_upload(int32_t n, const int32_t* in_ptr, const int32_t* in_idx, co
       for (int v = 0; v < n; ++v)
         for (int q = in_ptr[v]; q < in_ptr[v + 1]; ++q) out_idx[fill[in_idx[q]]++] = v;
     }
+    const std::vector<uint32_t> slices = out_slices(n, C, out_ptr.data(), out_idx.data());
     std::vector<int32_t> in_ptr_v(in_ptr, in_ptr + n + 1), in_idx_v(in_idx, in_idx + m);
 
     moc_graph* g = new moc_graph();   // all members zero
@@ -233,6 +235,7 @@ int moc_graph_upload(int32_t n, const int32_t* in_ptr, const int32_t* in_idx, co
     if (rc == MOC_OK) rc = upload(g, in_idx_v, &w.in_idx);
     if (rc == MOC_OK) rc = upload(g, out_ptr, &w.out_ptr);
     if (rc == MOC_OK) rc = upload(g, out_idx, &w.out_idx);
+    if (rc == MOC_OK && !slices.empty()) rc = upload(g, slices, &g->slices);
     if (rc == MOC_OK) {
       const std::vector<uint32_t> zeros((size_t)kTicketSlots * kTicketSlotWords, 0u);
       const uint32_t* dev = nullptr;

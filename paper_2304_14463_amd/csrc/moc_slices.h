@@ -1,0 +1,53 @@
+// The consumers of every node as the decode kernel walks them: plain C++, so that it can be checked
+// without a GPU.
+//
+// A lane takes a node and looks at the starts of its consumers one after the other, so the nodes of a
+// wave should have the same number of them: nodes in order of falling out-degree, 64 to a slice.  A slice
+// is stored by rows of 64 words, one word a lane: row 0 the nodes, each further row two consumers per
+// lane (low and high half) as byte offsets of their starts.  Lanes and halves without one hold node n,
+// which is never computed.  Nodes with more than kSliceDegree consumers are listed apart: a wave takes
+// one of them with all its lanes.
+#pragma once
+
+#include <stdint.h>
+
+#include <algorithm>
+#include <vector>
+
+constexpr int kSliceLanes = 64, kSliceDegree = 32;
+constexpr int starts_stride(int C) { return C == 3 ? 4 : C; }   // 16-bit entries of a node's starts in LDS
+
+// word 0: slices, word 1: nodes listed apart; then the word at which each slice begins and the one behind
+// the last, the nodes listed apart, the slices.  Empty if the byte offsets need more than 16 bits.
+inline std::vector<uint32_t> out_slices(int n, int C, const int32_t* out_ptr, const int32_t* out_idx) {
+  if (C > 4 || (int64_t)n * 2 * starts_stride(C) > 0xFFFF) return {};
+  std::vector<int32_t> order, apart;
+  for (int v = 0; v < n; ++v) (out_ptr[v + 1] - out_ptr[v] > kSliceDegree ? apart : order).push_back(v);
+  std::stable_sort(order.begin(), order.end(),
+                   [&](int a, int b) { return out_ptr[a + 1] - out_ptr[a] > out_ptr[b + 1] - out_ptr[b]; });
+  const int slices = ((int)order.size() + kSliceLanes - 1) / kSliceLanes;
+  const uint32_t bytes = 2u * (uint32_t)starts_stride(C), none = bytes * (uint32_t)n;
+  std::vector<uint32_t> w(2 + slices + 1 + apart.size());
+  w[0] = (uint32_t)slices;
+  w[1] = (uint32_t)apart.size();
+  for (size_t i = 0; i < apart.size(); ++i) w[2 + slices + 1 + i] = (uint32_t)apart[i];
+  for (int s = 0; s < slices; ++s) {
+    const size_t at = w.size();
+    w[2 + s] = (uint32_t)at;
+    const int first = order[(size_t)s * kSliceLanes], rows = (out_ptr[first + 1] - out_ptr[first] + 1) / 2;
+    w.resize(at + (size_t)(1 + rows) * kSliceLanes, none | none << 16);
+    for (int l = 0; l < kSliceLanes; ++l) {
+      const size_t i = (size_t)s * kSliceLanes + l;
+      w[at + l] = i < order.size() ? (uint32_t)order[i] : (uint32_t)n;
+      if (i >= order.size()) continue;
+      const int v = order[i];
+      for (int y = out_ptr[v], k = 0; y < out_ptr[v + 1]; ++y, ++k) {
+        uint32_t& word = w[at + (size_t)(1 + k / 2) * kSliceLanes + l];
+        const uint32_t c = bytes * (uint32_t)out_idx[y];
+        word = k & 1 ? (word & 0xFFFFu) | c << 16 : (word & 0xFFFF0000u) | c;
+      }
+    }
+  }
+  w[2 + slices] = (uint32_t)w.size();
+  return w;
+}

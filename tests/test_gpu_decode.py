@@ -140,6 +140,56 @@ def test_decode_rows_at_odd_addresses(moc, n, C):
     gh.free()
 
 
+def dense_candidates(rng, g, C, B):
+    """Every copy of every node computed, at places shuffled within runs of the order (even rows: valid as a
+    whole up to the shuffling), or a random set of copies at random places (odd rows)."""
+    n, T = g.n, g.n * C
+    s = np.empty((B, T), np.int32)
+    a = np.zeros((B, T), np.uint8)
+    for b in range(B):
+        s[b] = rng.permutation(T)
+        if b % 2 == 0:
+            s[b] = np.argsort(np.argsort(np.arange(T) + rng.uniform(0, 3 * C, T)))   # copies of a node lie close together
+            a[b] = 1
+        else:
+            a[b] = rng.random(T) < rng.choice([0.1, 0.5, 0.95])
+    return s, a
+
+
+# at, below and above the sizes at which the workgroup grows (nodes and positions per lane) and at which the
+# kernel goes over a candidate in rounds
+@pytest.mark.parametrize("n,C", [(255, 1), (257, 1), (4096, 1), (4097, 1), (251, 2), (252, 2), (1020, 2), (1024, 2), (2043, 2),
+                                 (2045, 2), (4091, 2), (4093, 2), (6001, 2), (127, 3), (129, 3), (2045, 3), (2049, 3), (3001, 3),
+                                 (125, 4), (128, 4), (2044, 4), (2048, 4), (3000, 4), (15900, 1)])
+def test_decode_every_workgroup_size(moc, n, C):
+    from paper_2304_14463_amd.inputs import graph_from_edges
+    rng = np.random.default_rng(53 * n + C)
+    edges = {(int(u), v) for v in range(1, n) for u in rng.integers(max(0, v - 20), v, size=rng.integers(0, 4))}
+    edges |= {(3, int(v)) for v in rng.integers(4, n, n // 3)}          # a node with very many consumers
+    edges |= {(u, int(v)) for u in (0, 40, 90) for v in rng.integers(91, n, 40)}   # some with more than a slice's rows in registers
+    g = graph_from_edges(n, sorted(edges), rng.integers(0, 50, n), rng.integers(1, 9, n))
+    gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, 1, C)
+    for s, a in (orderly_candidates(rng, g, C, 4), dense_candidates(rng, g, C, 6)):
+        want, want_seq = oracle.decode(g, C, s, a)
+        got, seq = gpu_decode(moc, gh, s, a)
+        assert_same(got, seq, want, want_seq, f"n={n} C={C}")
+        got, _ = gpu_decode(moc, gh, s, a, want_seq=False)
+        assert_same(got, None, want, want_seq, f"n={n} C={C} without the sequences")
+    gh.free()
+
+
+def test_decode_graph_without_edges(moc):
+    from paper_2304_14463_amd.inputs import graph_from_edges
+    rng = np.random.default_rng(5)
+    g = graph_from_edges(77, [], rng.integers(0, 50, 77), rng.integers(1, 9, 77))
+    gh = moc.moc_graph_upload(77, g.in_ptr, g.in_idx, g.size, g.dur, 1, 2)
+    s, a = dense_candidates(rng, g, 2, 3000)   # more than fit the chip at a time
+    want, want_seq = oracle.decode(g, 2, s, a)
+    got, seq = gpu_decode(moc, gh, s, a)
+    assert_same(got, seq, want, want_seq)
+    gh.free()
+
+
 def test_decode_self_loop_and_duplicate_edges(moc):
     from paper_2304_14463_amd.inputs import graph_from_edges
     g = graph_from_edges(4, [(0, 1), (0, 1), (1, 1), (1, 2), (0, 3)], [3, 5, 2, 7], [1, 2, 3, 4])

@@ -1,0 +1,82 @@
+"""The consumers of every node as the decode kernel walks them (csrc/moc_slices.h): a small program of the
+header alone, compiled with g++.  No GPU."""
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2304_14463_amd", "csrc")
+
+PROGRAM = r"""
+#include <cstdio>
+#include "moc_slices.h"
+int main() {   // n C m, then m edges (u, v) in the order of u
+  int n, C, m;
+  if (scanf("%d %d %d", &n, &C, &m) != 3) return 1;
+  std::vector<int32_t> ptr(n + 1), idx(m);
+  for (int q = 0; q < m; ++q) {
+    int u, v;
+    if (scanf("%d %d", &u, &v) != 2) return 1;
+    ++ptr[u + 1];
+    idx[q] = v;
+  }
+  for (int v = 0; v < n; ++v) ptr[v + 1] += ptr[v];
+  for (uint32_t w : out_slices(n, C, ptr.data(), idx.data())) printf("%u\n", w);
+  return 0;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    at = tmp_path_factory.mktemp("slices")
+    (at / "slices.cpp").write_text(PROGRAM)
+    subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, "-o", str(at / "slices"), str(at / "slices.cpp")], check=True)
+
+    def run(n, C, edges):
+        text = f"{n} {C} {len(edges)}\n" + "\n".join(f"{u} {v}" for u, v in edges)
+        out = subprocess.run([str(at / "slices")], input=text, check=True, capture_output=True, text=True).stdout
+        return np.array(out.split(), dtype=np.int64)
+    return run
+
+
+@pytest.mark.parametrize("n,C,degree", [(1, 1, 0), (63, 1, 3), (64, 2, 5), (65, 3, 33), (200, 4, 32), (700, 2, 90), (8190, 2, 2)])
+def test_every_edge_once(program, n, C, degree):
+    """Every node stands in one slice or apart, with its own consumers and no others; lanes and halves that
+    hold none lead to node n; nodes apart are those with more than 32."""
+    rng = np.random.default_rng(n * 8 + C)
+    out = [np.sort(rng.integers(0, n, rng.integers(0, degree + 1))) for _ in range(n)]
+    if n > 64:
+        out[5] = rng.integers(0, n, 300)   # a hub, with some consumers twice
+    edges = [(u, int(v)) for u in range(n) for v in out[u]]
+    w = program(n, C, edges)
+    stride = 2 * (4 if C == 3 else C)
+    slices, apart = int(w[0]), int(w[1])
+    begin = w[2:3 + slices]
+    aside = w[3 + slices:3 + slices + apart]
+    assert begin[0] == 3 + slices + apart and begin[-1] == w.size
+    assert sorted(aside) == [u for u in range(n) if len(out[u]) > 32]
+    seen, lengths = list(aside), []
+    for i in range(slices):
+        rows = w[begin[i]:begin[i + 1]].reshape(-1, 64)
+        lengths.append(rows.shape[0])
+        for lane in range(64):
+            node, words = int(rows[0, lane]), rows[1:, lane]
+            uses = np.stack([words & 0xFFFF, words >> 16], 1).reshape(-1)
+            assert (uses % stride == 0).all()
+            uses = uses // stride
+            if node == n:
+                assert (uses == n).all()
+                continue
+            seen.append(node)
+            k = len(out[node])
+            assert list(uses[:k]) == [int(v) for v in out[node]] and (uses[k:] == n).all()
+    assert sorted(seen) == list(range(n))
+    assert lengths == sorted(lengths, reverse=True)   # the long ones first
+
+
+def test_sizes_beyond_16_bits_have_none(program):
+    assert program(19455, 1, []).size > 0
+    assert program(8191, 4, []).size > 0 and program(8192, 4, []).size == 0
+    assert program(100, 5, []).size == 0
