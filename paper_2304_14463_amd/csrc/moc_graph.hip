@@ -228,6 +228,11 @@ int moc_graph_upload(int32_t n, const int32_t* in_ptr, const int32_t* in_idx, co
     }
     GraphView& w = g->view;
     w.budget = budget; w.n = n; w.m = m; w.C = C; w.T = T;
+    for (int v = 0; v < n && !w.parallel; ++v) {
+      std::vector<int32_t> inputs(in_idx + in_ptr[v], in_idx + in_ptr[v + 1]);
+      std::sort(inputs.begin(), inputs.end());
+      w.parallel = std::adjacent_find(inputs.begin(), inputs.end()) != inputs.end() ? 1 : 0;
+    }
     if (rc == MOC_OK) rc = upload(g, size_dur, &w.size_dur);
     if (rc == MOC_OK) rc = upload(g, edge_pair, &w.edge_pair);
     if (rc == MOC_OK) rc = upload(g, edge_pair_c, &w.edge_pair_c);

@@ -28,6 +28,7 @@ struct GraphView {
   const int32_t* out_idx;      // [m]
   int64_t budget;
   int32_t n, m, C, T;
+  int32_t parallel;            // 1: some edge is listed more than once
 };
 
 constexpr int kTicketSlots = 16;   // sets of work counters per graph handle = streams that get one of their own

@@ -66,7 +66,7 @@ struct Lists<false> {
 };
 
 struct BaseLds {
-  int32_t *profile, *table, *pre, *suf, *peak_before, *scratch;
+  int32_t *profile, *table, *pre, *suf, *peak_before, *scratch, *marks;   // marks: positions at the peak: how many, the first, the last
   uint32_t *packed, *occ1, *occ2, *peak_bits, *extra;
   __device__ __forceinline__ void carve(uint32_t* raw, const MvLayout& l) {
     profile = reinterpret_cast<int32_t*>(raw);
@@ -79,6 +79,7 @@ struct BaseLds {
     peak_bits = raw + l.peak_bits;
     peak_before = profile + l.peak_before;
     scratch = profile + l.scratch;
+    marks = scratch + kScratchWords - 4;
     extra = raw + l.extra;
   }
 };
@@ -214,48 +215,61 @@ __device__ __forceinline__ void scan_profile(const BaseLds& L, const MvLayout& l
   __syncthreads();
 }
 
-// The levels of the table above 0, and the maxima before and from every block: one wave each.
-// Ends with a barrier.
+// The levels of the table above 0, three at a time by all threads (a barrier behind each three), and the
+// maxima before and from every block by the last two waves.  Ends with a barrier.  (All levels by one
+// wave, one after the other: n = 1000, a step of the descent 1.7 instead of 1.4 us, toggles at n = 2000 111.8
+// instead of 109.5.)
 template <int NT>
 __device__ __forceinline__ void build_maxima(const BaseLds& L, const MvLayout& lay, int t) {
   constexpr int NW = NT / kWave;
   const int lane = t & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(t / kWave);
   const int blocks = lay.blocks;
-  if (wave == 0) {
-    for (int l = 1; l < lay.levels; ++l) {
-      const int half = 1 << (l - 1);
-      const int32_t* below = L.table + table_level(l - 1, blocks);
-      int32_t* here = L.table + table_level(l, blocks);
-      for (int x = lane; x + 2 * half <= blocks; x += kWave) here[x] = max(below[x], below[x + half]);
-      wave_lds_order();
+  for (int l = 0; l == 0 || l + 1 < lay.levels; l += 3) {
+    const int step = 1 << l;   // blocks an entry of level l stands for
+    const int32_t* below = L.table + table_level(l, blocks);
+    int32_t* const up1 = L.table + table_level(l + 1, blocks);
+    int32_t* const up2 = L.table + table_level(l + 2, blocks);
+    int32_t* const up3 = L.table + table_level(l + 3, blocks);
+    const int last = blocks - step;   // the level's last entry
+    for (int x = t; x + 2 * step <= blocks; x += NT) {
+      int v[8];
+#pragma unroll
+      for (int d = 0; d < 8; ++d) v[d] = below[min(x + d * step, last)];
+      const int m2 = max(v[0], v[1]), m4 = max(m2, max(v[2], v[3])), m8 = max(max(m4, max(v[4], v[5])), max(v[6], v[7]));
+      up1[x] = m2;
+      if (x + 4 * step <= blocks) up2[x] = m4;
+      if (x + 8 * step <= blocks) up3[x] = m8;
     }
-  }
-  if (wave == (NW > 1 ? 1 : 0)) {
-    int carry = 0;
-    for (int x0 = 0; x0 < blocks; x0 += kWave) {
-      const int x = x0 + lane;
-      const int incl = max(carry, scan_max(x < blocks ? L.table[x] : 0));
-      if (x < blocks) L.pre[x + 1] = incl;
-      carry = last_lane(incl);
+    if (l == 0) {
+      if (wave == NW - 1) {
+        int carry = 0;
+        for (int x0 = 0; x0 < blocks; x0 += kWave) {
+          const int x = x0 + lane;
+          const int incl = max(carry, scan_max(x < blocks ? L.table[x] : 0));
+          if (x < blocks) L.pre[x + 1] = incl;
+          carry = last_lane(incl);
+        }
+        if (lane == 0) { L.pre[0] = 0; L.suf[blocks] = 0; }
+      }
+      if (wave == (NW > 1 ? NW - 2 : 0)) {
+        int carry = 0;
+        for (int x0 = 0; x0 < blocks; x0 += kWave) {
+          const int x = blocks - 1 - (x0 + lane);
+          const int incl = max(carry, scan_max(x >= 0 ? L.table[x] : 0));
+          if (x >= 0) L.suf[x] = incl;
+          carry = last_lane(incl);
+        }
+      }
     }
-    if (lane == 0) { L.pre[0] = 0; L.suf[blocks] = 0; }
+    __syncthreads();
   }
-  if (wave == (NW > 2 ? 2 : 0)) {
-    int carry = 0;
-    for (int x0 = 0; x0 < blocks; x0 += kWave) {
-      const int x = blocks - 1 - (x0 + lane);
-      const int incl = max(carry, scan_max(x >= 0 ? L.table[x] : 0));
-      if (x >= 0) L.suf[x] = incl;
-      carry = last_lane(incl);
-    }
-  }
-  __syncthreads();
 }
 
 // profile += change on [lo, hi], level 0 of the table with it.  Ends with a barrier.
+// MARK: the positions at which it then reaches `peak` are marked, too (begin_marks before, a barrier between).
 struct Range { int lo, hi, change; };
-template <int NT, typename R>
-__device__ __forceinline__ void add_ranges(const BaseLds& L, const MvLayout& lay, const R* ranges, int count, int t) {
+template <int NT, bool MARK, typename R>
+__device__ __forceinline__ void add_ranges(const BaseLds& L, const MvLayout& lay, const R* ranges, int count, int peak, int T, int t) {
   for (int x0 = 0; x0 < lay.blocks * kBlk; x0 += 4 * NT) {   // whole waves
     const int x = x0 + 4 * t;
     int4 v = make_int4(0, 0, 0, 0);
@@ -268,6 +282,16 @@ __device__ __forceinline__ void add_ranges(const BaseLds& L, const MvLayout& lay
       v.w += lo <= x + 3 && x + 3 <= hi ? d : 0;
     }
     int top = max(max(v.x, v.y), max(v.z, v.w));
+    if (MARK && top >= peak && x < T) {   // few lanes
+      const uint32_t hit = ((v.x >= peak ? 1u : 0u) | (v.y >= peak ? 2u : 0u) | (v.z >= peak ? 4u : 0u) | (v.w >= peak ? 8u : 0u)) &
+                           (0xFu >> max(x + 4 - T, 0));
+      if (hit != 0) {
+        atomicOr(&L.peak_bits[x >> 5], hit << (x & 31));
+        atomicAdd(&L.marks[0], __popc(hit));
+        atomicMin(&L.marks[1], x + __ffs(hit) - 1);
+        atomicMax(&L.marks[2], x + 31 - __clz(hit));
+      }
+    }
     top = max(top, __builtin_amdgcn_update_dpp(0, top, 0xB1, 0xF, 0xF, true));
     if (x < lay.blocks * kBlk) {
       *reinterpret_cast<int4*>(L.profile + x) = v;
@@ -275,6 +299,18 @@ __device__ __forceinline__ void add_ranges(const BaseLds& L, const MvLayout& lay
     }
   }
   __syncthreads();
+}
+__device__ __forceinline__ void clear_marks(const BaseLds& L, int t) {
+  if (t == 0) {
+    L.marks[0] = 0;
+    L.marks[1] = 0x7FFFFFFF;
+    L.marks[2] = -1;
+  }
+}
+template <int NT>
+__device__ __forceinline__ void begin_marks(const BaseLds& L, const MvLayout& lay, int t) {
+  for (int w = t; w < lay.bit_words; w += NT) L.peak_bits[w] = 0;
+  clear_marks(L, t);
 }
 
 // Maxima of the profile over [lo, hi], 0 <= lo <= hi < T, and over all other positions: whole

@@ -21,12 +21,14 @@ static_assert(kMaxRanges == kWave + 1 && kCutWords == (int)(sizeof(Cut) / 4), "d
 
 // One workgroup per candidate: up to max_steps cuts, each the best of the candidate as it stands,
 // applied if it lowers (violations, max(peak, M)) or, above the budget with both unchanged, leaves
-// fewer positions at the peak.  Bound by the chain of instructions and LDS latencies of a step (a
-// lone wave issues one vector instruction in 8 clocks): 15 to 21 us, of which the sieve takes 5
-// and the scoring 3 (plain cuts) to 12 (cuts that keep inputs).  The walkers are all resident, so the
-// launch lasts as long as those with the most steps: n = 442, 1024 walkers, up to 64 keeping cuts 0.76,
-// 1.36 and 1.41 ms for three sets of inputs (27 ms for the first with two launches a step that staged
-// and scored everything again); n = 1000, 32 walkers, 32 plain cuts: 1.31 -> 0.42 ms.
+// fewer positions at the peak.  A step is a chain of short phases; 1024 walkers at n = 442 (four to a compute
+// unit) are bound by the vector instructions of all of them together, 77 % busy, a few walkers by the chain:
+// 13.6 us with cuts that keep inputs (sieve 6, scoring 3.5, edit 2, tables 1; 21 to 25 with one lane per
+// move), 8 with plain cuts at n = 1000 (sieve 1.5, scoring 1.6, edit 1.3, tables 1.4; 13).  The walkers are
+// all resident, so the launch lasts as long as those with the most steps: n = 442, 1024 walkers, up to 64
+// keeping cuts 0.40 and 0.7 ms for two sets of inputs (0.76 and 1.36 with one lane per move; 27 ms with two
+// launches a step that staged and scored everything again); n = 1000, 32 walkers, 32 plain cuts: 0.27 ms
+// (0.42; 1.31).
 template <int CT, int NT, bool LISTS, int MODE>
 __global__ __launch_bounds__(NT) void descend_cuts_kernel(GraphView g, int32_t* __restrict__ starts, int32_t* __restrict__ ends,
                                                           uint8_t* __restrict__ active, int max_steps,
@@ -44,7 +46,7 @@ __global__ __launch_bounds__(NT) void descend_cuts_kernel(GraphView g, int32_t* 
   Range* const ranges = reinterpret_cast<Range*>(queue + 2 * kWave * NW);
   int32_t* const n_ranges = reinterpret_cast<int32_t*>(ranges + kMaxRanges);
   Cut* const chosen_cut = reinterpret_cast<Cut*>(n_ranges + 1);
-  const SiftLds sift = carve_sift(L.extra + descend_words(NT), g.n, cap);
+  const SiftLds sift = carve_sift(L.extra + descend_words(NT), cap);
   const int64_t row = (int64_t)blockIdx.x * T;
 
   const StageSums sums = stage_copies<CT, NT>(g, L, lay, starts + row, ends + row, active + row, t);
@@ -52,6 +54,7 @@ __global__ __launch_bounds__(NT) void descend_cuts_kernel(GraphView g, int32_t* 
   for (int w = t; w < lay.bit_words; w += NT) viol -= __popc(L.occ1[w]);   // Eq. (6): live copies - distinct starts
   viol = last_lane(scan_sum(viol));
   if (lane == 0) L.scratch[128 + wave] = viol;
+  clear_marks(L, t);
   scan_profile<NT>(L, lay, T, t);
   build_maxima<NT>(L, lay, t);
   int base_viol = 0, base_peak = L.pre[lay.blocks];
@@ -60,14 +63,15 @@ __global__ __launch_bounds__(NT) void descend_cuts_kernel(GraphView g, int32_t* 
 
   int steps = 0;
   moc_best_move chosen{-1, 0, 0};
+  clear_sift<NT>(sift, t);
+  PeakCount at_peak = mark_peak<NT>(L, lay, T, base_peak, t);
   for (; steps < max_steps; ++steps) {
     chosen = moc_best_move{-1, 0, 0};
     if (base_viol == 0 && (int64_t)base_peak <= g.budget) break;   // no move lowers anything a step looks at
-    const PeakCount at_peak = mark_peak<NT>(L, lay, T, base_peak, t);
     BestCut best;
     Cut cut{};
     bool known = false;   // this lane holds the chosen move in `cut`
-    if (base_viol != 0 || !best_cut_of_clean_base<CT, NT>(g, lists, L, lay, queue, sift, MODE, base_peak, at_peak, best, cut, known, t)) {
+    if (base_viol != 0 || !best_cut_of_clean_base<CT, NT, MODE>(g, lists, L, lay, sift, base_peak, at_peak, best, cut, known, t)) {
       best = BestCut{};
       known = false;
       score_cuts<CT, NT>(g, lists, L, lay, queue, MODE, base_viol, base_peak, at_peak, base_viol == 0, best, t,
@@ -91,6 +95,8 @@ __global__ __launch_bounds__(NT) void descend_cuts_kernel(GraphView g, int32_t* 
 
     // ---- apply it: one wave edits the copies and lists the stretches of the profile that change
     if (known) *chosen_cut = cut;
+    begin_marks<NT>(L, lay, t);
+    clear_sift<NT>(sift, t);
     __syncthreads();
     cut = *chosen_cut;
     const int ub = (int)(lists.pair(q / C) & 0xFFFFu), u = ub / C;
@@ -146,11 +152,13 @@ __global__ __launch_bounds__(NT) void descend_cuts_kernel(GraphView g, int32_t* 
         }
       }
       __syncthreads();
-      add_ranges<NT>(L, lay, ranges, *n_ranges, t);
+      if (round == rounds - 1) add_ranges<NT, true>(L, lay, ranges, *n_ranges, best.peak(), T, t);
+      else add_ranges<NT, false>(L, lay, ranges, *n_ranges, 0, T, t);
     }
     build_maxima<NT>(L, lay, t);
     base_viol = best.viol();
     base_peak = best.peak();
+    at_peak = count_marks<NT>(L, lay, t);
   }
   if (t == 0) {
     out_steps[blockIdx.x] = steps;
@@ -183,8 +191,9 @@ __device__ __forceinline__ Range merged_range(uint32_t pc, uint32_t pb, int size
 // step is a chain of LDS latencies (list, walk over the node's edges, range maxima, tables), so
 // the workgroup is small and several share a compute unit: 256 threads for every size (n = 442, C = 2,
 // up to 32 steps of K = 64 by 256 / 512 / 1024 threads: 1024 walkers 251 / 386 / 840 us, 32 walkers
-// 217 / 213 / 239; where no step is found, staging alone, n = 2000, 256 walkers 32 / 25 / 20).  1024
-// walkers at n = 442, up to 48 steps of K = 64: 0.25 to 0.29 ms on three sets of inputs.  (Every merge
+// 217 / 213 / 239; where no step is found, staging alone, n = 2000, 256 walkers 32 / 25 / 20; taken with one
+// lane per entry).  1024 walkers at n = 442, up to 48 steps of K = 64: 0.18 ms (0.25 with one lane per entry,
+// whose edges one lane then walks one after the other).  (Every merge
 // written out as a row of its own and evaluated by moc_eval_batch, four launches a step: 19 ms on the
 // first of them, 9.8 the writing and 7.9 the evaluation.)
 template <int CT, int NT, bool LISTS>
@@ -239,39 +248,40 @@ __global__ __launch_bounds__(NT) void merge_kernel(GraphView g, int32_t* __restr
     count = min(count, K);
     __syncthreads();
 
-    // ---- one lane per entry.  key = (2^31 - 1 - w_v) << 32 | peak: the lowest duration, then the
+    // ---- eight lanes per entry (moc_cut_moves.h), the node's inputs and consumers side by side.  key = (2^31 - 1 - w_v) << 32 | peak: the lowest duration, then the
     // lowest peak; then the lowest copy index.
     uint64_t best = ~0ull;
     int best_copy = 0x7FFFFFFF;
-    for (int r = t; r < count; r += NT) {
+    const int gl = t & (kGroup - 1);
+    for (int r = t / kGroup; r < count; r += NT / kGroup) {
       const int k = list[r];
       const int v = k / C, below = live_below(L.packed, C, k);
       const uint32_t pc = L.packed[k], pb = L.packed[below];
       const uint32_t sc = pc & 0xFFFFu;
       const uint32_t joined = (pb & 0xFFFFu) | (max(pb >> 16, pc >> 16) << 16);
-      int vv = base_viol;
+      int vv = gl == 0 ? base_viol : 0;   // shares of the lanes
       // Eq. (3) among the live copies of v, before and after
       int end_before = -1, end_after = -1;
       for (int i = 0; i < C; ++i) {
         const uint32_t p = L.packed[v * C + i];
         if (!live_of(p)) continue;
         const int start = (int)(p & 0xFFFFu);
-        vv -= end_before > start ? 1 : 0;
+        vv -= gl == 0 && end_before > start ? 1 : 0;
         end_before = (int)(p >> 16);
         if (v * C + i == k) continue;
-        vv += end_after > start ? 1 : 0;
+        vv += gl == 0 && end_after > start ? 1 : 0;
         end_after = (int)((v * C + i == below ? joined : p) >> 16);
       }
-      if (bit_at(L.occ2, (int)sc)) --vv;   // Eq. (6): a shared start loses one of its copies
+      if (gl == 0 && bit_at(L.occ2, (int)sc)) --vv;   // Eq. (6): a shared start loses one of its copies
       // Eq. (5): the inputs of c are not asked for any more
-      for (int x = lists.in_begin(v), x1 = lists.in_begin(v + 1); x < x1; ++x) {
+      for (int x = lists.in_begin(v) + gl, x1 = lists.in_begin(v + 1); x < x1; x += kGroup) {
         const uint32_t* const pu = L.packed + (lists.pair(x) & 0xFFFFu);
         bool held = false;
         for (int i = 0; i < C; ++i) held = held || covers1(pu[i], sc);
         vv -= held ? 0 : 1;
       }
       // Eq. (5): the consumers of v, served by the copies as they stand and as they would be
-      for (int y = lists.out_begin(v), y1 = lists.out_begin(v + 1); y < y1; ++y) {
+      for (int y = lists.out_begin(v) + gl, y1 = lists.out_begin(v + 1); y < y1; y += kGroup) {
         const uint32_t* const pw = L.packed + lists.consumer_copy(y, C);
         for (int j = 0; j < C; ++j) {
           const uint32_t at = pw[j] & 0xFFFFu;
@@ -283,14 +293,15 @@ __global__ __launch_bounds__(NT) void merge_kernel(GraphView g, int32_t* __restr
           vv += (covers1(joined, at) ? 0 : 1) - (covers1(pc, at) || covers1(pb, at) ? 0 : 1);
         }
       }
+      vv = group_sum(vv);
       if (vv != 0) continue;
       const Range range = merged_range(pc, pb, lists.size_of(v));
       int peak = L.pre[lay.blocks];
       if (range.change != 0) {
-        const InOut m = range_maxima<true>(L, lay.blocks, range.lo, range.hi);
+        const InOut m = group_range_maxima(L, lay.blocks, range.lo, range.hi, gl);
         peak = max(m.in + range.change, m.out);
       }
-      if ((int64_t)peak > g.budget) continue;
+      if ((int64_t)peak > g.budget || gl != 0) continue;
       const uint64_t key = (uint64_t)(0x7FFFFFFFu - (uint32_t)g.size_dur[v].y) << 32 | (uint32_t)peak;
       if (key < best || (key == best && k < best_copy)) {
         best = key;
@@ -298,7 +309,7 @@ __global__ __launch_bounds__(NT) void merge_kernel(GraphView g, int32_t* __restr
       }
     }
 #pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
+    for (int off = kWave / 2; off >= kGroup; off >>= 1) {   // the groups' first lanes
       const uint64_t o = (uint64_t)__shfl_xor((unsigned long long)best, off);
       const int oc = __shfl_xor(best_copy, off);
       if (o < best || (o == best && oc < best_copy)) {
@@ -339,7 +350,7 @@ __global__ __launch_bounds__(NT) void merge_kernel(GraphView g, int32_t* __restr
       ends[row + below] = (int32_t)end;
       active[row + k] = 0;
     }
-    add_ranges<NT>(L, lay, &range, 1, t);
+    add_ranges<NT, false>(L, lay, &range, 1, 0, T, t);
     if (range.change != 0) build_maxima<NT>(L, lay, t);
   }
   if (t == 0) merges[blockIdx.x] = steps;

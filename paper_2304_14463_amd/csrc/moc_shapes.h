@@ -81,7 +81,7 @@ constexpr int kBuckets = 64;     // of the sieve's histogram of bounds
 // Words of LDS beyond the base: a queue of two moves per lane, the stretches, the chosen move.
 constexpr int descend_words(int nt) { return (2 * nt + 3 * kMaxRanges + 1 + kCutWords + 1) & ~1; }
 // ... and the lists of `cap` moves that pass the sieve.
-inline int sift_words(int n, int cap) { return 3 * cap + cap / 2 + 2 * ((n + 63) / 64) + kBuckets + 4 + 2; }
+inline int sift_words(int /*n*/, int cap) { return 3 * cap + cap / 2 + kBuckets + 4; }
 
 struct DescendShape {
   int nt;    // threads per candidate

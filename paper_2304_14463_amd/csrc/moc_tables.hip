@@ -229,6 +229,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 1024 ?
       L.scratch[96 + wave] = viol;
       L.scratch[112 + wave] = dur;
     }
+    clear_marks(L, own);
     scan_profile<NT>(L, lay, T, own);
     build_maxima<NT>(L, lay, own);
     int base_viol = 0, base_dur = 0;

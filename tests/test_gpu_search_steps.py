@@ -119,6 +119,38 @@ def test_cuts_follow_the_oracle(moc, n, C, B, mode):
     gh.free()
 
 
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("n,C,B,duplicates", [(40, 2, 3, False), (40, 2, 3, True), (150, 2, 600, False), (150, 3, 6, True), (150, 2, 1500, True),
+                                              (260, 2, 1500, False), (130, 4, 9, False)])
+def test_cuts_with_equal_peaks_and_many_inputs(moc, n, C, B, duplicates, mode):
+    """Sizes 1 to 3, so that many positions share the peak and many moves their score, and up to 14
+    inputs per node, more than the lanes that score a move; with and without edges listed twice."""
+    from paper_2304_14463_amd.inputs import graph_from_edges
+    rng = np.random.default_rng(n + C + mode)
+    edges = [(int(u), v) for v in range(1, n) for u in rng.integers(max(0, v - 30), v, size=rng.integers(1, 15))]
+    g = graph_from_edges(n, sorted(edges if duplicates else set(edges)), rng.integers(1, 4, n), rng.integers(1, 9, n))
+    rows, steps = 3, 14
+    s, e, a = schedules(rng, g, C, 3 * rows, wild=False)
+    s, e, a = s[::3], e[::3], a[::3]   # the orderly ones
+    e[2, ::C] = np.maximum(s[2, ::C], e[2, ::C] - rng.integers(0, 2, n) * C)   # some outputs end early: violations
+    assert (oracle.evaluate(g, 0, C, s, e, a)[:2, 2] == 0).all()
+    budget = int(0.5 * oracle.evaluate(g, 0, C, s, e, a)[0, 0])
+    pick = np.arange(B) % rows
+    gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, budget, C)
+    ds, de, da = to_dev(s[pick], e[pick], a[pick])
+    if mode == 1:
+        count, merges = moc.moc_search_two_phase(gh, ds, de, da, steps, 0)
+    else:
+        count = moc.moc_search_cuts(gh, ds, de, da, steps)
+    count, gs, ge, ga = count.cpu().numpy(), ds.cpu().numpy(), de.cpu().numpy(), da.cpu().numpy()
+    for r in range(rows):
+        k, ws, we, wa = oracle.search_cuts(g, budget, C, s[r], e[r], a[r], steps, mode=mode)
+        same = (count[r::rows] == k) & (ga[r::rows] == wa).all(1) & (gs[r::rows] == ws).all(1) & (ge[r::rows] == we).all(1)
+        assert same.all(), (r, k, np.flatnonzero(~same)[:4])
+    assert count.max() > 0
+    gh.free()
+
+
 def moves_through_the_peak(g, C, s, e, a):
     """How many (in-edge, consumer copy) moves have a position at the candidate's peak between the
     start of the producer's copy and the consumer's, and a copy of the producer to spare."""
