@@ -534,11 +534,7 @@ __device__ __forceinline__ InOut group_range_maxima(const BaseLds& L, int blocks
   const int bl = lo / kBlk, bh = hi / kBlk;
   const int first = bl + 1, count = bh - first;   // whole blocks between
   InOut r{0, max(L.pre[bl], L.suf[bh + 1])};
-  if (count > 0) {
-    const int level = 31 - __clz(count);
-    const int32_t* row = L.table + table_level(level, blocks);
-    r.in = max(row[first], row[bh - (1 << level)]);
-  }
+  if (count > 0) r.in = blocks_maximum(L, blocks, first, count);
   static_assert(kBlk == kGroup, "a position of the blocks at either end per lane");
   const int xl = bl * kBlk + gl, xh = bh * kBlk + gl;
   const int vl = L.profile[xl], vh = L.profile[xh];

@@ -316,32 +316,39 @@ __device__ __forceinline__ void begin_marks(const BaseLds& L, const MvLayout& la
 // Maxima of the profile over [lo, hi], 0 <= lo <= hi < T, and over all other positions: whole
 // blocks from the tables, the two blocks at the ends position by position.
 struct InOut { int in, out; };
+// The maximum over `count` >= 1 blocks from `first` on.
+__device__ __forceinline__ int blocks_maximum(const BaseLds& L, int blocks, int first, int count) {
+  const int level = 31 - __clz(count);
+  const int32_t* const row = L.table + ((int)__umul24((uint32_t)level, (uint32_t)blocks + 1u) - (1 << level) + 1);   // table_level
+  return max(row[first], row[first + count - (1 << level)]);
+}
+// v where `on` is all ones or all zeros: v or 0, and the other way round (written out: the compiler makes a
+// compare and a select of the second).
+__device__ __forceinline__ int where_off(int on, int v) {
+  int r;
+  asm("v_bfi_b32 %0, %1, 0, %2" : "=v"(r) : "v"(on), "v"(v));
+  return r;
+}
 template <bool OUTSIDE>
 __device__ __forceinline__ InOut range_maxima(const BaseLds& L, int blocks, int lo, int hi) {
-  const int bl = lo / kBlk, bh = hi / kBlk;
+  const int bl = (int)((uint32_t)lo / kBlk), bh = (int)((uint32_t)hi / kBlk);
   const int4* const fl = reinterpret_cast<const int4*>(L.profile + bl * kBlk);
   const int4* const fh = reinterpret_cast<const int4*>(L.profile + bh * kBlk);
   const int4 l0 = fl[0], l1 = fl[1], h0 = fh[0], h1 = fh[1];
   const int first = bl + 1, count = bh - first;   // whole blocks between
   InOut r{0, 0};
-  if (count > 0) {
-    const int level = 31 - __clz(count);
-    const int32_t* row = L.table + table_level(level, blocks);
-    r.in = max(row[first], row[bh - (1 << level)]);
-  }
+  if (count > 0) r.in = blocks_maximum(L, blocks, first, count);
   if constexpr (OUTSIDE) r.out = max(L.pre[bl], L.suf[bh + 1]);
   // bit j: position j of the block lies in the range
   uint32_t ml = 0xFFu << (lo & (kBlk - 1)), mh = 0xFFu >> (kBlk - 1 - (hi & (kBlk - 1)));
   if (bl == bh) { ml &= mh; mh = ml; }
-  auto take = [&](uint32_t m, int j, int v) {
-    const int on = (int)(m << (31 - j)) >> 31;   // all ones or zero
-    r.in = max(r.in, v & on);
-    if constexpr (OUTSIDE) r.out = max(r.out, v & ~on);
+  auto take = [&](uint32_t m, int j, int v, int w) {   // positions j and j + 1
+    const int on_v = __builtin_amdgcn_sbfe((int)m, j, 1), on_w = __builtin_amdgcn_sbfe((int)m, j + 1, 1);   // all ones or zero
+    r.in = max(max(v & on_v, w & on_w), r.in);
+    if constexpr (OUTSIDE) r.out = max(max(where_off(on_v, v), where_off(on_w, w)), r.out);
   };
-  take(ml, 0, l0.x); take(ml, 1, l0.y); take(ml, 2, l0.z); take(ml, 3, l0.w);
-  take(ml, 4, l1.x); take(ml, 5, l1.y); take(ml, 6, l1.z); take(ml, 7, l1.w);
-  take(mh, 0, h0.x); take(mh, 1, h0.y); take(mh, 2, h0.z); take(mh, 3, h0.w);
-  take(mh, 4, h1.x); take(mh, 5, h1.y); take(mh, 6, h1.z); take(mh, 7, h1.w);
+  take(ml, 0, l0.x, l0.y); take(ml, 2, l0.z, l0.w); take(ml, 4, l1.x, l1.y); take(ml, 6, l1.z, l1.w);
+  take(mh, 0, h0.x, h0.y); take(mh, 2, h0.z, h0.w); take(mh, 4, h1.x, h1.y); take(mh, 6, h1.z, h1.w);
   return r;
 }
 

@@ -4,6 +4,7 @@
 #include <algorithm>
 
 #include "moc_cut_moves.h"
+#include "moc_masks.h"
 
 namespace {
 
@@ -92,28 +93,31 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 512 ? 
     for (int k = kAhead * NT + t; k < T; k += NT)
       stage(k, starts[row + k], ends[row + k], a_row[k], g.size_dur[k / C]);
     __syncthreads();
-    // ---- Eq. (5), one lane per edge
-    auto edge = [&](uint32_t pair) {
+    // ---- Eq. (5), one lane per edge; which copies cover what as lane masks, `in` the lanes that have an edge
+    auto edge = [&](uint32_t pair, lanemask in) {
       const uint32_t* const pu = L.packed + (pair & 0xFFFFu);
       const uint32_t* const pv = L.packed + (pair >> 16);
       for (int i = 0; i < C; ++i) {
-        const uint32_t low = pv[i] & 0xFFFFu, s = low & ~kOff;
-        if (low == 0xFFFFu) continue;
-        int covers = 0, who = 0;
-        for (int j = 0; j < C; ++j)
-          if (covers1(pu[j], s)) {
-            ++covers;
-            who = j;
-          }
-        if (covers == 0) {   // the copy has no input: its flip adds or takes away a violation
-          atomicAdd(&delta[(pair >> 16) + i], low & kOff ? 1 : -1);
-          if (!(low & kOff)) {
+        const uint32_t copy = pv[i], s = copy & (0xFFFFu & ~kOff);
+        lanemask some = 0, several = 0;
+        uint32_t who = 0;
+        for (int j = 0; j < C; ++j) {
+          const lanemask c = covers_lanes(pu[j], s);
+          several |= some & c;
+          some |= c;
+          if (j > 0) who = pick(c, (uint32_t)j, who);
+        }
+        const lanemask well = low_ne_k(copy, 0xFFFFu) & in, off = __ballot((copy & kOff) != 0);
+        // a live copy that has its input from one copy of u alone loses it with that one's flip
+        if (lanes(well & some & ~several & ~off)) atomicAdd(&delta[(pair & 0xFFFFu) + who], 1);
+        if (lanes(well & ~some)) {   // the copy has no input: its flip adds or takes away a violation
+          const bool live = !(copy & kOff);
+          atomicAdd(&delta[(pair >> 16) + i], live ? -1 : 1);
+          if (live) {
             ++viol;
             for (int j = 0; j < C; ++j)   // and the copies of u that would serve it take it away
               if ((pu[j] & 0xFFFFu) != 0xFFFFu && covers1(pu[j] & ~kOff, s)) atomicSub(&delta[(pair & 0xFFFFu) + j], 1);
           }
-        } else if (covers == 1 && !(low & kOff)) {
-          atomicAdd(&delta[(pair & 0xFFFFu) + who], 1);
         }
       }
     };
@@ -122,8 +126,11 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 512 ? 
 #pragma unroll
       for (int d = 0; d < 4; ++d) pair[d] = g.edge_pair_c[min(x0 + d * NT + t, g.m - 1)];
 #pragma unroll
-      for (int d = 0; d < 4; ++d)
-        if (x0 + d * NT + t < g.m) edge(pair[d]);
+      for (int d = 0; d < 4; ++d) {
+        const int left = g.m - (x0 + d * NT + wave * kWave);   // the same in all lanes
+        if (left <= 0) break;
+        edge(pair[d], left >= kWave ? ~(lanemask)0 : ((lanemask)1 << left) - 1);
+      }
     }
     // ---- the base's violations and duration; its profile
     for (int v = t; v < g.n; v += NT) {   // Eq. (3): each live copy against the next live copy of its node
@@ -165,16 +172,22 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 512 ? 
         vv += was ? -1 : 1;   // Eq. (2)/(8)
       } else {
         // Eq. (3) among the live copies of v, with and without copy k
-        int with = 0, without = 0, end_with = -1, end_without = -1;
-        for (int j = 0; j < C; ++j) {
-          const uint32_t p = L.packed[v * C + j];
-          if ((p & kOff) && j != i) continue;   // not live (MOC_DEAD carries the bit as well)
-          const int start = j == i ? s : (int)(p & 0xFFFFu), end = (int)(p >> 16);
-          with += end_with > start ? 1 : 0;
-          end_with = end;
-          if (j != i) {
-            without += end_without > start ? 1 : 0;
-            end_without = end;
+        int with = 0, without = 0;
+        if constexpr (CT == 2) {
+          const uint32_t p = L.packed[k ^ 1];
+          if (!(p & kOff)) with = i == 0 ? (e > (int)(p & 0xFFFFu) ? 1 : 0) : ((int)(p >> 16) > s ? 1 : 0);
+        } else {
+          int end_with = -1, end_without = -1;
+          for (int j = 0; j < C; ++j) {
+            const uint32_t p = L.packed[v * C + j];
+            if ((p & kOff) && j != i) continue;   // not live (MOC_DEAD carries the bit as well)
+            const int start = j == i ? s : (int)(p & 0xFFFFu), end = (int)(p >> 16);
+            with += end_with > start ? 1 : 0;
+            end_with = end;
+            if (j != i) {
+              without += end_without > start ? 1 : 0;
+              end_without = end;
+            }
           }
         }
         vv += (was ? without - with : with - without) + delta[k];
