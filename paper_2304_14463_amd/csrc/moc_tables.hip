@@ -25,10 +25,10 @@ namespace {
 // A staged copy that is well formed and not active carries bit 15 on top of its start (positions
 // stay below 2^15: LDS bounds T), which keeps it from covering anything.
 //
-// Bound by the vector ALU and LDS latency.  n = 2000, C = 2, 2048 bases: 475 us with a walk per copy
-// over adjacency lists kept in LDS (one workgroup per compute unit), 112 us now, of which the edges take
-// 20 and the maxima of the copies' intervals 34 (calls on the same bases one behind the other; 118 on
-// bases that are new to the caches).
+// Bound by the vector ALU (69 %) and LDS latency.  n = 2000, C = 2, 2048 bases: 475 us with a walk per copy
+// over adjacency lists kept in LDS (one workgroup per compute unit), 112 us with the edges' conditions in
+// vector registers and the positions at the ends of an interval picked by compares, 102 us now (calls on the
+// same bases one behind the other; 109 on bases that are new to the caches).
 constexpr uint32_t kOff = 0x8000u;
 
 template <int CT, int NT>
@@ -211,8 +211,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 512 ? 
 // The table, the best move, or both.  MODE 1: the cuts that keep the producer's inputs.  Bound by
 // instruction issue and LDS latency: scoring a move is some hundred instructions in a chain of reads.
 // n = 1000, C = 2, 2048 bases, plain cuts, table and best move: 303 us with one workgroup of 16 waves
-// per compute unit (adjacency lists of 32-bit words, prefix and suffix maxima per position), 90 us
-// now (on the same bases again and again; 96 on new ones); 126 us with the mode read at run time, whose
+// per compute unit (adjacency lists of 32-bit words, prefix and suffix maxima per position), 87.5 us
+// now (on the same bases again and again; 94.5 on new ones); 126 us with the mode read at run time, whose
 // registers cost a workgroup per compute unit.
 template <int CT, int NT, bool LISTS, int MODE>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 1024 ? 4 : 6))) void cuts_kernel(GraphView g, int64_t B, const int32_t* __restrict__ starts,
@@ -384,7 +384,8 @@ extern "C" int moc_eval_toggles(const moc_graph* g, int64_t B, const int32_t* st
   const MvLayout lay = mv_layout(v.T, v.n, v.m, v.T, false, g->max_lds);
   if (lay.bytes > g->max_lds) return MOC_EOVERFLOW;
   // Threads as above; the kernel is held to 64 registers where that lets two workgroups of 1024 in.
-  // n = 2000, C = 2 (two fit), 2048 bases: 165 us with 256 threads, 122 with 512, 112 with 1024.
+  // n = 2000, C = 2 (two fit), 2048 bases: 165 us with 256 threads, 122 with 512, 112 with 1024 (102 on the
+  // present kernel).
   const int together = bases_together(g, B, lay.bytes);
   const int nt = together <= 2 ? 1024 : together <= 4 ? 512 : 256;
   const TogglesKernel kern = nt == 1024 ? pick_toggles<1024>(v.C) : nt == 512 ? pick_toggles<512>(v.C) : pick_toggles<256>(v.C);
