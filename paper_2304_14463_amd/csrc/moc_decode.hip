@@ -289,7 +289,7 @@ constexpr int kDropped = 0x40000000;     // an offset beyond any buffer here
 static_assert(sizeof(moc_decode_result) == 24, "stored as six words; peak and duration stay below 2^31");
 
 constexpr int node_slots(int C) { return C <= 2 ? 4 : 2; }   // nodes of a lane (with more copies a lane's positions set the limit)
-constexpr int kRows = 2;                                     // of a slice that stay in registers
+constexpr int kRows = kHeldRows;
 
 struct DfLayout {
   int T_pad;                       // > T + 1, a multiple of 8
@@ -555,7 +555,7 @@ void decode_fixed_kernel(GraphView G, const uint32_t* __restrict__ slices, int64
     if constexpr (!LOOP) {
 #pragma unroll
       for (int k = 0; k < kRows; ++k)
-        more_rows[k] = slices[mine[0].rows + (uint32_t)(max(min(kRows + k, mine[0].count - 1), 0) * kWave + lane_)];
+        more_rows[k] = slices[row_ahead(mine[0].rows, mine[0].count, kRows + k) + (uint32_t)lane_];
       place(0, ahead);
     } else {
       for (int round = 0; round < n; round += kSlots * NT) {

@@ -44,7 +44,7 @@ struct moc_graph {
   GraphView view;    // device pointers
   void* allocs[9];   // device allocations backing `view`, `tickets` and `slices`
   int n_allocs;
-  const uint32_t* slices;   // device: the consumers of every node (out_slices in moc_slices.h); null where that has none
+  const uint32_t* slices;   // device: the consumers of every node (slices_for_kernel in moc_slices.h); null where that has none
   int32_t* place;    // device, [n]: place of every node in the order given to moc_graph_set_order; null before
   // Work counters of the evaluation kernel: kTicketSlots sets of kTicketGroups + 1 counters,
   // each counter on a 64-byte line of its own, all zero between launches (a launch leaves its

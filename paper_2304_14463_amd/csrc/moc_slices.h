@@ -15,6 +15,7 @@
 #include <vector>
 
 constexpr int kSliceLanes = 64, kSliceDegree = 32;
+constexpr int kHeldRows = 2;   // of a slice that the kernel keeps in registers
 constexpr int starts_stride(int C) { return C == 3 ? 4 : C; }   // 16-bit entries of a node's starts in LDS
 
 // word 0: slices, word 1: nodes listed apart; then the word at which each slice begins and the one behind
@@ -50,4 +51,19 @@ inline std::vector<uint32_t> out_slices(int n, int C, const int32_t* out_ptr, co
   }
   w[2 + slices] = (uint32_t)w.size();
   return w;
+}
+
+// The list as the kernel is given it, a row longer: the rows behind the kHeldRows of a wave's first slice are
+// asked for whether there are any or not.  (With the index kept inside the list instead the kernel holds
+// more in scalar registers than there are: 31 of them spilled instead of 21.)
+inline std::vector<uint32_t> slices_for_kernel(int n, int C, const int32_t* out_ptr, const int32_t* out_idx) {
+  std::vector<uint32_t> w = out_slices(n, C, out_ptr, out_idx);
+  if (!w.empty()) w.resize(w.size() + kSliceLanes);
+  return w;
+}
+// Where row r of a slice begins for a wave that reads it so: its last row, the row behind it if it has none;
+// (0, -1): no slice.
+constexpr uint32_t row_ahead(uint32_t rows, int count, int r) {
+  const int row = r < count - 1 ? r : count - 1;
+  return rows + (uint32_t)((row > 0 ? row : 0) * kSliceLanes);
 }

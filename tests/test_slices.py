@@ -10,6 +10,7 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 
 PROGRAM = r"""
 #include <cstdio>
+#include <cstdlib>
 #include "moc_slices.h"
 int main() {   // n C m, then m edges (u, v) in the order of u
   int n, C, m;
@@ -22,7 +23,18 @@ int main() {   // n C m, then m edges (u, v) in the order of u
     idx[q] = v;
   }
   for (int v = 0; v < n; ++v) ptr[v + 1] += ptr[v];
-  for (uint32_t w : out_slices(n, C, ptr.data(), idx.data())) printf("%u\n", w);
+  const std::vector<uint32_t> list = out_slices(n, C, ptr.data(), idx.data());
+  if (getenv("READS")) {   // words the kernel is given; where a wave's rows begin that it reads ahead, 16 waves
+    printf("%zu\n", slices_for_kernel(n, C, ptr.data(), idx.data()).size());
+    for (uint32_t wave = 0; wave < 16; ++wave)
+      for (int r = kHeldRows; r < 2 * kHeldRows; ++r) {
+        const bool any = wave < list[0];
+        const uint32_t at = any ? list[2 + wave] : 0;
+        printf("%u\n", row_ahead(any ? at + kSliceLanes : 0, any ? (int)((list[3 + wave] - at) / kSliceLanes) - 1 : -1, r));
+      }
+    return 0;
+  }
+  for (uint32_t w : list) printf("%u\n", w);
   return 0;
 }
 """
@@ -34,9 +46,10 @@ def program(tmp_path_factory):
     (at / "slices.cpp").write_text(PROGRAM)
     subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, "-o", str(at / "slices"), str(at / "slices.cpp")], check=True)
 
-    def run(n, C, edges):
+    def run(n, C, edges, reads=False):
         text = f"{n} {C} {len(edges)}\n" + "\n".join(f"{u} {v}" for u, v in edges)
-        out = subprocess.run([str(at / "slices")], input=text, check=True, capture_output=True, text=True).stdout
+        env = dict(os.environ, READS="1") if reads else {k: v for k, v in os.environ.items() if k != "READS"}
+        out = subprocess.run([str(at / "slices")], input=text, check=True, capture_output=True, text=True, env=env).stdout
         return np.array(out.split(), dtype=np.int64)
     return run
 
@@ -74,6 +87,21 @@ def test_every_edge_once(program, n, C, degree):
             assert list(uses[:k]) == [int(v) for v in out[node]] and (uses[k:] == n).all()
     assert sorted(seen) == list(range(n))
     assert lengths == sorted(lengths, reverse=True)   # the long ones first
+
+
+@pytest.mark.parametrize("n,C,edges", [
+    *[(n, 2, []) for n in (1, 2, 63, 64)], (65, 1, []), (64, 4, []),          # nodes without consumers only
+    (1, 2, [(0, 0)] * 33), (3, 1, [(0, 1)] * 33 + [(1, 2)] * 40 + [(2, 0)] * 50),   # every node apart
+    (40, 2, [(0, v) for v in range(1, 40)]), (60, 3, [(0, v) for v in range(1, 60)]),   # one apart, the others last
+    (128, 4, [(u, u + 64) for u in range(64)]), (128, 2, [(u, u + 64) for u in range(64)] * 5),
+    (360, 2, [(u, 300 + (u + k) % 60) for u in range(300) for k in range(33)]),
+    (1016, 2, [(u, 956 + (u + k) % 60) for u in range(956) for k in range(33)]),
+    (200, 2, [(u, u + 1) for u in range(199)])])
+def test_rows_read_ahead_lie_in_the_list(program, n, C, edges):
+    """The rows a wave reads whether or not its first slice has them: no word beyond the list, whatever
+    slices there are."""
+    words, *ahead = program(n, C, sorted(edges), reads=True)
+    assert len(ahead) == 32 and min(ahead) >= 0 and max(ahead) + 64 <= words
 
 
 def test_sizes_beyond_16_bits_have_none(program):
