@@ -17,30 +17,14 @@
 #include <algorithm>
 
 #include "moc_masks.h"
-#include "moc_slices.h"
+#include "moc_shapes.h"
 #include "moc_wave.h"
 
 namespace {
 
-constexpr int kNT = 512;
+constexpr int kNT = kDecodeThreads;
 constexpr int kNW = kNT / kWave;
 constexpr uint32_t kNoStart = 0xFFFFu;
-
-struct DcLayout {
-  int T_pad;      // words in each of the two position arrays (>= T + 1, a multiple of 4)
-  int st_words;   // words of the array of starts (16-bit entries; C = 3: 4 per node, so that a node's starts are two words)
-  int bytes;
-};
-
-DcLayout dc_layout(int n, int C) {
-  const int T = n * C;
-  DcLayout l;
-  l.T_pad = (T + 4) & ~3;   // > T, a multiple of 4
-  l.st_words = C == 3 ? 2 * n + 2 : l.T_pad / 2;
-  const int words = 2 * l.T_pad + l.st_words + 2 * kNW + 16;
-  l.bytes = words * 4;
-  return l;
-}
 
 // Both scans below walk the array in rows of 64 consecutive positions, one lane per position
 // (no bank conflicts); wave w owns the rows [w * rows_per_wave, (w + 1) * rows_per_wave).
@@ -288,27 +272,7 @@ constexpr int kRawBuffer = 0x00020000;   // word 3 of a buffer descriptor: plain
 constexpr int kDropped = 0x40000000;     // an offset beyond any buffer here
 static_assert(sizeof(moc_decode_result) == 24, "stored as six words; peak and duration stay below 2^31");
 
-constexpr int node_slots(int C) { return C <= 2 ? 4 : 2; }   // nodes of a lane (with more copies a lane's positions set the limit)
 constexpr int kRows = kHeldRows;
-
-struct DfLayout {
-  int T_pad;                       // > T + 1, a multiple of 8
-  int pos_off, list_off, a_off;    // byte offsets; the starts lie at 0
-  int told_off;                    // what the waves tell each other
-  int bytes;
-};
-
-DfLayout df_layout(int n, int C, int nt) {
-  const int T = n * C;
-  DfLayout l;
-  l.T_pad = (T + 9) & ~7;
-  l.pos_off = (2 * starts_stride(C) * (n + 1) + 15) & ~15;
-  l.list_off = l.pos_off + 2 * l.T_pad;
-  l.a_off = l.list_off + 2 * l.T_pad;
-  l.told_off = l.a_off + 4 * l.T_pad;
-  l.bytes = l.told_off + (nt / kWave) * (16 + 2 * 8);
-  return l;
-}
 
 // Two 16-bit numbers in a register.
 typedef short Halves __attribute__((ext_vector_type(2)));
@@ -425,8 +389,12 @@ void decode_fixed_kernel(GraphView G, const uint32_t* __restrict__ slices, int64
   uint16_t* const pos = reinterpret_cast<uint16_t*>(raw + lay.pos_off);     // copy (+ 1) that starts at a position, 0: none
   uint16_t* const list = reinterpret_cast<uint16_t*>(raw + lay.list_off);   // the sequence, copies (+ 1), 0 behind its end
   int32_t* const a = reinterpret_cast<int32_t*>(raw + lay.a_off);           // memory differences
-  int4* const told = reinterpret_cast<int4*>(raw + lay.told_off);           // per wave: copies computed, positions taken, duration, what is wrong
-  int2* const sums = reinterpret_cast<int2*>(told + NW);                    // per round and wave: sum and highest running sum
+  int32_t* const told = reinterpret_cast<int32_t*>(raw + lay.told_off);     // of all waves: copies computed beyond the positions taken, duration, is it not valid
+  int32_t* const told_taken = told + (LOOP ? 4 : 4 + 2 * NW);               // per wave: positions taken
+  // Per round and wave: sum and highest running sum.  LOOP: nobody asks for the starts any more when they are written,
+  // and the wave that reads them is the one that writes these nodes' starts again.
+  const auto sums = [&](int r, int w) { return reinterpret_cast<int2*>(LOOP ? raw + r * NT * 2 * SS : raw + lay.told_off + 16) + w; };
+  static_assert(NW * 8 <= kWave * 2 * SS || !LOOP, "sums of a round in the starts of 64 nodes");
   const int tid = threadIdx.x;
   const int T = G.T, n = G.n;
 
@@ -519,8 +487,9 @@ void decode_fixed_kernel(GraphView G, const uint32_t* __restrict__ slices, int64
     int32_t* const seq_row = out_seq ? out_seq + cand * T : nullptr;
 
     // ---- 1. who is computed where.  Predicates are lane masks; those of lanes past the last node are 0.
-    int n_active = 0;                      // copies computed
-    lanemask outside = 0, missing = 0;     // a start outside [0, T), Eq. (8); a node that is not computed
+    if (t_ == 0) *reinterpret_cast<int4*>(told) = make_int4(0, 0, 0, 0);
+    int n_active = 0;           // copies computed, also where the start lies outside [0, T), Eq. (8)
+    lanemask missing = 0;       // a node that is not computed
     auto lanes_in = [&](int round, int u) -> lanemask {   // the lanes that have a node in this slot
       const int left = n - (round + u * NT + wave_ * kWave);
       return left <= 0 ? 0 : left >= kWave ? ~(lanemask)0 : ((lanemask)1 << left) - 1;
@@ -541,7 +510,6 @@ void decode_fixed_kernel(GraphView G, const uint32_t* __restrict__ slices, int64
           const lanemask on = r.active(u, i) & in, well = u_lt_k(at, (uint32_t)T), ok = on & well;
           n_active += count(on);
           any |= on;
-          outside |= on & ~well;
           where[i] = pick(ok, at + 1u);
           lds_write16_lanes<0>(ok, (uint32_t)lay.pos_off + 2u * at, name + i);
         }
@@ -666,13 +634,17 @@ void decode_fixed_kernel(GraphView G, const uint32_t* __restrict__ slices, int64
     }
     if constexpr (!LOOP) request(cand + gridDim.x < B ? cand + gridDim.x : cand, 0, t_, ahead);   // (the last candidate asks for itself again)
     dur = scan_sum(dur);
-    if (lane_ == kWave - 1)
-      told[wave_] = make_int4(n_active, upto, dur, (outside ? 1 : 0) | (missing ? 2 : 0) | (unserved ? 4 : 0));
+    if (lane_ == kWave - 1) {
+      told_taken[wave_] = upto;
+      raise(&told[0], n_active - ((upto & 0xFFFF) + (upto >> 16)));
+      raise(&told[1], dur);
+      if (missing | unserved) told[2] = 1;
+    }
     __syncthreads();
 
     // ---- 3. what the waves know together: lanes 0 .. NW - 1 hold one wave each
-    int4 all = make_int4(0, 0, 0, 0);
-    if (lane_ < NW) all = told[lane_];
+    const int4 all = *reinterpret_cast<const int4*>(told);
+    const int took = lane_ < NW ? told_taken[lane_] : 0;
     const auto scan_row = [](int x) {
       x += lane_shift<0x111, 0xF>(x);
       x += lane_shift<0x112, 0xF>(x);
@@ -680,15 +652,14 @@ void decode_fixed_kernel(GraphView G, const uint32_t* __restrict__ slices, int64
       x += lane_shift<0x118, 0xF>(x);
       return x;
     };
-    const int pairs = scan_row(all.y);
-    const int total_active = __builtin_amdgcn_readlane(scan_row(all.x), NW - 1);
+    const int pairs = scan_row(took);
     const int total_taken = __builtin_amdgcn_readlane(pairs, NW - 1);
-    const int total_dur = __builtin_amdgcn_readlane(scan_row(all.z), NW - 1);
+    const int total_dur = __builtin_amdgcn_readfirstlane(all.y);
     const int taken_before = NW > 1 && wave_ > 0 ? __builtin_amdgcn_readlane(pairs, max(wave_ - 1, 0)) : 0;
     const int length = (total_taken & 0xFFFF) + (total_taken >> 16);
-    // a start outside the domain, or two copies on one position: no order
-    const bool decodable = __ballot(all.w & 1) == 0 && total_active == length;
-    const bool valid = decodable && __ballot(all.w & 6) == 0;
+    // a start outside the domain, or two copies on one position: more copies than positions, no order
+    const bool decodable = __builtin_amdgcn_readfirstlane(all.x) == 0;
+    const bool valid = decodable && __builtin_amdgcn_readfirstlane(all.z) == 0;
     // the names in order
     if (seq_row && decodable) {
 #pragma unroll
@@ -727,7 +698,7 @@ void decode_fixed_kernel(GraphView G, const uint32_t* __restrict__ slices, int64
         S += hi.w; P = max(P, S);
       }
       combine_segments(S, P);
-      if (lane_ == kWave - 1) sums[r * NW + wave_] = make_int2(S, P);   // the lane that holds the wave's
+      if (lane_ == kWave - 1) *sums(r, wave_) = make_int2(S, P);   // the lane that holds the wave's
     }
     wait_for_lds_writes();
     __syncthreads();
@@ -768,7 +739,7 @@ void decode_fixed_kernel(GraphView G, const uint32_t* __restrict__ slices, int64
     // No barrier behind this: what is read here is written again behind the next candidate's second.
     int2 segment = make_int2(0, 0);
     if (wave_ == 0) {
-      if (lane_ < R * NW) segment = sums[lane_];
+      if (lane_ < R * NW) segment = *sums(lane_ / NW, lane_ % NW);
       combine_segments(segment.x, segment.y);
     }
     const auto result = __builtin_amdgcn_make_buffer_rsrc(out + cand, 0, (int)sizeof(moc_decode_result), kRawBuffer);
@@ -806,8 +777,7 @@ extern "C" int moc_decode_batch(const moc_graph* g, int64_t B, const int32_t* st
   if (dev != g->device) return MOC_EDEVICE;
   const GraphView& v = g->view;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  const DcLayout any = dc_layout(v.n, v.C);
-  if (any.bytes > g->max_lds) return MOC_EOVERFLOW;
+  if (!decode_fits(v.n, v.C, g->max_lds)) return MOC_EOVERFLOW;
   const auto resident = [&](const void* kern, int nt, int bytes, bool no_static_lds, unsigned* grid) -> int {
     int per_cu = 0;
     if (const int rc = moc_kernel_occupancy(g, kern, nt, bytes, no_static_lds, &per_cu)) return rc;
@@ -815,33 +785,24 @@ extern "C" int moc_decode_batch(const moc_graph* g, int64_t B, const int32_t* st
     return MOC_OK;
   };
   if (g->slices) {   // C <= 4
-    // As few threads as hold the candidate: a workgroup's waves meet at three barriers per candidate, and
-    // lanes without a node still take their part of every pass.  By 64 / 128 / 256 / 512 / 1024 threads
-    // (before: 512 for every size): n = 100, C = 2, 16384 candidates 17.6 / 24.3 / 39.8 / 71.4 / 137 us
-    // (before 72.1); n = 442, 4096 candidates - / 14.5 / 17.7 / 26.5 / 46.2 (29.8); n = 1000, 4096
-    // candidates - / - / 24.9 / 31.0 / 49.6 (44.1).  With batches that leave compute units idle (n = 442, 16
-    // candidates; n = 2000, 128) every choice takes as long as the launch.  n = 2500, 2000 candidates: 1024
-    // threads 35.0 (44.1).
-    int nt = 64;
-    const auto holds = [&](int t) { return v.n <= node_slots(v.C) * t && df_layout(v.n, v.C, t).T_pad <= 8 * t; };
-    while (nt < 1024 && !holds(nt)) nt *= 2;
-    const bool loop = !holds(nt);
-    const DfLayout lay = df_layout(v.n, v.C, nt);
-    if (lay.bytes <= g->max_lds && lay.T_pad <= 16 * 1024) {
-      DfKernel kern = nullptr;
-      switch (v.C) {
-        case 1: kern = pick_fixed<1>(nt, loop); break;
-        case 2: kern = pick_fixed<2>(nt, loop); break;
-        case 3: kern = pick_fixed<3>(nt, loop); break;
-        default: kern = pick_fixed<4>(nt, loop); break;
-      }
-      unsigned grid = 0;
-      if (const int rc = resident(reinterpret_cast<const void*>(kern), nt, lay.bytes, true, &grid)) return rc;
-      hipLaunchKernelGGL(kern, dim3(grid), dim3(nt), lay.bytes, stream, v, g->slices, B, starts, active, out, out_seq, lay);
-      MOC_HIP(hipGetLastError());
-      return MOC_OK;
+    const DecodeShape shape = decode_shape(v.n, v.C);
+    const int nt = shape.nt;
+    const DfLayout lay = shape.lay;
+    if (lay.bytes > g->max_lds) return MOC_EOVERFLOW;   // (fits wherever decode_fits holds)
+    DfKernel kern = nullptr;
+    switch (v.C) {
+      case 1: kern = pick_fixed<1>(nt, shape.loop); break;
+      case 2: kern = pick_fixed<2>(nt, shape.loop); break;
+      case 3: kern = pick_fixed<3>(nt, shape.loop); break;
+      default: kern = pick_fixed<4>(nt, shape.loop); break;
     }
+    unsigned grid = 0;
+    if (const int rc = resident(reinterpret_cast<const void*>(kern), nt, lay.bytes, true, &grid)) return rc;
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(nt), lay.bytes, stream, v, g->slices, B, starts, active, out, out_seq, lay);
+    MOC_HIP(hipGetLastError());
+    return MOC_OK;
   }
+  const DcLayout any = dc_layout(v.n, v.C);
   unsigned grid = 0;
   if (const int rc = resident(reinterpret_cast<const void*>(decode_kernel), kNT, any.bytes, false, &grid)) return rc;
   hipLaunchKernelGGL(decode_kernel, dim3(grid), dim3(kNT), any.bytes, stream, v, B, starts, active, out, out_seq, any);

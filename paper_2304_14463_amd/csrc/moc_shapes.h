@@ -6,6 +6,8 @@
 
 #include <algorithm>
 
+#include "moc_slices.h"
+
 // ------------------------------------------------------------------ moc_eval_batch_staged
 constexpr int kStagedThreads = 512;
 
@@ -16,6 +18,72 @@ constexpr int staged_nodes_per_lane(int n, int C) {
   int u = 1;
   while (u * kStagedThreads < n) u *= 2;
   return C <= 4 && u <= 8 && u * C <= 16 ? u : 0;
+}
+
+// ------------------------------------------------------------------ moc_decode_batch
+// The largest sizes the call takes: as many words as its first kernels kept in LDS, 2.5 per copy (C = 3:
+// starts in four 16-bit entries per node).
+inline bool decode_fits(int n, int C, int max_lds) {
+  const int T = n * C, T_pad = (T + 4) & ~3, starts = C == 3 ? 2 * n + 2 : T_pad / 2;
+  return 4 * (2 * T_pad + starts + 32) <= max_lds;
+}
+
+// The kernel for any C.
+constexpr int kDecodeThreads = 512;
+struct DcLayout {
+  int T_pad;   // words in each of the two position arrays (>= T + 1, a multiple of 4); half as many hold the starts
+  int bytes;
+};
+inline DcLayout dc_layout(int n, int C) {
+  DcLayout l;
+  l.T_pad = (n * C + 4) & ~3;
+  l.bytes = 4 * (2 * l.T_pad + l.T_pad / 2 + 2 * (kDecodeThreads / 64) + 16);
+  return l;
+}
+
+// The kernel for C <= 4.
+constexpr int node_slots(int C) { return C <= 2 ? 4 : 2; }   // nodes of a lane (with more copies a lane's positions set the limit)
+struct DfLayout {
+  int T_pad;                       // > T + 1, a multiple of 8
+  int pos_off, list_off, a_off;    // byte offsets; the starts lie at 0
+  int told_off;                    // what the waves tell each other
+  int bytes;
+};
+// loop: the running sums have no place of their own but lie in the entries of starts that the first wave writes,
+// so that every size of decode_fits has this kernel (the other takes twice as long: n = 8170, C = 2, 1000
+// candidates 211 us).
+inline DfLayout df_layout(int n, int C, int nt, bool loop) {
+  const int T = n * C, waves = nt / 64;
+  DfLayout l;
+  l.T_pad = (T + 9) & ~7;
+  l.pos_off = (2 * starts_stride(C) * (n + 1) + 15) & ~15;
+  l.list_off = l.pos_off + 2 * l.T_pad;
+  l.a_off = l.list_off + 2 * l.T_pad;
+  l.told_off = l.a_off + 4 * l.T_pad;
+  l.bytes = l.told_off + 16 + waves * (loop ? 4 : 4 + 8);
+  return l;
+}
+
+struct DecodeShape {
+  int nt;
+  bool loop;   // more nodes or positions than a workgroup of 1024 takes at once: in rounds
+  DfLayout lay;
+};
+// As few threads as hold the candidate: a workgroup's waves meet at three barriers per candidate, and
+// lanes without a node still take their part of every pass.  By 64 / 128 / 256 / 512 / 1024 threads
+// (before: 512 for every size): n = 100, C = 2, 16384 candidates 17.6 / 24.3 / 39.8 / 71.4 / 137 us
+// (before 72.1); n = 442, 4096 candidates - / 14.5 / 17.7 / 26.5 / 46.2 (29.8); n = 1000, 4096
+// candidates - / - / 24.9 / 31.0 / 49.6 (44.1).  With batches that leave compute units idle (n = 442, 16
+// candidates; n = 2000, 128) every choice takes as long as the launch.  n = 2500, 2000 candidates: 1024
+// threads 35.0 (44.1).
+// In rounds: n = 4500, C = 2, 2000 candidates 80 us (127); n = 7000, 1000 candidates 64 (95); n = 2500, C = 3,
+// 2000 candidates 61 (79); n = 16340, C = 1, 1000 candidates 106 (157).
+inline DecodeShape decode_shape(int n, int C) {
+  int nt = 64;
+  const auto holds = [&](int t) { return n <= node_slots(C) * t && df_layout(n, C, t, false).T_pad <= 8 * t; };
+  while (nt < 1024 && !holds(nt)) nt *= 2;
+  const bool loop = !holds(nt);
+  return DecodeShape{nt, loop, df_layout(n, C, nt, loop)};
 }
 
 // ------------------------------------------------------------------ a base in LDS (moc_moves.h)

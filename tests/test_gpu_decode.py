@@ -178,6 +178,38 @@ def test_decode_every_workgroup_size(moc, n, C):
     gh.free()
 
 
+def rows_of_every_kind(rng, g, C):
+    """Eleven rows: decodable ones and ones without an order, which share a start or start outside the domain."""
+    T = g.n * C
+    s, a = (np.concatenate(x) for x in zip(orderly_candidates(rng, g, C, 4), dense_candidates(rng, g, C, 2)))
+    s, a = s[[0, 0, 1, 0, 4, 2, 5, 4, 3, 0, 0]], a[[0, 0, 1, 0, 4, 2, 5, 4, 3, 0, 0]]
+    on = [np.flatnonzero(row) for row in a]
+    for row, at in ((1, T), (3, -1), (9, T + 5)):
+        s[row, rng.choice(on[row])] = at
+    for row in (4, 10):
+        first, second = rng.choice(on[row], 2, replace=False) if on[row].size > 1 else (0, 0)
+        s[row, first] = s[row, second] if first != second else -1
+    s[7, on[7]] = s[7, on[7][0]]     # every copy at one position
+    return s, a
+
+
+# the sizes at which LDS is short; rows of every kind follow each other in a workgroup
+@pytest.mark.parametrize("n,C", [(16324, 1), (16360, 1), (16367, 1), (8163, 2), (8183, 2), (5103, 3), (5115, 3)])
+def test_decode_largest_sizes(moc, n, C):
+    from paper_2304_14463_amd.inputs import graph_from_edges
+    rng = np.random.default_rng(n)
+    edges = sorted({(int(u), v) for v in range(1, n) for u in rng.integers(max(0, v - 20), v, size=2)})
+    g = graph_from_edges(n, edges, rng.integers(0, 50, n), rng.integers(1, 9, n))
+    gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, 1, C)
+    s, a = rows_of_every_kind(rng, g, C)
+    want, want_seq = oracle.decode(g, C, s, a)
+    assert set(want[:, 0]) == {-1, 0, 1}
+    pick = np.arange(700) % 11   # more rows than the chip holds workgroups of this size
+    got, seq = gpu_decode(moc, gh, s[pick], a[pick])
+    assert_same(got, seq, want[pick], want_seq[pick])
+    gh.free()
+
+
 def test_decode_graph_without_edges(moc):
     from paper_2304_14463_amd.inputs import graph_from_edges
     rng = np.random.default_rng(5)

@@ -18,6 +18,15 @@ int main(int argc, char** argv) {
   if (argc == 2 && !strcmp(argv[1], "staged"))
     for (int C = 1; C <= 8; ++C)
       for (int n = 1; n * C <= 19455; ++n) printf("%d %d %d\n", C, n, staged_nodes_per_lane(n, C));
+  if (argc == 2 && !strcmp(argv[1], "decode"))
+    for (int C = 1; C <= 8; ++C)
+      for (int n = 1; n * C <= 19455; ++n) {
+        const DecodeShape s = decode_shape(n, C);
+        const int rounds = s.loop ? 2 : 1;   // the kernel's
+        const bool covered = C <= 4 && s.lay.bytes <= kMaxLds && s.lay.T_pad <= 8 * s.nt * rounds && (s.loop || n <= node_slots(C) * s.nt);
+        const int any = dc_layout(n, C).bytes;
+        printf("%d %d %d %d %d %d\n", C, n, decode_fits(n, C, kMaxLds), covered, s.nt, any);
+      }
   if (argc == 5 && !strcmp(argv[1], "descend")) {   // C, edges per node, candidates
     const int C = atoi(argv[2]);
     const int64_t B = atoll(argv[4]);
@@ -70,3 +79,17 @@ def test_descent_keeps_the_adjacency_lists(shapes, C, edges, B):
     assert np.isin(cap, (256, 512, 1024, 2048)).all()
     lost = n[lists < lists_with_512]
     assert lost.size == 0, f"n = {lost.min()} .. {lost.max()}"
+
+
+def test_decode_kernels_hold_every_size_the_call_takes(shapes):
+    """C <= 4: the kernel with one lane per node at every size, with as few threads as hold the candidate;
+    more copies: the one for any C.  The largest sizes are those of the call's first kernels."""
+    C, n, fits, covered, nt, any_bytes = shapes("decode").T
+    fits, few = fits == 1, C <= 4
+    assert (covered[fits & few] == 1).all(), n[fits & few & (covered == 0)]
+    assert (any_bytes[fits & ~few] <= 160 * 1024).all()
+    assert [int(n[fits & (C == c)].max()) for c in range(1, 9)] == [16367, 8183, 5115, 4091, 3273, 2727, 2338, 2045]
+    for c, per_lane in ((1, 4), (2, 4), (3, 2), (4, 2)):
+        at = C == c
+        least = np.ceil(np.maximum(n[at] / per_lane, (c * n[at] + 2) / 8))
+        assert (nt[at] == np.clip(2 ** np.ceil(np.log2(np.maximum(least, 64))), 64, 1024)).all()
