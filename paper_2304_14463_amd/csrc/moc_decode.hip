@@ -235,26 +235,28 @@ void decode_kernel(GraphView G, int64_t B, const int32_t* __restrict__ starts, c
   }
 }
 
-// ---- the same for C <= 4, in three passes with a barrier behind each.
+// ---- the same for C <= 4, in four passes with a barrier behind each.
 //
 // 1. One lane per node: its starts go to an entry of the node (16 bits each, counted from 1, 0: not
 //    computed) and the copy's name to the position it starts at, without atomics: two copies on one
 //    position show as fewer occupied positions than active copies (Eq. (6)).
-// 2. The occupied positions are counted, eight to a thread in one 16-byte read.  One lane per node walks
-//    the node's consumers (moc_slices.h) and keeps, for every computation of the node in order, the last
-//    start that falls between it and the next one: that is how long its output is held, known to one
-//    lane, without atomics or an array to meet in.  Two starts at a time in 16-bit halves of a register.
-//    Memory rises at the computation and falls behind the last use (Eq. (4) by events).
-// 3. The running sum's maximum; the names in order of position, from where the sequence is written out
-//    in 16-byte stores.
+// 2. The occupied positions are counted, eight to a thread in one 16-byte read.  Behind this every wave knows
+//    whether there is an order; a row without one is left here.
+// 3. The names in order of position.  One lane per node walks the node's consumers (moc_slices.h) and keeps,
+//    for every computation of the node in order, the last start that falls between it and the next one: that
+//    is how long its output is held, known to one lane, without atomics or an array to meet in.  Two starts
+//    at a time in 16-bit halves of a register.  Memory rises at the computation and falls behind the last
+//    use (Eq. (4) by events).
+// 4. The running sum's maximum.  Then the sequence is written out in 16-byte stores.
 //
-// Bound by HBM (295 MB read and written, 61 us at the rate of a copy), with the vector ALU at 60 % and LDS
-// at 45 % beside it.  n = 2000, C = 2, 8192 candidates: 124 us with one lane per edge, the last use of a
-// computation collected by atomic maxima (five passes, 824 vector and 114 LDS instructions per wave and
-// candidate); 82 us now (480 and 64).  Without pass 2's walk the kernel takes 61 us, without storing the
-// sequence 67, without anything else it does as long as with it.
-// A row without an order costs as much as one with (it was left after the first pass before: 8192 such rows
-// 53 us, now 81): searches decode what they accept.
+// Bound by HBM (295 MB read and written, 61 us at the rate of a copy), with the vector ALU and LDS about half
+// busy beside it.  n = 2000, C = 2, 8192 candidates: 124 us with one lane per edge, the last use of a
+// computation collected by atomic maxima (five passes), 81 us now.  Without the walk the kernel takes 61 us,
+// without storing the sequence 67, without anything else it does as long as with it.
+// Rows without an order, as many: 70 us (59 where each of them was found by an atomic on its start, at a cost
+// to the others; 81 with passes 2 and 3 in one, which is no quicker for the others); n = 1000, 4096 rows 18 us
+// (18; 25), n = 7000, 1000 rows 30 (36; 63), n = 3000, C = 1, 4096 rows 34 (23; 49): a row's loads are asked for
+// when the one before it is decided, and to ask earlier takes registers that the walk needs.
 
 // The copies of a node as they lie in a candidate's row: aligned as their elements are, no more
 // (the global loads of this chip take several words at any word boundary).
@@ -389,7 +391,7 @@ void decode_fixed_kernel(GraphView G, const uint32_t* __restrict__ slices, int64
   uint16_t* const pos = reinterpret_cast<uint16_t*>(raw + lay.pos_off);     // copy (+ 1) that starts at a position, 0: none
   uint16_t* const list = reinterpret_cast<uint16_t*>(raw + lay.list_off);   // the sequence, copies (+ 1), 0 behind its end
   int32_t* const a = reinterpret_cast<int32_t*>(raw + lay.a_off);           // memory differences
-  int32_t* const told = reinterpret_cast<int32_t*>(raw + lay.told_off);     // of all waves: copies computed beyond the positions taken, duration, is it not valid
+  int32_t* const told = reinterpret_cast<int32_t*>(raw + lay.told_off);     // by all waves: [0] copies computed beyond the positions taken, all candidates together; [2] is it not valid, [3] duration
   int32_t* const told_taken = told + (LOOP ? 4 : 4 + 2 * NW);               // per wave: positions taken
   // Per round and wave: sum and highest running sum.  LOOP: nobody asks for the starts any more when they are written,
   // and the wave that reads them is the one that writes these nodes' starts again.
@@ -406,6 +408,7 @@ void decode_fixed_kernel(GraphView G, const uint32_t* __restrict__ slices, int64
     *reinterpret_cast<int4*>(a + x + 4) = zero;
   }
   if (tid < SS) reinterpret_cast<uint16_t*>(lds)[n * SS + tid] = 0;   // node n is never computed
+  if (tid < 4) told[tid] = 0;
 
   // The loads of a round of nodes are issued without conditions (lanes past the last node read
   // it again and drop what they get) and all of them before the first is looked at; a node's flags
@@ -477,6 +480,7 @@ void decode_fixed_kernel(GraphView G, const uint32_t* __restrict__ slices, int64
   __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
   __syncthreads();
 
+  int beyond_before = 0;
   for (int64_t cand = blockIdx.x; cand < B; cand += gridDim.x) {
     // What derives from the thread index (row bounds, LDS addresses) is formed again for every
     // candidate: kept across candidates it takes registers that the next candidate's copies need.
@@ -487,7 +491,6 @@ void decode_fixed_kernel(GraphView G, const uint32_t* __restrict__ slices, int64
     int32_t* const seq_row = out_seq ? out_seq + cand * T : nullptr;
 
     // ---- 1. who is computed where.  Predicates are lane masks; those of lanes past the last node are 0.
-    if (t_ == 0) *reinterpret_cast<int4*>(told) = make_int4(0, 0, 0, 0);
     int n_active = 0;           // copies computed, also where the start lies outside [0, T), Eq. (8)
     lanemask missing = 0;       // a node that is not computed
     auto lanes_in = [&](int round, int u) -> lanemask {   // the lanes that have a node in this slot
@@ -552,99 +555,9 @@ void decode_fixed_kernel(GraphView G, const uint32_t* __restrict__ slices, int64
       taken += (int)((c & 0xFFFFu) + (c >> 16)) << (16 * r);
     }
     const int upto = scan_sum(taken);
-    // ---- and how long every output is held
-    lanemask unserved = 0;
-    int dur = 0;   // Eq. (1), this lane's nodes
-    auto hold = [&](const Uses<CT>& uses, int size, int w) {
-#pragma unroll
-      for (int i = 0; i < CT; ++i)
-        if (lanes(u_lt_k(uses.at[i], kNever))) {   // computed
-          raise(&a[uses.at[i]], size);
-          lower(&a[upper_half(uses.last[i]) + 1u], size);
-          dur += w;
-        }
+    const auto ask_for_next = [&] {   // (the last candidate asks for itself again)
+      if constexpr (!LOOP) request(cand + gridDim.x < B ? cand + gridDim.x : cand, 0, t_, ahead);
     };
-    auto two_uses = [&](Uses<CT>& uses, uint32_t row) {
-      uint32_t lo, hi;   // taken apart here: moved out of the loop over the candidates the halves would take registers of their own
-      asm volatile("v_and_b32 %0, 0xffff, %1" : "=v"(lo) : "v"(row));
-      asm volatile("v_lshrrev_b32 %0, 16, %1" : "=v"(hi) : "v"(row));
-      const NodeStarts<CT> x = read_starts<CT>(lo), y = read_starts<CT>(hi);
-      uses.use(x);
-      uses.use(y);
-    };
-    auto walk = [&](const Slice& s, const uint32_t* first_rows, const uint32_t* next_rows) {   // the first kRows, the kRows behind them, or null
-      Uses<CT> uses;
-      uses.begin(read_starts<CT>(s.node * (2u * SS)));
-      int count = s.count, r = 0;
-      asm volatile("" : "+s"(count));   // (compared here, not kept as a condition across the candidates)
-      if (first_rows) {
-#pragma unroll
-        for (int k = 0; k < kRows; ++k)
-          if (k < count) two_uses(uses, first_rows[k]);
-        r = kRows;
-      }
-      if (next_rows) {
-#pragma unroll
-        for (int k = 0; k < kRows; ++k)
-          if (kRows + k < count) two_uses(uses, next_rows[k]);
-        r = 2 * kRows;
-      }
-      for (; r < count; r += kRows) {
-        uint32_t row[kRows];
-#pragma unroll
-        for (int k = 0; k < kRows; ++k) row[k] = slices[s.rows + (uint32_t)(min(r + k, count - 1) * kWave + lane_)];
-#pragma unroll
-        for (int k = 0; k < kRows; ++k)
-          if (k == 0 || r + k < count) two_uses(uses, row[k]);
-      }
-      unserved |= u_lt(lower_half(uses.least), uses.at[0]);
-      hold(uses, s.size, s.dur);
-    };
-    if constexpr (!LOOP) {
-#pragma unroll
-      for (int u = 0; u < kSlots; ++u)
-        if (mine[u].count >= 0) walk(mine[u], my_rows[u], u == 0 ? more_rows : nullptr);
-    } else {
-      for (int u = 0; u * NW < n_slices; ++u) {
-        const int i = slice_of(u, wave_);
-        if (i < n_slices) walk(open_slice(i, lane_), nullptr, nullptr);
-      }
-    }
-    for (int i = wave_; i < n_apart; i += NW) {   // a node with very many consumers: all lanes of a wave
-      const int v = (int)slices[3 + n_slices + i];
-      Uses<CT> uses;
-      uses.begin(read_starts<CT>((uint32_t)v * (2u * SS)));
-      const int y1 = G.out_ptr[v + 1];
-      for (int y = G.out_ptr[v]; y < y1; y += kWave)
-        uses.use(read_starts<CT>((uint32_t)(y + lane_ < y1 ? G.out_idx[y + lane_] : n) * (2u * SS)));
-      const int first = kNoUse - last_lane(scan_max(kNoUse - (int)lower_half(uses.least)));
-      unserved |= (uint32_t)first < (uint32_t)__builtin_amdgcn_readfirstlane((int)uses.at[0]) ? 1 : 0;
-#pragma unroll
-      for (int k = 0; k < CT; ++k) uses.last[k] = (uint32_t)last_lane(scan_max((int)upper_half(uses.last[k])));
-      if (lane_ == 0) {
-        const int2 sd = G.size_dur[v];
-#pragma unroll
-        for (int k = 0; k < CT; ++k)
-          if (uses.at[k] < kNever) {
-            raise(&a[uses.at[k]], sd.x);
-            lower(&a[uses.last[k] + 1u], sd.x);
-            dur += sd.y;
-          }
-      }
-    }
-    if constexpr (!LOOP) request(cand + gridDim.x < B ? cand + gridDim.x : cand, 0, t_, ahead);   // (the last candidate asks for itself again)
-    dur = scan_sum(dur);
-    if (lane_ == kWave - 1) {
-      told_taken[wave_] = upto;
-      raise(&told[0], n_active - ((upto & 0xFFFF) + (upto >> 16)));
-      raise(&told[1], dur);
-      if (missing | unserved) told[2] = 1;
-    }
-    __syncthreads();
-
-    // ---- 3. what the waves know together: lanes 0 .. NW - 1 hold one wave each
-    const int4 all = *reinterpret_cast<const int4*>(told);
-    const int took = lane_ < NW ? told_taken[lane_] : 0;
     const auto scan_row = [](int x) {
       x += lane_shift<0x111, 0xF>(x);
       x += lane_shift<0x112, 0xF>(x);
@@ -652,56 +565,153 @@ void decode_fixed_kernel(GraphView G, const uint32_t* __restrict__ slices, int64
       x += lane_shift<0x118, 0xF>(x);
       return x;
     };
-    const int pairs = scan_row(took);
+    if (lane_ == kWave - 1) {
+      told_taken[wave_] = upto;
+      raise(&told[0], n_active - ((upto & 0xFFFF) + (upto >> 16)));
+    }
+    __syncthreads();
+
+    // ---- is there an order: lanes 0 .. NW - 1 hold one wave each
+    const int beyond = __builtin_amdgcn_readfirstlane(told[0]);
+    const int pairs = scan_row(lane_ < NW ? told_taken[lane_] : 0);
     const int total_taken = __builtin_amdgcn_readlane(pairs, NW - 1);
-    const int total_dur = __builtin_amdgcn_readfirstlane(all.y);
     const int taken_before = NW > 1 && wave_ > 0 ? __builtin_amdgcn_readlane(pairs, max(wave_ - 1, 0)) : 0;
     const int length = (total_taken & 0xFFFF) + (total_taken >> 16);
     // a start outside the domain, or two copies on one position: more copies than positions, no order
-    const bool decodable = __builtin_amdgcn_readfirstlane(all.x) == 0;
-    const bool valid = decodable && __builtin_amdgcn_readfirstlane(all.z) == 0;
-    // the names in order
-    if (seq_row && decodable) {
+    const bool decodable = beyond == beyond_before;
+    beyond_before = beyond;
+    if (decodable) {
+      // ---- 3. the names in order
+      if (seq_row) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+          const int before = (taken_before + upto - taken) >> (16 * r) & 0xFFFF;
+          uint32_t at = (uint32_t)(before + (r ? total_taken & 0xFFFF : 0));
+          const auto put_two = [&](uint32_t w) {
+            const lanemask lo = low_ne_k(w, 0u), hi = high_ne_k(w, 0u);
+            lds_write16_lanes<0>(lo, (uint32_t)lay.list_off + 2u * at, w);
+            at = add_lanes(lo, at);
+            lds_write16_lanes<1>(hi, (uint32_t)lay.list_off + 2u * at, w);
+            at = add_lanes(hi, at);
+          };
+          put_two((uint32_t)who[r].x);
+          put_two((uint32_t)who[r].y);
+          put_two((uint32_t)who[r].z);
+          put_two((uint32_t)who[r].w);
+        }
+      }
+      // ---- and how long every output is held
+      lanemask unserved = 0;
+      int dur = 0;   // Eq. (1), this lane's nodes
+      auto hold = [&](const Uses<CT>& uses, int size, int w) {
+#pragma unroll
+        for (int i = 0; i < CT; ++i)
+          if (lanes(u_lt_k(uses.at[i], kNever))) {   // computed
+            raise(&a[uses.at[i]], size);
+            lower(&a[upper_half(uses.last[i]) + 1u], size);
+            dur += w;
+          }
+      };
+      auto two_uses = [&](Uses<CT>& uses, uint32_t row) {
+        uint32_t lo, hi;   // taken apart here: moved out of the loop over the candidates the halves would take registers of their own
+        asm volatile("v_and_b32 %0, 0xffff, %1" : "=v"(lo) : "v"(row));
+        asm volatile("v_lshrrev_b32 %0, 16, %1" : "=v"(hi) : "v"(row));
+        const NodeStarts<CT> x = read_starts<CT>(lo), y = read_starts<CT>(hi);
+        uses.use(x);
+        uses.use(y);
+      };
+      auto walk = [&](const Slice& s, const uint32_t* first_rows, const uint32_t* next_rows) {   // the first kRows, the kRows behind them, or null
+        Uses<CT> uses;
+        uses.begin(read_starts<CT>(s.node * (2u * SS)));
+        int count = s.count, r = 0;
+        asm volatile("" : "+s"(count));   // (compared here, not kept as a condition across the candidates)
+        if (first_rows) {
+#pragma unroll
+          for (int k = 0; k < kRows; ++k)
+            if (k < count) two_uses(uses, first_rows[k]);
+          r = kRows;
+        }
+        if (next_rows) {
+#pragma unroll
+          for (int k = 0; k < kRows; ++k)
+            if (kRows + k < count) two_uses(uses, next_rows[k]);
+          r = 2 * kRows;
+        }
+        for (; r < count; r += kRows) {
+          uint32_t row[kRows];
+#pragma unroll
+          for (int k = 0; k < kRows; ++k) row[k] = slices[s.rows + (uint32_t)(min(r + k, count - 1) * kWave + lane_)];
+#pragma unroll
+          for (int k = 0; k < kRows; ++k)
+            if (k == 0 || r + k < count) two_uses(uses, row[k]);
+        }
+        unserved |= u_lt(lower_half(uses.least), uses.at[0]);
+        hold(uses, s.size, s.dur);
+      };
+      if constexpr (!LOOP) {
+#pragma unroll
+        for (int u = 0; u < kSlots; ++u)
+          if (mine[u].count >= 0) walk(mine[u], my_rows[u], u == 0 ? more_rows : nullptr);
+      } else {
+        for (int u = 0; u * NW < n_slices; ++u) {
+          const int i = slice_of(u, wave_);
+          if (i < n_slices) walk(open_slice(i, lane_), nullptr, nullptr);
+        }
+      }
+      for (int i = wave_; i < n_apart; i += NW) {   // a node with very many consumers: all lanes of a wave
+        const int v = (int)slices[3 + n_slices + i];
+        Uses<CT> uses;
+        uses.begin(read_starts<CT>((uint32_t)v * (2u * SS)));
+        const int y1 = G.out_ptr[v + 1];
+        for (int y = G.out_ptr[v]; y < y1; y += kWave)
+          uses.use(read_starts<CT>((uint32_t)(y + lane_ < y1 ? G.out_idx[y + lane_] : n) * (2u * SS)));
+        const int first = kNoUse - last_lane(scan_max(kNoUse - (int)lower_half(uses.least)));
+        unserved |= (uint32_t)first < (uint32_t)__builtin_amdgcn_readfirstlane((int)uses.at[0]) ? 1 : 0;
+#pragma unroll
+        for (int k = 0; k < CT; ++k) uses.last[k] = (uint32_t)last_lane(scan_max((int)upper_half(uses.last[k])));
+        if (lane_ == 0) {
+          const int2 sd = G.size_dur[v];
+#pragma unroll
+          for (int k = 0; k < CT; ++k)
+            if (uses.at[k] < kNever) {
+              raise(&a[uses.at[k]], sd.x);
+              lower(&a[uses.last[k] + 1u], sd.x);
+              dur += sd.y;
+            }
+        }
+      }
+      dur = scan_sum(dur);
+      if (lane_ == kWave - 1) raise(&told[3], dur);
+      if ((missing | unserved) != 0 && lane_ == 0) told[2] = 1;
+    }
+    ask_for_next();
+    if (decodable) {
+      __syncthreads();
+
+      // ---- 4. the peak of the running sum, eight positions per thread and round; the differences are left at zero
 #pragma unroll
       for (int r = 0; r < R; ++r) {
-        const int before = (taken_before + upto - taken) >> (16 * r) & 0xFFFF;
-        uint32_t at = (uint32_t)(before + (r ? total_taken & 0xFFFF : 0));
-        const auto put_two = [&](uint32_t w) {
-          const lanemask lo = low_ne_k(w, 0u), hi = high_ne_k(w, 0u);
-          lds_write16_lanes<0>(lo, (uint32_t)lay.list_off + 2u * at, w);
-          at = add_lanes(lo, at);
-          lds_write16_lanes<1>(hi, (uint32_t)lay.list_off + 2u * at, w);
-          at = add_lanes(hi, at);
-        };
-        put_two((uint32_t)who[r].x);
-        put_two((uint32_t)who[r].y);
-        put_two((uint32_t)who[r].z);
-        put_two((uint32_t)who[r].w);
+        const int x = (r * NT + t_) * 8;
+        int S = 0, P = 0;
+        if (x < lay.T_pad) {
+          const int4 lo = *reinterpret_cast<const int4*>(a + x), hi = *reinterpret_cast<const int4*>(a + x + 4);
+          *reinterpret_cast<int4*>(a + x) = make_int4(0, 0, 0, 0);
+          *reinterpret_cast<int4*>(a + x + 4) = make_int4(0, 0, 0, 0);
+          S = lo.x; P = max(S, 0);
+          S += lo.y; P = max(P, S);
+          S += lo.z; P = max(P, S);
+          S += lo.w; P = max(P, S);
+          S += hi.x; P = max(P, S);
+          S += hi.y; P = max(P, S);
+          S += hi.z; P = max(P, S);
+          S += hi.w; P = max(P, S);
+        }
+        combine_segments(S, P);
+        if (lane_ == kWave - 1) *sums(r, wave_) = make_int2(S, P);   // the lane that holds the wave's
       }
+      wait_for_lds_writes();
+      __syncthreads();
     }
-    // peak of the running sum, eight positions per thread and round; the differences are left at zero
-#pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int x = (r * NT + t_) * 8;
-      int S = 0, P = 0;
-      if (x < lay.T_pad) {
-        const int4 lo = *reinterpret_cast<const int4*>(a + x), hi = *reinterpret_cast<const int4*>(a + x + 4);
-        *reinterpret_cast<int4*>(a + x) = make_int4(0, 0, 0, 0);
-        *reinterpret_cast<int4*>(a + x + 4) = make_int4(0, 0, 0, 0);
-        S = lo.x; P = max(S, 0);
-        S += lo.y; P = max(P, S);
-        S += lo.z; P = max(P, S);
-        S += lo.w; P = max(P, S);
-        S += hi.x; P = max(P, S);
-        S += hi.y; P = max(P, S);
-        S += hi.z; P = max(P, S);
-        S += hi.w; P = max(P, S);
-      }
-      combine_segments(S, P);
-      if (lane_ == kWave - 1) *sums(r, wave_) = make_int2(S, P);   // the lane that holds the wave's
-    }
-    wait_for_lds_writes();
-    __syncthreads();
 
     // The sequence and the result.  Every wave issues the same stores, with lanes that have nothing to write
     // out of the buffer's range (such a store is dropped): a wave waits for its loads by the number of
@@ -738,9 +748,18 @@ void decode_fixed_kernel(GraphView G, const uint32_t* __restrict__ slices, int64
     }
     // No barrier behind this: what is read here is written again behind the next candidate's second.
     int2 segment = make_int2(0, 0);
-    if (wave_ == 0) {
+    int total_dur = 0;
+    bool valid = false;
+    if (wave_ == 0 && decodable) {
       if (lane_ < R * NW) segment = *sums(lane_ / NW, lane_ % NW);
       combine_segments(segment.x, segment.y);
+      const int2 about = *reinterpret_cast<const int2*>(told + 2);   // faults, duration
+      valid = __builtin_amdgcn_readfirstlane(about.x) == 0;
+      total_dur = __builtin_amdgcn_readfirstlane(about.y);
+      int zero = 0;
+      asm volatile("" : "+v"(zero));   // (a constant here is kept in registers across the candidates)
+      lds_write_lanes(1, (uint32_t)lay.told_off + 8u, (uint32_t)zero);
+      lds_write_lanes(1, (uint32_t)lay.told_off + 12u, (uint32_t)zero);
     }
     const auto result = __builtin_amdgcn_make_buffer_rsrc(out + cand, 0, (int)sizeof(moc_decode_result), kRawBuffer);
     const int off = wave_ == 0 && lane_ == kWave - 1 ? 0 : kDropped;

@@ -156,8 +156,8 @@ def dense_candidates(rng, g, C, B):
     return s, a
 
 
-# at, below and above the sizes at which the workgroup grows (nodes and positions per lane) and at which the
-# kernel goes over a candidate in rounds
+# sizes around those at which the workgroup grows and at which the kernel goes over a candidate in rounds
+# (every one of them: test_decode_rows_of_every_kind_in_every_workgroup); nodes with many consumers
 @pytest.mark.parametrize("n,C", [(255, 1), (257, 1), (4096, 1), (4097, 1), (251, 2), (252, 2), (1020, 2), (1024, 2), (2043, 2),
                                  (2045, 2), (4091, 2), (4093, 2), (6001, 2), (127, 3), (129, 3), (2045, 3), (2049, 3), (3001, 3),
                                  (125, 4), (128, 4), (2044, 4), (2048, 4), (3000, 4), (15900, 1)])
@@ -191,6 +191,27 @@ def rows_of_every_kind(rng, g, C):
         s[row, first] = s[row, second] if first != second else -1
     s[7, on[7]] = s[7, on[7][0]]     # every copy at one position
     return s, a
+
+
+# the largest size of every workgroup (nodes or positions per lane) and the smallest of the next one, or of the
+# kernel that goes over a candidate in rounds; several rows of every kind one behind the other in a workgroup
+@pytest.mark.parametrize("C,n", [(C, n) for C, last in ((1, lambda t: 4 * t), (2, lambda t: 4 * t - 1), (3, lambda t: 2 * t), (4, lambda t: 2 * t - 1))
+                                 for t in (64, 128, 256, 512, 1024) for n in (last(t), last(t) + 1)])
+def test_decode_rows_of_every_kind_in_every_workgroup(moc, C, n):
+    from paper_2304_14463_amd.inputs import graph_from_edges
+    rng = np.random.default_rng(7 * n + C)
+    edges = sorted({(int(u), v) for v in range(1, n) for u in rng.integers(max(0, v - 20), v, size=2)})
+    g = graph_from_edges(n, edges, rng.integers(0, 50, n), rng.integers(1, 9, n))
+    gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, 1, C)
+    s, a = rows_of_every_kind(rng, g, C)
+    want, want_seq = oracle.decode(g, C, s, a)
+    assert set(want[:, 0]) == {-1, 0, 1}
+    pick = np.arange(256 * 3 * max(1, 8192 // n)) % 11   # about three rows for each workgroup that the chip holds
+    got, seq = gpu_decode(moc, gh, s[pick], a[pick])
+    assert_same(got, seq, want[pick], want_seq[pick])
+    got, _ = gpu_decode(moc, gh, s[pick], a[pick], want_seq=False)
+    assert_same(got, None, want[pick], None, "without the sequences")
+    gh.free()
 
 
 # the sizes at which LDS is short; rows of every kind follow each other in a workgroup
