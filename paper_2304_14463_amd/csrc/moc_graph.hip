@@ -12,7 +12,7 @@
 #include <vector>
 
 #include "moc_internal.h"
-#include "moc_slices.h"
+#include "moc_shapes.h"
 
 static thread_local int g_last_hip_error = 0;
 
@@ -205,7 +205,7 @@ int moc_graph_upload(int32_t n, const int32_t* in_ptr, const int32_t* in_idx, co
       for (int v = 0; v < n; ++v)
         for (int q = in_ptr[v]; q < in_ptr[v + 1]; ++q) out_idx[fill[in_idx[q]]++] = v;
     }
-    const std::vector<uint32_t> slices = slices_for_kernel(n, C, out_ptr.data(), out_idx.data());
+    const std::vector<uint32_t> slices = slices_for_kernel(n, C, decode_shape(n, C).nt / kWave, out_ptr.data(), out_idx.data());
     std::vector<int32_t> in_ptr_v(in_ptr, in_ptr + n + 1), in_idx_v(in_idx, in_idx + m);
 
     moc_graph* g = new moc_graph();   // all members zero

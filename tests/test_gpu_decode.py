@@ -231,6 +231,22 @@ def test_decode_largest_sizes(moc, n, C):
     gh.free()
 
 
+@pytest.mark.parametrize("n,C,consumers,hubs", [(70, 1, 60, 0), (300, 2, 45, 0), (300, 2, 100, 2), (300, 3, 60, 5), (500, 4, 33, 20), (4200, 2, 40, 3)])
+def test_decode_many_consumers(moc, n, C, consumers, hubs):
+    """Most nodes with more consumers than a slice of an ordinary graph has rows for, and some with very many."""
+    from paper_2304_14463_amd.inputs import graph_from_edges
+    rng = np.random.default_rng(n + consumers)
+    edges = {(u, int(v)) for u in range(n - 1) for v in rng.integers(u + 1, min(n, u + 3 * consumers), size=consumers)}
+    edges |= {(int(u), int(v)) for u in rng.integers(0, n // 2, hubs) for v in rng.integers(n // 2, n, size=n // 2)}
+    g = graph_from_edges(n, sorted(edges), rng.integers(0, 50, n), rng.integers(1, 9, n))
+    gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, 1, C)
+    for s, a in (orderly_candidates(rng, g, C, 8), rows_of_every_kind(rng, g, C)):
+        want, want_seq = oracle.decode(g, C, s, a)
+        got, seq = gpu_decode(moc, gh, s, a)
+        assert_same(got, seq, want, want_seq)
+    gh.free()
+
+
 def test_decode_graph_without_edges(moc):
     from paper_2304_14463_amd.inputs import graph_from_edges
     rng = np.random.default_rng(5)

@@ -12,7 +12,7 @@ PROGRAM = r"""
 #include <cstdio>
 #include <cstdlib>
 #include "moc_slices.h"
-int main() {   // n C m, then m edges (u, v) in the order of u
+int main(int argc, char** argv) {   // n C m, then m edges (u, v) in the order of u
   int n, C, m;
   if (scanf("%d %d %d", &n, &C, &m) != 3) return 1;
   std::vector<int32_t> ptr(n + 1), idx(m);
@@ -23,9 +23,14 @@ int main() {   // n C m, then m edges (u, v) in the order of u
     idx[q] = v;
   }
   for (int v = 0; v < n; ++v) ptr[v + 1] += ptr[v];
-  const std::vector<uint32_t> list = out_slices(n, C, ptr.data(), idx.data());
-  if (getenv("READS")) {   // words the kernel is given; where a wave's rows begin that it reads ahead, 16 waves
-    printf("%zu\n", slices_for_kernel(n, C, ptr.data(), idx.data()).size());
+  if (argc == 3) {   // limit WAVES
+    printf("%d\n", slice_degree(n, atoi(argv[2]), ptr.data()));
+    return 0;
+  }
+  std::vector<uint32_t> list = out_slices(n, C, ptr.data(), idx.data());
+  if (argc == 2) {   // reads: words the kernel is given; where a wave's rows begin that it reads ahead, 16 waves
+    list = slices_for_kernel(n, C, 16, ptr.data(), idx.data());
+    printf("%zu\n", list.size());
     for (uint32_t wave = 0; wave < 16; ++wave)
       for (int r = kHeldRows; r < 2 * kHeldRows; ++r) {
         const bool any = wave < list[0];
@@ -46,10 +51,9 @@ def program(tmp_path_factory):
     (at / "slices.cpp").write_text(PROGRAM)
     subprocess.run(["g++", "-O1", "-std=c++17", "-Wall", "-Werror", "-I", CSRC, "-o", str(at / "slices"), str(at / "slices.cpp")], check=True)
 
-    def run(n, C, edges, reads=False):
+    def run(n, C, edges, *args):
         text = f"{n} {C} {len(edges)}\n" + "\n".join(f"{u} {v}" for u, v in edges)
-        env = dict(os.environ, READS="1") if reads else {k: v for k, v in os.environ.items() if k != "READS"}
-        out = subprocess.run([str(at / "slices")], input=text, check=True, capture_output=True, text=True, env=env).stdout
+        out = subprocess.run([str(at / "slices"), *map(str, args)], input=text, check=True, capture_output=True, text=True).stdout
         return np.array(out.split(), dtype=np.int64)
     return run
 
@@ -100,8 +104,20 @@ def test_every_edge_once(program, n, C, degree):
 def test_rows_read_ahead_lie_in_the_list(program, n, C, edges):
     """The rows a wave reads whether or not its first slice has them: no word beyond the list, whatever
     slices there are."""
-    words, *ahead = program(n, C, sorted(edges), reads=True)
+    words, *ahead = program(n, C, sorted(edges), "reads")
     assert len(ahead) == 32 and min(ahead) >= 0 and max(ahead) + 64 <= words
+
+
+def test_many_consumers_are_listed_apart_where_few_nodes_have_them(program):
+    """Apart are the nodes that would keep the other lanes of a slice and the other waves waiting, not all nodes
+    of a graph whose nodes have many consumers."""
+    def limit(degrees, waves):
+        return int(program(len(degrees), 2, [(u, (u + 1 + k) % len(degrees)) for u, d in enumerate(degrees) for k in range(d)], "limit", waves)[0])
+    assert limit([3] * 500, 8) == 32 and limit([32] * 500, 8) == 32
+    assert limit([40] * 1000, 4) >= 40 and limit([100] * 1000, 4) >= 100 and limit([5, 100] * 500, 4) >= 100
+    assert limit([3] * 980 + [200] * 20, 4) < 200 and limit([3] * 1960 + [1000] * 40, 8) < 1000
+    assert limit([60] * 1960 + [1000] * 40, 8) in range(60, 1000)   # both
+    assert limit([33], 1) == 32 and limit([0], 1) == 32
 
 
 def test_sizes_beyond_16_bits_have_none(program):
