@@ -830,9 +830,31 @@ __device__ __forceinline__ bool best_cut_of_clean_base(const GraphView& g, const
       if (want) S.picked[first + (int)__popcll(m & ((1ull << lane) - 1))] = (uint16_t)r;
     }
   };
-  BestCut own;   // of the group, in its first lane
+  BestCut own;   // of the group, in its first lane, or of the lane
   const int gl = t & (kGroup - 1);
-  auto score_picked = [&](int count) {
+  // Where several workgroups share a compute unit (fewer than 1024 threads) its vector ALU is what they wait for, and
+  // plain cuts, whose score is short, are scored one lane each once there are more than the groups take at
+  // once: 1024 walkers, 32 steps, n = 700 1341 us (by groups alone 1870), n = 442 516 (650), n = 1000 1075 (1363), where
+  // few moves are scored, training graph n = 1000, 657 (660).  One workgroup to a compute unit waits for the chain:
+  // 64 walkers, n = 442 383 us by groups, 425 with this.
+  constexpr bool kByLanes = MODE == 0 && NT < 1024;
+  auto score_picked = [&](int count) {   // the lane's best to `own`, the group's to `best` in its first lane
+    if (kByLanes && count > NT / kGroup) {
+      for (int r = t; r < count; r += NT) {
+        const int at = S.picked[r];
+        const uint32_t q = S.moves[at], where = S.where[at];
+        CutScore sc{};
+        Cut c{};
+        if (score_cut(lists, C, L, lay, (int)(where >> 16), (int)(where & 0xFFFFu), 0, 0, base_peak, at_peak, true, sc, c) &&
+            own.take((uint64_t)(uint32_t)sc.viol << 32 | (uint32_t)sc.peak, (uint64_t)(uint32_t)sc.at << 32 | q))
+          cut = c;
+      }
+      best = own;
+#pragma unroll
+      for (int off = kGroup / 2; off > 0; off >>= 1)
+        best.take((uint64_t)__shfl_xor((unsigned long long)best.score, off), (uint64_t)__shfl_xor((unsigned long long)best.tie, off));
+      return;
+    }
     for (int r = t / kGroup; r < count; r += NT / kGroup) {
       const int at = S.picked[r];
       const uint32_t q = S.moves[at], where = S.where[at];
@@ -844,12 +866,12 @@ __device__ __forceinline__ bool best_cut_of_clean_base(const GraphView& g, const
         if (own.take((uint64_t)(uint32_t)sc.peak, (uint64_t)(uint32_t)sc.at << 32 | q)) cut = c;
       }
     }
+    best = own;
   };
   pick(1, [&](uint32_t bound) { return bucket_of(bound) <= last_bucket; });
   __syncthreads();
   const int first_round = __builtin_amdgcn_readfirstlane(S.counts[1]);
   score_picked(first_round);
-  best = own;
   best_of_workgroup<NT, kGroup>(best, L.scratch, t);
   if (first_round < passed) {   // the others, unless their bound lies above what was reached
     const uint64_t reached = best.score;
@@ -858,7 +880,6 @@ __device__ __forceinline__ bool best_cut_of_clean_base(const GraphView& g, const
     const int second_round = __builtin_amdgcn_readfirstlane(S.counts[3]);
     if (second_round > 0) {
       score_picked(second_round);
-      best = own;
       best_of_workgroup<NT, kGroup>(best, L.scratch + 4 * NW, t);
     }
   }
