@@ -545,8 +545,8 @@ __device__ __forceinline__ InOut group_range_maxima(const BaseLds& L, int blocks
 }
 
 // score_cut for a base without violations, by a group: false also for a move that raises the violations or
-// the peak.  (Loops that groups leave at different times carry integers, not booleans, to their end.)
-template <int MODE, typename A>
+// the peak.  WIDE: for graphs with nodes of many inputs.  (Loops that groups leave at different times carry integers, not booleans, to their end.)
+template <int MODE, bool WIDE, typename A>
 __device__ __forceinline__ bool score_cut_by_group(const A& lists, int C, bool parallel, const BaseLds& L, const MvLayout& lay,
                                                    int ub, int t, int base_peak, const PeakCount& at_peak, CutScore& out,
                                                    Cut& cut, int gl) {
@@ -641,9 +641,11 @@ __device__ __forceinline__ bool score_cut_by_group(const A& lists, int C, bool p
         end = (int)(pw >> 16);
       }
     }
-    if (parallel)   // listed before: it is kept already
-      for (int z = y0; z < y; ++z) held |= (int)(lists.pair(z) & 0xFFFFu) == w ? 1 : 0;
     if (held || kept < 0) return Step{kNone, 0};
+    if (parallel) {   // listed before: it is kept already
+      for (int z = y0; z < y; ++z) held |= (int)(lists.pair(z) & 0xFFFFu) == w ? 1 : 0;
+      if (held) return Step{kNone, 0};
+    }
     for (int q = C - 1; q >= 0; --q) {   // Eq. (3): the kept copy against the next live copy of its node
       const uint32_t pw = L.packed[w + q];
       if (q > kept && live_of(pw)) next = (int)(pw & 0xFFFFu);
@@ -651,13 +653,21 @@ __device__ __forceinline__ bool score_cut_by_group(const A& lists, int C, bool p
     if (next >= 0 && p > next) order = 1;
     return Step{end + 1, lists.size_of(w / C)};
   };
+  // WIDE: which eights of steps hold any (a bit for each, for several of them from 33 eights on); most inputs of a
+  // node with many are held.
+  uint32_t eights = 0;
+  const int per_bit = max(0, 27 - __clz((n_steps - 1) / kGroup));
+  const auto bit_of = [&](int i0) { return (uint32_t)i0 / kGroup >> per_bit; };
+  const auto empty = [&](int i0) { return WIDE && (eights >> bit_of(i0) & 1) == 0; };
   // f(begin, end, change, first): the stretch behind a step; first: no earlier step begins there
   auto stretches = [&](auto f) {
     for (int i0 = 0; i0 < n_steps; i0 += kGroup) {
+      if (empty(i0)) continue;   // the same in all lanes of the group
       int ignored = 0;
       const Step own = step_of(i0 + gl, ignored);
       int next = p, change = own.size, first = 1;
       for (int o0 = 0; o0 < n_steps; o0 += kGroup) {
+        if (empty(o0)) continue;
         const Step o = o0 == i0 ? own : step_of(o0 + gl, ignored);
         auto meet = [&](int begin, int size, int index) {
           if (begin > own.begin) next = min(next, begin);
@@ -681,6 +691,12 @@ __device__ __forceinline__ bool score_cut_by_group(const A& lists, int C, bool p
     const Step own = step_of(i0 + gl, order);
     lo = min(lo, own.begin);
     kept_size += i0 + gl == 0 ? 0 : own.size;
+    if (WIDE) eights |= (own.begin != kNone ? 1u : 0u) << bit_of(i0);
+  }
+  if (WIDE) {
+    eights |= (uint32_t)group_xor<1>((int)eights);
+    eights |= (uint32_t)group_xor<2>((int)eights);
+    eights |= (uint32_t)group_xor<7>((int)eights);
   }
   if (group_max(order) != 0) return false;
   lo = group_min(lo);
@@ -707,7 +723,7 @@ __device__ __forceinline__ bool score_cut_by_group(const A& lists, int C, bool p
 
 // True: `best` is the best move over the workgroup and, in the lane that scored it, `cut` the move.
 // False: more moves passed than the lists hold, nothing has been scored.  Ends with a barrier.
-template <int CT, int NT, int MODE, typename A>
+template <int CT, int NT, int MODE, bool WIDE, typename A>
 __device__ __forceinline__ bool best_cut_of_clean_base(const GraphView& g, const A& lists, const BaseLds& L, const MvLayout& lay,
                                                        const SiftLds& S, int base_peak, const PeakCount& at_peak,
                                                        BestCut& best, Cut& cut, bool& mine_is_best, int t) {
@@ -776,8 +792,8 @@ __device__ __forceinline__ bool best_cut_of_clean_base(const GraphView& g, const
       if (useful) {
         const int x = last < at_peak.first && at_peak.first < p ? at_peak.first : last < at_peak.last && at_peak.last < p ? at_peak.last : -1;
         int carried = 0;
-        if (g.parallel == 0)   // (an input listed twice is carried once)
-          for (int y = lists.in_begin(u), y1 = lists.in_begin(u + 1); y < y1; y += 4) {   // four at a time, the last one again beyond the end
+        if (g.parallel == 0)   // (an input listed twice is carried once; left as soon as the move raises the peak)
+          for (int y = lists.in_begin(u), y1 = lists.in_begin(u + 1); y < y1 && carried <= lists.size_of(u); y += 4) {   // four at a time, the last one again beyond the end
             int w[4];
 #pragma unroll
             for (int d = 0; d < 4; ++d) w[d] = (int)(lists.pair(min(y + d, y1 - 1)) & 0xFFFFu);
@@ -860,7 +876,7 @@ __device__ __forceinline__ bool best_cut_of_clean_base(const GraphView& g, const
       const uint32_t q = S.moves[at], where = S.where[at];
       CutScore sc{};
       Cut c{};
-      const bool scored = score_cut_by_group<MODE>(lists, C, g.parallel != 0, L, lay, (int)(where >> 16), (int)(where & 0xFFFFu),
+      const bool scored = score_cut_by_group<MODE, WIDE>(lists, C, g.parallel != 0, L, lay, (int)(where >> 16), (int)(where & 0xFFFFu),
                                                    base_peak, at_peak, sc, c, gl);
       if (scored && gl == 0) {
         if (own.take((uint64_t)(uint32_t)sc.peak, (uint64_t)(uint32_t)sc.at << 32 | q)) cut = c;

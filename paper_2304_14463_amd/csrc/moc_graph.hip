@@ -233,6 +233,7 @@ int moc_graph_upload(int32_t n, const int32_t* in_ptr, const int32_t* in_idx, co
       std::sort(inputs.begin(), inputs.end());
       w.parallel = std::adjacent_find(inputs.begin(), inputs.end()) != inputs.end() ? 1 : 0;
     }
+    for (int v = 0; v < n; ++v) w.wide |= in_ptr[v + 1] - in_ptr[v] > kWideInputs ? 1 : 0;
     if (rc == MOC_OK) rc = upload(g, size_dur, &w.size_dur);
     if (rc == MOC_OK) rc = upload(g, edge_pair, &w.edge_pair);
     if (rc == MOC_OK) rc = upload(g, edge_pair_c, &w.edge_pair_c);

@@ -29,7 +29,9 @@ struct GraphView {
   int64_t budget;
   int32_t n, m, C, T;
   int32_t parallel;            // 1: some edge is listed more than once
+  int32_t wide;                // 1: some node has more than kWideInputs in-edges
 };
+constexpr int kWideInputs = 64;
 
 constexpr int kTicketSlots = 16;   // sets of work counters per graph handle = streams that get one of their own
 constexpr int kTicketGroups = 64;  // counters a launch draws candidates from (+1: workgroups that have left)

@@ -29,7 +29,7 @@ static_assert(kMaxRanges == kWave + 1 && kCutWords == (int)(sizeof(Cut) / 4), "d
 // keeping cuts 0.40 and 0.7 ms for two sets of inputs (0.76 and 1.36 with one lane per move; 27 ms with two
 // launches a step that staged and scored everything again); n = 1000, 32 walkers, 32 plain cuts: 0.27 ms
 // (0.42; 1.31).
-template <int CT, int NT, bool LISTS, int MODE>
+template <int CT, int NT, bool LISTS, int MODE, bool WIDE>
 __global__ __launch_bounds__(NT) void descend_cuts_kernel(GraphView g, int32_t* __restrict__ starts, int32_t* __restrict__ ends,
                                                           uint8_t* __restrict__ active, int max_steps,
                                                           moc_best_move* __restrict__ last_move, int32_t* __restrict__ out_steps,
@@ -71,7 +71,7 @@ __global__ __launch_bounds__(NT) void descend_cuts_kernel(GraphView g, int32_t* 
     BestCut best;
     Cut cut{};
     bool known = false;   // this lane holds the chosen move in `cut`
-    if (base_viol != 0 || !best_cut_of_clean_base<CT, NT, MODE>(g, lists, L, lay, sift, base_peak, at_peak, best, cut, known, t)) {
+    if (base_viol != 0 || !best_cut_of_clean_base<CT, NT, MODE, WIDE>(g, lists, L, lay, sift, base_peak, at_peak, best, cut, known, t)) {
       best = BestCut{};
       known = false;
       score_cuts<CT, NT>(g, lists, L, lay, queue, MODE, base_viol, base_peak, at_peak, base_viol == 0, best, t,
@@ -358,18 +358,24 @@ __global__ __launch_bounds__(NT) void merge_kernel(GraphView g, int32_t* __restr
 
 using DescendKernel = void (*)(GraphView, int32_t*, int32_t*, uint8_t*, int, moc_best_move*, int32_t*, int, MvLayout);
 
-template <int NT, bool LISTS, int MODE>
+// WIDE: keeping cuts look at all inputs of a node for every stretch between two of the steps they make, and pass
+// over the inputs that are held anyway where nodes have more than kWideInputs; the code for it costs other graphs
+// 2 % (n = 442, 1024 walkers 550 us, 540 without).  31 nodes of 600 inputs among 620, 64 walkers: 1430 us
+// without, 418 with; every 20th of 320 nodes with 300 inputs 211 and 137 (one lane per move: 389, 154).
+template <int NT, bool LISTS, int MODE, bool WIDE>
 DescendKernel pick_descend(int C) {
   switch (C) {
-    case 2: return descend_cuts_kernel<2, NT, LISTS, MODE>;
-    case 3: return descend_cuts_kernel<3, NT, LISTS, MODE>;
-    default: return descend_cuts_kernel<0, NT, LISTS, MODE>;
+    case 2: return descend_cuts_kernel<2, NT, LISTS, MODE, WIDE>;
+    case 3: return descend_cuts_kernel<3, NT, LISTS, MODE, WIDE>;
+    default: return descend_cuts_kernel<0, NT, LISTS, MODE, WIDE>;
   }
 }
-template <int MODE>
+template <int MODE, bool WIDE>
 DescendKernel pick_descend(int C, int nt, bool lists) {
-  if (!lists) return pick_descend<1024, false, MODE>(C);
-  return nt == 256 ? pick_descend<256, true, MODE>(C) : nt == 512 ? pick_descend<512, true, MODE>(C) : pick_descend<1024, true, MODE>(C);
+  if (!lists) return pick_descend<1024, false, MODE, WIDE>(C);
+  return nt == 256   ? pick_descend<256, true, MODE, WIDE>(C)
+         : nt == 512 ? pick_descend<512, true, MODE, WIDE>(C)
+                     : pick_descend<1024, true, MODE, WIDE>(C);
 }
 
 using MergeKernel = void (*)(GraphView, int32_t*, int32_t*, uint8_t*, int, int, int32_t*, MvLayout);
@@ -393,7 +399,10 @@ int queue_cut_descent(const moc_graph* g, int64_t B, int32_t* starts, int32_t* e
   const int nt = shape.nt, cap = shape.cap;
   const MvLayout lay = shape.lay;
   if (lay.bytes > g->max_lds) return MOC_EOVERFLOW;
-  const DescendKernel kern = mode == 0 ? pick_descend<0>(g->view.C, nt, lay.lists != 0) : pick_descend<1>(g->view.C, nt, lay.lists != 0);
+  const bool lists = lay.lists != 0;
+  const DescendKernel kern = mode == 0      ? pick_descend<0, false>(g->view.C, nt, lists)
+                             : g->view.wide ? pick_descend<1, true>(g->view.C, nt, lists)
+                                            : pick_descend<1, false>(g->view.C, nt, lists);
   int per_cu = 0;   // not used: the call is for the kernel's LDS limit
   if (const int rc = moc_kernel_occupancy(g, reinterpret_cast<const void*>(kern), nt, lay.bytes, false, &per_cu)) return rc;
   for (int64_t at = 0; at < B; at += kMaxLaunch)

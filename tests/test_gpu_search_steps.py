@@ -277,6 +277,40 @@ def test_moves_follow_the_oracle(moc, n, C, B, R, steps):
     gh.free()
 
 
+@pytest.mark.parametrize("duplicates", [False, True])
+@pytest.mark.parametrize("C,inputs,B", [(2, 17, 3), (2, 40, 600), (2, 63, 3), (2, 65, 3), (2, 80, 300), (2, 130, 1500), (2, 255, 3), (2, 256, 3), (2, 300, 600),
+                                        (2, 520, 3), (3, 64, 3), (3, 100, 600), (5, 90, 3), (5, 270, 600)])
+def test_keeping_cuts_with_a_few_of_many_inputs_kept(moc, C, inputs, B, duplicates):
+    """Producers with many inputs of which a few are kept: around the number from which a graph has the kernel for
+    it and the numbers of inputs that share a bit there."""
+    from paper_2304_14463_amd.inputs import graph_from_edges
+    rng = np.random.default_rng(inputs + 10 * C + duplicates)
+    n = inputs + 90
+    edges = {(v - 1, v) for v in range(1, n)}
+    wide = [inputs + 5, inputs + 15, inputs + 25]   # the second is gone when the others are needed again
+    for u, v in zip(wide, (n - 5, inputs + 50, n - 20)):
+        edges |= {(int(w), u) for w in rng.choice(inputs + 3, inputs, replace=False)} | {(u, v)}
+    edges |= {(w, n - 1) for w in range(inputs) if w % 9 != 0}   # these inputs are held anyway
+    edges = sorted(edges) + ([(int(w), wide[i % 3]) for i, w in enumerate(rng.integers(0, inputs, 40))] if duplicates else [])
+    size = rng.integers(1, 4, n)
+    size[wide], size[inputs + 40:inputs + 60] = 20 * inputs + rng.integers(2000, 2600, 3), rng.integers(20, 60, 20)
+    g = graph_from_edges(n, sorted(edges), size, rng.integers(1, 9, n))
+    assert np.diff(g.in_ptr).max() >= inputs
+    s = np.zeros((1, n * C), np.int32); e = s.copy(); a = np.zeros((1, n * C), np.uint8)
+    last = np.arange(n) * C
+    for u, v in edges:
+        last[u] = max(last[u], v * C)
+    s[0, ::C], e[0, ::C], a[0, ::C] = np.arange(n) * C, last, 1
+    gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, 10, C)
+    ds, de, da = to_dev(*(np.repeat(x, B, 0) for x in (s, e, a)))
+    count, _ = moc.moc_search_two_phase(gh, ds, de, da, 8, 0)
+    k, ws, we, wa = oracle.search_cuts(g, 10, C, s[0], e[0], a[0], 8, mode=1)
+    assert k > 1 and all(wa[u * C + 1] for u in wide)
+    assert (count.cpu().numpy() == k).all()
+    assert (da.cpu().numpy() == wa).all() and (ds.cpu().numpy() == ws).all() and (de.cpu().numpy() == we).all()
+    gh.free()
+
+
 def wide_producers(rng):
     """Two large outputs, each made from more than 130 small ones that nothing else needs later and
     consumed far behind the peak: a keeping cut of one keeps all of its inputs.  The inputs are listed
