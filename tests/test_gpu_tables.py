@@ -21,7 +21,8 @@ def moc():
 
 
 @pytest.mark.parametrize("n,C,B", [(1, 1, 6), (1, 2, 6), (7, 1, 6), (8, 1, 6), (9, 1, 1500), (4, 2, 6), (31, 2, 900), (32, 2, 1500), (33, 2, 6),
-                                   (21, 3, 1500), (64, 4, 900), (13, 5, 1500), (129, 2, 6), (511, 2, 900), (1025, 2, 3), (700, 5, 3)])
+                                   (21, 3, 1500), (64, 4, 900), (13, 5, 1500), (129, 2, 6), (511, 2, 900), (1025, 2, 3), (700, 5, 3),
+                                   (63, 1, 1500), (130, 1, 900), (1100, 1, 6)])
 def test_toggles(moc, n, C, B):
     rng = np.random.default_rng(7 * n + C)
     g = random_graph(rng, n)
