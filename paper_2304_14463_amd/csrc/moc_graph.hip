@@ -206,6 +206,18 @@ int moc_graph_upload(int32_t n, const int32_t* in_ptr, const int32_t* in_idx, co
         for (int q = in_ptr[v]; q < in_ptr[v + 1]; ++q) out_idx[fill[in_idx[q]]++] = v;
     }
     const std::vector<uint32_t> slices = slices_for_kernel(n, C, decode_shape(n, C).nt / kWave, out_ptr.data(), out_idx.data());
+    int parallel = 0, wide = 0, self_loop = 0;
+    {
+      std::vector<int32_t> read_by(n, -1);   // the last node that was seen to read a node
+      for (int v = 0; v < n; ++v) {
+        wide |= in_ptr[v + 1] - in_ptr[v] > kWideInputs ? 1 : 0;
+        for (int q = in_ptr[v]; q < in_ptr[v + 1]; ++q) {
+          parallel |= read_by[in_idx[q]] == v ? 1 : 0;
+          self_loop |= in_idx[q] == v ? 1 : 0;
+          read_by[in_idx[q]] = v;
+        }
+      }
+    }
     std::vector<int32_t> in_ptr_v(in_ptr, in_ptr + n + 1), in_idx_v(in_idx, in_idx + m);
 
     moc_graph* g = new moc_graph();   // all members zero
@@ -217,9 +229,7 @@ int moc_graph_upload(int32_t n, const int32_t* in_ptr, const int32_t* in_idx, co
       delete g;
       return moc_set_hip_error(e);
     }
-    for (int v = 0; v < n; ++v)
-      for (int q = in_ptr[v]; q < in_ptr[v + 1]; ++q)
-        if (in_idx[q] == v) g->has_self_loop = 1;
+    g->has_self_loop = self_loop;
     g->num_cu = prop.multiProcessorCount;
     g->max_lds = (int)prop.sharedMemPerBlock;
     if (moc_eval_lds_bytes(n, m, C, g->max_lds) > g->max_lds) {
@@ -228,12 +238,7 @@ int moc_graph_upload(int32_t n, const int32_t* in_ptr, const int32_t* in_idx, co
     }
     GraphView& w = g->view;
     w.budget = budget; w.n = n; w.m = m; w.C = C; w.T = T;
-    for (int v = 0; v < n && !w.parallel; ++v) {
-      std::vector<int32_t> inputs(in_idx + in_ptr[v], in_idx + in_ptr[v + 1]);
-      std::sort(inputs.begin(), inputs.end());
-      w.parallel = std::adjacent_find(inputs.begin(), inputs.end()) != inputs.end() ? 1 : 0;
-    }
-    for (int v = 0; v < n; ++v) w.wide |= in_ptr[v + 1] - in_ptr[v] > kWideInputs ? 1 : 0;
+    w.parallel = parallel; w.wide = wide;
     if (rc == MOC_OK) rc = upload(g, size_dur, &w.size_dur);
     if (rc == MOC_OK) rc = upload(g, edge_pair, &w.edge_pair);
     if (rc == MOC_OK) rc = upload(g, edge_pair_c, &w.edge_pair_c);
