@@ -8,6 +8,7 @@
 // out-edge CSR of single nodes.
 #include <algorithm>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <vector>
 
@@ -158,6 +159,14 @@ static int upload(moc_graph* g, const std::vector<T>& host, const T** dev) {
   return MOC_OK;
 }
 
+// A handle that is not finished yet: given up with its device memory, also when an exception passes by.
+struct GiveUp {
+  void operator()(moc_graph* g) const {
+    for (int i = 0; i < g->n_allocs; ++i) (void)hipFree(g->allocs[i]);
+    delete g;
+  }
+};
+
 extern "C" {
 
 int moc_graph_upload(int32_t n, const int32_t* in_ptr, const int32_t* in_idx, const int32_t* size,
@@ -220,22 +229,17 @@ int moc_graph_upload(int32_t n, const int32_t* in_ptr, const int32_t* in_idx, co
     }
     std::vector<int32_t> in_ptr_v(in_ptr, in_ptr + n + 1), in_idx_v(in_idx, in_idx + m);
 
-    moc_graph* g = new moc_graph();   // all members zero
+    std::unique_ptr<moc_graph, GiveUp> owner(new moc_graph());   // all members zero
+    moc_graph* const g = owner.get();
     int rc = MOC_OK;
     hipError_t e = hipGetDevice(&g->device);
     hipDeviceProp_t prop;
     if (e == hipSuccess) e = hipGetDeviceProperties(&prop, g->device);
-    if (e != hipSuccess) {
-      delete g;
-      return moc_set_hip_error(e);
-    }
+    if (e != hipSuccess) return moc_set_hip_error(e);
     g->has_self_loop = self_loop;
     g->num_cu = prop.multiProcessorCount;
     g->max_lds = (int)prop.sharedMemPerBlock;
-    if (moc_eval_lds_bytes(n, m, C, g->max_lds) > g->max_lds) {
-      delete g;
-      return MOC_EOVERFLOW;
-    }
+    if (moc_eval_lds_bytes(n, m, C, g->max_lds) > g->max_lds) return MOC_EOVERFLOW;
     GraphView& w = g->view;
     w.budget = budget; w.n = n; w.m = m; w.C = C; w.T = T;
     w.parallel = parallel; w.wide = wide;
@@ -258,13 +262,8 @@ int moc_graph_upload(int32_t n, const int32_t* in_ptr, const int32_t* in_idx, co
       rc = moc_eval_prepare(g);
     }
     if (rc == MOC_OK) rc = moc_eval_static_setup(g->device);
-    if (rc != MOC_OK) {
-      for (int i = 0; i < g->n_allocs; ++i) (void)hipFree(g->allocs[i]);
-      delete g;
-      return rc;
-    }
-    *out = g;
-    return MOC_OK;
+    if (rc == MOC_OK) *out = owner.release();
+    return rc;
   } catch (const std::bad_alloc&) {
     return MOC_ENOMEM;
   }
