@@ -854,8 +854,10 @@ __device__ __forceinline__ bool best_cut_of_clean_base(const GraphView& g, const
   // few moves are scored, training graph n = 1000, 657 (660).  One workgroup to a compute unit waits for the chain:
   // 64 walkers, n = 442 383 us by groups, 425 with this.
   constexpr bool kByLanes = MODE == 0 && NT < 1024;
+  bool by_lanes = false;   // one of the rounds was: any lane may hold the best so far
   auto score_picked = [&](int count) {   // the lane's best to `own`, the group's to `best` in its first lane
     if (kByLanes && count > NT / kGroup) {
+      by_lanes = true;
       for (int r = t; r < count; r += NT) {
         const int at = S.picked[r];
         const uint32_t q = S.moves[at], where = S.where[at];
@@ -865,24 +867,25 @@ __device__ __forceinline__ bool best_cut_of_clean_base(const GraphView& g, const
             own.take((uint64_t)(uint32_t)sc.viol << 32 | (uint32_t)sc.peak, (uint64_t)(uint32_t)sc.at << 32 | q))
           cut = c;
       }
-      best = own;
-#pragma unroll
-      for (int off = kGroup / 2; off > 0; off >>= 1)
-        best.take((uint64_t)__shfl_xor((unsigned long long)best.score, off), (uint64_t)__shfl_xor((unsigned long long)best.tie, off));
-      return;
-    }
-    for (int r = t / kGroup; r < count; r += NT / kGroup) {
-      const int at = S.picked[r];
-      const uint32_t q = S.moves[at], where = S.where[at];
-      CutScore sc{};
-      Cut c{};
-      const bool scored = score_cut_by_group<MODE, WIDE>(lists, C, g.parallel != 0, L, lay, (int)(where >> 16), (int)(where & 0xFFFFu),
-                                                   base_peak, at_peak, sc, c, gl);
-      if (scored && gl == 0) {
-        if (own.take((uint64_t)(uint32_t)sc.peak, (uint64_t)(uint32_t)sc.at << 32 | q)) cut = c;
+    } else {
+      for (int r = t / kGroup; r < count; r += NT / kGroup) {
+        const int at = S.picked[r];
+        const uint32_t q = S.moves[at], where = S.where[at];
+        CutScore sc{};
+        Cut c{};
+        const bool scored = score_cut_by_group<MODE, WIDE>(lists, C, g.parallel != 0, L, lay, (int)(where >> 16), (int)(where & 0xFFFFu),
+                                                           base_peak, at_peak, sc, c, gl);
+        if (scored && gl == 0) {
+          if (own.take((uint64_t)(uint32_t)sc.peak, (uint64_t)(uint32_t)sc.at << 32 | q)) cut = c;
+        }
       }
     }
     best = own;
+    if (kByLanes && by_lanes) {
+#pragma unroll
+      for (int off = kGroup / 2; off > 0; off >>= 1)
+        best.take((uint64_t)__shfl_xor((unsigned long long)best.score, off), (uint64_t)__shfl_xor((unsigned long long)best.tie, off));
+    }
   };
   pick(1, [&](uint32_t bound) { return bucket_of(bound) <= last_bucket; });
   __syncthreads();

@@ -223,6 +223,33 @@ def test_cuts_with_more_moves_than_the_groups_take_at_once(moc, C, n, B):
     gh.free()
 
 
+@pytest.mark.parametrize("C,n,B,smaller", [(2, 200, 300, 6), (2, 200, 600, 3), (2, 202, 1024, 5), (2, 260, 1024, 2), (3, 150, 1024, 4), (5, 120, 1024, 3)])
+def test_cuts_scored_by_lanes_and_then_by_groups(moc, C, n, B, smaller):
+    """Hundreds of moves share the lowest bound and are scored first, one lane each; a few with a higher bound
+    follow, a group of lanes each.  The best of both rounds counts, in whichever lane it was found."""
+    from paper_2304_14463_amd.inputs import graph_from_edges
+    rng = np.random.default_rng(n + C)
+    half = n // 2
+    edges = sorted({(u, half + int(v)) for u in range(half) for v in rng.integers(0, n - half, 4)} | {(u, u + 1) for u in range(half)})
+    size = np.full(n, 3)
+    size[rng.choice(half, smaller, replace=False)] = 2
+    g = graph_from_edges(n, edges, size, rng.integers(1, 9, n))
+    s = np.zeros((1, n * C), np.int32); e = s.copy(); a = np.zeros((1, n * C), np.uint8)
+    last = np.arange(n) * C
+    for u, v in edges:
+        last[u] = max(last[u], v * C)
+    s[0, ::C], e[0, ::C], a[0, ::C] = np.arange(n) * C, last, 1
+    budget, steps = int(oracle.evaluate(g, 0, C, s, e, a)[0, 0]) // 3, 30
+    gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, budget, C)
+    ds, de, da = to_dev(*(np.repeat(x, B, 0) for x in (s, e, a)))
+    count = moc.moc_search_cuts(gh, ds, de, da, steps).cpu().numpy()
+    k, ws, we, wa = oracle.search_cuts(g, budget, C, s[0], e[0], a[0], steps)
+    assert k > 1
+    assert (count == k).all()
+    assert (da.cpu().numpy() == wa).all() and (ds.cpu().numpy() == ws).all() and (de.cpu().numpy() == we).all()
+    gh.free()
+
+
 @pytest.mark.parametrize("call", ["cuts", "two_phase"])
 def test_more_candidates_than_a_launch_takes(moc, call):
     """2^21 candidates go into a launch of a descent: a batch that needs a second one, whose
