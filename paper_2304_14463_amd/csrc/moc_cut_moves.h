@@ -473,7 +473,8 @@ __device__ __forceinline__ void score_cuts(const GraphView& g, const A& lists, c
 // Eight lanes score a move: the lists of a node's inputs and consumers and the blocks at the ends of a range
 // of positions are taken by the lanes side by side, and every stretch of the profile that a move changes
 // has a lane of its own.  One lane per move left 3 waves of 4 (15 of 16) idle through a chain of dependent
-// reads: n = 442, cuts that keep inputs, 12 to 15 us a step, now 3.3; n = 1000, plain cuts, 3.7, now 1.3.
+// reads: n = 442, cuts that keep inputs, 12 to 15 us a step, now 3.3; n = 1000, plain cuts, 3.7, now 1.3.  (Plain cuts
+// of which there are many go by lanes all the same where workgroups share a compute unit: kByLanes below.)
 struct SiftLds {
   uint32_t* moves;       // [cap] the moves that passed
   uint32_t* where;       // [cap] u*C << 16 | start of the consumer's copy
@@ -484,9 +485,10 @@ struct SiftLds {
   int cap;
 };
 
-// Lanes that score a move (four: n = 442, 1024 walkers 802 us instead of 758 and, on other inputs, 1259 instead
-// of 1184), and moves that are scored before the bounds of the others are looked at: as many as the groups of 256
-// threads (64 / 32 / 16 / 8: 721 / 676 / 684 / 689 us; n = 1000, 32 walkers 317 / 314 / 313 / 411).
+// Lanes that score a move (four: n = 442, 1024 walkers, two phases 802 us instead of 758 and, on other inputs, 1259
+// instead of 1184; on the first kernel with groups), and moves that are scored before the bounds of the others are
+// looked at (16 / 32 / 64: keeping cuts, n = 442, 1024 walkers 537 / 542 / 567 us, 32 walkers 410 / 405 / 390; plain
+// cuts, n = 1000, 32 walkers 565 / 504 / 443, training graph 275 / 277 / 278, 1024 walkers 660 / 651 / 681).
 constexpr int kGroup = 8, kFirstRound = 32;
 constexpr int kNoBound = 0x7FFFFFFF;   // of a move that is of no use
 
@@ -545,7 +547,8 @@ __device__ __forceinline__ InOut group_range_maxima(const BaseLds& L, int blocks
 }
 
 // score_cut for a base without violations, by a group: false also for a move that raises the violations or
-// the peak.  WIDE: for graphs with nodes of many inputs.  (Loops that groups leave at different times carry integers, not booleans, to their end.)
+// the peak.  It says for such a base what find_cut and score_cut say for any: a change to the rule of the move has to
+// be made in both.  WIDE: for graphs with nodes of many inputs.  (Loops that groups leave at different times carry integers, not booleans, to their end.)
 template <int MODE, bool WIDE, typename A>
 __device__ __forceinline__ bool score_cut_by_group(const A& lists, int C, bool parallel, const BaseLds& L, const MvLayout& lay,
                                                    int ub, int t, int base_peak, const PeakCount& at_peak, CutScore& out,

@@ -249,10 +249,11 @@ void decode_kernel(GraphView G, int64_t B, const int32_t* __restrict__ starts, c
 //    use (Eq. (4) by events).
 // 4. The running sum's maximum.  Then the sequence is written out in 16-byte stores.
 //
-// Bound by HBM (295 MB read and written, 61 us at the rate of a copy), with the vector ALU and LDS about half
-// busy beside it.  n = 2000, C = 2, 8192 candidates: 124 us with one lane per edge, the last use of a
-// computation collected by atomic maxima (five passes), 81 us now.  Without the walk the kernel takes 61 us,
-// without storing the sequence 67, without anything else it does as long as with it.
+// Bound by HBM (295 MB read and written, 61 us at the rate of a copy), with the vector ALU 63 % and LDS 45 % busy
+// beside it.  n = 2000, C = 2, 8192 candidates: 124 us with one lane per edge, the last use of a
+// computation collected by atomic maxima (five passes, 824 vector and 114 LDS instructions per wave and
+// candidate); 81 us now (480 and 69).  Without the walk the kernel takes 61 us, without storing the sequence 67,
+// without anything else it does as long as with it.
 // Rows without an order, as many: 70 us (59 where each of them was found by an atomic on its start, at a cost
 // to the others; 81 with passes 2 and 3 in one, which is no quicker for the others); n = 1000, 4096 rows 18 us
 // (18; 25), n = 7000, 1000 rows 30 (36; 63), n = 3000, C = 1, 4096 rows 34 (23; 49): a row's loads are asked for

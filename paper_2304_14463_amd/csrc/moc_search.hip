@@ -3,7 +3,7 @@
 // first step to its last (gfx950).
 //
 // The base is staged once -- packed copies, profile with range maxima (moc_moves.h) -- and stays in
-// LDS: a step scores the moves, one lane each, chooses, edits the candidate's rows and the staged
+// LDS: a step scores the moves, eight lanes each, chooses, edits the candidate's rows and the staged
 // base alike, and brings the maxima up to date.  Nothing is read from global memory between two
 // steps, and a candidate that has come to its end costs nothing more.
 //
@@ -186,16 +186,15 @@ __device__ __forceinline__ Range merged_range(uint32_t pc, uint32_t pb, int size
 }
 
 // One workgroup per candidate, a step per merge applied: list the copies that have a merge, in
-// index order, as many as K; one lane per entry scores it; the feasible one of lowest duration,
+// index order, as many as K; eight lanes per entry score it; the feasible one of lowest duration,
 // then peak, then index is applied to the staged base and to the candidate's rows.  What bounds a
 // step is a chain of LDS latencies (list, walk over the node's edges, range maxima, tables), so
-// the workgroup is small and several share a compute unit: 256 threads for every size (n = 442, C = 2,
-// up to 32 steps of K = 64 by 256 / 512 / 1024 threads: 1024 walkers 251 / 386 / 840 us, 32 walkers
-// 217 / 213 / 239; where no step is found, staging alone, n = 2000, 256 walkers 32 / 25 / 20; taken with one
-// lane per entry).  1024 walkers at n = 442, up to 48 steps of K = 64: 0.18 ms (0.25 with one lane per entry,
-// whose edges one lane then walks one after the other).  (Every merge
-// written out as a row of its own and evaluated by moc_eval_batch, four launches a step: 19 ms on the
-// first of them, 9.8 the writing and 7.9 the evaluation.)
+// the workgroup is small and several share a compute unit: 256 threads for every size.  C = 2, up to 32 steps of
+// K = 64 by 256 / 512 / 1024 threads: n = 442, 1024 walkers 168 / 249 / 556 us, 32 walkers 136 / 135 / 162; one
+// walker to a compute unit would rather have 512: n = 2000, 256 walkers 376 / 270 / 268, training graph n = 1000
+// 243 / 186 / 212.  (1024 walkers at n = 442, up to 48 steps: 0.18 ms, 0.25 with one lane per entry, whose edges one
+// lane then walks one after the other; 19 with every merge written out as a row of its own and evaluated by
+// moc_eval_batch, four launches a step, 9.8 the writing and 7.9 the evaluation.)
 template <int CT, int NT, bool LISTS>
 __global__ __launch_bounds__(NT) void merge_kernel(GraphView g, int32_t* __restrict__ starts, int32_t* __restrict__ ends,
                                                    uint8_t* __restrict__ active, int K, int max_steps,
@@ -248,8 +247,8 @@ __global__ __launch_bounds__(NT) void merge_kernel(GraphView g, int32_t* __restr
     count = min(count, K);
     __syncthreads();
 
-    // ---- eight lanes per entry (moc_cut_moves.h), the node's inputs and consumers side by side.  key = (2^31 - 1 - w_v) << 32 | peak: the lowest duration, then the
-    // lowest peak; then the lowest copy index.
+    // ---- eight lanes per entry (moc_cut_moves.h), the node's inputs and consumers side by side.
+    // key = (2^31 - 1 - w_v) << 32 | peak: the lowest duration, then the lowest peak; then the lowest copy index.
     uint64_t best = ~0ull;
     int best_copy = 0x7FFFFFFF;
     const int gl = t & (kGroup - 1);

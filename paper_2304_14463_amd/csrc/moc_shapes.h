@@ -160,9 +160,12 @@ struct DescendShape {
 // As many threads per candidate as the candidates that share a compute unit leave room for (a
 // thread takes about 96 registers): a step is a chain of short phases, which more waves shorten,
 // but a wave with nothing to do in a phase still takes its part of the barriers and the issue
-// slots.  C = 2, microseconds with 256 / 512 / 1024 threads: n = 442, 1024 walkers, keeping cuts 763 /
-// 1078 / 1877, plain cuts 512 walkers 554 / 538 / 1072, 256 walkers 507 / 474 / 545; n = 1000, 1024
-// walkers 1640 / 1386 / 2409, 32 walkers 598 / 450 / 427.  Without the adjacency lists in LDS: 1024.
+// slots.  C = 2, 32 steps, microseconds with 256 / 512 / 1024 threads: keeping cuts, n = 442, 1024 walkers 539 /
+// 850 / 1556, 512 walkers 465 / 437 / 798, 256 walkers 434 / 390 / 413, 32 walkers 423 / 386 / 405; n = 1000, 1024
+// walkers 1471 / 1137 / 1859, 32 walkers 693 / 495 / 484; plain cuts, n = 442, 1024 walkers 519 / 851 / 1501, 512
+// walkers 454 / 443 / 766, 256 walkers 423 / 399 / 400; n = 1000, 512 walkers 709 / 556 / 1012, 32 walkers 631 / 462
+// / 501, training graph 385 / 292 / 276.  (With one walker to a compute unit neither 512 nor 1024 is the better
+// one throughout.)  Without the adjacency lists in LDS: 1024.
 inline DescendShape descend_shape(int T, int n, int m, int64_t B, int num_cu, int max_lds) {
   const auto layout = [&](int nt, int cap) { return mv_layout(T, n, m, descend_words(nt) + sift_words(n, cap), true, max_lds); };
   const int64_t share = (B + num_cu - 1) / num_cu;
@@ -170,11 +173,11 @@ inline DescendShape descend_shape(int T, int n, int m, int64_t B, int num_cu, in
   const int nt = !layout(1024, 256).lists || share <= 1 || by_lds <= 1 ? 1024 : share <= 2 || by_lds <= 2 ? 512 : 256;
   // The lists of moves that pass the sieve: as long as costs neither a resident workgroup nor, down to
   // 512, the adjacency lists their place in LDS (32 walkers, 32 plain cuts, with 2048 and without the
-  // adjacency lists / with them and what then fits: n = 2500, C = 2 781 / 739 us, n = 3000, training
-  // graph 1106 / 1012; with them and 256, which overflows, n = 2790 784 / 811).  A list that overflows
+  // adjacency lists / with them and what then fits: n = 2500, C = 2 647 / 618 us, 512 walkers 1313 / 1251;
+  // n = 3000, training graph, and n = 2790 the same either way).  A list that overflows
   // costs the scoring of every move, a resident workgroup mostly more: 1024 walkers, 32 plain cuts,
-  // C = 2, 256 and one more workgroup / 512: n = 590 980 / 1374 us, n = 1320 1609 / 2460, n = 850
-  // 1625 / 1492, n = 1400, where most steps overflow, 2719 / 2455.
+  // C = 2, 256 and one more workgroup / 512: n = 590 869 / 1120 us, n = 1320 1294 / 2081, n = 850
+  // 1498 / 1422, n = 1400, where most steps overflow, 2379 / 1971.
   const int want = (int)std::min<int64_t>({share, by_lds, 1024 / nt});
   int cap = 2048;
   while (cap > 256 && (layout(nt, cap).bytes * std::max(want, 1) > max_lds || (!layout(nt, cap).lists && layout(nt, 512).lists))) cap /= 2;

@@ -227,8 +227,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT >= 512 ? 
 // The table, the best move, or both.  MODE 1: the cuts that keep the producer's inputs.  Bound by
 // instruction issue and LDS latency: scoring a move is some hundred instructions in a chain of reads.
 // n = 1000, C = 2, 2048 bases, plain cuts, table and best move: 303 us with one workgroup of 16 waves
-// per compute unit (adjacency lists of 32-bit words, prefix and suffix maxima per position), 87.5 us
-// now (on the same bases again and again; 94.5 on new ones); 126 us with the mode read at run time, whose
+// per compute unit (adjacency lists of 32-bit words, prefix and suffix maxima per position), 88 to
+// 90 us now (on the same bases again and again; 94 to 96 on new ones); 126 us with the mode read at run time, whose
 // registers cost a workgroup per compute unit.
 template <int CT, int NT, bool LISTS, int MODE>
 __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(NT == 1024 ? 4 : 6))) void cuts_kernel(GraphView g, int64_t B, const int32_t* __restrict__ starts,
