@@ -490,6 +490,10 @@ struct SiftLds {
 // looked at (16 / 32 / 64: keeping cuts, n = 442, 1024 walkers 537 / 542 / 567 us, 32 walkers 410 / 405 / 390; plain
 // cuts, n = 1000, 32 walkers 565 / 504 / 443, training graph 275 / 277 / 278, 1024 walkers 660 / 651 / 681).
 constexpr int kGroup = 8, kFirstRound = 32;
+// A producer with more consumers than this has a move for each, and each of them would walk them all for its bound:
+// it gets the one of plain cuts (C = 5, n = 1600, out-degrees falling as 200 / rank^0.7, 53 walkers, 24 steps, by 16 /
+// 32 / 64 / no limit 1155 / 1382 / 1936 / 4541 us; 30 consumers a node, n = 600, 32 walkers 6270 / 2008 / 2067 / 2011).
+constexpr int kLongList = 32;
 constexpr int kNoBound = 0x7FFFFFFF;   // of a move that is of no use
 
 static_assert(kBuckets == kWave, "one lane per bucket");
@@ -784,6 +788,10 @@ __device__ __forceinline__ bool best_cut_of_clean_base(const GraphView& g, const
       for (int c = 0; c < C; ++c) {
         const uint32_t pu = L.packed[ub + c];
         if (covers1(pu, (uint32_t)at)) sk = max(sk, (int)(pu & 0xFFFFu));
+      }
+      if (z1 - z0 > kLongList) {
+        note_bound(r, u, sk, at, 0);
+        continue;
       }
       const int p = last_free(L, sk, at - 1);
       int last = sk, useful = 0;
