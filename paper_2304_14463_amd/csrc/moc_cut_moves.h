@@ -487,9 +487,13 @@ struct SiftLds {
 
 // Lanes that score a move (four: n = 442, 1024 walkers, two phases 802 us instead of 758 and, on other inputs, 1259
 // instead of 1184; on the first kernel with groups), and moves that are scored before the bounds of the others are
-// looked at (16 / 32 / 64: keeping cuts, n = 442, 1024 walkers 537 / 542 / 567 us, 32 walkers 410 / 405 / 390; plain
-// cuts, n = 1000, 32 walkers 565 / 504 / 443, training graph 275 / 277 / 278, 1024 walkers 660 / 651 / 681).
-constexpr int kGroup = 8, kFirstRound = 32;
+// looked at.  With 16 / 32 / 64 of them, several walkers to a compute unit: keeping cuts, n = 442, 1024 walkers 537 /
+// 542 / 567 us, plain cuts, training graph, n = 1000, 1024 walkers 660 / 651 / 681.  One walker to a compute unit, whose
+// 128 groups take more at once: keeping cuts, n = 442, 32 walkers 410 / 405 / 390; plain cuts, n = 1000, 32 walkers 565 /
+// 504 / 443, training graph 275 / 277 / 278; with 32 / 64 / 128, out-degrees falling as 200 / rank^0.7, n = 1903, 97
+// walkers, 1460 / 729 / 377, n = 737, 72 walkers 236 / 79 / 75, but the training graph 277 / 278 / 292.
+constexpr int kGroup = 8;
+constexpr int first_round_moves(int nt) { return nt == 1024 ? 64 : 32; }
 // A producer with more consumers than this has a move for each, and each of them would walk them all for its bound:
 // it gets the one of plain cuts (C = 5, n = 1600, out-degrees falling as 200 / rank^0.7, 53 walkers, 24 steps, by 16 /
 // 32 / 64 / no limit 1155 / 1382 / 1936 / 4541 us; 30 consumers a node, n = 600, 32 walkers 6270 / 2008 / 2067 / 2011).
@@ -836,13 +840,13 @@ __device__ __forceinline__ bool best_cut_of_clean_base(const GraphView& g, const
   const float scale = (float)(kBuckets - 1) / (float)max(1, base_peak - lo_bound);
   auto bucket_of = [&](uint32_t bound) { return min(kBuckets - 1, (int)((float)((int)bound - lo_bound) * scale)); };
   int last_bucket = kBuckets - 1;
-  if (passed > kFirstRound) {
+  if (passed > first_round_moves(NT)) {
     for (int r = t; r < passed; r += NT)
       if (S.bounds[r] != (uint32_t)kNoBound) atomicAdd(&S.hist[bucket_of(S.bounds[r])], 1);
     __syncthreads();
     const int below = scan_sum(S.hist[lane]);
-    last_bucket = max((int)__popcll(__ballot(below <= kFirstRound)) - 1, 0);
-    if (S.hist[0] > kFirstRound) last_bucket = 0;
+    last_bucket = max((int)__popcll(__ballot(below <= first_round_moves(NT))) - 1, 0);
+    if (S.hist[0] > first_round_moves(NT)) last_bucket = 0;
   }
   auto pick = [&](int slot_of_count, auto wanted) {   // entries for which `wanted` holds, to `picked`
     for (int r0 = wave * kWave; r0 < passed; r0 += NT) {
