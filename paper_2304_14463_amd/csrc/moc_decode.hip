@@ -805,7 +805,7 @@ extern "C" int moc_decode_batch(const moc_graph* g, int64_t B, const int32_t* st
     return MOC_OK;
   };
   if (g->slices) {   // C <= 4
-    const DecodeShape shape = decode_shape(v.n, v.C);
+    const DecodeShape shape = decode_shape(v.n, v.C, B, g->num_cu);
     const int nt = shape.nt;
     const DfLayout lay = shape.lay;
     if (lay.bytes > g->max_lds) return MOC_EOVERFLOW;   // (fits wherever decode_fits holds)

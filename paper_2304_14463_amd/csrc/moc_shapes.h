@@ -73,16 +73,20 @@ struct DecodeShape {
 // lanes without a node still take their part of every pass.  By 64 / 128 / 256 / 512 / 1024 threads
 // (before: 512 for every size): n = 100, C = 2, 16384 candidates 17.6 / 24.3 / 39.8 / 71.4 / 137 us
 // (before 72.1); n = 442, 4096 candidates - / 14.5 / 17.7 / 26.5 / 46.2 (29.8); n = 1000, 4096
-// candidates - / - / 24.9 / 31.0 / 49.6 (44.1).  With batches that leave compute units idle (n = 442, 16
-// candidates; n = 2000, 128) every choice takes as long as the launch.  n = 2500, 2000 candidates: 1024
-// threads 35.0 (44.1).
+// candidates - / - / 24.9 / 31.0 / 49.6 (44.1); n = 2500, 2000 candidates: 1024 threads 35.0 (44.1).  A batch of one
+// candidate to a compute unit or less waits for the longest walk of a wave, and gets as many threads as it has nodes: 30
+// consumers a node, n = 454, up to 256 candidates 13.5 us with as few as hold it, 8.8 with these (9.1), and as long as the
+// launch where nodes have few consumers either way; with two candidates to a compute unit 14.8 and 9.8 (12.6), but
+// training graph, n = 1000, 8.7 and 9.9.
 // In rounds: n = 4500, C = 2, 2000 candidates 80 us (127); n = 7000, 1000 candidates 64 (95); n = 2500, C = 3,
 // 2000 candidates 61 (79); n = 16340, C = 1, 1000 candidates 106 (157).
-inline DecodeShape decode_shape(int n, int C) {
+inline DecodeShape decode_shape(int n, int C, int64_t B = INT64_MAX, int num_cu = 1) {
   int nt = 64;
   const auto holds = [&](int t) { return n <= node_slots(C) * t && df_layout(n, C, t, false).T_pad <= 8 * t; };
   while (nt < 1024 && !holds(nt)) nt *= 2;
   const bool loop = !holds(nt);
+  if (B <= num_cu)
+    while (nt < 1024 && nt < n) nt *= 2;
   return DecodeShape{nt, loop, df_layout(n, C, nt, loop)};
 }
 

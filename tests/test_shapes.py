@@ -25,7 +25,9 @@ int main(int argc, char** argv) {
         const int rounds = s.loop ? 2 : 1;   // the kernel's
         const bool covered = C <= 4 && s.lay.bytes <= kMaxLds && s.lay.T_pad <= 8 * s.nt * rounds && (s.loop || n <= node_slots(C) * s.nt);
         const int any = dc_layout(n, C).bytes;
-        printf("%d %d %d %d %d %d\n", C, n, decode_fits(n, C, kMaxLds), covered, s.nt, any);
+        const DecodeShape few = decode_shape(n, C, 256, 256);   // a small batch
+        const bool as_well = few.loop == s.loop && few.nt >= s.nt && few.nt <= 1024 && (few.nt >= n || few.nt == 1024) && (C > 4 || few.lay.bytes <= kMaxLds);
+        printf("%d %d %d %d %d %d %d\n", C, n, decode_fits(n, C, kMaxLds), covered, s.nt, any, as_well);
       }
   if (argc == 5 && !strcmp(argv[1], "descend")) {   // C, edges per node, candidates
     const int C = atoi(argv[2]);
@@ -84,9 +86,10 @@ def test_descent_keeps_the_adjacency_lists(shapes, C, edges, B):
 def test_decode_kernels_hold_every_size_the_call_takes(shapes):
     """C <= 4: the kernel with one lane per node at every size, with as few threads as hold the candidate;
     more copies: the one for any C.  The largest sizes are those of the call's first kernels."""
-    C, n, fits, covered, nt, any_bytes = shapes("decode").T
+    C, n, fits, covered, nt, any_bytes, few_as_well = shapes("decode").T
     fits, few = fits == 1, C <= 4
     assert (covered[fits & few] == 1).all(), n[fits & few & (covered == 0)]
+    assert (few_as_well[fits & few] == 1).all()
     assert (any_bytes[fits & ~few] <= 160 * 1024).all()
     assert [int(n[fits & (C == c)].max()) for c in range(1, 9)] == [16367, 8183, 5115, 4091, 3273, 2727, 2338, 2045]
     for c, per_lane in ((1, 4), (2, 4), (3, 2), (4, 2)):
