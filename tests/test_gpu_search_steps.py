@@ -338,6 +338,34 @@ def test_keeping_cuts_with_a_few_of_many_inputs_kept(moc, C, inputs, B, duplicat
     gh.free()
 
 
+@pytest.mark.parametrize("mode", [0, 1])
+@pytest.mark.parametrize("C,n,B,consumers", [(2, 120, 3, 31), (2, 120, 3, 34), (2, 180, 600, 70), (2, 180, 1500, 40), (3, 150, 300, 60), (5, 100, 6, 50)])
+def test_cuts_of_producers_with_many_consumers(moc, mode, C, n, B, consumers):
+    """Producers read all along the schedule, on either side of the number of consumers from which the sieve of
+    the keeping cuts does not walk them."""
+    from paper_2304_14463_amd.inputs import graph_from_edges
+    rng = np.random.default_rng(n + consumers + C)
+    edges = {(v - 1, v) for v in range(1, n)} | {(int(u), v) for v in range(2, n) for u in rng.integers(max(0, v - 25), v, 2)}
+    for u in (2, 9, 17, 30):
+        edges |= {(u, int(v)) for v in rng.choice(np.arange(u + 1, n), min(consumers, n - u - 1), replace=False)}
+    size = rng.integers(1, 30, n)
+    size[[2, 9, 17, 30]] = rng.integers(400, 600, 4)
+    g = graph_from_edges(n, sorted(edges), size, rng.integers(1, 9, n))
+    s = np.zeros((1, n * C), np.int32); e = s.copy(); a = np.zeros((1, n * C), np.uint8)
+    last = np.arange(n) * C
+    for u, v in edges:
+        last[u] = max(last[u], v * C)
+    s[0, ::C], e[0, ::C], a[0, ::C] = np.arange(n) * C, last, 1
+    gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, 10, C)
+    ds, de, da = to_dev(*(np.repeat(x, B, 0) for x in (s, e, a)))
+    count = moc.moc_search_two_phase(gh, ds, de, da, 12, 0)[0] if mode == 1 else moc.moc_search_cuts(gh, ds, de, da, 12)
+    k, ws, we, wa = oracle.search_cuts(g, 10, C, s[0], e[0], a[0], 12, mode=mode)
+    assert k > 0
+    assert (count.cpu().numpy() == k).all()
+    assert (da.cpu().numpy() == wa).all() and (ds.cpu().numpy() == ws).all() and (de.cpu().numpy() == we).all()
+    gh.free()
+
+
 def wide_producers(rng):
     """Two large outputs, each made from more than 130 small ones that nothing else needs later and
     consumed far behind the peak: a keeping cut of one keeps all of its inputs.  The inputs are listed
