@@ -57,7 +57,7 @@
  * code.  Arguments are checked before anything is queued: with MOC_EINVAL,
  * MOC_EDEVICE or MOC_EOVERFLOW nothing has been queued on the stream.  MOC_EHIP
  * reports a failed HIP runtime call; from the calls that queue several kernels
- * (moc_search_two_phase, moc_search_moves, and moc_search_cuts above 2^21
+ * (moc_search_two_phase, and moc_search_cuts above 2^21
  * candidates) the kernels queued before the failing one still run.  Contents of a candidate are never an error: bad values are
  * violations.
  */
@@ -382,10 +382,10 @@ int moc_search_two_phase(const moc_graph* g, int64_t B, int32_t* starts, int32_t
  * move does not stays as it is from then on.
  *   starts, ends    device, [B][T], edited in place; active is only read
  *   R               radius of the moves, 1 <= R <= 32
- *   work_results    device, moc_result [B], 8-byte aligned: workspace
+ *   work_results    device, moc_result [B], 8-byte aligned: asked for, neither read nor written
  *   work_best       device, moc_best_move [B], 8-byte aligned: workspace
  *   out_steps       device, int32 [B]: number of moves applied
- * Queues max_steps + 1 kernels on the stream and returns; allocates
+ * Queues one kernel on the stream and returns; allocates
  * nothing.  Limits as moc_eval_neighbours; B <= 2^31 - 1.
  * Errors: MOC_EINVAL, MOC_EDEVICE, MOC_EOVERFLOW, MOC_EHIP.
  */

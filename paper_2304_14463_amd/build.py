@@ -27,11 +27,12 @@ HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-shared", "-fPIC",
 # Per source file.  The evaluation kernels are scheduled for instruction-level parallelism
 # rather than for occupancy (their workgroup sizes fix the waves per SIMD anyway): n = 5000,
 # C = 3 gains 1.7 points of HBM peak (64.4 -> 66.1 %; repeated on four machines), the other
-# evaluation workloads stay within what two runs differ by.  The neighbourhood kernel does not
-# move; decode, the staged evaluator, toggles and cuts stay within 2 % either way and keep the
-# default.
+# evaluation workloads stay within what two runs differ by.  The table of neighbourhood
+# scores takes 3 % less (n = 2000: 363 -> 352 us); decode, the staged evaluator, toggles and cuts stay
+# within 2 % either way and keep the default, and so does the best single-field move (4096 bases, n =
+# 442 52 us, 58 with it: more registers).
 FILE_FLAGS = {"moc_eval.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"],
-              "moc_neighbours.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
+              "moc_neighbours_table.hip": ["-mllvm", "-amdgpu-sched-strategy=max-ilp"]}
 
 
 def _run(cmd):

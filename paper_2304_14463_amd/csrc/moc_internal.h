@@ -101,6 +101,10 @@ int moc_eval_static_setup(int device);
 // MOC_EINVAL (an edge (v,v)), MOC_EOVERFLOW.
 int moc_check_cuts(const moc_graph* g);
 
+// moc_eval_neighbours with the table: queues its kernel (arguments checked by the caller).
+int moc_queue_neighbour_table(const moc_graph* g, int64_t B, const int32_t* starts, const int32_t* ends, const uint8_t* active,
+                              int32_t R, moc_move_score* out_moves, moc_best_move* out_best, hipStream_t stream);
+
 int moc_set_hip_error(hipError_t e);  // records e, returns MOC_EHIP
 
 #define MOC_HIP(call)                                  \

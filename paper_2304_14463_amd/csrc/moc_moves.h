@@ -95,7 +95,8 @@ struct StageSums {
 // formed MOC_DEAD | 1 << 16), deltas of Eq. (4) in the profile array, start bitmaps.  The first
 // loads go out before the arrays are cleared.  Starts with no barrier (the arrays must be free),
 // ends with one.
-template <int CT, int NT>
+// LOOP: there may be more copies than the threads ask for ahead.
+template <int CT, int NT, bool LOOP = true>
 __device__ __forceinline__ StageSums stage_copies(const GraphView& g, const BaseLds& L, const MvLayout& lay,
                                                   const int32_t* s_row, const int32_t* e_row, const uint8_t* a_row, int t) {
   constexpr int kAhead = 4;
@@ -135,7 +136,8 @@ __device__ __forceinline__ StageSums stage_copies(const GraphView& g, const Base
     const int k = j * NT + t;
     if (k < T) stage(k, as[j], ae[j], aa[j], asd[j]);
   }
-  for (int k = kAhead * NT + t; k < T; k += NT) stage(k, s_row[k], e_row[k], a_row[k], g.size_dur[k / C]);
+  if constexpr (LOOP)
+    for (int k = kAhead * NT + t; k < T; k += NT) stage(k, s_row[k], e_row[k], a_row[k], g.size_dur[k / C]);
   __syncthreads();
   return sums;
 }
@@ -170,9 +172,11 @@ __device__ __forceinline__ int count_order_and_inputs(const GraphView& g, const 
 }
 
 // profile <- running sums of the profile array (0 behind the last position), and level 0 of the
-// table.  A wave takes rows of 256 positions, four per lane.  Ends with a barrier.
-template <int NT>
-__device__ __forceinline__ void scan_profile(const BaseLds& L, const MvLayout& lay, int T, int t) {
+// table.  A wave takes rows of 256 positions, four per lane.  Ends with a barrier; between(): behind the barrier
+// that all threads have met at before (none with one wave).
+struct Nothing { __device__ __forceinline__ void operator()() const {} };
+template <int NT, typename F = Nothing>
+__device__ __forceinline__ void scan_profile(const BaseLds& L, const MvLayout& lay, int T, int t, F between = F{}) {
   constexpr int NW = NT / kWave;
   const int lane = t & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(t / kWave);
   const int words = lay.blocks * kBlk;
@@ -191,6 +195,7 @@ __device__ __forceinline__ void scan_profile(const BaseLds& L, const MvLayout& l
     if (lane == kWave - 1) L.scratch[wave] = sum;
     __syncthreads();
   }
+  between();
   int before = 0;
   for (int w = 0; w < wave; ++w) before += L.scratch[w];
   for (int r = r0; r < r1; ++r) {
@@ -215,14 +220,38 @@ __device__ __forceinline__ void scan_profile(const BaseLds& L, const MvLayout& l
   __syncthreads();
 }
 
+// The maxima before and from every block, by the last two waves; a barrier before they are read.
+template <int NT>
+__device__ __forceinline__ void maxima_before_and_from(const BaseLds& L, int blocks, int t) {
+  constexpr int NW = NT / kWave;
+  const int lane = t & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(t / kWave);
+  if (wave == NW - 1) {
+    int carry = 0;
+    for (int x0 = 0; x0 < blocks; x0 += kWave) {
+      const int x = x0 + lane;
+      const int incl = max(carry, scan_max(x < blocks ? L.table[x] : 0));
+      if (x < blocks) L.pre[x + 1] = incl;
+      carry = last_lane(incl);
+    }
+    if (lane == 0) { L.pre[0] = 0; L.suf[blocks] = 0; }
+  }
+  if (wave == (NW > 1 ? NW - 2 : 0)) {
+    int carry = 0;
+    for (int x0 = 0; x0 < blocks; x0 += kWave) {
+      const int x = blocks - 1 - (x0 + lane);
+      const int incl = max(carry, scan_max(x >= 0 ? L.table[x] : 0));
+      if (x >= 0) L.suf[x] = incl;
+      carry = last_lane(incl);
+    }
+  }
+}
+
 // The levels of the table above 0, three at a time by all threads (a barrier behind each three), and the
 // maxima before and from every block by the last two waves.  Ends with a barrier.  (All levels by one
 // wave, one after the other: n = 1000, a step of the descent 1.7 instead of 1.4 us, toggles at n = 2000 111.8
 // instead of 109.5.)
 template <int NT>
 __device__ __forceinline__ void build_maxima(const BaseLds& L, const MvLayout& lay, int t) {
-  constexpr int NW = NT / kWave;
-  const int lane = t & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(t / kWave);
   const int blocks = lay.blocks;
   for (int l = 0; l == 0 || l + 1 < lay.levels; l += 3) {
     const int step = 1 << l;   // blocks an entry of level l stands for
@@ -240,27 +269,7 @@ __device__ __forceinline__ void build_maxima(const BaseLds& L, const MvLayout& l
       if (x + 4 * step <= blocks) up2[x] = m4;
       if (x + 8 * step <= blocks) up3[x] = m8;
     }
-    if (l == 0) {
-      if (wave == NW - 1) {
-        int carry = 0;
-        for (int x0 = 0; x0 < blocks; x0 += kWave) {
-          const int x = x0 + lane;
-          const int incl = max(carry, scan_max(x < blocks ? L.table[x] : 0));
-          if (x < blocks) L.pre[x + 1] = incl;
-          carry = last_lane(incl);
-        }
-        if (lane == 0) { L.pre[0] = 0; L.suf[blocks] = 0; }
-      }
-      if (wave == (NW > 1 ? NW - 2 : 0)) {
-        int carry = 0;
-        for (int x0 = 0; x0 < blocks; x0 += kWave) {
-          const int x = blocks - 1 - (x0 + lane);
-          const int incl = max(carry, scan_max(x >= 0 ? L.table[x] : 0));
-          if (x >= 0) L.suf[x] = incl;
-          carry = last_lane(incl);
-        }
-      }
-    }
+    if (l == 0) maxima_before_and_from<NT>(L, blocks, t);
     __syncthreads();
   }
 }
@@ -329,7 +338,7 @@ __device__ __forceinline__ int where_off(int on, int v) {
   asm("v_bfi_b32 %0, %1, 0, %2" : "=v"(r) : "v"(on), "v"(v));
   return r;
 }
-template <bool OUTSIDE>
+template <bool OUTSIDE, bool LEVELS = true>   // without LEVELS: the table has its level 0 only, the range is short
 __device__ __forceinline__ InOut range_maxima(const BaseLds& L, int blocks, int lo, int hi) {
   const int bl = (int)((uint32_t)lo / kBlk), bh = (int)((uint32_t)hi / kBlk);
   const int4* const fl = reinterpret_cast<const int4*>(L.profile + bl * kBlk);
@@ -337,7 +346,11 @@ __device__ __forceinline__ InOut range_maxima(const BaseLds& L, int blocks, int 
   const int4 l0 = fl[0], l1 = fl[1], h0 = fh[0], h1 = fh[1];
   const int first = bl + 1, count = bh - first;   // whole blocks between
   InOut r{0, 0};
-  if (count > 0) r.in = blocks_maximum(L, blocks, first, count);
+  if constexpr (LEVELS) {
+    if (count > 0) r.in = blocks_maximum(L, blocks, first, count);
+  } else {
+    for (int x = first; x < bh; ++x) r.in = max(r.in, L.table[x]);
+  }
   if constexpr (OUTSIDE) r.out = max(L.pre[bl], L.suf[bh + 1]);
   // bit j: position j of the block lies in the range
   uint32_t ml = 0xFFu << (lo & (kBlk - 1)), mh = 0xFFu >> (kBlk - 1 - (hi & (kBlk - 1)));

@@ -145,6 +145,57 @@ inline bool moves_fit(int T, int max_lds) {
   return 4 * words <= max_lds;
 }
 
+// ------------------------------------------------------------------ the best single-field move (moc_best_moves.h)
+// The largest T the calls on single-field moves take: what the table's kernel keeps in LDS with 1024 threads.
+inline bool neighbours_fit(int T, int max_lds) {
+  const int T_pad = (T + 3) & ~3, bits = (T + 31) / 32, masks = 2 * ((T + 63) / 64);
+  return 4 * (4 * T_pad + T_pad / 2 + 8 + 2 * bits + 2 * masks + 8 * 16 + 16) <= max_lds;
+}
+
+// Word offsets; the profile at 0.
+struct BmLayout {
+  MvLayout base;   // what the staging of a base needs of it
+  int counts, red, queue;
+  int cap;         // fields that wait for their scoring, at most
+  int bytes;
+};
+constexpr int kBmCounts = 16;
+inline BmLayout bm_layout(int T, int nt) {
+  BmLayout l{};
+  MvLayout& b = l.base;
+  b.blocks = (T + kBlk - 1) / kBlk;
+  b.levels = 1;
+  b.bit_words = 2 * ((T + 63) / 64);
+  b.table = b.blocks * kBlk;
+  b.pre = b.table + b.blocks;
+  b.suf = b.pre + b.blocks + 1;
+  b.packed = (b.suf + b.blocks + 1 + 3) & ~3;
+  b.occ1 = b.packed + ((T + 3) & ~3);
+  b.occ2 = b.occ1 + b.bit_words;
+  b.peak_bits = b.peak_before = b.occ2;   // not used
+  b.scratch = b.occ2 + b.bit_words;
+  b.extra = l.counts = (b.scratch + kScratchWords + 3) & ~3;
+  l.red = l.counts + kBmCounts;
+  l.queue = l.red + T;
+  l.cap = 2 * nt;
+  l.bytes = 4 * (l.queue + l.cap / 2);
+  return l;
+}
+
+// Threads per base: a chain of short passes, which more waves shorten as long as a base feeds them and the bases
+// of a compute unit do not compete.  C = 2, R = 8, microseconds by 256 / 512 / 1024 threads
+// (before, with every field that could win scored: 256 to 1024 threads): n = 50, 1024 bases 19 / 28 / 53 (27); n = 442, 16 bases
+// 16.5 / 15.2 / 15.7 (26), 512 bases 22.5 / 20.2 / 29.6 (28), 1024 bases 22.7 / 28.4 / 50.4 (45), 4096 bases, R = 4 56 / 80 / 185 (114); n =
+// 1000, 300 bases 27.5 / 22.7 / 31.3 (43), 1024 bases 35.9 / 35.6 / 56.4 (72); n = 2000, 512 bases 50 / 34 / 41 (72); n = 2500, C = 3, 100
+// bases 79 / 51 / 38 (135), 600 bases 215 / 134 / 98 (342).
+inline int best_threads(int T, int64_t B, int num_cu, int max_lds) {
+  const int64_t share = (B + num_cu - 1) / num_cu;
+  if (T <= 1024 && (share > 2 || T <= 256)) return 256;
+  if (T <= 2048) return 512;
+  // two workgroups of 1024 do not fit a compute unit (80 registers a thread)
+  return share > 1 && T <= 5000 && 2 * bm_layout(T, 512).bytes <= max_lds ? 512 : 1024;
+}
+
 // ------------------------------------------------------------------ the descent by cuts (moc_search.hip)
 constexpr int kMaxRanges = 65;   // stretches of the profile that are changed together: one per lane and the producer's
 constexpr int kCutWords = 6;     // of the chosen move

@@ -30,6 +30,19 @@ __device__ __forceinline__ int scan_max(int x) {
   x = max(x, lane_shift<0x143, 0xC>(x));
   return x;
 }
+__device__ __forceinline__ unsigned long long scan_max64(unsigned long long x) {
+  const auto step = [&](int lo, int hi) {
+    const unsigned long long o = (unsigned long long)(uint32_t)hi << 32 | (uint32_t)lo;
+    x = o > x ? o : x;
+  };
+  step(lane_shift<0x111, 0xF>((int)x), lane_shift<0x111, 0xF>((int)(x >> 32)));
+  step(lane_shift<0x112, 0xF>((int)x), lane_shift<0x112, 0xF>((int)(x >> 32)));
+  step(lane_shift<0x114, 0xF>((int)x), lane_shift<0x114, 0xF>((int)(x >> 32)));
+  step(lane_shift<0x118, 0xF>((int)x), lane_shift<0x118, 0xF>((int)(x >> 32)));
+  step(lane_shift<0x142, 0xA>((int)x), lane_shift<0x142, 0xA>((int)(x >> 32)));
+  step(lane_shift<0x143, 0xC>((int)x), lane_shift<0x143, 0xC>((int)(x >> 32)));
+  return x;
+}
 __device__ __forceinline__ int last_lane(int x) { return __builtin_amdgcn_readlane(x, kWave - 1); }
 
 // (sum, max prefix >= 0) of consecutive segments, one per lane, combined in lane order: each lane takes
