@@ -54,6 +54,37 @@ __device__ __forceinline__ void count_live_uncovered(int& viol, const Record<CT>
     asm(MOC_COVER_FIRST("%7") MOC_COVER_NEXT("%8") MOC_COVER_NEXT("%9") MOC_COVER_NEXT("%10") MOC_COVER_LAST_SE
         : MOC_COVER_REGS, "v"(pu.w[0]), "v"(pu.w[1]), "v"(pu.w[2]), "v"(pu.w[3]) : "scc", "vcc");
 }
+// The same as a lane mask.
+#define MOC_COVER_MASK                                                            \
+  "v_cmp_le_u32_sdwa %1, %3, %3 src0_sel:WORD_0 src1_sel:WORD_1\n\t"              \
+  "s_andn2_b64 %0, %1, %0"
+#define MOC_COVER_M1(U)                                                           \
+  "v_cmp_lt_u32_sdwa %0, " U ", %3 src0_sel:WORD_0 src1_sel:WORD_0\n\t"           \
+  "v_cmp_ge_u32_sdwa %1, " U ", %3 src0_sel:WORD_1 src1_sel:WORD_0\n\t"           \
+  "s_and_b64 %0, %0, %1\n\t"
+#define MOC_COVER_M(U)                                                            \
+  "v_cmp_lt_u32_sdwa %1, " U ", %3 src0_sel:WORD_0 src1_sel:WORD_0\n\t"           \
+  "v_cmp_ge_u32_sdwa %2, " U ", %3 src0_sel:WORD_1 src1_sel:WORD_0\n\t"           \
+  "s_and_b64 %1, %1, %2\n\t"                                                      \
+  "s_or_b64 %0, %0, %1\n\t"
+template <int CT>
+__device__ __forceinline__ lanemask live_uncovered_lanes(const Record<CT>& pu, uint32_t pv) {
+  lanemask m, t1, t2;
+  if constexpr (CT == 1)
+    asm(MOC_COVER_M1("%4") MOC_COVER_MASK : "=&s"(m), "=&s"(t1), "=&s"(t2) : "v"(pv), "v"(pu.w[0]) : "scc");
+  else if constexpr (CT == 2)
+    asm(MOC_COVER_M1("%4") MOC_COVER_M("%5") MOC_COVER_MASK : "=&s"(m), "=&s"(t1), "=&s"(t2) : "v"(pv), "v"(pu.w[0]), "v"(pu.w[1]) : "scc");
+  else if constexpr (CT == 3)
+    asm(MOC_COVER_M1("%4") MOC_COVER_M("%5") MOC_COVER_M("%6") MOC_COVER_MASK
+        : "=&s"(m), "=&s"(t1), "=&s"(t2) : "v"(pv), "v"(pu.w[0]), "v"(pu.w[1]), "v"(pu.w[2]) : "scc");
+  else
+    asm(MOC_COVER_M1("%4") MOC_COVER_M("%5") MOC_COVER_M("%6") MOC_COVER_M("%7") MOC_COVER_MASK
+        : "=&s"(m), "=&s"(t1), "=&s"(t2) : "v"(pv), "v"(pu.w[0]), "v"(pu.w[1]), "v"(pu.w[2]), "v"(pu.w[3]) : "scc");
+  return m;
+}
+#undef MOC_COVER_MASK
+#undef MOC_COVER_M1
+#undef MOC_COVER_M
 #undef MOC_COVER_FIRST
 #undef MOC_COVER_NEXT
 #undef MOC_COVER_LAST

@@ -33,6 +33,7 @@ __device__ __forceinline__ uint32_t lds_read_u16(uint32_t addr) { return *(const
   }
 MOC_MASK_CMP(u_lt, "v_cmp_lt_u32_e64 %0, %1, %2", "v")
 MOC_MASK_CMP(u_le, "v_cmp_le_u32_e64 %0, %1, %2", "v")
+MOC_MASK_CMP(u_eq, "v_cmp_eq_u32_e64 %0, %1, %2", "v")
 MOC_MASK_CMP(i_gt, "v_cmp_gt_i32_e64 %0, %1, %2", "v")
 // b the same in every lane (a scalar register)
 MOC_MASK_CMP(u_lt_k, "v_cmp_lt_u32_e64 %0, %1, %2", "s")

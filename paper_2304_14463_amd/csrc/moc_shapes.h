@@ -20,6 +20,34 @@ constexpr int staged_nodes_per_lane(int n, int C) {
   return C <= 4 && u <= 8 && u * C <= 16 ? u : 0;
 }
 
+// Threads per candidate of that kernel: two nodes a lane (four beyond 2048 nodes), so that no wave is idle in the
+// passes that every wave takes part in.  C = 2, microseconds with 64 / 128 / 256 / 512 / 1024 threads (before, with 512 for
+// every size): n = 50, 32000 candidates 20 / 30 / 53 / 103 / 202 (115); n = 100, 16384 candidates 17.5 / 19.5 / 30 / 55 / 106 (62);
+// n = 200, 8192 candidates 18.8 / 17.8 / 20 / 30 / 55 (35); n = 442, 16384 candidates - / 57 / 58 / 68 / 112 (77); n = 700, 8192 candidates
+// - / - / 50 / 52.5 / 64 (56); n = 1000, 16384 candidates - / - / 103 / 98.6 / 127 (105); n = 2000, 4096 candidates - / - / - / 69 / 60
+// (85), 512 candidates 13.4 / 11.6 with 512 / 1024 (15.1).
+inline int staged_threads(int n) {
+  int nt = 64;
+  while (2 * nt < n && nt < 1024) nt *= 2;
+  return nt;
+}
+struct SfLayout {
+  int cur_off, bucket_off, delta_off, red_off;   // word offsets; the copies' records at 0, one node more than the graph has
+  int chunk;   // delta entries per thread (odd: conflict-free strided reads)
+  int bytes;
+};
+inline SfLayout sf_layout(int n, int C, int nt) {
+  const int T = n * C;
+  SfLayout l;
+  l.chunk = ((T + 1 + nt - 1) / nt) | 1;
+  l.cur_off = T + C;                               // int32 [n]: per stage count, then end of the stage's bucket
+  l.bucket_off = l.cur_off + n;                    // uint16 [T]: node places, stage by stage
+  l.delta_off = l.bucket_off + (T + 1) / 2;        // int32 [nt * chunk]
+  l.red_off = (l.delta_off + nt * l.chunk + 3) & ~3;
+  l.bytes = 4 * (l.red_off + 16 + 4 * (nt / 64));
+  return l;
+}
+
 // ------------------------------------------------------------------ moc_decode_batch
 // The largest sizes the call takes: as many words as its first kernels kept in LDS, 2.5 per copy (C = 3:
 // starts in four 16-bit entries per node).

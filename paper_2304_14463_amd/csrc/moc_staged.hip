@@ -22,7 +22,7 @@
 // hold the few nodes recomputed in a stage, and the stage's own node).
 //
 // One workgroup per candidate at a time, one lane per node, all in LDS.
-#include "moc_cover.h"
+#include "moc_masks.h"
 #include "moc_shapes.h"
 #include "moc_wave.h"
 
@@ -263,7 +263,7 @@ __global__ __launch_bounds__(kNT) void eval_staged_general_kernel(GraphView g, c
 }
 
 // C <= 4: the copies of a lane's nodes are held in registers, the workgroup's next candidate is asked
-// for as soon as they are used.  U = nodes per lane, at least n / kNT (staged_nodes_per_lane).  What the renumbering needs for a
+// for as soon as they are used.  U = nodes per lane, at least n / NT (staged_threads).  What the renumbering needs for a
 // node's first copy follows from its place k alone: its start can only be slot k of stage k, the
 // highest slot of that stage, so that its rank is the last of the stage's; only the copies beyond
 // the first, which are few, are put into buckets and searched for.  An end at the last slot of its
@@ -271,9 +271,11 @@ __global__ __launch_bounds__(kNT) void eval_staged_general_kernel(GraphView g, c
 // stage's recomputed nodes up to its slot.  cur[j] holds, in the high bits, first the number of
 // distinct recomputed starts of stage j, then the offset of its bucket, then the end of the bucket;
 // bit 0 says whether the stage's own node starts there (it comes behind the bucket).
-// Bound by the vector ALU.  n = 1000, C = 2, 16384 candidates: 208 us with every copy put into a
-// bucket and searched for, correctly rounded square roots and the whole delta array scanned; 131 us
-// without these; 103 us with the wave scans and sums by lane shifts instead of the LDS crossbar.
+// Bound by the vector ALU (68 %) and by the barriers between the passes.  n = 1000, C = 2, 16384 candidates: 208 us
+// with every copy put into a bucket and searched for, correctly rounded square roots and the whole delta array
+// scanned; 131 us without these; 103 us with the wave scans and sums by lane shifts instead of the LDS crossbar; 98
+// us with predicates as lane masks and violations counted by the scalar unit, the further copies of a lane's nodes
+// taken together, and two and a half edges a node (vector instructions per wave and candidate 416 -> 337).
 __device__ __forceinline__ int stage_and_slot(uint32_t p, uint32_t* slot) {   // stage_of(p) and the slot in it
   int j = (int)(__builtin_amdgcn_sqrtf(8.0f * (float)p + 1.0f) * 0.5f - 0.5f);   // off by one at most: as in stage_of, with one more ulp (2^-7 at most) in the root
   int at = (int)(p - stage_start(j));
@@ -288,23 +290,24 @@ __device__ __forceinline__ int stage_and_slot(uint32_t p, uint32_t* slot) {   //
   return j;
 }
 
-template <int CT, int U, int EDGES>
-__global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(CT * U <= 4 && U <= 2 && CT <= 3 ? 8 : 4, 8)))
+template <int CT, int NT, int U, int EDGES>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CT * U <= 4 && U <= 2 && CT <= 3 ? 8 : 4, 8)))
 void eval_staged_kernel(GraphView g, const int32_t* __restrict__ place, int64_t B, const int32_t* __restrict__ starts,
                         const int32_t* __restrict__ ends, const uint8_t* __restrict__ active,
-                        moc_result* __restrict__ out, StLayout lay) {
-  extern __shared__ uint32_t st_raw[];
+                        moc_result* __restrict__ out, SfLayout lay) {
+  extern __shared__ uint32_t st_raw[];   // at LDS address 0; the records come first
+  constexpr int NW = NT / kWave;
+  uint32_t* const rec = st_raw;   // records of the copies; one more node that is never live
   int32_t* const cur = reinterpret_cast<int32_t*>(st_raw + lay.cur_off);
   uint16_t* const bucket = reinterpret_cast<uint16_t*>(st_raw + lay.bucket_off);
-  uint32_t* const rec = st_raw + lay.pj_off;   // records of the copies; one more node that is never live
   int32_t* const delta = reinterpret_cast<int32_t*>(st_raw + lay.delta_off);
-  int32_t* const red = reinterpret_cast<int32_t*>(st_raw + lay.red_off);
+  int32_t* const red = reinterpret_cast<int32_t*>(st_raw + lay.red_off);   // NW words, then four for each wave
   const int tid = threadIdx.x;
   const int n = g.n, T = g.T, m = g.m;
   const uint32_t D = (uint32_t)n * (uint32_t)(n + 1) / 2u;   // positions of the domain
 
-  for (int i = tid; i < kNT * lay.chunk; i += kNT) delta[i] = 0;
-  for (int j = tid; j < n; j += kNT) cur[j] = 0;
+  for (int i = tid; i < NT * lay.chunk; i += NT) delta[i] = 0;
+  for (int j = tid; j < n; j += NT) cur[j] = 0;
   if (tid < CT) rec[T + tid] = MOC_DEAD;
 
   int rs[U][CT], re[U][CT];
@@ -326,7 +329,7 @@ void eval_staged_kernel(GraphView g, const int32_t* __restrict__ place, int64_t 
     asm volatile("" : "+v"(t));
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const uint32_t off = (uint32_t)min(u * kNT + t, n - 1) * CT;   // lanes past the last node re-read it
+      const uint32_t off = (uint32_t)min(u * NT + t, n - 1) * CT;   // lanes past the last node re-read it
       const Ints sv = *reinterpret_cast<const Ints*>(s_row + off * 4u);
       const Ints ev = *reinterpret_cast<const Ints*>(e_row + off * 4u);
       const Flags f = *reinterpret_cast<const Flags*>(a_row + off);
@@ -346,7 +349,7 @@ void eval_staged_kernel(GraphView g, const int32_t* __restrict__ place, int64_t 
   int2 rsd[U];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const int v = min(u * kNT + tid, n - 1);
+    const int v = min(u * NT + tid, n - 1);
     rk[u] = place[v];
     rsd[u] = g.size_dur[v];
   }
@@ -354,7 +357,7 @@ void eval_staged_kernel(GraphView g, const int32_t* __restrict__ place, int64_t 
   uint32_t edge[EDGES > 0 ? EDGES : 1];
 #pragma unroll
   for (int x = 0; x < EDGES; ++x) {
-    const int at = x * kNT + tid;
+    const int at = x * NT + tid;
     edge[x] = at < m ? g.edge_pair_c[at] : no_edge;
   }
   __syncthreads();
@@ -364,96 +367,143 @@ void eval_staged_kernel(GraphView g, const int32_t* __restrict__ place, int64_t 
     asm volatile("" : "+v"(t_));
     const int lane = t_ & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(t_ / kWave);
     // ---- per node: Eq. (1), (2), (3), (7), (8) and the domain of the starts; count the distinct
-    //      usable starts per stage.  A start's register takes the copy's code: stage << 1 | first at
-    //      its position, -2 if not usable.
-    int viol = 0, dur = 0;
+    //      usable starts per stage.  Predicates are lane masks (moc_masks.h), violations are counted by the
+    //      scalar unit.
+    int viol = 0;   // of the wave
+    int dur = 0, viol_more = 0;
+    lanemask in_graph[U], live0[U], more[U][CT];   // lanes with a node; whose first copy is usable; further active copies
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int v = u * kNT + t_;
-      if (v < n) {
-        const int k = rk[u], w = rsd[u].y;
-        const uint32_t flags = ra[u];
-        const int e0 = re[u][0];
-        const bool act0 = (flags & 0xFFu) != 0;
-        const bool live0 = act0 && (uint32_t)rs[u][0] == stage_start(k) + (uint32_t)k && (uint32_t)rs[u][0] <= (uint32_t)e0 && (uint32_t)e0 < D;
-        viol += live0 ? 0 : 1;   // Eq. (2), (8) if it is active, Eq. (7) if it is not
-        dur += act0 ? w : 0;
-        rs[u][0] = live0 ? k << 1 | 1 : -2;
-        if (live0) atomicAdd(&cur[k], 1);
-        if constexpr (CT > 1) {
-          int prev_end = live0 ? e0 : -1;   // end of the node's latest usable copy so far
+      const int left = n - (u * NT + wave * kWave);   // the same in all lanes
+      in_graph[u] = left >= kWave ? ~(lanemask)0 : left > 0 ? ((lanemask)1 << left) - 1 : 0;
+      const lanemask act = byte0_ne_k(ra[u], 0u) & in_graph[u];
+      const uint32_t s = (uint32_t)rs[u][0], e = (uint32_t)re[u][0], own = stage_start(rk[u]) + (uint32_t)rk[u];
+      live0[u] = act & u_eq(s, own) & u_le(s, e) & u_lt_k(e, D);
+      viol += count(in_graph[u] & ~live0[u]);   // Eq. (2), (8) if it is active, Eq. (7) if it is not
+      dur += (int)pick(act, (uint32_t)rsd[u].y);
+      if (lanes(live0[u])) atomicAdd(&cur[rk[u]], 1);
 #pragma unroll
-          for (int i = 1; i < CT; ++i) {
-            const int s = rs[u][i], e = re[u][i];
-            int code = -2;
-            if ((flags >> (8 * i)) & 0xFFu) {
-              dur += w;
-              bool live = (uint32_t)s <= (uint32_t)e && (uint32_t)e < D;
-              uint32_t slot = 0;
-              const int j = stage_and_slot(live ? (uint32_t)s : 0u, &slot);
-              live = live && slot == (uint32_t)k;
-              if (live) {
-                viol += prev_end > s ? 1 : 0;   // Eq. (3), on the positions as given
-                prev_end = e;
-                // Eq. (6): a usable start shares its position only with copies of its own node, which
-                // sit in the same stage; the first of them stands for the position
-                bool first_here = true;
+      for (int i = 1; i < CT; ++i) more[u][i] = byte_ne_k(ra[u], i, 0u) & in_graph[u];
+    }
+    // Further copies are few: those of a lane's first such node and copy are taken together, whatever their place
+    // among the lane's (`has`), and the others, which most waves have none of, one by one (`rest`; a start's
+    // register then holds the copy's code: stage << 1 | first at its position, -2 if not usable).
+    lanemask has = 0, rest = 0, usable = 0, opens = 0;   // opens: it is the first start at its position
+    int ps = 0, pe = 0, pk = 0, pat = 0, pj = 0, pw = 0, psz = 0;   // start, end, place, index, stage, duration, size of the one that is taken
+    if constexpr (CT > 1) {
+      int pend = -1;
 #pragma unroll
-                for (int q = 0; q < i; ++q) first_here = first_here && rs[u][q] >> 1 != j;
-                if (first_here) atomicAdd(&cur[j], 2);
-                else viol += 1;
-                code = j << 1 | (first_here ? 1 : 0);
-              } else {
-                viol += 1;   // Eq. (2), (8)
-              }
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int i = 1; i < CT; ++i) {
+          const lanemask here = more[u][i] & ~has;
+          rest |= more[u][i] & has;
+          has |= here;
+          if (u == 0 && i == 1) {
+            ps = rs[0][1]; pe = re[0][1]; pk = rk[0]; pat = t_ * CT + 1; pw = rsd[0].y; psz = rsd[0].x;
+            pend = (int)pick(live0[0], (uint32_t)re[0][0], 0xFFFFFFFFu);
+          } else {
+            ps = (int)pick(here, (uint32_t)rs[u][i], (uint32_t)ps);
+            pe = (int)pick(here, (uint32_t)re[u][i], (uint32_t)pe);
+            pat = (int)pick(here, (uint32_t)((u * NT + t_) * CT + i), (uint32_t)pat);
+            if (u > 0) {
+              pk = (int)pick(here, (uint32_t)rk[u], (uint32_t)pk);
+              pw = (int)pick(here, (uint32_t)rsd[u].y, (uint32_t)pw);
+              psz = (int)pick(here, (uint32_t)rsd[u].x, (uint32_t)psz);
+              pend = (int)pick(here, pick(live0[u], (uint32_t)re[u][0], 0xFFFFFFFFu), (uint32_t)pend);
             }
-            rs[u][i] = code;
           }
         }
+      if (has != 0) {
+        dur += (int)pick(has, (uint32_t)pw);
+        const lanemask formed = has & u_le((uint32_t)ps, (uint32_t)pe) & u_lt_k((uint32_t)pe, D);
+        uint32_t slot = 0;
+        pj = stage_and_slot(pick(formed, (uint32_t)ps), &slot);
+        usable = formed & u_eq(slot, (uint32_t)pk);
+        // Eq. (6): a usable start shares its position only with copies of its own node, which sit in the same stage;
+        // the first of them stands for the position.  Eq. (3) on the positions as given.
+        opens = usable & ~(~u_eq((uint32_t)pend, 0xFFFFFFFFu) & u_eq((uint32_t)pj, (uint32_t)pk));
+        viol += count(has & ~usable) + count(usable & ~opens) + count(usable & i_gt((uint32_t)pend, (uint32_t)ps));
+        if (lanes(opens)) atomicAdd(&cur[pj], 2);
+      }
+      if (rest != 0) {
+        lanemask before = 0;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          int end = (int)pick(live0[u], (uint32_t)re[u][0], 0xFFFFFFFFu);   // of the node's latest usable copy so far
+          int code[CT];
+          code[0] = (int)pick(live0[u], (uint32_t)(rk[u] << 1), 0xFFFFFFFEu);
+#pragma unroll
+          for (int i = 1; i < CT; ++i) {
+            const lanemask taken = more[u][i] & ~before;   // done above
+            const lanemask mine = more[u][i] & before;
+            before |= more[u][i];
+            const int s = rs[u][i], e = re[u][i];
+            code[i] = (int)pick(taken & usable, (uint32_t)(pj << 1), 0xFFFFFFFEu);
+            if (lanes(mine)) {
+              dur += rsd[u].y;
+              const bool formed = (uint32_t)s <= (uint32_t)e && (uint32_t)e < D;
+              uint32_t slot = 0;
+              const int j = stage_and_slot(formed ? (uint32_t)s : 0u, &slot);
+              if (formed && slot == (uint32_t)rk[u]) {
+                bool first_here = true;
+#pragma unroll
+                for (int q = 0; q < i; ++q) first_here = first_here && code[q] >> 1 != j;
+                if (first_here) atomicAdd(&cur[j], 2);
+                code[i] = j << 1 | (first_here ? 1 : 0);
+                viol_more += (first_here ? 0 : 1) + (end > s ? 1 : 0);
+              } else {
+                viol_more += 1;   // Eq. (2), (8)
+              }
+            }
+            rs[u][i] = code[i];
+            if (code[i] >= 0) end = e;
+          }
+        }
+        viol += last_lane(scan_sum(viol_more));
       }
     }
     __syncthreads();
 
     // ---- cur[j] <- offset of the stage's bucket, by a running sum of the starts in the stages before
-    int total = 0;   // distinct usable starts
+    int total;   // distinct usable starts
     {
-      constexpr int per = U;
-      const int j0 = t_ * per;
-      int c[per], sum = 0;
+      const int j0 = t_ * U;
+      int c[U], sum = 0;
 #pragma unroll
-      for (int d = 0; d < per; ++d) {
+      for (int d = 0; d < U; ++d) {
         c[d] = j0 + d < n ? cur[j0 + d] : 0;
         sum += (c[d] >> 1) + (c[d] & 1);
       }
       const int incl = scan_sum(sum);
       if (lane == kWave - 1) red[wave] = incl;
       __syncthreads();
-      int before = incl - sum;
+      const int upto = scan_sum_first<NW>(lane < NW ? red[lane] : 0);   // lane w: the waves up to w
+      total = __builtin_amdgcn_readlane(upto, NW - 1);
+      int before = incl - sum + (wave == 0 ? 0 : __builtin_amdgcn_readlane(upto, wave - 1));
 #pragma unroll
-      for (int w = 0; w < kNW; ++w) {
-        const int x = red[w];
-        before += w < wave ? x : 0;
-        total += x;
-      }
-#pragma unroll
-      for (int d = 0; d < per; ++d) {
+      for (int d = 0; d < U; ++d) {
         if (j0 + d < n) cur[j0 + d] = before << 1 | (c[d] & 1);
         before += (c[d] >> 1) + (c[d] & 1);
       }
-      total = __builtin_amdgcn_readfirstlane(total);
     }
     __syncthreads();
 
     // ---- buckets: the place of every node that is computed again in the stage
     if constexpr (CT > 1) {
+      if (lanes(opens)) bucket[atomicAdd(&cur[pj], 2) >> 1] = (uint16_t)pk;
+      if (rest != 0) {
+        lanemask before = 0;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        if (u * kNT + t_ >= n) continue;
+        for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int i = 1; i < CT; ++i) {
-          const int code = rs[u][i];
-          if (code >= 0 && (code & 1)) bucket[atomicAdd(&cur[code >> 1], 2) >> 1] = (uint16_t)rk[u];
-        }
+          for (int i = 1; i < CT; ++i) {
+            const lanemask mine = more[u][i] & before;
+            before |= more[u][i];
+            const int code = rs[u][i];
+            if (lanes(mine))
+              if (code >= 0 && (code & 1)) bucket[atomicAdd(&cur[code >> 1], 2) >> 1] = (uint16_t)rk[u];
+          }
       }
       __syncthreads();
     }
@@ -476,25 +526,38 @@ void eval_staged_kernel(GraphView g, const int32_t* __restrict__ place, int64_t 
       }
       return rank_in_stage(j, slot + 1) - 1;
     };
+    auto settle = [&](int cs, uint32_t e, int size) -> uint32_t {
+      const int ce = rank_of_end(e);
+      atomicAdd(&delta[cs], size);
+      atomicSub(&delta[ce + 1], size);
+      return (uint32_t)cs | (uint32_t)ce << 16;
+    };
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int v = u * kNT + t_;
-      if (v >= n) continue;
-      uint32_t r[CT];
+      if (in_graph[u] == 0) continue;
+      const int v = u * NT + t_;
+      uint32_t r = MOC_DEAD;
+      if (lanes(live0[u])) r = settle(cur[rk[u]] >> 1, (uint32_t)re[u][0], rsd[u].x);
+      if (lanes(in_graph[u])) {
+        rec[v * CT] = r;
 #pragma unroll
-      for (int i = 0; i < CT; ++i) {
-        const int code = rs[u][i];
-        r[i] = MOC_DEAD;
-        if (code >= 0) {
-          const int cs = i == 0 ? cur[rk[u]] >> 1 : rank_in_stage(code >> 1, (uint32_t)rk[u]);
-          const int ce = rank_of_end((uint32_t)re[u][i]);
-          r[i] = (uint32_t)cs | (uint32_t)ce << 16;
-          atomicAdd(&delta[cs], rsd[u].x);
-          atomicSub(&delta[ce + 1], rsd[u].x);
-        }
+        for (int i = 1; i < CT; ++i) rec[v * CT + i] = MOC_DEAD;
       }
+    }
+    if constexpr (CT > 1) {   // (LDS operations of a wave complete in order: behind the words above)
+      if (lanes(usable)) rec[pat] = settle(rank_in_stage(pj, (uint32_t)pk), (uint32_t)pe, psz);
+      if (rest != 0) {
+        lanemask before = 0;
 #pragma unroll
-      for (int i = 0; i < CT; ++i) rec[v * CT + i] = r[i];
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+          for (int i = 1; i < CT; ++i) {
+            const lanemask mine = more[u][i] & before;
+            before |= more[u][i];
+            if (lanes(mine))
+              if (rs[u][i] >= 0) rec[(u * NT + t_) * CT + i] = settle(rank_in_stage(rs[u][i] >> 1, (uint32_t)rk[u]), (uint32_t)re[u][i], rsd[u].x);
+          }
+      }
     }
     if (b + gridDim.x < B) request(b + gridDim.x);   // the rest of this turn works from LDS
     __syncthreads();
@@ -503,7 +566,7 @@ void eval_staged_kernel(GraphView g, const int32_t* __restrict__ place, int64_t 
     // last of them change no maximum but are cleared)
     int S = 0, P = 0;
     {
-      const int chunk = ((total + 1 + kNT - 1) / kNT) | 1;   // <= lay.chunk
+      const int chunk = ((total + 1 + NT - 1) / NT) | 1;   // <= lay.chunk
       int own = t_;
       asm volatile("" : "+v"(own));
       int32_t* d = delta + own * chunk;
@@ -515,65 +578,80 @@ void eval_staged_kernel(GraphView g, const int32_t* __restrict__ place, int64_t 
       }
       combine_segments(S, P);
     }
-    for (int j = t_; j < n; j += kNT) cur[j] = 0;   // for the next candidate
+    for (int j = t_; j < n; j += NT) cur[j] = 0;   // for the next candidate
     // ---- Eq. (5): one lane per edge, every usable copy of the consumer
     auto check = [&](uint32_t pair) {
       Record<CT> pu, pv;
+      const uint32_t ua = (pair & 0xFFFFu) << 2, va = pair >> 16 << 2;   // LDS addresses
+      if constexpr (CT == 2) {
+        const uint2 a = lds_read2(ua), c = lds_read2(va);
+        pu.w[0] = a.x; pu.w[1] = a.y; pv.w[0] = c.x; pv.w[1] = c.y;
+      } else {
 #pragma unroll
-      for (int q = 0; q < CT; ++q) {
-        pu.w[q] = rec[(pair & 0xFFFFu) + q];
-        pv.w[q] = rec[(pair >> 16) + q];
+        for (int q = 0; q < CT; ++q) {
+          pu.w[q] = lds_read(ua + 4 * q);
+          pv.w[q] = lds_read(va + 4 * q);
+        }
       }
 #pragma unroll
-      for (int i = 0; i < CT; ++i) count_live_uncovered<CT>(viol, pu, pv.w[i]);
+      for (int i = 0; i < CT; ++i) viol += count(live_uncovered_lanes<CT>(pu, pv.w[i]));
     };
     if constexpr (EDGES > 0) {
 #pragma unroll
       for (int x = 0; x < EDGES; ++x) check(edge[x]);
     } else {
-      for (int x0 = 0; x0 < m; x0 += kNT) {   // every lane the same number of rounds
+      for (int x0 = 0; x0 < m; x0 += NT) {   // every lane the same number of rounds
         const uint32_t pair = g.edge_pair_c[min(x0 + t_, m - 1)];
         check(x0 + t_ < m ? pair : no_edge);
       }
     }
-    viol = scan_sum(viol);
     dur = scan_sum(dur);
-    if (lane == kWave - 1) {   // the lane that holds the wave's totals
-      int32_t* r = red + 8 + wave * 4;
-      r[0] = S; r[1] = P; r[2] = viol; r[3] = dur;
-    }
+    if (lane == kWave - 1)   // the lane that holds the wave's totals
+      *reinterpret_cast<int4*>(red + 16 + wave * 4) = make_int4(S, P, viol, dur);
     __syncthreads();
     // (no barrier behind this: the words read here are written again behind several)
-    if (t_ == 0) {
-      int S0 = 0, P0 = 0, V = 0, W = 0;
-      for (int w = 0; w < kNW; ++w) {
-        const int32_t* r = red + 8 + w * 4;
-        P0 = max(P0, S0 + r[1]);
-        S0 += r[0];
-        V += r[2];
-        W += r[3];
+    if (wave == 0) {
+      int4 r = *reinterpret_cast<const int4*>(red + 16 + min(lane, NW - 1) * 4);
+      combine_first<NW>(r.x, r.y);
+      const int V = scan_sum_first<NW>(r.z), W = scan_sum_first<NW>(r.w);
+      if (lane == NW - 1) {
+        moc_result res;
+        res.peak = r.y;
+        res.duration = W;
+        res.violations = V;
+        res.feasible = (V == 0 && (int64_t)r.y <= g.budget) ? 1 : 0;
+        out[b] = res;
       }
-      moc_result res;
-      res.peak = P0;
-      res.duration = W;
-      res.violations = V;
-      res.feasible = (V == 0 && (int64_t)P0 <= g.budget) ? 1 : 0;
-      out[b] = res;
     }
   }
 }
 
-using StagedKernel = void (*)(GraphView, const int32_t*, int64_t, const int32_t*, const int32_t*, const uint8_t*, moc_result*, StLayout);
+using StagedKernel = void (*)(GraphView, const int32_t*, int64_t, const int32_t*, const int32_t*, const uint8_t*, moc_result*, SfLayout);
 
-// The edges of a lane stay in registers where there are at most kEdges of them.
-constexpr int kEdges = 6;
-template <int CT, int U>
-StagedKernel pick_edges(int per_lane) {
+// The edges of a lane stay in registers where there are at most three to a node (of two and a half a sixth less is padding).
+template <int CT, int NT, int U>
+StagedKernel pick_edges(int m) {
+  const int per_lane = (m + NT - 1) / NT;
+  if (per_lane <= 5 * U / 2) return eval_staged_kernel<CT, NT, U, 5 * U / 2>;
+  if (per_lane <= 3 * U) return eval_staged_kernel<CT, NT, U, 3 * U>;
+  return eval_staged_kernel<CT, NT, U, 0>;
+}
+template <int NT, int U>
+StagedKernel pick_copies(int C, int m) {
   if constexpr (U <= 2) {
-    if (per_lane <= 3) return eval_staged_kernel<CT, U, 3>;
-    if (per_lane <= kEdges) return eval_staged_kernel<CT, U, kEdges>;
+    if (C == 3) return pick_edges<3, NT, U>(m);
+    if (C == 4) return pick_edges<4, NT, U>(m);
   }
-  return eval_staged_kernel<CT, U, 0>;
+  return C == 1 ? pick_edges<1, NT, U>(m) : pick_edges<2, NT, U>(m);
+}
+StagedKernel pick_kernel(int nt, int n, int C, int m) {
+  switch (nt) {
+    case 64: return pick_copies<64, 2>(C, m);
+    case 128: return pick_copies<128, 2>(C, m);
+    case 256: return pick_copies<256, 2>(C, m);
+    case 512: return pick_copies<512, 2>(C, m);
+    default: return n <= 2048 ? pick_copies<1024, 2>(C, m) : pick_copies<1024, 4>(C, m);
+  }
 }
 
 }  // namespace
@@ -590,31 +668,21 @@ extern "C" int moc_eval_batch_staged(const moc_graph* g, int64_t B, const int32_
   if (dev != g->device) return MOC_EDEVICE;
   const StLayout lay = st_layout(g->view.n, g->view.C);
   if (lay.bytes > g->max_lds || g->view.T >= 0xFFFF) return MOC_EOVERFLOW;
-  const int edges = (g->view.m + kNT - 1) / kNT;
-  StagedKernel kern = eval_staged_general_kernel;
-  switch (g->view.C * 16 + staged_nodes_per_lane(g->view.n, g->view.C)) {
-    case 1 * 16 + 1: kern = pick_edges<1, 1>(edges); break;
-    case 1 * 16 + 2: kern = pick_edges<1, 2>(edges); break;
-    case 1 * 16 + 4: kern = pick_edges<1, 4>(edges); break;
-    case 1 * 16 + 8: kern = pick_edges<1, 8>(edges); break;
-    case 2 * 16 + 1: kern = pick_edges<2, 1>(edges); break;
-    case 2 * 16 + 2: kern = pick_edges<2, 2>(edges); break;
-    case 2 * 16 + 4: kern = pick_edges<2, 4>(edges); break;
-    case 2 * 16 + 8: kern = pick_edges<2, 8>(edges); break;
-    case 3 * 16 + 1: kern = pick_edges<3, 1>(edges); break;
-    case 3 * 16 + 2: kern = pick_edges<3, 2>(edges); break;
-    case 3 * 16 + 4: kern = pick_edges<3, 4>(edges); break;
-    case 4 * 16 + 1: kern = pick_edges<4, 1>(edges); break;
-    case 4 * 16 + 2: kern = pick_edges<4, 2>(edges); break;
-    case 4 * 16 + 4: kern = pick_edges<4, 4>(edges); break;
-    default: break;
-  }
+  const hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  const bool in_registers = staged_nodes_per_lane(g->view.n, g->view.C) > 0;
+  const int nt = in_registers ? staged_threads(g->view.n) : kNT;
+  const StagedKernel kern = in_registers ? pick_kernel(nt, g->view.n, g->view.C, g->view.m) : nullptr;
+  const SfLayout sf = sf_layout(g->view.n, g->view.C, nt);
+  const int bytes = in_registers ? sf.bytes : lay.bytes;
+  const void* const entry = in_registers ? reinterpret_cast<const void*>(kern) : reinterpret_cast<const void*>(eval_staged_general_kernel);
   int per_cu = 0;
-  if (const int rc = moc_kernel_occupancy(g, reinterpret_cast<const void*>(kern), kNT, lay.bytes, false, &per_cu)) return rc;
+  if (const int rc = moc_kernel_occupancy(g, entry, nt, bytes, in_registers, &per_cu)) return rc;
   const int64_t resident = (int64_t)per_cu * g->num_cu;
   const unsigned grid = (unsigned)(B < resident ? B : resident);
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(kNT), lay.bytes, static_cast<hipStream_t>(hip_stream), g->view,
-                     g->place, B, starts, ends, active, out, lay);
+  if (in_registers)
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(nt), bytes, stream, g->view, g->place, B, starts, ends, active, out, sf);
+  else
+    hipLaunchKernelGGL(eval_staged_general_kernel, dim3(grid), dim3(nt), bytes, stream, g->view, g->place, B, starts, ends, active, out, lay);
   MOC_HIP(hipGetLastError());
   return MOC_OK;
 }

@@ -63,4 +63,21 @@ __device__ __forceinline__ void combine_segments(int& S, int& P) {
   combine_earlier<0x143, 0xC>(S, P);
 }
 
+// The same over the first N <= 16 lanes, the others' values of no use.
+template <int N>
+__device__ __forceinline__ int scan_sum_first(int x) {
+  if constexpr (N > 1) x += lane_shift<0x111, 0xF>(x);
+  if constexpr (N > 2) x += lane_shift<0x112, 0xF>(x);
+  if constexpr (N > 4) x += lane_shift<0x114, 0xF>(x);
+  if constexpr (N > 8) x += lane_shift<0x118, 0xF>(x);
+  return x;
+}
+template <int N>
+__device__ __forceinline__ void combine_first(int& S, int& P) {
+  if constexpr (N > 1) combine_earlier<0x111, 0xF>(S, P);
+  if constexpr (N > 2) combine_earlier<0x112, 0xF>(S, P);
+  if constexpr (N > 4) combine_earlier<0x114, 0xF>(S, P);
+  if constexpr (N > 8) combine_earlier<0x118, 0xF>(S, P);
+}
+
 }  // namespace
