@@ -2,6 +2,7 @@
 
   paper_2304_14463_amd/libmoccasin_hip.so          the C-ABI evaluator (include/moccasin.h)
   paper_2304_14463_amd/inputs/libmoc_inputs_hip.so device twin of the candidate generator
+  paper_2304_14463_amd/_candidates.so              the native part of the Python binding (host code)
 
 hipcc cross-compiles without a GPU.  Run as `python -m paper_2304_14463_amd.build`.
 """
@@ -16,6 +17,7 @@ import tempfile
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libmoccasin_hip.so")
+BINDING = os.path.join(PKG, "_candidates.so")
 INPUTS_LIB = os.path.join(PKG, "inputs", "libmoc_inputs_hip.so")
 
 HIPCC_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-shared", "-fPIC",
@@ -68,8 +70,21 @@ def build_inputs():
     return _hipcc(INPUTS_LIB, srcs)
 
 
+def build_binding():
+    """Host code against torch's headers: g++, no HIP."""
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    lib_dir = os.path.join(os.path.dirname(torch.__file__), "lib")
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
+          *[f"-I{p}" for p in include_paths()], f"-I{sysconfig.get_paths()['include']}", "-o", BINDING,
+          os.path.join(PKG, "binding", "candidates.cpp"), f"-L{lib_dir}", f"-Wl,-rpath,{lib_dir}", "-ltorch_python", "-ltorch_cpu", "-lc10"])
+    return BINDING
+
+
 def build_all():
-    return [build_library(), build_inputs()]
+    return [build_binding(), build_library(), build_inputs()]
 
 
 if __name__ == "__main__":

@@ -16,6 +16,7 @@ _PKG = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_PKG, "libmoccasin_hip.so")
 _lib = None
 _torch = None
+_native = None
 
 MOC_MAX_T = 19455
 MOC_ABI_VERSION = 2
@@ -87,6 +88,8 @@ def lib():
         L.moc_strerror.restype = ctypes.c_char_p
         L.moc_last_hip_error.argtypes = []
         L.moc_last_hip_error.restype = ctypes.c_int
+        # the calls that _candidates.evaluate makes itself
+        L.address = {name: ctypes.cast(getattr(L, name), VP).value for name in ("moc_eval_batch", "moc_eval_batch_staged", "moc_eval_toggles")}
         _lib = L
     return _lib
 
@@ -160,34 +163,46 @@ def moc_graph_upload(n, in_ptr, in_idx, size, dur, budget, C) -> Graph:
     return Graph(h, n, m, int(C))
 
 
-def _cand_ptrs(g, B, starts, ends, active):
-    torch = _tc()
-    n = B * g.T
-    if not (starts.is_cuda and ends.is_cuda and active.is_cuda and starts.dtype is torch.int32 and ends.dtype is torch.int32
-            and active.dtype is torch.uint8 and starts.is_contiguous() and ends.is_contiguous() and active.is_contiguous()
-            and starts.numel() == n and ends.numel() == n and active.numel() == n):
-        raise ValueError("candidate arrays must be contiguous CUDA tensors [B][T]: int32, int32, uint8")
-    return starts.data_ptr(), ends.data_ptr(), active.data_ptr()
+def _candidates():
+    """The native part of the binding (binding/candidates.cpp), loaded on first use: it needs torch."""
+    global _native
+    if _native is None:
+        _tc()
+        from . import _candidates as native   # built with the library
+        _native = native
+    return _native
+
+
+def _cand_ptrs(g, starts, ends, active):
+    """(B, addresses of the three arrays)"""
+    return (_native or _candidates()).pointers(g.T, starts, ends, active)
+
+
+def _room(out, wanted, like, size, *dims):
+    """(tensor, address) of a result: the caller's, or a new one if it is wanted, or (None, None)"""
+    if out is not None:
+        return out, out.data_ptr()
+    return _candidates().empty(like, size, *dims) if wanted else (None, None)
+
+
+def _evaluate(name, g, starts, ends, active, out, per, size, stream):
+    code, out = (_native or _candidates()).evaluate((_lib or lib()).address[name], g._h.value if g._h is not None else None, g.T,
+                                                    starts, ends, active, out, per, size, _stream_handle(stream))
+    if code != 0:
+        raise MoccasinError(code, name)
+    return out
 
 
 def moc_eval_batch(g: Graph, starts, ends, active, out=None, stream=None):
     """Evaluate B candidates; returns a uint8 CUDA tensor [B][24] holding moc_result records
     (see results_to_numpy).  Asynchronous on `stream` (default: torch's current stream)."""
-    torch = _tc()
-    B = starts.numel() // g.T if g.T else 0
-    ps, pe, pa = _cand_ptrs(g, B, starts, ends, active)
-    if out is None:
-        out = torch.empty((B, RESULT_DTYPE.itemsize), dtype=torch.uint8, device=starts.device)
-    code = lib().moc_eval_batch(g._h, B, ps, pe, pa, out.data_ptr(), _stream_handle(stream))
-    _check(code, "moc_eval_batch")
-    return out
+    return _evaluate("moc_eval_batch", g, starts, ends, active, out, 0, RESULT_DTYPE.itemsize, stream)
 
 
 def moc_eval_batch_noalloc(g: Graph, starts, ends, active, out, stream=None):
     """moc_eval_batch with the work counters in the library's static device array; `out` is the
     caller's uint8 CUDA tensor [B][24].  Nothing is allocated, here or in the library."""
-    B = starts.numel() // g.T if g.T else 0
-    ps, pe, pa = _cand_ptrs(g, B, starts, ends, active)
+    B, ps, pe, pa = _cand_ptrs(g, starts, ends, active)
     if not (out.is_cuda and out.is_contiguous() and out.numel() * out.element_size() >= B * RESULT_DTYPE.itemsize):
         raise ValueError("out must be a contiguous CUDA tensor of at least B * 24 bytes")
     code = lib().moc_eval_batch_noalloc(g._h, B, ps, pe, pa, out.data_ptr(), _stream_handle(stream))
@@ -204,31 +219,17 @@ def moc_graph_set_order(g: Graph, order):
 def moc_eval_batch_staged(g: Graph, starts, ends, active, out=None, stream=None):
     """Evaluate B candidates in the stage-restricted domain; returns a uint8 CUDA tensor [B][24]
     of moc_result records."""
-    torch = _tc()
-    B = starts.numel() // g.T if g.T else 0
-    ps, pe, pa = _cand_ptrs(g, B, starts, ends, active)
-    if out is None:
-        out = torch.empty((B, RESULT_DTYPE.itemsize), dtype=torch.uint8, device=starts.device)
-    code = lib().moc_eval_batch_staged(g._h, B, ps, pe, pa, out.data_ptr(), _stream_handle(stream))
-    _check(code, "moc_eval_batch_staged")
-    return out
+    return _evaluate("moc_eval_batch_staged", g, starts, ends, active, out, 0, RESULT_DTYPE.itemsize, stream)
 
 
 def moc_eval_neighbours(g: Graph, starts, ends, active, R, want_moves=True, want_best=True, out_moves=None,
                         out_best=None, stream=None):
     """Score all single-field moves of B candidates.  Returns (moves, best): uint8 CUDA tensors
     [B][T*4R][8] (moc_move_score) and [B][16] (moc_best_move), or None where not requested."""
-    torch = _tc()
-    B = starts.numel() // g.T if g.T else 0
-    ps, pe, pa = _cand_ptrs(g, B, starts, ends, active)
-    if want_moves and out_moves is None:
-        out_moves = torch.empty((B, g.T * 4 * R, MOVE_SCORE_DTYPE.itemsize), dtype=torch.uint8, device=starts.device)
-    if want_best and out_best is None:
-        out_best = torch.empty((B, BEST_MOVE_DTYPE.itemsize), dtype=torch.uint8, device=starts.device)
-    code = lib().moc_eval_neighbours(
-        g._h, B, ps, pe, pa, int(R),
-        out_moves.data_ptr() if out_moves is not None else None,
-        out_best.data_ptr() if out_best is not None else None, _stream_handle(stream))
+    B, ps, pe, pa = _cand_ptrs(g, starts, ends, active)
+    out_moves, pm = _room(out_moves, want_moves, starts, 1, B, g.T * 4 * R, MOVE_SCORE_DTYPE.itemsize)
+    out_best, pb = _room(out_best, want_best, starts, 1, B, BEST_MOVE_DTYPE.itemsize)
+    code = lib().moc_eval_neighbours(g._h, B, ps, pe, pa, int(R), pm, pb, _stream_handle(stream))
     _check(code, "moc_eval_neighbours")
     return out_moves, out_best
 
@@ -236,31 +237,18 @@ def moc_eval_neighbours(g: Graph, starts, ends, active, R, want_moves=True, want
 def moc_eval_toggles(g: Graph, starts, ends, active, out=None, stream=None):
     """Score the B x T candidates that differ from a base in one active flag.  Returns a uint8
     CUDA tensor [B][T][16] (moc_toggle_score)."""
-    torch = _tc()
-    B = starts.numel() // g.T if g.T else 0
-    ps, pe, pa = _cand_ptrs(g, B, starts, ends, active)
-    if out is None:
-        out = torch.empty((B, g.T, TOGGLE_SCORE_DTYPE.itemsize), dtype=torch.uint8, device=starts.device)
-    code = lib().moc_eval_toggles(g._h, B, ps, pe, pa, out.data_ptr(), _stream_handle(stream))
-    _check(code, "moc_eval_toggles")
-    return out
+    return _evaluate("moc_eval_toggles", g, starts, ends, active, out, g.T, TOGGLE_SCORE_DTYPE.itemsize, stream)
 
 
 def moc_eval_cuts(g: Graph, starts, ends, active, want_moves=True, want_best=False, out_moves=None, out_best=None,
                   stream=None, keep_inputs=False):
     """Score the B x m*C cut-and-recompute moves.  Returns (uint8 CUDA tensor [B][m*C][16] of
     moc_cut_score or None, uint8 CUDA tensor [B][16] of moc_best_move or None)."""
-    torch = _tc()
-    B = starts.numel() // g.T if g.T else 0
-    ps, pe, pa = _cand_ptrs(g, B, starts, ends, active)
-    if out_moves is None and want_moves:
-        out_moves = torch.empty((B, g.m * g.C, TOGGLE_SCORE_DTYPE.itemsize), dtype=torch.uint8, device=starts.device)
-    if out_best is None and want_best:
-        out_best = torch.empty((B, BEST_MOVE_DTYPE.itemsize), dtype=torch.uint8, device=starts.device)
+    B, ps, pe, pa = _cand_ptrs(g, starts, ends, active)
+    out_moves, pm = _room(out_moves, want_moves, starts, 1, B, g.m * g.C, TOGGLE_SCORE_DTYPE.itemsize)
+    out_best, pb = _room(out_best, want_best, starts, 1, B, BEST_MOVE_DTYPE.itemsize)
     call = lib().moc_eval_cuts_keep if keep_inputs else lib().moc_eval_cuts
-    code = call(
-        g._h, B, ps, pe, pa, out_moves.data_ptr() if out_moves is not None else None,
-        out_best.data_ptr() if out_best is not None else None, _stream_handle(stream))
+    code = call(g._h, B, ps, pe, pa, pm, pb, _stream_handle(stream))
     _check(code, "moc_eval_cuts")
     return out_moves, out_best
 
@@ -269,8 +257,7 @@ def moc_search_cuts(g: Graph, starts, ends, active, max_steps, work_best=None, o
     """Greedy descent by cut-and-recompute moves, in place.  Returns the int32 CUDA tensor [B] of
     moves applied per candidate."""
     torch = _tc()
-    B = starts.numel() // g.T if g.T else 0
-    ps, pe, pa = _cand_ptrs(g, B, starts, ends, active)
+    B, ps, pe, pa = _cand_ptrs(g, starts, ends, active)
     with _on(stream):
         if work_best is None:
             work_best = torch.empty((B, BEST_MOVE_DTYPE.itemsize), dtype=torch.uint8, device=starts.device)
@@ -286,8 +273,7 @@ def moc_search_two_phase(g: Graph, starts, ends, active, max_cuts, max_merges, K
     """Two-phase local search in place (cuts that keep the inputs towards the budget, then merges
     that lower the duration).  Returns (cuts, merges): int32 CUDA tensors [B] of moves applied."""
     torch = _tc()
-    B = starts.numel() // g.T if g.T else 0
-    ps, pe, pa = _cand_ptrs(g, B, starts, ends, active)
+    B, ps, pe, pa = _cand_ptrs(g, starts, ends, active)
     if B > 0 and max_merges > 0 and not 1 <= K <= 0x7FFFFFFF // B:   # the call's limit, before K becomes an int32
         raise MoccasinError(-1, "moc_search_two_phase")
     dev = starts.device
@@ -307,8 +293,7 @@ def moc_search_moves(g: Graph, starts, ends, active, R, max_steps, out_steps=Non
     """Greedy descent by single-field start/end moves of radius R, in place.  Returns the int32
     CUDA tensor [B] of moves applied per candidate."""
     torch = _tc()
-    B = starts.numel() // g.T if g.T else 0
-    ps, pe, pa = _cand_ptrs(g, B, starts, ends, active)
+    B, ps, pe, pa = _cand_ptrs(g, starts, ends, active)
     with _on(stream):
         work_results = torch.empty((B, RESULT_DTYPE.itemsize), dtype=torch.uint8, device=starts.device)
         work_best = torch.empty((B, BEST_MOVE_DTYPE.itemsize), dtype=torch.uint8, device=starts.device)
@@ -324,19 +309,10 @@ def moc_search_moves(g: Graph, starts, ends, active, R, max_steps, out_steps=Non
 def moc_decode_batch(g: Graph, starts, active, want_seq=True, out=None, out_seq=None, stream=None):
     """Decode B candidates to their sequences.  Returns (uint8 CUDA tensor [B][24] of
     moc_decode_result, int32 CUDA tensor [B][T] of sequences or None)."""
-    torch = _tc()
-    B = starts.numel() // g.T if g.T else 0
-    for t, dt in ((starts, torch.int32), (active, torch.uint8)):
-        if not (t.is_cuda and t.is_contiguous() and t.dtype == dt and t.numel() == B * g.T):
-            raise ValueError("candidate arrays must be contiguous CUDA tensors [B][T]: int32 starts, uint8 active")
-    if out is None:
-        out = torch.empty((B, DECODE_RESULT_DTYPE.itemsize), dtype=torch.uint8, device=starts.device)
-    if out_seq is None and want_seq:
-        out_seq = torch.empty((B, g.T), dtype=torch.int32, device=starts.device)
-    code = lib().moc_decode_batch(
-        g._h, B, starts.data_ptr(), active.data_ptr(),
-        out.data_ptr(), out_seq.data_ptr() if out_seq is not None else None,
-        _stream_handle(stream))
+    B, ps, _, pa = _cand_ptrs(g, starts, None, active)
+    out, po = _room(out, True, starts, 1, B, DECODE_RESULT_DTYPE.itemsize)
+    out_seq, pq = _room(out_seq, want_seq, starts, 4, B, g.T)
+    code = lib().moc_decode_batch(g._h, B, ps, pa, po, pq, _stream_handle(stream))
     _check(code, "moc_decode_batch")
     return out, out_seq
 

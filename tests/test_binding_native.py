@@ -1,0 +1,32 @@
+"""The native part of the binding refuses what is no candidate before any call of the library.  No GPU."""
+import numpy as np
+import pytest
+import torch
+
+
+def test_refusals():
+    from paper_2304_14463_amd import _candidates as native
+    s, a = torch.zeros(8, dtype=torch.int32), torch.zeros(8, dtype=torch.uint8)
+    for bad in ((s, s, a), (s, None, a), (a, s, a), (s, s, s)):   # on the CPU, or of another type
+        with pytest.raises(ValueError):
+            native.pointers(4, *bad)
+        if bad[1] is not None:
+            with pytest.raises(ValueError):
+                native.evaluate(0, 0, 4, *bad, None, 0, 24, 0)
+    for bad in (np.zeros(8, np.int32), None, 3):
+        with pytest.raises(TypeError):
+            native.pointers(4, bad, s, a)
+    with pytest.raises(TypeError):
+        native.pointers(4, s, s)
+    with pytest.raises(TypeError):
+        native.evaluate("moc_eval_batch", 0, 4, s, s, a, None, 0, 24, 0)
+
+
+def test_results_are_made_like_the_candidates():
+    from paper_2304_14463_amd import _candidates as native
+    x, at = native.empty(torch.zeros(2), 1, 5, 24)
+    assert x.shape == (5, 24) and x.dtype is torch.uint8 and x.data_ptr() == at and x.is_contiguous() and not x.requires_grad
+    x, at = native.empty(torch.zeros(2, requires_grad=True), 4, 7)
+    assert x.shape == (7,) and x.dtype is torch.int32 and x.data_ptr() == at and not x.requires_grad
+    with pytest.raises(RuntimeError):
+        native.empty(torch.zeros(2), 1, -1, 24)
