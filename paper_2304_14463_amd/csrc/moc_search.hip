@@ -189,10 +189,8 @@ __device__ __forceinline__ Range merged_range(uint32_t pc, uint32_t pb, int size
 // index order, as many as K; eight lanes per entry score it; the feasible one of lowest duration,
 // then peak, then index is applied to the staged base and to the candidate's rows.  What bounds a
 // step is a chain of LDS latencies (list, walk over the node's edges, range maxima, tables), so
-// the workgroup is small and several share a compute unit: 256 threads for every size.  C = 2, up to 32 steps of
-// K = 64 by 256 / 512 / 1024 threads: n = 442, 1024 walkers 168 / 249 / 556 us, 32 walkers 136 / 135 / 162; one
-// walker to a compute unit would rather have 512: n = 2000, 256 walkers 376 / 270 / 268, training graph n = 1000
-// 243 / 186 / 212.  (1024 walkers at n = 442, up to 48 steps: 0.18 ms, 0.25 with one lane per entry, whose edges one
+// the workgroup is small and several share a compute unit: 256 threads, 512 where a walker has one to itself
+// (queue_merges).  C = 2, up to 32 steps of K = 64 by 256 / 512 / 1024 threads: n = 442, 1024 walkers 168 / 249 / 556 us.  (1024 walkers at n = 442, up to 48 steps: 0.18 ms, 0.25 with one lane per entry, whose edges one
 // lane then walks one after the other; 19 with every merge written out as a row of its own and evaluated by
 // moc_eval_batch, four launches a step, 9.8 the writing and 7.9 the evaluation.)
 template <int CT, int NT, bool LISTS>
@@ -415,12 +413,16 @@ int queue_merges(const moc_graph* g, int64_t B, int32_t* starts, int32_t* ends, 
   const int T = g->view.T;
   const MvLayout lay = mv_layout(T, g->view.n, g->view.m, (T + 1) / 2, true, g->max_lds);
   if (lay.bytes > g->max_lds) return MOC_EOVERFLOW;
-  constexpr int NT = 256;
-  const MergeKernel kern = lay.lists ? pick_merge<NT, true>(g->view.C) : pick_merge<NT, false>(g->view.C);
+  // One walker to a compute unit: 512 threads, where a base feeds them.  K = 64, 32 to 48 steps, 256 / 512 / 1024 threads: n =
+  // 200, 100 walkers 75 / 79 / 97 us; n = 442, 200 walkers 133 / 134 / 160, 500 walkers 143 / 150 / 284; n = 700, 250 walkers 207 / 184 / 208;
+  // training graph, n = 1000, 100 walkers 323 / 254 / 291; n = 2000, 100 walkers 534 / 381 / 376.
+  const int nt = B <= g->num_cu && T > 900 ? 512 : 256;
+  const MergeKernel kern = nt == 512 ? lay.lists ? pick_merge<512, true>(g->view.C) : pick_merge<512, false>(g->view.C)
+                                     : lay.lists ? pick_merge<256, true>(g->view.C) : pick_merge<256, false>(g->view.C);
   int per_cu = 0;   // not used: the call is for the kernel's LDS limit
-  if (const int rc = moc_kernel_occupancy(g, reinterpret_cast<const void*>(kern), NT, lay.bytes, false, &per_cu)) return rc;
+  if (const int rc = moc_kernel_occupancy(g, reinterpret_cast<const void*>(kern), nt, lay.bytes, false, &per_cu)) return rc;
   for (int64_t at = 0; at < B; at += kMaxLaunch)
-    hipLaunchKernelGGL(kern, dim3((unsigned)std::min(B - at, kMaxLaunch)), dim3(NT), lay.bytes, stream, g->view, starts + at * T,
+    hipLaunchKernelGGL(kern, dim3((unsigned)std::min(B - at, kMaxLaunch)), dim3(nt), lay.bytes, stream, g->view, starts + at * T,
                        ends + at * T, active + at * T, K, max_steps, out_merges + at, lay);
   return MOC_OK;
 }
