@@ -1,7 +1,7 @@
 // moc_eval_batch: one workgroup evaluates one candidate at a time (Eq. (1)-(8)
 // of the paper's Section 2.1) with its whole working set in LDS.
 //
-// Per candidate (register-resident kernel, C <= 4):
+// Per candidate (register-resident kernel, C <= 5):
 //   phase 1  one lane per node, nodes in id order.  The lane holds the C copies
 //            of its node in registers (requested from HBM while the previous
 //            candidate was being worked on), classifies them (active / live),
@@ -280,7 +280,7 @@ template <int CT>
 struct NodeIn {
   int s[CT], e[CT];
   // The flag bytes, byte i = a of copy i.  C <= 2: one 16-bit value; C = 3: a 16-bit value and
-  // the third byte in a2; C = 4: one 32-bit value.  The 16-bit values are never widened: they
+  // the third byte in a2; C = 4: one 32-bit value; C = 5: that and the fifth byte in a2.  The 16-bit values are never widened: they
   // go into the byte compares as they are, so that no conversion instruction sits between
   // the load and its first use (the compiler places such a conversion, and with it the wait
   // for the load, at the end of the iteration that issued the load).
@@ -289,6 +289,8 @@ struct NodeIn {
 };
 
 struct __attribute__((packed, aligned(4))) Int3 { int x, y, z; };
+struct __attribute__((packed, aligned(4))) Int5 { int x[5]; };
+struct __attribute__((packed, aligned(1))) Flags4 { uint32_t x; };
 
 // Loads the C copies of one node.  s_row/e_row/a_row point at the candidate's row (uniform
 // over the workgroup, so they live in scalar registers) and `off` = v*C is the lane's
@@ -316,6 +318,13 @@ __device__ __forceinline__ void load_node(const int32_t* __restrict__ s_row, con
     r.s[0] = sv.x; r.s[1] = sv.y; r.s[2] = sv.z; r.e[0] = ev.x; r.e[1] = ev.y; r.e[2] = ev.z;
     r.a = load_at<uint16_t>(a_row, off);            // flags of copies 0 and 1 (any alignment)
     r.a2 = load_at<uint8_t>(a_row, off + 2);        // flag of copy 2, widened to 16 bits by the load itself
+  } else if constexpr (CT == 5) {
+    const Int5 sv = load_at<Int5>(s_row, boff);
+    const Int5 ev = load_at<Int5>(e_row, boff);
+#pragma unroll
+    for (int i = 0; i < 5; ++i) { r.s[i] = sv.x[i]; r.e[i] = ev.x[i]; }
+    r.a = load_at<Flags4>(a_row, off).x;            // flags of copies 0 to 3 (any alignment)
+    r.a2 = load_at<uint8_t>(a_row, off + 4);
   } else {
     const int4 sv = load_at<int4>(s_row, boff);
     const int4 ev = load_at<int4>(e_row, boff);
@@ -417,6 +426,7 @@ __device__ __forceinline__ void drain_queue(int& viol, const Lds& L, const uint3
       const uint4 rv = *reinterpret_cast<const uint4*>(L.rest + v * RS);
       const uint4 ru = *reinterpret_cast<const uint4*>(L.rest + u * RS);
       pv.w[1] = rv.x; pv.w[2] = rv.y; pv.w[3] = rv.z; pu.w[1] = ru.x; pu.w[2] = ru.y; pu.w[3] = ru.z;
+      if constexpr (CT == 5) { pv.w[4] = rv.w; pu.w[4] = ru.w; }
     }
 #pragma unroll
     for (int i = 0; i < CT; ++i) count_live_uncovered<CT>(viol, pu, pv.w[i]);
@@ -572,7 +582,7 @@ __global__ __launch_bounds__(NT) void eval_batch_kernel(GraphView g, int64_t B, 
         Record<CT> rec;
 #pragma unroll
         for (int i = 0; i < CT; ++i) {
-          if constexpr (CT == 3) act[i] = (i < 2 ? byte_ne_k(r.a, i, 0u) : byte_ne_k(r.a2, 0, 0u)) & isn;
+          if constexpr (CT == 3 || CT == 5) act[i] = (i < CT - 1 ? byte_ne_k(r.a, i, 0u) : byte_ne_k(r.a2, 0, 0u)) & isn;
           else act[i] = byte_ne_k(r.a, i, 0u) & isn;
           const lanemask well = u_le((uint32_t)r.s[i], (uint32_t)r.e[i]) & u_lt_k((uint32_t)r.e[i], (uint32_t)T);
           live[i] = act[i] & well;
@@ -607,7 +617,7 @@ __global__ __launch_bounds__(NT) void eval_batch_kernel(GraphView g, int64_t B, 
             L.packed[v] = rec.w[0];
             L.cons[v] = (uint16_t)(rec.w[0] | pick(others, 0x00008000u));
             if constexpr (CT == 3) *reinterpret_cast<uint2*>(L.rest + v * RS) = make_uint2(rec.w[1], rec.w[2]);
-            else *reinterpret_cast<uint4*>(L.rest + v * RS) = make_uint4(rec.w[1], rec.w[2], rec.w[3], MOC_DEAD);
+            else *reinterpret_cast<uint4*>(L.rest + v * RS) = make_uint4(rec.w[1], rec.w[2], rec.w[3], CT == 5 ? rec.w[CT - 1] : MOC_DEAD);
           }
         }
         if (lanes(live[0])) scatter(r.s[0], r.e[0], sd[it].x);
@@ -866,19 +876,24 @@ int slots_per_lane(int n, int m, int nt) {
   return by_nodes > by_edges ? by_nodes : by_edges;
 }
 
-// Workgroup size: the smallest that leaves at most 5 node slots per lane and at most one delta
+// Workgroup size: the smallest that leaves at most 5 node slots per lane (C = 5: 3, whose copies
+// take 87 registers; with 5 n = 2000, 4444 candidates 106 us instead of 96) and at most one delta
 // chunk per thread (one wave per
 // candidate for small graphs, up to a full 1024-thread workgroup per compute unit).
 int block_threads(int n, int m, int C) {
   for (int nt = 64; nt < 1024; nt *= 2)
-    if (slots_per_lane(n, m, nt) <= 5 && (n * C + chunk_positions(nt)) / chunk_positions(nt) <= nt) return nt;
+    if (slots_per_lane(n, m, nt) <= (C == 5 ? 3 : 5) && (n * C + chunk_positions(nt)) / chunk_positions(nt) <= nt) return nt;
   return 1024;
 }
 
-// The register-resident kernel applies when C <= 4, a lane's nodes and edges fit its
-// registers, and every thread has at most one delta chunk.
+// The register-resident kernel applies when C <= 5, a lane's nodes and edges fit its
+// registers, and every thread has at most one delta chunk.  (C = 5: four to seven times as fast as the general kernel,
+// which keeps the sizes that do not fit LDS, some 3300 nodes and more.  n = 50, 177777 candidates 370 -> 187 us; n = 150, 59259
+// 586 -> 134; n = 442, 20110 362 -> 91; n = 1000, 8888 492 -> 87; n = 2000, 4444 705 -> 96, every copy live 712 -> 164.)
+constexpr int kLdsBytes = 160 * 1024;
 bool fast_shape(int n, int m, int C, int nt) {
-  return C <= 4 && n * C >= 4 && slots_per_lane(n, m, nt) <= kMaxIters && (n * C + chunk_positions(nt)) / chunk_positions(nt) <= nt &&
+  if (C == 5 && fast_layout(n, m, C, nt, kLdsBytes).bytes > kLdsBytes) return false;
+  return C <= 5 && n * C >= 4 && slots_per_lane(n, m, nt) <= kMaxIters && (n * C + chunk_positions(nt)) / chunk_positions(nt) <= nt &&
          (n + 3) * moc_node_stride(C) <= 0xFFFF;
 }
 
@@ -893,7 +908,8 @@ int launch_nt(const moc_graph* g, int64_t B, const int32_t* s, const int32_t* e,
       case 1: return launch_iters<NT, 1>(iters, g, lay, B, s, e, a, out, st, src);
       case 2: return launch_iters<NT, 2>(iters, g, lay, B, s, e, a, out, st, src);
       case 3: return launch_iters<NT, 3>(iters, g, lay, B, s, e, a, out, st, src);
-      default: return launch_iters<NT, 4>(iters, g, lay, B, s, e, a, out, st, src);
+      case 4: return launch_iters<NT, 4>(iters, g, lay, B, s, e, a, out, st, src);
+      default: return launch_iters<NT, 5>(iters, g, lay, B, s, e, a, out, st, src);
     }
   }
   return launch_kernel(eval_batch_general_kernel<NT>, NT, g, general_layout(n, C, NT), B, s, e, a, out, st, src);
