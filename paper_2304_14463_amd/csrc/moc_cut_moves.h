@@ -163,12 +163,12 @@ __device__ __forceinline__ bool find_cut(const A& lists, int C, const BaseLds& L
           missing += held_at(C, L.packed, w, pos) || latest_end(C, L.packed, w, pos) >= 0 ? 0 : 1;
         }
       }
-      if (missing == 0) {
-        p = pos;
-        break;
-      }
-      hi = pos - 1;
-      continue;
+      // An input that is missing at pos is missing below it, too: none of its live copies ends before pos or covers it,
+      // so all of them start at pos or behind it.  The last free position decides.  (Going on to the next one down until
+      // s_k: tables of keeping cuts, half of the bases with violations, n = 1000, 256 bases, C = 2
+      // 666 -> 135 us, C = 4 3172 -> 232; n = 2000, C = 3, 100 bases 2593 -> 236.)
+      if (missing == 0) p = pos;
+      break;
     }
     // where an input is missing, the search resumes at the end of that input's nearest earlier copy
     int resume = pos;
