@@ -859,11 +859,14 @@ NbKernel pick_kernel(int nt, bool adj_lds, int C, int R) {
 // Threads per base.  A wave scores 64 (copy, field) pairs at a time, and the staging is a chain of
 // short passes over T positions: a small base does not feed 16 waves, and several bases on a compute
 // unit hide each other's latencies, as long as the batch has several per unit.  R = 8, C = 2, 1024 bases,
-// microseconds by 256 / 512 / 1024 threads: n = 442 90 / 99 / 112, n = 1000 191 / 178 / 208, n = 2000 577 / 376 / 346.
-int nb_threads(int T, int64_t B, int num_cu) {
+// microseconds by 256 / 512 / 1024 threads: n = 442 90 / 99 / 112, n = 1000 191 / 178 / 208, n = 2000 577 / 376 / 346.  At most
+// one base to a compute unit: n = 60, 250 bases 28 / 30 / 32; n = 128, R = 4, 191 bases 23.5 / 21.1 / 23.9; n = 250, 250 bases 42 / 33 / 32; n =
+// 442, 60 bases 60 / 39 / 33.  (C = 4, n = 40, 16 bases 37 with 256, which read C at run time, 33 with 1024.)
+int nb_threads(int T, int C, int64_t B, int num_cu) {
+  const bool own = C == 2 || C == 3;   // C as a constant with any number of threads
   const int64_t per_cu = (B + num_cu - 1) / num_cu;
-  if (T <= 1024 && per_cu >= 4) return 256;
-  if (T <= 2560 && per_cu >= 2) return 512;
+  if ((own && T <= 160) || (T <= 1024 && per_cu >= 4)) return 256;
+  if ((own && T <= 320) || (T <= 2560 && per_cu >= 2)) return 512;
   return 1024;
 }
 
@@ -872,7 +875,7 @@ int nb_threads(int T, int64_t B, int num_cu) {
 // One launch over B bases: the table of scores, and the best moves where they are asked for.
 int moc_queue_neighbour_table(const moc_graph* g, int64_t B, const int32_t* starts, const int32_t* ends, const uint8_t* active,
                               int32_t R, moc_move_score* out_moves, moc_best_move* out_best, hipStream_t stream) {
-  const int nt = nb_threads(g->view.T, B, g->num_cu);
+  const int nt = nb_threads(g->view.T, g->view.C, B, g->num_cu);
   const NbLayout lay = nb_layout(g->view.T, g->view.n, g->view.m, g->max_lds, nt);
   const NbKernel kern = pick_kernel(nt, lay.adj_off != 0, g->view.C, R);
   int per_cu = 0;
