@@ -27,8 +27,8 @@ HBM_PEAK_GBS = 8000.0
 # HBM traffic of the evaluation kernel on the default workload, from rocprofv3 counter runs
 # (profiles/eval_batch_kernel_n5000_C3_B262144.md): KiB per dispatch and the factors that the same
 # counters need to reproduce a 1 GiB device copy.  Valid for the kernel sources they were taken with.
-TRAFFIC = {"workload": 4, "B": 262144, "fetch_kib": 17328000.0, "fetch_scale": 2.0, "write_kib": 20497.0,
-           "write_scale": 1.0, "sources_sha256": "cde93ef180e42f604f0915d5ab482e3d532467073c912cebae7cd4777afec5d2"}
+TRAFFIC = {"workload": 4, "B": 262144, "fetch_kib": 17327018.0, "fetch_scale": 2.0, "write_kib": 20497.0,
+           "write_scale": 1.0, "sources_sha256": "b621d5c914c634d2dec83b94190e7c4c092e700e43e4ef4e0df7089cba2d201a"}
 KERNEL_SOURCES = ("csrc/moc_eval.hip", "csrc/moc_cover.h", "csrc/moc_masks.h", "csrc/moc_wave.h", "csrc/moc_internal.h", "build.py")   # the kernel and how it is compiled
 
 
