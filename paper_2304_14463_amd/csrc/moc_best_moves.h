@@ -6,8 +6,8 @@
 // where it is needed, a shared start by its copies, an order pair by its two copies.  One pass over the edges,
 // one lane each, counts for each copy and field the violations that its moves could mend (`red`); it counts the
 // base's violations on its way.  The fields with the highest count are scored first, one lane per move; what is
-// left is scored only if its bound (violations - red, and the base's peak unless the field reaches over all
-// positions at the peak) is no worse than the best move so far.  Of 900 to 4000 fields of a base 1 to 8 are
+// left is scored only if its bound (violations - red, and the base's peak, less the node's size if the field reaches
+// over all positions at the peak) is no worse than the best move so far.  Of 900 to 4000 fields of a base 1 to 8 are
 // scored where it has violations, and about as many as fit one round where it has none.
 #pragma once
 
@@ -162,6 +162,7 @@ __global__ __launch_bounds__(NT) void best_neighbours_kernel(GraphView g, int64_
   const bool overflows = (int64_t)g.m * C >= kMany - 64;   // more edges than a count can take
   constexpr int kNone = 0x7FFFFFFF;
   constexpr int kEdgesAhead = 6;
+  constexpr int kFewRounds = 4;
   const int last_edge = max(g.m - 1, 0);   // (the list of a graph without edges has one entry, too)
 
   for (int64_t b = blockIdx.x; b < B; b += gridDim.x) {
@@ -310,24 +311,29 @@ __global__ __launch_bounds__(NT) void best_neighbours_kernel(GraphView g, int64_
         // moves that mend nothing: one round of them mostly has one that leaves the peak where it is
         const bool first_of_many = lo == 0 && (c0 == 0 || best == 0 || best_viol > base_viol || (best_viol == base_viol && best_peak > base_peak));
         int c1 = first_of_many ? min(c0 + NW * rows, T) : T;
-        auto gather = [&]() {
+        // whether a field that leaves at least `viol` violations can still have the best move; size: what it lowers the peak by at most
+        auto could_win = [&](int k, int f, uint32_t p, int viol, int size) {
+          if (viol != best_viol) return viol < best_viol;
+          // only a field that gives up all positions at the peak lowers it
+          const int s = (int)(p & 0xFFFFu), e = (int)(p >> 16);
+          const bool lowers = live_of(p) && (f == 0 ? s <= first && last < s + R : last <= e && first > e - R);
+          const int peak = lowers ? base_peak - size : base_peak;
+          return peak < best_peak || (peak == best_peak && (2 * k + f) * two_r < best_move);
+        };
+        // Where far more are queued than are scored at once they are queued again, with the sizes of their nodes: every output
+        // kept to the end, where all ends lower the peak, R = 8, n = 442, 1024 bases 77 -> 24 us (48 before there were bounds);
+        // n = 4000, C = 1, R = 2, 300 bases 185 -> 50 (92).  (The sizes are in memory: looked at for every field, clean rows, n =
+        // 442, 3000 walkers, 8 steps take 187 us instead of 182.)
+        int count;
+        for (bool sized = false;;) {
           for (int k = c0 + t; k < c1; k += NT) {
             const uint32_t p = L.packed[k], r = red[k];
             if (p == MOC_DEAD) continue;
-            const int s = (int)(p & 0xFFFFu), e = (int)(p >> 16);
 #pragma unroll
             for (int f = 0; f < 2; ++f) {
               const int mends = (int)(f == 0 ? r & 0xFFFFu : r >> 16);
               bool take = mends >= lo && mends < hi;
-              if (best != 0 && take && mends < (int)kMany) {
-                const int at_best = base_viol - mends;   // violations, at best
-                take = at_best <= best_viol;
-                if (at_best == best_viol) {
-                  // only a field that gives up all positions at the peak lowers it
-                  const bool lowers = live_of(p) && (f == 0 ? s <= first && last < s + R : last <= e && first > e - R);
-                  take = lowers || base_peak < best_peak || (base_peak == best_peak && (2 * k + f) * two_r < best_move);
-                }
-              }
+              if (best != 0 && take && mends < (int)kMany) take = could_win(k, f, p, base_viol - mends, sized ? g.size_dur[k / C].x : base_peak);
               if (take) {
                 const int at = atomicAdd(queued, 1);
                 if (at < lay.cap) queue[at] = (uint16_t)(2 * k + f);
@@ -335,16 +341,14 @@ __global__ __launch_bounds__(NT) void best_neighbours_kernel(GraphView g, int64_
             }
           }
           __syncthreads();
-        };
-        gather();
-        int count = __builtin_amdgcn_readfirstlane(*queued);
-        if (count > lay.cap) {   // too many at once: as many copies as fit whatever their counts
+          count = __builtin_amdgcn_readfirstlane(*queued);
+          const bool again = !sized && best != 0 && count > kFewRounds * NW * rows;
+          if (!again && count <= lay.cap) break;
+          if (!again) c1 = min(c0 + lay.cap / 2, T);   // too many at once: as many copies as fit whatever their counts
+          sized = best != 0;
           __syncthreads();
           if (t == 0) *queued = 0;
-          c1 = min(c0 + lay.cap / 2, T);
           __syncthreads();
-          gather();
-          count = __builtin_amdgcn_readfirstlane(*queued);
         }
         base_peak = __builtin_amdgcn_readfirstlane(L.pre[blocks]);
         if (count > 0) {
