@@ -2,14 +2,18 @@
 // that.  (The table of all scores: moc_neighbours_table.hip, where the moves are defined.)
 //
 // How many violations a move can take away at most is known before any move is scored: an uncovered input can
-// be mended by the consumer's start or by an end of the field of a copy of the producer that lies within R of
-// where it is needed, a shared start by its copies, an order pair by its two copies.  One pass over the edges,
+// be mended by the consumer's start, if a copy of the producer is kept somewhere within R of it, by a move of the
+// consumer's that leaves it not live, or by that end of the field of a copy of the producer that lies within R of
+// where it is needed; a shared start by its copies, an order pair by its two copies.  One pass over the edges,
 // one lane each, counts for each copy and field the violations that its moves could mend (`red`); it counts the
 // base's violations on its way.  The fields with the highest count are scored first, one lane per move; what is
 // left is scored only if its bound (violations - red, and the base's peak, less the node's size if the field reaches
-// over all positions at the peak) is no worse than the best move so far.  Of 900 to 4000 fields of a base 1 to 8 are
-// scored where it has violations, and about as many as fit one round where it has none.
+// over all positions at the peak) is no worse than the best move so far.  Of the 900 to 4000 fields of a schedule 1 to 8
+// are scored where it has violations, and about as many as fit one round where it has none; of rows of random intervals,
+// whose fields have much the same counts, 1 to 30 (n = 442, 1700 fields), later in a descent 100 to 200.
 #pragma once
+
+#include <type_traits>
 
 #include "moc_masks.h"
 #include "moc_moves.h"
@@ -60,18 +64,23 @@ __device__ __forceinline__ MoveScore score_row(const GraphView& g, const BaseLds
       left &= left - 1;
     }
   };
-  // Eq. (5), the copy as consumer: inputs that are not there at every start the field can take
+  // Eq. (5), the copy as consumer: inputs that are there at some of the starts the field can take and not at others;
+  // one that is at none counts as often as the copy is live
   {
     const int from = f.field == 0 ? f.s - R : f.s, to = f.field == 0 ? f.s + R : f.s;
+    const int life = (live_new ? 1 : 0) - (live_old ? 1 : 0);
     for (int x = in_lo; __any(x < in_hi); x += row_lanes) {
       if (x != in_lo) u = x + in_row < in_hi ? g.in_idx[x + in_row] : -1;
-      bool matters = u >= 0;
+      bool always = false, sometimes = false;
       if (u >= 0)
         for (int j = 0; j < C; ++j) {
-          const uint32_t pu = L.packed[u * C + j];
-          matters = matters && !((int)(pu & 0xFFFFu) < from && (int)(pu >> 16) >= to);
+          const int su = (int)(L.packed[u * C + j] & 0xFFFFu), eu = (int)(L.packed[u * C + j] >> 16);
+          always = always || (su < from && eu >= to);
+          sometimes = sometimes || (su < to && eu >= from);
         }
-      each(matters, [&](int lane_of, bool on) {
+      const uint32_t never = (uint32_t)(__ballot(u >= 0 && !sometimes) >> row0) & ((1u << row_lanes) - 1);
+      d += life * __popc(never);
+      each(sometimes && !always, [&](int lane_of, bool on) {
         const int un = __builtin_amdgcn_ds_bpermute(lane_of << 2, u);
         if (!on) return;
         bool cov_old = !live_old, cov_new = !live_new;
@@ -127,8 +136,11 @@ __device__ __forceinline__ MoveScore score_row(const GraphView& g, const BaseLds
 // Bound by the chain of passes over a base, each short and with a barrier behind it: n = 442, 1024 bases, four
 // workgroups of 256 to a compute unit, 14 us of a base are 2 staging, 3 the edges, 2 nodes and profile, 2 picking,
 // 4.5 scoring in 1.4 rounds.  R = 8, C = 2, n = 442, 1024 bases 45 -> 21 us, n = 1000 73 -> 33, n = 2000, 2048 bases 261 -> 104 (before, one
-// lane per copy and field over all that could have fewer violations than the best so far).  80 registers a thread:
-// 64 spill (n = 442 26 us); one lane per move with all edges of a node in turn scores in twice the time.
+// lane per copy and field over all that could have fewer violations than the best so far).  Rows of random intervals, where
+// few fields can be left out: n = 442, 1024 bases 27 us, 92 while the consumer's start was counted for every uncovered input
+// (82 before there were bounds); 256 walkers, 16 steps 434 (778, 522).  80 registers a thread
+// with C <= 2 (82, one wave a SIMD fewer, for 4096 bases 60 us instead of 51; 64 spill, n = 442 26 us), 85 to 92 with
+// more copies, five waves; one lane per move with all edges of a node in turn scores in twice the time.
 template <bool KEPT>
 struct RowPtr { using Ptr = const int32_t* __restrict__; };
 template <>
@@ -141,7 +153,8 @@ struct MoveSteps {
 };
 
 template <int NT, bool LOOP, int CT, bool SEARCH, bool KEPT>
-__global__ __launch_bounds__(NT) void best_neighbours_kernel(GraphView g, int64_t B, typename RowPtr<KEPT>::Ptr starts,
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(KEPT && (CT == 1 || CT == 2) ? 6 : 5)))
+void best_neighbours_kernel(GraphView g, int64_t B, typename RowPtr<KEPT>::Ptr starts,
                                                              typename RowPtr<KEPT>::Ptr ends, const uint8_t* __restrict__ active, int R,
                                                              moc_best_move* __restrict__ out_best, MoveSteps search, BmLayout lay) {
   static_assert(SEARCH != KEPT, "a search edits the rows");
@@ -208,11 +221,11 @@ __global__ __launch_bounds__(NT) void best_neighbours_kernel(GraphView g, int64_
         __syncthreads();
       }
       // ---- violations, and by which fields they could be mended
-      auto could = [&](int k, bool by_start, bool by_end) {
-        uint32_t add = (by_start ? 1u : 0u) + (by_end ? 0x10000u : 0u);
+      constexpr uint32_t kStart = 1, kEnd = 0x10000;
+      auto could = [&](int k, uint32_t add) {
         if (overflows) {   // stops about kMany
           const uint32_t now = red[k];
-          add = (by_start && (now & 0xFFFFu) < kMany ? 1u : 0u) + (by_end && now >> 16 < kMany ? 0x10000u : 0u);
+          add &= ((now & 0xFFFFu) < kMany ? kStart : 0u) | (now >> 16 < kMany ? kEnd : 0u);
         }
         if (add != 0) atomicAdd(&red[k], add);
       };
@@ -226,20 +239,21 @@ __global__ __launch_bounds__(NT) void best_neighbours_kernel(GraphView g, int64_
           const lanemask miss = low_ne_k(copy, 0xFFFFu) & in & ~held;
           if (miss == 0) continue;
           if (lanes(miss)) {
-            const int x = (int)at;
+            const int x = (int)at, until = (int)(copy >> 16);
             ++viol;
-            could((int)(pair >> 16) + i, true, (int)(copy >> 16) - R < x);   // the consumer elsewhere, or not live
+            // the consumer not live any more (positions are in [0, T)), or its start where a copy of the producer is kept
+            uint32_t mine = until - R < x ? (until < T - 1 ? kStart : 0u) | (x > 0 ? kEnd : 0u) : 0u;
             for (int j = 0; j < C; ++j) {
               const uint32_t p = pu[j];
               const int s = (int)(p & 0xFFFFu), e = (int)(p >> 16);
-              if (!live_of(p)) {
-                if (p != MOC_DEAD) could((int)(pair & 0xFFFFu) + j, true, true);
-              } else if (s >= x) {
-                if (e >= x && s - R < x) could((int)(pair & 0xFFFFu) + j, true, false);
-              } else if (e + R >= x) {
-                could((int)(pair & 0xFFFFu) + j, false, true);
+              if (s - R < x && e + R >= x) {   // live
+                mine |= s < e ? kStart : 0u;
+                could((int)(pair & 0xFFFFu) + j, s < x ? kEnd : x > 0 ? kStart : 0u);
+              } else if (p == (MOC_DEAD | 0x10000u)) {
+                could((int)(pair & 0xFFFFu) + j, kStart | kEnd);
               }
             }
+            could((int)(pair >> 16) + i, mine);
           }
         }
       };
@@ -266,14 +280,14 @@ __global__ __launch_bounds__(NT) void best_neighbours_kernel(GraphView g, int64_
           const uint32_t p = L.packed[k];
           const int s = (int)(p & 0xFFFFu), e = (int)(p >> 16);
           if (!live_of(p)) {
-            if (p != MOC_DEAD) could(k, true, true);   // Eq. (2)/(8)
+            if (p != MOC_DEAD) could(k, kStart | kEnd);   // Eq. (2)/(8)
             continue;
           }
-          if (bit_at(L.occ2, s)) could(k, true, e - R < s);   // Eq. (6)
+          if (bit_at(L.occ2, s)) could(k, kStart | (e - R < s && s > 0 ? kEnd : 0u));   // Eq. (6)
           if (end > s) {                                      // Eq. (3)
             ++viol;
-            could(prev, true, true);
-            could(k, true, true);
+            could(prev, kStart | kEnd);
+            could(k, kStart | kEnd);
           }
           prev = k;
           end = e;
@@ -295,7 +309,7 @@ __global__ __launch_bounds__(NT) void best_neighbours_kernel(GraphView g, int64_
       maxima_before_and_from<NT>(L, blocks, t);   // no barrier yet: the first fields can be picked without
       // ---- rounds: fields whose counts lie in [lo, hi), of copies from c0 on, then the next lower counts
       const int top = __builtin_amdgcn_readfirstlane(counts[1]);
-      int lo = top - top / 4, hi = kNone, span = 1, c0 = 0;
+      int lo = top - top / 4, hi = top + 1, span = 1, c0 = 0;
       unsigned long long best = 0;   // ~(violations << 32 | peak), 0: none yet
       int best_move = kNone, base_peak = 0;
       bool marked = false;
@@ -320,12 +334,16 @@ __global__ __launch_bounds__(NT) void best_neighbours_kernel(GraphView g, int64_
           const int peak = lowers ? base_peak - size : base_peak;
           return peak < best_peak || (peak == best_peak && (2 * k + f) * two_r < best_move);
         };
-        // Where far more are queued than are scored at once they are queued again, with the sizes of their nodes: every output
-        // kept to the end, where all ends lower the peak, R = 8, n = 442, 1024 bases 77 -> 24 us (48 before there were bounds);
-        // n = 4000, C = 1, R = 2, 300 bases 185 -> 50 (92).  (The sizes are in memory: looked at for every field, clean rows, n =
-        // 442, 3000 walkers, 8 steps take 187 us instead of 182.)
-        int count;
-        for (bool sized = false;;) {
+        // Where far more are queued than are scored at once: only the upper half of these counts, whose best mostly leaves
+        // nothing to do for the others; of one count those that pass with the sizes of their nodes looked at (they are in
+        // memory); no more than there is room for.
+        // Where far more are queued than are scored at once: only the upper half of these counts, whose best mostly leaves
+        // nothing to do for the others; of a single count those that pass with the sizes of their nodes looked at; no more
+        // than there is room for.  Random intervals, n = 442, 256 walkers, 16 steps: 434 us, 1174 with counts taken together as
+        // the rounds go on, however many fields that makes.  Every output kept to the end, where all ends lower the peak, R =
+        // 8, n = 442, 1024 bases: 24 us, 77 without the sizes (48 before there were bounds).  (They are in memory: looked at
+        // for every field, clean rows, n = 442, 3000 walkers, 8 steps take 187 us instead of 182.)
+        auto gather = [&](auto with_sizes) {
           for (int k = c0 + t; k < c1; k += NT) {
             const uint32_t p = L.packed[k], r = red[k];
             if (p == MOC_DEAD) continue;
@@ -333,7 +351,7 @@ __global__ __launch_bounds__(NT) void best_neighbours_kernel(GraphView g, int64_
             for (int f = 0; f < 2; ++f) {
               const int mends = (int)(f == 0 ? r & 0xFFFFu : r >> 16);
               bool take = mends >= lo && mends < hi;
-              if (best != 0 && take && mends < (int)kMany) take = could_win(k, f, p, base_viol - mends, sized ? g.size_dur[k / C].x : base_peak);
+              if (best != 0 && take && mends < (int)kMany) take = could_win(k, f, p, base_viol - mends, with_sizes() ? g.size_dur[k / C].x : base_peak);
               if (take) {
                 const int at = atomicAdd(queued, 1);
                 if (at < lay.cap) queue[at] = (uint16_t)(2 * k + f);
@@ -341,14 +359,25 @@ __global__ __launch_bounds__(NT) void best_neighbours_kernel(GraphView g, int64_
             }
           }
           __syncthreads();
-          count = __builtin_amdgcn_readfirstlane(*queued);
-          const bool again = !sized && best != 0 && count > kFewRounds * NW * rows;
-          if (!again && count <= lay.cap) break;
-          if (!again) c1 = min(c0 + lay.cap / 2, T);   // too many at once: as many copies as fit whatever their counts
-          sized = best != 0;
+          return __builtin_amdgcn_readfirstlane(*queued);
+        };
+        int count = gather(std::false_type{});
+        bool sized = best == 0;
+        while (__builtin_expect(count > kFewRounds * NW * rows, 0)) {   // (never more than there is room for)
+          if (hi - lo > 1 && c0 == 0 && !overflows) {   // (where counts may have stopped, all that have come first)
+            lo = (lo + hi) / 2;
+            span = 1;
+          } else if (!sized) {
+            sized = true;
+          } else if (count > lay.cap) {
+            c1 = min(c0 + lay.cap / 2, T);
+          } else {
+            break;
+          }
           __syncthreads();
           if (t == 0) *queued = 0;
           __syncthreads();
+          count = gather(std::true_type{});
         }
         base_peak = __builtin_amdgcn_readfirstlane(L.pre[blocks]);
         if (count > 0) {
@@ -408,10 +437,11 @@ __global__ __launch_bounds__(NT) void best_neighbours_kernel(GraphView g, int64_
         if (best != 0) {
           const int best_mends = base_viol - (int)(~best >> 32);
           if (hi - 1 < best_mends) break;
-          lo = max(max(hi - span, best_mends), 0);
+          lo = max(hi - span, best_mends);
         } else {
-          lo = max(hi - span, 0);
+          lo = hi - span;
         }
+        lo = max(lo, hi > 1 ? 1 : 0);   // fields that mend nothing are many, and come by themselves
         span *= 2;
       }
       // ---- the best move; in a descent it is applied if it lowers (violations, max(peak, M), peak)

@@ -34,3 +34,29 @@ def test_outputs_kept_to_the_end(moc, n, C, R, sizes):  # noqa: F811
         e[b, ::C] -= rng.integers(0, 2 * b, n, dtype=np.int32)      # ends on either side of the peak's positions
     e = np.maximum(e, s)
     same_best(moc, g, C, R, s, e, a)
+
+
+# rows in which most fields have much the same bound, and rows at the ends of the domain, where a field's moves are cut off
+@pytest.mark.parametrize("kind", ["anywhere", "short", "at the ends", "all at 0", "none well formed", "in any order"])
+@pytest.mark.parametrize("n,C,R,per_node", [(60, 2, 8, 2), (442, 2, 8, 2), (300, 3, 1, 3), (250, 4, 32, 2), (1100, 2, 2, 2), (50, 5, 16, 20)])
+def test_bases_far_from_a_schedule(moc, n, C, R, per_node, kind):  # noqa: F811
+    rng = np.random.default_rng(n + C + R + len(kind))
+    g = graph(rng, n, per_node, size_hi=4 if n % 100 else 1000)
+    B, T = 14, n * C
+    s, e = (rng.integers(0, T, (B, T), dtype=np.int32) for _ in range(2))
+    s, e, a = np.minimum(s, e), np.maximum(s, e), (rng.random((B, T)) < 0.8).astype(np.uint8)
+    if kind == "short":
+        e = np.minimum(s + rng.integers(0, 1 + T // 20, (B, T), dtype=np.int32), T - 1)
+    elif kind == "at the ends":
+        s = rng.choice([-1, 0, 0, 1, T - 2, T - 1], (B, T)).astype(np.int32)
+        e = np.minimum(s + rng.choice([0, 1, R, T], (B, T)).astype(np.int32), T - 1 + (rng.random((B, T)) < 0.1))
+    elif kind == "all at 0":
+        s[:], e[:] = 0, np.arange(B, dtype=np.int32)[:, None] // 2
+    elif kind == "none well formed":
+        s, e = np.maximum(s, 1), np.minimum(s, T - 2) - rng.integers(1, 2 * R + 1, (B, T), dtype=np.int32)
+    elif kind == "in any order":
+        a[:], a[:, ::C] = 0, 1
+        for b in range(B):
+            s[b, ::C] = rng.permutation(n) * C
+        e = np.minimum(s + rng.integers(0, T // 2, (B, T), dtype=np.int32), T - 1)
+    same_best(moc, g, C, R, s, e.astype(np.int32), a)
