@@ -174,6 +174,7 @@ void best_neighbours_kernel(GraphView g, int64_t B, typename RowPtr<KEPT>::Ptr s
   constexpr uint32_t kMany = 0x7FFF;
   const bool overflows = (int64_t)g.m * C >= kMany - 64;   // more edges than a count can take
   constexpr int kNone = 0x7FFFFFFF;
+  constexpr int kFar = 1 << 20;   // beyond T + R, and sums with R stay far from the ends of 32 bits
   constexpr int kEdgesAhead = 6;
   constexpr int kFewRounds = 4;
   const int last_edge = max(g.m - 1, 0);   // (the list of a graph without edges has one entry, too)
@@ -388,13 +389,13 @@ void best_neighbours_kernel(GraphView g, int64_t B, typename RowPtr<KEPT>::Ptr s
             const int entry = queue[min(at, count - 1)], k = entry >> 1, v = k / C;
             const uint32_t p = L.packed[k];
             FieldOf f{v, k - v * C, entry & 1, (int)(p & 0xFFFFu), (int)(p >> 16)};
-            if (!live_of(p)) {   // not well formed: its values are not in LDS
-              f.s = starts[row + k];
-              f.e = ends[row + k];
+            if (!live_of(p)) {   // not well formed: its values are not in LDS, and any so far outside the domain do the same
+              f.s = min(max(starts[row + k], -kFar), kFar);
+              f.e = min(max(ends[row + k], -kFar), kFar);
             }
             for (int d0 = 0; d0 < two_r; d0 += row_lanes) {
               const int disp = d0 + (lane & (row_lanes - 1));
-              const int moved = (int)((uint32_t)(f.field == 0 ? f.s : f.e) + (uint32_t)(disp < R ? disp - R : disp - R + 1));
+              const int moved = (f.field == 0 ? f.s : f.e) + (disp < R ? disp - R : disp - R + 1);
               const bool applies = at < count && disp < two_r && moved >= 0 && moved < T;
               const MoveScore sc = score_row<CT>(g, L, blocks, f, f.field == 0 && applies ? moved : f.s, f.field == 1 && applies ? moved : f.e, R, row_lanes,
                                                  base_viol, base_peak, lane);

@@ -60,3 +60,17 @@ def test_bases_far_from_a_schedule(moc, n, C, R, per_node, kind):  # noqa: F811
             s[b, ::C] = rng.permutation(n) * C
         e = np.minimum(s + rng.integers(0, T // 2, (B, T), dtype=np.int32), T - 1)
     same_best(moc, g, C, R, s, e.astype(np.int32), a)
+
+
+# copies whose starts or ends lie at the ends of 32 bits: sums of them with the radius stay within int
+@pytest.mark.parametrize("n,C,R", [(90, 2, 32), (200, 1, 8), (40, 5, 1)])
+def test_copies_at_the_ends_of_the_integers(moc, n, C, R):  # noqa: F811
+    rng = np.random.default_rng(n + C + R)
+    g = graph(rng, n, 2)
+    B, T, lim = 10, n * C, np.iinfo(np.int32)
+    s, e = (rng.integers(0, T, (B, T)) for _ in range(2))
+    s, e, a = np.minimum(s, e), np.maximum(s, e), np.ones((B, T), np.uint8)
+    far = np.array([lim.min, lim.min + R, lim.max - R, lim.max, -(1 << 20), 1 << 20, -R, T - 1 + R])
+    s = np.where(rng.random((B, T)) < 0.3, rng.choice(far, (B, T)), s).astype(np.int32)
+    e = np.where(rng.random((B, T)) < 0.3, rng.choice(far, (B, T)), e).astype(np.int32)
+    same_best(moc, g, C, R, s, e, a)
