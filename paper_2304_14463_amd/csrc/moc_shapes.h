@@ -11,25 +11,28 @@
 // ------------------------------------------------------------------ moc_eval_batch_staged
 constexpr int kStagedThreads = 512;
 
-// Nodes per lane of the kernel that holds the copies of a lane's nodes in registers (built for 1, 2,
-// 4 and 8, as long as a lane has at most 16 copies), 0: the kernel for any size.  The node loops and
-// the scan over the stages of the former cover kStagedThreads times this many nodes and no more.
-constexpr int staged_nodes_per_lane(int n, int C) {
-  int u = 1;
-  while (u * kStagedThreads < n) u *= 2;
-  return C <= 4 && u <= 8 && u * C <= 16 ? u : 0;
-}
-
-// Threads per candidate of that kernel: two nodes a lane (four beyond 2048 nodes), so that no wave is idle in the
-// passes that every wave takes part in.  C = 2, microseconds with 64 / 128 / 256 / 512 / 1024 threads (before, with 512 for
+// The kernel that holds the copies of a lane's nodes in registers: threads per candidate and nodes a lane (1, 2 or 4:
+// nt * nodes >= n).  nodes = 0: the kernel for any size, with kStagedThreads.
+struct StagedShape {
+  int nt, nodes;
+};
+// Two nodes a lane (four beyond 2048 nodes), so that no wave is idle in the passes that every wave takes part in.  C = 2,
+// microseconds with 64 / 128 / 256 / 512 / 1024 threads (before, with 512 for
 // every size): n = 50, 32000 candidates 20 / 30 / 53 / 103 / 202 (115); n = 100, 16384 candidates 17.5 / 19.5 / 30 / 55 / 106 (62);
 // n = 200, 8192 candidates 18.8 / 17.8 / 20 / 30 / 55 (35); n = 442, 16384 candidates - / 57 / 58 / 68 / 112 (77); n = 700, 8192 candidates
 // - / - / 50 / 52.5 / 64 (56); n = 1000, 16384 candidates - / - / 103 / 98.6 / 127 (105); n = 2000, 4096 candidates - / - / - / 69 / 60
 // (85), 512 candidates 13.4 / 11.6 with 512 / 1024 (15.1).
-inline int staged_threads(int n) {
+// Up to three candidates to a compute unit wait for the longest lane, and up to 512 threads have one node each.  With two nodes /
+// with one (before, with 512 threads for every size): C = 2, n = 100, 256 candidates 5.8 / 5.5 (5.3); n = 442, 256 candidates
+// 6.3 / 5.5 (5.3), 768 candidates 7.0 / 6.2 (6.7), n = 200 6.3 / 5.3 (5.8), four to a unit 6.4 / 6.7 (6.7); C = 4, n = 442, every
+// copy active, 256 candidates 23.2 / 14.7 (14.7), n = 700 23.9 / 18.9 (24.4), but few active, n = 1000 9.3 / 10.0 (9.4).
+inline StagedShape staged_shape(int n, int C, int64_t B, int num_cu) {
+  if (C > 4 || n > (C <= 2 ? 4096 : 2048)) return {kStagedThreads, 0};
+  if (n > 2048) return {1024, 4};
   int nt = 64;
-  while (2 * nt < n && nt < 1024) nt *= 2;
-  return nt;
+  while (2 * nt < n) nt *= 2;
+  if (nt < n && nt < 512 && B <= 3 * (int64_t)num_cu) nt *= 2;
+  return {nt, nt < n ? 2 : 1};
 }
 struct SfLayout {
   int cur_off, bucket_off, delta_off, red_off;   // word offsets; the copies' records at 0, one node more than the graph has

@@ -263,7 +263,7 @@ __global__ __launch_bounds__(kNT) void eval_staged_general_kernel(GraphView g, c
 }
 
 // C <= 4: the copies of a lane's nodes are held in registers, the workgroup's next candidate is asked
-// for as soon as they are used.  U = nodes per lane, at least n / NT (staged_threads).  What the renumbering needs for a
+// for as soon as they are used.  U = nodes per lane, at least n / NT (staged_shape).  What the renumbering needs for a
 // node's first copy follows from its place k alone: its start can only be slot k of stage k, the
 // highest slot of that stage, so that its rank is the last of the stage's; only the copies beyond
 // the first, which are few, are put into buckets and searched for.  An end at the last slot of its
@@ -638,19 +638,26 @@ StagedKernel pick_edges(int m) {
 }
 template <int NT, int U>
 StagedKernel pick_copies(int C, int m) {
-  if constexpr (U <= 2) {
-    if (C == 3) return pick_edges<3, NT, U>(m);
-    if (C == 4) return pick_edges<4, NT, U>(m);
+  switch (C) {
+    case 1: return pick_edges<1, NT, U>(m);
+    case 2: return pick_edges<2, NT, U>(m);
+    case 3: if constexpr (U <= 2) return pick_edges<3, NT, U>(m); else return nullptr;
+    case 4: if constexpr (U <= 2) return pick_edges<4, NT, U>(m); else return nullptr;
+    default: return nullptr;
   }
-  return C == 1 ? pick_edges<1, NT, U>(m) : pick_edges<2, NT, U>(m);
 }
-StagedKernel pick_kernel(int nt, int n, int C, int m) {
-  switch (nt) {
-    case 64: return pick_copies<64, 2>(C, m);
-    case 128: return pick_copies<128, 2>(C, m);
-    case 256: return pick_copies<256, 2>(C, m);
-    case 512: return pick_copies<512, 2>(C, m);
-    default: return n <= 2048 ? pick_copies<1024, 2>(C, m) : pick_copies<1024, 4>(C, m);
+template <int NT>
+StagedKernel pick_nodes(int nodes, int C, int m) {
+  return nodes == 1 ? pick_copies<NT, 1>(C, m) : pick_copies<NT, 2>(C, m);
+}
+StagedKernel pick_kernel(const StagedShape& shape, int C, int m) {
+  switch (shape.nt) {
+    case 64: return pick_nodes<64>(shape.nodes, C, m);
+    case 128: return pick_nodes<128>(shape.nodes, C, m);
+    case 256: return pick_nodes<256>(shape.nodes, C, m);
+    case 512: return pick_nodes<512>(shape.nodes, C, m);
+    case 1024: return shape.nodes == 4 ? pick_copies<1024, 4>(C, m) : pick_copies<1024, 2>(C, m);
+    default: return nullptr;
   }
 }
 
@@ -669,9 +676,11 @@ extern "C" int moc_eval_batch_staged(const moc_graph* g, int64_t B, const int32_
   const StLayout lay = st_layout(g->view.n, g->view.C);
   if (lay.bytes > g->max_lds || g->view.T >= 0xFFFF) return MOC_EOVERFLOW;
   const hipStream_t stream = static_cast<hipStream_t>(hip_stream);
-  const bool in_registers = staged_nodes_per_lane(g->view.n, g->view.C) > 0;
-  const int nt = in_registers ? staged_threads(g->view.n) : kNT;
-  const StagedKernel kern = in_registers ? pick_kernel(nt, g->view.n, g->view.C, g->view.m) : nullptr;
+  const StagedShape shape = staged_shape(g->view.n, g->view.C, B, g->num_cu);
+  const bool in_registers = shape.nodes > 0;
+  const int nt = shape.nt;
+  const StagedKernel kern = in_registers ? pick_kernel(shape, g->view.C, g->view.m) : nullptr;
+  if (in_registers && !kern) return MOC_EINVAL;
   const SfLayout sf = sf_layout(g->view.n, g->view.C, nt);
   const int bytes = in_registers ? sf.bytes : lay.bytes;
   const void* const entry = in_registers ? reinterpret_cast<const void*>(kern) : reinterpret_cast<const void*>(eval_staged_general_kernel);

@@ -17,7 +17,11 @@ constexpr int kMaxLds = 160 * 1024;
 int main(int argc, char** argv) {
   if (argc == 2 && !strcmp(argv[1], "staged"))
     for (int C = 1; C <= 8; ++C)
-      for (int n = 1; n * C <= 19455; ++n) printf("%d %d %d\n", C, n, staged_nodes_per_lane(n, C));
+      for (int n = 1; n * C <= 19455; ++n)
+        for (int64_t B : {1, 256, 768, 769, 100000}) {
+          const StagedShape s = staged_shape(n, C, B, 256);
+          printf("%d %d %d %d %d\n", C, n, (int)B, s.nt, s.nodes);
+        }
   if (argc == 2 && !strcmp(argv[1], "decode"))
     for (int C = 1; C <= 8; ++C)
       for (int n = 1; n * C <= 19455; ++n) {
@@ -58,14 +62,17 @@ def shapes(tmp_path_factory):
 
 
 def test_staged_kernel_holds_every_node(shapes):
-    """The kernel with the copies in registers is only taken for graphs whose nodes it covers."""
-    C, n, u = shapes("staged").T
-    taken = u > 0
-    assert (n[taken] <= 512 * u[taken]).all()
-    assert (u[taken] * C[taken] <= 16).all() and (C[taken] <= 4).all() and np.isin(u, (0, 1, 2, 4, 8)).all()
+    """The kernel with the copies in registers is only taken for graphs whose nodes it covers, in a shape that it is built for."""
+    C, n, B, nt, nodes = shapes("staged").T
+    taken = nodes > 0
+    assert (n[taken] <= (nt * nodes)[taken]).all() and (nt[~taken] == 512).all()
+    assert (C[taken] <= 4).all() and np.isin(nodes, (0, 1, 2, 4)).all() and np.isin(nt, (64, 128, 256, 512, 1024)).all()
+    assert (nodes[nt == 1024] != 1).all() and (nt[nodes == 4] == 1024).all() and (C[nodes == 4] <= 2).all()
     # and it is taken wherever an instantiation covers them
-    largest = np.array([0, 8, 8, 4, 4, 0, 0, 0, 0])[C] * 512
+    largest = np.array([0, 4096, 4096, 2048, 2048, 0, 0, 0, 0])[C]
     assert (taken == (n <= largest)).all()
+    # a lane has one node more rarely than a wave is idle, unless the batch is small
+    assert ((nodes[B > 768] != 1) | (n[B > 768] <= 64)).all()
 
 
 @pytest.mark.parametrize("C", [1, 2, 3, 4, 5])

@@ -23,14 +23,16 @@ int main(int argc, char**) {
       }
   else
     for (int C = 1; C <= 4; ++C)
-      for (int n = 1; n <= 8192; ++n) {
-        if (staged_nodes_per_lane(n, C) == 0) continue;
-        const int nt = staged_threads(n), T = n * C;
-        const SfLayout l = sf_layout(n, C, nt);
-        const bool apart = l.cur_off >= T + C && l.bucket_off >= l.cur_off + n && 2 * (l.delta_off - l.bucket_off) >= T &&
-                           nt * l.chunk > T && l.chunk % 2 == 1 && l.red_off >= l.delta_off + nt * l.chunk && l.red_off % 4 == 0;
-        printf("%d %d %d %d\n", nt, n <= 2048 ? (n + nt - 1) / nt : -((n + nt - 1) / nt), l.bytes, apart);
-      }
+      for (int n = 1; n <= 8192; ++n)
+        for (int64_t B : {1, 769}) {
+          const StagedShape s = staged_shape(n, C, B, 256);
+          if (s.nodes == 0) continue;
+          const int nt = s.nt, T = n * C;
+          const SfLayout l = sf_layout(n, C, nt);
+          const bool apart = l.cur_off >= T + C && l.bucket_off >= l.cur_off + n && 2 * (l.delta_off - l.bucket_off) >= T &&
+                             nt * l.chunk > T && l.chunk % 2 == 1 && l.red_off >= l.delta_off + nt * l.chunk && l.red_off % 4 == 0;
+          printf("%d %d %d %d %d\n", nt, (n + nt - 1) / nt, s.nodes, l.bytes, apart);
+        }
   return 0;
 }
 """
@@ -52,6 +54,6 @@ def test_best_move_layout_fits_wherever_the_table_s_does(rows):
 
 
 def test_staged_layout_fits_and_covers_every_node(rows):
-    nt, per_lane, size, ok = rows("staged").T
+    nt, per_lane, nodes, size, ok = rows("staged").T
     assert ok.all() and (size <= 160 * 1024).all()
-    assert (per_lane <= 2).all() and (per_lane >= -4).all() and (nt[per_lane < 0] == 1024).all()
+    assert (per_lane <= nodes).all() and (nt[nodes == 4] == 1024).all()
