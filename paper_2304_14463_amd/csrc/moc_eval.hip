@@ -858,7 +858,10 @@ int launch_kernel(K kern, int nt, const moc_graph* g, const LdsLayout& lay, int6
   return MOC_OK;
 }
 
-template <int NT, int CT, int IT = kMaxIters>
+// The most node slots per lane a kernel is built for: C = 5 has more than three with 1024 threads only (block_threads).
+constexpr int max_iters(int nt, int C) { return C == 5 && nt < 1024 ? 3 : kMaxIters; }
+
+template <int NT, int CT, int IT = max_iters(NT, CT)>
 int launch_iters(int iters, const moc_graph* g, const LdsLayout& lay, int64_t B, const int32_t* s, const int32_t* e,
                  const uint8_t* a, moc_result* out, hipStream_t st, const LaunchOpts& src) {
   if constexpr (IT == 0) {
@@ -882,7 +885,7 @@ int slots_per_lane(int n, int m, int nt) {
 // candidate for small graphs, up to a full 1024-thread workgroup per compute unit).
 int block_threads(int n, int m, int C) {
   for (int nt = 64; nt < 1024; nt *= 2)
-    if (slots_per_lane(n, m, nt) <= (C == 5 ? 3 : 5) && (n * C + chunk_positions(nt)) / chunk_positions(nt) <= nt) return nt;
+    if (slots_per_lane(n, m, nt) <= std::min(5, max_iters(nt, C)) && (n * C + chunk_positions(nt)) / chunk_positions(nt) <= nt) return nt;
   return 1024;
 }
 
@@ -890,10 +893,11 @@ int block_threads(int n, int m, int C) {
 // registers, and every thread has at most one delta chunk.  (C = 5: four to seven times as fast as the general kernel,
 // which keeps the sizes that do not fit LDS, some 3300 nodes and more.  n = 50, 177777 candidates 370 -> 187 us; n = 150, 59259
 // 586 -> 134; n = 442, 20110 362 -> 91; n = 1000, 8888 492 -> 87; n = 2000, 4444 705 -> 96, every copy live 712 -> 164.)
-constexpr int kLdsBytes = 160 * 1024;
+constexpr int kLdsBytes = 160 * 1024;   // of a compute unit
+bool fits_five(int n, int m, int C, int nt, int max_lds) { return C != 5 || fast_layout(n, m, C, nt, max_lds).bytes <= max_lds; }
 bool fast_shape(int n, int m, int C, int nt) {
-  if (C == 5 && fast_layout(n, m, C, nt, kLdsBytes).bytes > kLdsBytes) return false;
-  return C <= 5 && n * C >= 4 && slots_per_lane(n, m, nt) <= kMaxIters && (n * C + chunk_positions(nt)) / chunk_positions(nt) <= nt &&
+  if (!fits_five(n, m, C, nt, kLdsBytes)) return false;
+  return C <= 5 && n * C >= 4 && slots_per_lane(n, m, nt) <= max_iters(nt, C) && (n * C + chunk_positions(nt)) / chunk_positions(nt) <= nt &&
          (n + 3) * moc_node_stride(C) <= 0xFFFF;
 }
 
@@ -901,7 +905,7 @@ template <int NT>
 int launch_nt(const moc_graph* g, int64_t B, const int32_t* s, const int32_t* e, const uint8_t* a, moc_result* out,
               hipStream_t st, bool aligned, const LaunchOpts& src) {
   const int n = g->view.n, m = g->view.m, C = g->view.C;
-  if (aligned && fast_shape(n, m, C, NT)) {
+  if (aligned && fast_shape(n, m, C, NT) && fits_five(n, m, C, NT, g->max_lds)) {
     const LdsLayout lay = fast_layout(n, m, C, NT, g->max_lds);
     const int iters = slots_per_lane(n, m, NT);
     switch (C) {
@@ -929,7 +933,7 @@ bool moc_eval_shape(int n, int m, int C, int* nt, int* edges_per_lane, int* edge
 int moc_eval_lds_bytes(int n, int m, int C, int max_lds) {
   const int nt = block_threads(n, m, C);
   const int general = general_layout(n, C, nt).bytes;
-  if (!fast_shape(n, m, C, nt)) return general;
+  if (!fast_shape(n, m, C, nt) || !fits_five(n, m, C, nt, max_lds)) return general;
   const int fast = fast_layout(n, m, C, nt, max_lds).bytes;   // misaligned candidate arrays fall back to the general kernel
   return fast > general ? fast : general;
 }

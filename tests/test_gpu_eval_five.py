@@ -10,7 +10,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("n,degree,B", [(1, 0, 9), (2, 1, 9), (3, 1, 70), (64, 2, 600), (65, 3, 70), (191, 2, 3000), (192, 1, 40), (193, 3, 40), (385, 3, 40), (400, 9, 40),
-                                        (769, 2, 2000), (1537, 2, 40), (2960, 3, 300), (3343, 3, 12), (3344, 3, 12), (300, 40, 12)])
+                                        (769, 2, 2000), (1537, 2, 40), (2960, 3, 300), (3343, 3, 12), (3344, 3, 12), (300, 40, 12),
+                                        (1500, 10, 12), (1500, 13, 12), (3300, 5, 12), (1500, 14, 12)])
 def test_five_copies(moc, n, degree, B):  # noqa: F811
     import torch
     from paper_2304_14463_amd.inputs import graph_from_edges
