@@ -21,9 +21,8 @@
 // over the changed positions (at most R of them unless the copy was outside
 // the domain before the move).
 // The live copies are listed while the base is staged, and behind them the
-// active copies that are not live.  Pass 1 counts the violations of the base
-// and marks the copies that take part in one.  Pass 2 runs one lane per (live
-// copy, field): it builds the 0/1 terms of f as bit
+// active copies that are not live.  Pass 1 counts the violations of the base.
+// Pass 2 runs one lane per (live copy, field): it builds the 0/1 terms of f as bit
 // masks over the displacements, sums them in bit planes and walks outwards from
 // the old position (see build_field, walk_own); a wave writes the rows of
 // consecutive copies, the inactive ones filled in.  (The best move without the
@@ -87,7 +86,7 @@ struct NbLds {
   uint16_t* list;   // the live copies, in order, and behind them the active copies that are not live
   uint32_t* occ1;
   uint32_t* occ2;
-  uint32_t* involved;   // bit k: copy k takes part in a violation of Eq. (3) or (5)
+  uint32_t* lmask;      // bit k: copy k is live
   uint32_t* amask;      // bit k: copy k is active
   int32_t* scratch;   // 8 words per wave + 16
 };
@@ -525,8 +524,8 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
   L.list = reinterpret_cast<uint16_t*>(L.packed + lay.T_pad);
   L.occ1 = reinterpret_cast<uint32_t*>(L.list + lay.T_pad);
   L.occ2 = L.occ1 + lay.bit_words;
-  L.involved = L.occ2 + lay.bit_words;
-  L.amask = L.involved + lay.mask_words;
+  L.lmask = L.occ2 + lay.bit_words;
+  L.amask = L.lmask + lay.mask_words;
   L.scratch = reinterpret_cast<int32_t*>(L.amask + lay.mask_words);
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int T = g.T, C = CT ? CT : g.C;
@@ -538,7 +537,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
   const int pieces = four_r <= kWave ? 1 : 2;
   const int sub = four_r <= kWave ? lane / four_r : 0;
   const int rem = four_r <= kWave ? lane - sub * four_r : lane;
-  int32_t* const counts = L.scratch + 8 * (kNT / kWave);   // [0] base violations, [1] live copies, [2] fewest violations of a move so far, [3] work drawn, [4] active copies that are not live, [5] work drawn from their moves
+  int32_t* const counts = L.scratch + 8 * (kNT / kWave);   // [0] base violations, [1] live copies, [2] active copies that are not live, [3] work drawn, [4] work drawn from the moves of the latter
   const bool pairs = (R & 1) == 0 && (reinterpret_cast<uintptr_t>(out_moves) & 15) == 0;   // scores stored two at a time
   constexpr int kNW = kNT / kWave;
   Adj<ADJ_LDS> A;
@@ -563,7 +562,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     const int wave_ = __builtin_amdgcn_readfirstlane(t_ / kWave);
 
     const int64_t row = b * T;
-    moc_move_score* const row0 = out_moves ? out_moves + b * (int64_t)moves_per_cand : nullptr;   // this candidate's table
+    moc_move_score* const row0 = out_moves + b * (int64_t)moves_per_cand;   // this candidate's table
     // ---- base candidate: stage copies, scatter deltas, mark starts
     // The candidate's first kAhead * kNT copies are asked for before the arrays are cleared, all
     // at once and without conditions (lanes past the last copy read it again): they arrive
@@ -587,7 +586,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     }
     for (int t = t_; t < T; t += kNT) L.profile[t] = 0;
     for (int w = t_; w < 2 * lay.bit_words; w += kNT) L.occ1[w] = 0;   // occ1, occ2
-    if (t_ < 6) counts[t_] = t_ == 2 ? 0x7FFFFFFF : 0;
+    if (t_ < 5) counts[t_] = 0;
     if (t_ == 0) { L.pmax[-1] = 0; L.smax[T] = 0; }
     __syncthreads();
     // whole waves, 64 consecutive copies each: a ballot gives the active flags of the 64
@@ -614,10 +613,10 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
       if (lane_ == 0) {
         L.amask[k0 >> 5] = (uint32_t)am;
         L.amask[(k0 >> 5) + 1] = (uint32_t)(am >> 32);
-        L.involved[k0 >> 5] = (uint32_t)lm;   // the live copies, until pass 1 begins
-        L.involved[(k0 >> 5) + 1] = (uint32_t)(lm >> 32);
+        L.lmask[k0 >> 5] = (uint32_t)lm;
+        L.lmask[(k0 >> 5) + 1] = (uint32_t)(lm >> 32);
         atomicAdd(&counts[1], __popcll(lm));
-        atomicAdd(&counts[4], __popcll(am & ~lm));
+        atomicAdd(&counts[2], __popcll(am & ~lm));
       }
     };
 #pragma unroll
@@ -634,21 +633,20 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     // in the same way, the active copies that are not live
     auto chunk = [&](const uint32_t* bits, int c) { return (uint64_t)bits[2 * c] | ((uint64_t)bits[2 * c + 1] << 32); };
     const int chunks = lay.mask_words / 2;
-    const int n_live = __builtin_amdgcn_readfirstlane(counts[1]), n_ill = __builtin_amdgcn_readfirstlane(counts[4]);
+    const int n_live = __builtin_amdgcn_readfirstlane(counts[1]), n_ill = __builtin_amdgcn_readfirstlane(counts[2]);
     for (int c = wave_; c < chunks; c += kNW) {
       int both = 0;   // live copies before these 64, and (from bit 16 on) active copies that are not live
       for (int x = lane_; x < c; x += kWave) {
-        const int live = __popcll(chunk(L.involved, x));
+        const int live = __popcll(chunk(L.lmask, x));
         both += live + ((__popcll(chunk(L.amask, x)) - live) << 16);
       }
       both = last_lane(scan_sum(both));
       const int before = both & 0xFFFF, before_ill = both >> 16;
-      const uint64_t lm = chunk(L.involved, c), ill = chunk(L.amask, c) & ~lm, lower = ((uint64_t)1 << lane_) - 1;
+      const uint64_t lm = chunk(L.lmask, c), ill = chunk(L.amask, c) & ~lm, lower = ((uint64_t)1 << lane_) - 1;
       if ((lm >> lane_) & 1) L.list[before + __popcll(lm & lower)] = (uint16_t)(c * kWave + lane_);
       if ((ill >> lane_) & 1) L.list[n_live + before_ill + __popcll(ill & lower)] = (uint16_t)(c * kWave + lane_);
     }
     block_running_sum<kNT>(L.profile, T, L.scratch, t_);   // Eq. (4) per position
-    for (int w = t_; w < lay.mask_words; w += kNT) L.involved[w] = 0;
     block_max_both_ways<kNT>(L.profile, L.pmax, L.smax, T, L.scratch, t_);
 
     // ---- pass 1: the violations of the base, each instance once: the copies that are not well formed by
@@ -659,16 +657,10 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
       const uint32_t mine = L.packed[k];
       const int v = C == 1 ? k : (int)__umulhi((uint32_t)k, c_magic), i = k - v * C;
       const int s = (int)(mine & 0xFFFFu), e = (int)(mine >> 16);
-      auto mark = [&](int copy) { atomicOr(&L.involved[copy >> 5], 1u << (copy & 31)); };
-      if (bit_at(L.occ2, s)) mark(k);   // Eq. (6): the start is shared
       for (int jj = i + 1; jj < C; ++jj) {   // Eq. (3)
         const uint32_t p = L.packed[v * C + jj];
         if (live_of(p)) {
-          if (e > (int)(p & 0xFFFFu)) {
-            ++viol;
-            mark(k);
-            mark(v * C + jj);
-          }
+          viol += e > (int)(p & 0xFFFFu) ? 1 : 0;
           break;
         }
       }
@@ -676,11 +668,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
         const int u = A.in_idx[q];
         bool cov = false;
         for (int jj = 0; jj < C; ++jj) cov = cov || covers1(L.packed[u * C + jj], (uint32_t)s);
-        if (!cov) {   // the consumer and every copy of the provider could mend it
-          ++viol;
-          mark(k);
-          for (int jj = 0; jj < C; ++jj) mark(u * C + jj);
-        }
+        viol += cov ? 0 : 1;
       }
     }
     int distinct = 0;
@@ -694,25 +682,13 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     // writes one contiguous stretch of the table (HBM takes long runs much faster than
     // scattered 128-byte rows).
     Best best{0, 0, -1};
-    // (The pointer is tested although the table is always asked for: the build that knows it to be set orders its
-    // waits differently and takes 3.5 ms for the table instead of 3.0.)
-    const bool table = out_moves != nullptr;
-    const int draw = table ? kWave / 2 : kWave;
-    const int total = table ? max(n_live, 1) : 2 * n_live;
+    constexpr int draw = kWave / 2;
     for (;;) {
       int u0 = 0;
       if (lane == 0) u0 = atomicAdd(&counts[3], draw);
       u0 = __builtin_amdgcn_readfirstlane(u0);
-      if (u0 >= total) break;
-      int entry, field;
-      if (table) {
-        entry = u0 + (lane & 31);
-        field = lane >> 5;
-      } else {
-        const int u = u0 + lane;
-        field = u >= n_live ? 1 : 0;
-        entry = u - field * n_live;
-      }
+      if (u0 >= max(n_live, 1)) break;
+      const int entry = u0 + (lane & (draw - 1)), field = lane / draw;
       const bool has_unit = entry < n_live;
       const int k = has_unit ? L.list[entry] : 0;
       const int v = C == 1 ? k : (int)__umulhi((uint32_t)k, c_magic), i = k - v * C;
@@ -721,7 +697,8 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
       FieldState<WIDE> st{};
       st.field = -1;
       // (`left_out` is always false.  Without it the compiler spills one register more, inside this loop, where a reload
-      // waits behind the table's stores: 374 instead of 346 us.)
+      // waits behind the table's stores: n = 2000, C = 2, R = 8, 1024 bases 360 instead of 345 us.  Nor is row0 ever null: without
+      // the tests of it those take 342, but R = 32, n = 60, 256 bases 48 instead of 46.)
       const bool build = has_unit;
       bool left_out = false;
       if (build) build_field<CT, WIDE>(A, C, sz, L, T, R, v, i, field, L.packed[k], base_viol, q0, st);
@@ -737,7 +714,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
         const int s = starts[row + k], e = ends[row + k];
         const int base_rest = base_viol - node_part(A, C, L.packed, v, i, true, true, s, e);
         for (int d = 0; d < two_r; ++d) {
-          const int moved = (field == 0 ? s : e) + (d < R ? d - R : d - R + 1);
+          const int moved = (int)((uint32_t)(field == 0 ? s : e) + (uint32_t)(d < R ? d - R : d - R + 1));
           moc_move_score sc{-1, -1};
           if (moved >= 0 && moved < T) {
             score_move(A, C, sz, L, T, v, i, field, s, e, moved, base_rest, base_peak, sc);
@@ -747,7 +724,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
           if (row0) store_score(row0, (uint32_t)(q0 + d), sc);
         }
       }
-      if (table) {   // the moves of the inactive copies from this block's first copy to the next block's are not applicable
+      {   // the moves of the inactive copies from this block's first copy to the next block's are not applicable
         const int k_lo = u0 == 0 ? 0 : (int)L.list[u0];
         const int k_hi = u0 + draw < n_live ? (int)L.list[u0 + draw] : T;
         for (int kk0 = k_lo; kk0 < k_hi; kk0 += per_wave) {
@@ -765,7 +742,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
     // moves of a field cost every wave with one such copy 2R times the walk over the node's edges.
     for (;;) {
       int m0 = 0;
-      if (lane == 0) m0 = atomicAdd(&counts[5], kWave);
+      if (lane == 0) m0 = atomicAdd(&counts[4], kWave);
       m0 = __builtin_amdgcn_readfirstlane(m0);
       if (m0 >= n_ill * four_r) break;
       const int at = m0 + lane;
@@ -774,7 +751,7 @@ __global__ __launch_bounds__(kNT) __attribute__((amdgpu_waves_per_eu(8, 8))) voi
         const int k = L.list[n_live + j], field = in_copy >= two_r ? 1 : 0, d = in_copy - field * two_r;
         const int v = C == 1 ? k : (int)__umulhi((uint32_t)k, c_magic), i = k - v * C;
         const int s = starts[row + k], e = ends[row + k];
-        const int moved = (field == 0 ? s : e) + (d < R ? d - R : d - R + 1);
+        const int moved = (int)((uint32_t)(field == 0 ? s : e) + (uint32_t)(d < R ? d - R : d - R + 1));
         const int s2 = field == 0 ? moved : s, e2 = field == 0 ? e : moved;
         moc_move_score sc{-1, -1};
         if (moved >= 0 && moved < T) {
