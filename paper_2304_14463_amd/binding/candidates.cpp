@@ -10,6 +10,8 @@
 
 #include <stdint.h>
 
+#include "moccasin.h"
+
 namespace {
 
 using CandidateCall = int (*)(const void* g, int64_t B, const void* starts, const void* ends, const void* active, void* out, void* stream);
@@ -115,4 +117,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_candidates", nullptr, -1, methods
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__candidates() { return PyModule_Create(&module); }
+// abi_version: of the header that this was built with.
+PyMODINIT_FUNC PyInit__candidates() {
+  PyObject* const made = PyModule_Create(&module);
+  if (made && PyModule_AddIntConstant(made, "abi_version", MOC_ABI_VERSION) != 0) {
+    Py_DECREF(made);
+    return nullptr;
+  }
+  return made;
+}

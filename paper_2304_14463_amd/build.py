@@ -78,7 +78,7 @@ def build_binding():
     from torch.utils.cpp_extension import include_paths
     lib_dir = os.path.join(os.path.dirname(torch.__file__), "lib")
     _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}",
-          *[f"-I{p}" for p in include_paths()], f"-I{sysconfig.get_paths()['include']}", "-o", BINDING,
+          "-I", os.path.join(ROOT, "include"), *[f"-I{p}" for p in include_paths()], f"-I{sysconfig.get_paths()['include']}", "-o", BINDING,
           os.path.join(PKG, "binding", "candidates.cpp"), f"-L{lib_dir}", f"-Wl,-rpath,{lib_dir}", "-ltorch_python", "-ltorch_cpu", "-lc10"])
     return BINDING
 

@@ -168,7 +168,13 @@ def _candidates():
     global _native
     if _native is None:
         _tc()
-        from . import _candidates as native   # built with the library
+        try:
+            from . import _candidates as native   # built with the library
+        except ImportError as err:
+            raise RuntimeError(f"{_PKG}: the binding's native part does not load ({err}); run python -m paper_2304_14463_amd.build") from err
+        if getattr(native, "abi_version", None) != MOC_ABI_VERSION:
+            raise RuntimeError(f"{native.__file__}: ABI version {getattr(native, 'abi_version', None)}, expected {MOC_ABI_VERSION}; "
+                               "run python -m paper_2304_14463_amd.build")
         _native = native
     return _native
 

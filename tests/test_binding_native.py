@@ -30,3 +30,23 @@ def test_results_are_made_like_the_candidates():
     assert x.shape == (7,) and x.dtype is torch.int32 and x.data_ptr() == at and not x.requires_grad
     with pytest.raises(RuntimeError):
         native.empty(torch.zeros(2), 1, -1, 24)
+
+
+@pytest.mark.parametrize("native", [None, 1], ids=["missing", "of another version"])
+def test_native_part_that_does_not_fit_the_binding(monkeypatch, native):
+    """... is refused with the command that builds it."""
+    import sys
+    import types
+
+    import paper_2304_14463_amd
+    from paper_2304_14463_amd import moccasin
+    other = None if native is None else types.ModuleType("paper_2304_14463_amd._candidates")
+    if other is not None:
+        other.abi_version, other.__file__ = native, "elsewhere.so"
+    monkeypatch.setitem(sys.modules, "paper_2304_14463_amd._candidates", other)
+    monkeypatch.delattr(paper_2304_14463_amd, "_candidates", raising=False)
+    if other is not None:
+        monkeypatch.setattr(paper_2304_14463_amd, "_candidates", other, raising=False)
+    monkeypatch.setattr(moccasin, "_native", None)
+    with pytest.raises(RuntimeError, match="paper_2304_14463_amd.build"):
+        moccasin._candidates()
