@@ -301,12 +301,11 @@ def moc_search_moves(g: Graph, starts, ends, active, R, max_steps, out_steps=Non
     torch = _tc()
     B, ps, pe, pa = _cand_ptrs(g, starts, ends, active)
     with _on(stream):
-        work_results = torch.empty((B, RESULT_DTYPE.itemsize), dtype=torch.uint8, device=starts.device)
         work_best = torch.empty((B, BEST_MOVE_DTYPE.itemsize), dtype=torch.uint8, device=starts.device)
         if out_steps is None:
             out_steps = torch.empty((B,), dtype=torch.int32, device=starts.device)
-    code = lib().moc_search_moves(g._h, B, ps, pe, pa, int(R), int(max_steps),
-                                  work_results.data_ptr(), work_best.data_ptr(),
+    unused = work_best.data_ptr()   # the call asks for work_results and does not use them
+    code = lib().moc_search_moves(g._h, B, ps, pe, pa, int(R), int(max_steps), unused, work_best.data_ptr(),
                                   out_steps.data_ptr(), _stream_handle(stream))
     _check(code, "moc_search_moves")
     return out_steps
