@@ -100,7 +100,14 @@ PyObject* evaluate(PyObject*, PyObject* const* args, Py_ssize_t count) {
   }
   THPObjectPtr held(result);
   if (!held) throw python_error();
-  void* const out = tensor(result).data_ptr();
+  void* out;
+  if (THPVariable_Check(result)) {
+    out = THPVariable_Unpack(result).data_ptr();
+  } else {   // anything that says where it lies, a storage for one
+    THPObjectPtr at(PyObject_CallMethod(result, "data_ptr", nullptr));
+    if (!at) throw python_error();
+    out = reinterpret_cast<void*>(address(at));
+  }
   int code;
   Py_BEGIN_ALLOW_THREADS
   code = call(handle, c.B, c.starts, c.ends, c.active, out, stream);

@@ -50,3 +50,22 @@ def test_native_part_that_does_not_fit_the_binding(monkeypatch, native):
     monkeypatch.setattr(moccasin, "_native", None)
     with pytest.raises(RuntimeError, match="paper_2304_14463_amd.build"):
         moccasin._candidates()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("call", ["moc_eval_batch", "moc_eval_batch_staged", "moc_eval_toggles"])
+def test_results_into_a_storage(call):
+    """`out` may be whatever has a data_ptr()."""
+    from paper_2304_14463_amd import moccasin as moc
+    g = moc.moc_graph_upload(3, [0, 0, 1, 2], [0, 1], [5, 6, 7], [1, 1, 1], 100, 1)
+    moc.moc_graph_set_order(g, [0, 1, 2])
+    s = torch.tensor([0, 2, 5] if call.endswith("staged") else [0, 1, 2], dtype=torch.int32, device="cuda")
+    e, a = s + 1, torch.ones(3, dtype=torch.uint8, device="cuda")
+    want = getattr(moc, call)(g, s, e, a)
+    room = torch.zeros_like(want)
+    storage = room.untyped_storage()
+    assert getattr(moc, call)(g, s, e, a, out=storage) is storage
+    assert (room == want).all() and want.any()
+    with pytest.raises(AttributeError):
+        getattr(moc, call)(g, s, e, a, out=[0])
+    g.free()
