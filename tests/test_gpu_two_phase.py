@@ -61,6 +61,40 @@ def test_keep_cuts_small_graphs(moc, n, C):
     gh.free()
 
 
+@pytest.mark.parametrize("n,C", [(80, 2), (150, 3), (400, 4)])
+def test_keep_cuts_where_inputs_are_missing(moc, n, C):
+    """Inputs that are computed behind their use, switched off, not well formed, or there again only by a later copy: at
+    the last free position before a use some have a copy and some have not, at lower ones fewer."""
+    from paper_2304_14463_amd.inputs import graph_from_edges
+    rng = np.random.default_rng(n + C)
+    edges = sorted({(int(u), v) for v in range(1, n) for u in rng.integers(max(0, v - 12), v, size=3)})
+    g = graph_from_edges(n, edges, rng.integers(1, 50, n), rng.integers(1, 9, n))
+    B, T = 9, n * C
+    s, e, a = schedules(rng, g, C, B, wild=False)
+    for b in range(B):
+        v = np.flatnonzero(rng.random(n) < 0.3) * C
+        kind = rng.integers(0, 4, v.size)
+        late, off, bad, again = (v[kind == x] for x in range(4))
+        s[b, late] = np.minimum(s[b, late] + rng.integers(1, 20 * C, late.size), T - 1)
+        e[b, late] = np.maximum(e[b, late], s[b, late])
+        a[b, off] = 0
+        e[b, bad] = s[b, bad] - 1
+        e[b, again] = s[b, again]
+        s[b, again + 1], a[b, again + 1] = np.minimum(s[b, again] + 1 + rng.integers(0, 8 * C, again.size), T - 1), 1
+        e[b, again + 1] = np.minimum(s[b, again + 1] + rng.integers(0, 6, again.size), T - 1)
+    budget = int(g.size.sum()) // 2
+    gh = moc.moc_graph_upload(n, g.in_ptr, g.in_idx, g.size, g.dur, budget, C)
+    got, best = gpu_keep_cuts(moc, gh, *to_dev(s, e, a))
+    none = some = 0
+    for b in range(B):
+        want = oracle.cuts(g, budget, C, s[b], e[b], a[b], with_at_peak=True, mode=1)
+        assert_same(got[b], want, f"n={n} C={C} row {b}")
+        assert_best(best[b], want, f"n={n} C={C} row {b}")
+        none, some = none + int((want[:, 0] < 0).sum()), some + int((want[:, 0] >= 0).sum())
+    assert none > 0 and some > 0
+    gh.free()
+
+
 def test_keep_cuts_hub_and_long_inputs(moc):
     """One node feeds all others, another is fed by many: long walks over kept inputs."""
     from paper_2304_14463_amd.inputs import graph_from_edges
