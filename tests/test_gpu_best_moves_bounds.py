@@ -74,3 +74,21 @@ def test_copies_at_the_ends_of_the_integers(moc, n, C, R):  # noqa: F811
     s = np.where(rng.random((B, T)) < 0.3, rng.choice(far, (B, T)), s).astype(np.int32)
     e = np.where(rng.random((B, T)) < 0.3, rng.choice(far, (B, T)), e).astype(np.int32)
     same_best(moc, g, C, R, s, e, a)
+
+
+# copies that one move makes live over most of the domain: more blocks of it than a move of a live copy can change
+@pytest.mark.parametrize("n,C,R", [(4000, 2, 2), (900, 3, 32), (4300, 1, 1)])
+def test_copies_one_position_outside(moc, n, C, R):  # noqa: F811
+    rng = np.random.default_rng(n)
+    g = graph(rng, n, 1)
+    B, T = 6, n * C
+    s, e, a = (np.zeros((B, T), t) for t in (np.int32, np.int32, np.uint8))
+    s[:, ::C], a[:, ::C] = np.arange(n) * C, 1
+    e[:, ::C] = np.maximum(s[:, ::C], T - 1 - rng.integers(0, 9, (B, n), dtype=np.int32))
+    for b in range(B):
+        at = np.flatnonzero(rng.random(n) < (0.01, 0.5)[b % 2]) * C
+        if b < 4:
+            e[b, at] = T - 1 + rng.integers(1, R + 2, at.size)
+        if b >= 2:
+            s[b, at] = -rng.integers(1, R + 2, at.size)
+    same_best(moc, g, C, R, s, e, a)
