@@ -135,12 +135,13 @@ __device__ __forceinline__ MoveScore score_row(const GraphView& g, const BaseLds
 //
 // Bound by the chain of passes over a base, each short and with a barrier behind it: n = 442, 1024 bases, four
 // workgroups of 256 to a compute unit, 14 us of a base are 2 staging, 3 the edges, 2 nodes and profile, 2 picking,
-// 4.5 scoring in 1.4 rounds.  R = 8, C = 2, n = 442, 1024 bases 45 -> 21 us, n = 1000 73 -> 33, n = 2000, 2048 bases 261 -> 104 (before, one
+// 4.5 scoring in 1.4 rounds.  R = 8, C = 2, n = 442, 1024 bases 43 -> 20 us, n = 1000 72 -> 34, n = 2000, 2048 bases 265 -> 103 (before, one
 // lane per copy and field over all that could have fewer violations than the best so far).  Rows of random intervals, where
 // few fields can be left out: n = 442, 1024 bases 27 us, 92 while the consumer's start was counted for every uncovered input
 // (82 before there were bounds); 256 walkers, 16 steps 434 (778, 522).  80 registers a thread
-// with C <= 2 (82, one wave a SIMD fewer, for 4096 bases 60 us instead of 51; 64 spill, n = 442 26 us), 85 to 92 with
-// more copies, five waves; one lane per move with all edges of a node in turn scores in twice the time.
+// with C <= 2, of which a descent spills two (82 are one wave a SIMD fewer: 4096 bases 60 us instead of 51, descents, 3000
+// walkers 253 instead of 187, n = 1000, 700 walkers 123 instead of 96; 64 spill, n = 442 26 us), 85 to 92 with more copies,
+// five waves; one lane per move with all edges of a node in turn scores in twice the time.
 template <bool KEPT>
 struct RowPtr { using Ptr = const int32_t* __restrict__; };
 template <>
@@ -153,7 +154,7 @@ struct MoveSteps {
 };
 
 template <int NT, bool LOOP, int CT, bool SEARCH, bool KEPT>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(KEPT && (CT == 1 || CT == 2) ? 6 : 5)))
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(CT == 1 || CT == 2 ? 6 : 5)))
 void best_neighbours_kernel(GraphView g, int64_t B, typename RowPtr<KEPT>::Ptr starts,
                                                              typename RowPtr<KEPT>::Ptr ends, const uint8_t* __restrict__ active, int R,
                                                              moc_best_move* __restrict__ out_best, MoveSteps search, BmLayout lay) {
