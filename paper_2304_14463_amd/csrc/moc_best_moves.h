@@ -55,9 +55,9 @@ __device__ __forceinline__ MoveScore score_row(const GraphView& g, const BaseLds
       }
     }
   }
-  // the lanes of the row for which `matters` holds, one after the other; take(lane)
-  auto each = [&](bool matters, auto take) {
-    uint32_t left = (uint32_t)(__ballot(matters) >> row0) & ((1u << row_lanes) - 1);
+  // the row's lanes of `matters`, one after the other; take(lane)
+  auto each = [&](lanemask matters, auto take) {
+    uint32_t left = (uint32_t)(matters >> row0) & ((1u << row_lanes) - 1);
     while (__any(left != 0)) {
       const int from = row0 + (left ? __ffs(left) - 1 : 0);
       take(from, left != 0);
@@ -67,20 +67,20 @@ __device__ __forceinline__ MoveScore score_row(const GraphView& g, const BaseLds
   // Eq. (5), the copy as consumer: inputs that are there at some of the starts the field can take and not at others;
   // one that is at none counts as often as the copy is live
   {
-    const int from = f.field == 0 ? f.s - R : f.s, to = f.field == 0 ? f.s + R : f.s;
+    const uint32_t from = (uint32_t)max(f.field == 0 ? f.s - R : f.s, 0), to = (uint32_t)max(f.field == 0 ? f.s + R : f.s, 0);
     const int life = (live_new ? 1 : 0) - (live_old ? 1 : 0);
     for (int x = in_lo; __any(x < in_hi); x += row_lanes) {
       if (x != in_lo) u = x + in_row < in_hi ? g.in_idx[x + in_row] : -1;
-      bool always = false, sometimes = false;
-      if (u >= 0)
-        for (int j = 0; j < C; ++j) {
-          const int su = (int)(L.packed[u * C + j] & 0xFFFFu), eu = (int)(L.packed[u * C + j] >> 16);
-          always = always || (su < from && eu >= to);
-          sometimes = sometimes || (su < to && eu >= from);
-        }
-      const uint32_t never = (uint32_t)(__ballot(u >= 0 && !sometimes) >> row0) & ((1u << row_lanes) - 1);
-      d += life * __popc(never);
-      each(sometimes && !always, [&](int lane_of, bool on) {
+      const uint32_t* const inputs = L.packed + max(u, 0) * C;
+      const lanemask input = __ballot(u >= 0);
+      lanemask always = 0, sometimes = 0;
+      for (int j = 0; j < C; ++j) {
+        const uint32_t pu = inputs[j];
+        always |= spans_lanes(pu, from, to);
+        sometimes |= spans_lanes(pu, to, from);
+      }
+      d += life * __popc((uint32_t)((input & ~sometimes) >> row0) & ((1u << row_lanes) - 1));
+      each(input & sometimes & ~always, [&](int lane_of, bool on) {
         const int un = __builtin_amdgcn_ds_bpermute(lane_of << 2, u);
         if (!on) return;
         bool cov_old = !live_old, cov_new = !live_new;
@@ -100,11 +100,11 @@ __device__ __forceinline__ MoveScore score_row(const GraphView& g, const BaseLds
     for (int x = out_lo; __any(x < out_hi); x += row_lanes) {
       if (x != out_lo) w = x + in_row < out_hi ? g.out_idx[x + in_row] : -1;
       for (int j = 0; j < C; ++j) {
-        const int at = w >= 0 ? (int)(L.packed[w * C + j] & 0xFFFFu) : 0xFFFF;
-        bool matters = at != 0xFFFF && at > from && at <= to;
-        for (int q = 0; q < C; ++q) matters = matters && !(q != f.i && covers1(row[q], (uint32_t)at));
-        each(matters, [&](int lane_of, bool on) {
-          const uint32_t t = (uint32_t)__builtin_amdgcn_ds_bpermute(lane_of << 2, at);
+        const uint32_t at = w >= 0 ? L.packed[w * C + j] & 0xFFFFu : 0xFFFFu;
+        lanemask held = 0;   // by another copy of v
+        for (int q = 0; q < C; ++q) held |= covers_lanes(row[q], at) & __ballot(q != f.i);
+        each(low_ne_k(at, 0xFFFFu) & i_gt(at, (uint32_t)from) & ~i_gt(at, (uint32_t)to) & ~held, [&](int lane_of, bool on) {
+          const uint32_t t = (uint32_t)__builtin_amdgcn_ds_bpermute(lane_of << 2, (int)at);
           if (on) d += (covers1(before, t) ? 1 : 0) - (covers1(after, t) ? 1 : 0);
         });
       }
@@ -137,8 +137,8 @@ __device__ __forceinline__ MoveScore score_row(const GraphView& g, const BaseLds
 // workgroups of 256 to a compute unit, 14 us of a base are 2 staging, 3 the edges, 2 nodes and profile, 2 picking,
 // 4.5 scoring in 1.4 rounds.  R = 8, C = 2, n = 442, 1024 bases 43 -> 20 us, n = 1000 72 -> 34, n = 2000, 2048 bases 265 -> 103 (before, one
 // lane per copy and field over all that could have fewer violations than the best so far).  Rows of random intervals, where
-// few fields can be left out: n = 442, 1024 bases 27 us, 92 while the consumer's start was counted for every uncovered input
-// (82 before there were bounds); 256 walkers, 16 steps 434 (778, 522).  80 registers a thread
+// few fields can be left out: n = 442, 1024 bases 26 us, 92 while the consumer's start was counted for every uncovered input
+// (82 before there were bounds); 256 walkers, 16 steps 411 (770, 520).  80 registers a thread
 // with C <= 2, of which a descent spills two (82 are one wave a SIMD fewer: 4096 bases 60 us instead of 51, descents, 3000
 // walkers 253 instead of 187, n = 1000, 700 walkers 123 instead of 96; 64 spill, n = 442 26 us), 85 to 92 with more copies,
 // five waves; one lane per move with all edges of a node in turn scores in twice the time.
@@ -232,8 +232,15 @@ void best_neighbours_kernel(GraphView g, int64_t B, typename RowPtr<KEPT>::Ptr s
         if (add != 0) atomicAdd(&red[k], add);
       };
       auto edge = [&](uint32_t pair, lanemask in) {
-        const uint32_t* const pu = L.packed + (pair & 0xFFFFu);
-        const uint32_t* const pv = L.packed + (pair >> 16);
+        const uint32_t* pu = L.packed + (pair & 0xFFFFu);
+        const uint32_t* pv = L.packed + (pair >> 16);
+        uint32_t copies[CT ? 2 * CT : 1];   // all at once: read one by one they would be read again behind each atomic below
+        if constexpr (CT > 0) {
+#pragma unroll
+          for (int j = 0; j < CT; ++j) { copies[j] = pu[j]; copies[CT + j] = pv[j]; }
+          pu = copies;
+          pv = copies + CT;
+        }
         for (int i = 0; i < C; ++i) {
           const uint32_t copy = pv[i], at = copy & 0xFFFFu;
           lanemask held = 0;
@@ -248,12 +255,9 @@ void best_neighbours_kernel(GraphView g, int64_t B, typename RowPtr<KEPT>::Ptr s
             for (int j = 0; j < C; ++j) {
               const uint32_t p = pu[j];
               const int s = (int)(p & 0xFFFFu), e = (int)(p >> 16);
-              if (s - R < x && e + R >= x) {   // live
-                mine |= s < e ? kStart : 0u;
-                could((int)(pair & 0xFFFFu) + j, s < x ? kEnd : x > 0 ? kStart : 0u);
-              } else if (p == (MOC_DEAD | 0x10000u)) {
-                could((int)(pair & 0xFFFFu) + j, kStart | kEnd);
-              }
+              const bool close = s - R < x && e + R >= x;   // (no copy that is not live)
+              mine |= close && s < e ? kStart : 0u;
+              could((int)(pair & 0xFFFFu) + j, close ? (s < x ? kEnd : x > 0 ? kStart : 0u) : p == (MOC_DEAD | 0x10000u) ? kStart | kEnd : 0u);
             }
             could((int)(pair >> 16) + i, mine);
           }
@@ -327,23 +331,24 @@ void best_neighbours_kernel(GraphView g, int64_t B, typename RowPtr<KEPT>::Ptr s
         // moves that mend nothing: one round of them mostly has one that leaves the peak where it is
         const bool first_of_many = lo == 0 && (c0 == 0 || best == 0 || best_viol > base_viol || (best_viol == base_viol && best_peak > base_peak));
         int c1 = first_of_many ? min(c0 + NW * rows, T) : T;
-        // whether a field that leaves at least `viol` violations can still have the best move; size: what it lowers the peak by at most
-        auto could_win = [&](int k, int f, uint32_t p, int viol, int size) {
+        // whether a field that leaves at least `viol` violations can still have the best move
+        auto could_win = [&](int k, int f, uint32_t p, int viol, auto with_sizes) {
           if (viol != best_viol) return viol < best_viol;
-          // only a field that gives up all positions at the peak lowers it
+          const bool earlier = (2 * k + f) * two_r < best_move;
+          // only a field that gives up all positions at the peak lowers it, by its node's size at most
           const int s = (int)(p & 0xFFFFu), e = (int)(p >> 16);
-          const bool lowers = live_of(p) && (f == 0 ? s <= first && last < s + R : last <= e && first > e - R);
-          const int peak = lowers ? base_peak - size : base_peak;
-          return peak < best_peak || (peak == best_peak && (2 * k + f) * two_r < best_move);
+          if (live_of(p) && (f == 0 ? s <= first && last < s + R : last <= e && first > e - R)) {
+            if (!with_sizes()) return true;
+            const int peak = base_peak - g.size_dur[k / C].x;
+            return peak < best_peak || (peak == best_peak && earlier);
+          }
+          return base_peak < best_peak || (base_peak == best_peak && earlier);
         };
         // Where far more are queued than are scored at once: only the upper half of these counts, whose best mostly leaves
-        // nothing to do for the others; of one count those that pass with the sizes of their nodes looked at (they are in
-        // memory); no more than there is room for.
-        // Where far more are queued than are scored at once: only the upper half of these counts, whose best mostly leaves
         // nothing to do for the others; of a single count those that pass with the sizes of their nodes looked at; no more
-        // than there is room for.  Random intervals, n = 442, 256 walkers, 16 steps: 434 us, 1174 with counts taken together as
+        // than there is room for.  Random intervals, n = 442, 256 walkers, 16 steps: 411 us, 1174 with counts taken together as
         // the rounds go on, however many fields that makes.  Every output kept to the end, where all ends lower the peak, R =
-        // 8, n = 442, 1024 bases: 24 us, 77 without the sizes (48 before there were bounds).  (They are in memory: looked at
+        // 8, n = 442, 1024 bases: 23 us, 77 without the sizes (48 before there were bounds).  (They are in memory: looked at
         // for every field, clean rows, n = 442, 3000 walkers, 8 steps take 187 us instead of 182.)
         auto gather = [&](auto with_sizes) {
           for (int k = c0 + t; k < c1; k += NT) {
@@ -353,7 +358,7 @@ void best_neighbours_kernel(GraphView g, int64_t B, typename RowPtr<KEPT>::Ptr s
             for (int f = 0; f < 2; ++f) {
               const int mends = (int)(f == 0 ? r & 0xFFFFu : r >> 16);
               bool take = mends >= lo && mends < hi;
-              if (best != 0 && take && mends < (int)kMany) take = could_win(k, f, p, base_viol - mends, with_sizes() ? g.size_dur[k / C].x : base_peak);
+              if (best != 0 && take && mends < (int)kMany) take = could_win(k, f, p, base_viol - mends, with_sizes);
               if (take) {
                 const int at = atomicAdd(queued, 1);
                 if (at < lay.cap) queue[at] = (uint16_t)(2 * k + f);

@@ -1,4 +1,5 @@
-// Predicates as lane masks, shared by the evaluation and the decode kernels.
+// Predicates as lane masks, shared by the kernels of the evaluation, the staged evaluation, decode, toggles and the best
+// single-field move.
 #pragma once
 
 #include "moc_cover.h"
@@ -52,13 +53,15 @@ MOC_BYTE_CMP(byte3_ne_k, "BYTE_3")
 MOC_BYTE_CMP(low_ne_k, "WORD_0")
 MOC_BYTE_CMP(high_ne_k, "WORD_1")
 #undef MOC_BYTE_CMP
-// a copy packed as s | e << 16 covers position x: s < x and e >= x
-__device__ __forceinline__ lanemask covers_lanes(uint32_t packed, uint32_t x) {
+// of a copy packed as s | e << 16: s < x and e >= y
+__device__ __forceinline__ lanemask spans_lanes(uint32_t packed, uint32_t x, uint32_t y) {
   lanemask below, reaches;
   asm("v_cmp_lt_u32_sdwa %0, %1, %2 src0_sel:WORD_0 src1_sel:DWORD" : "=s"(below) : "v"(packed), "v"(x));
-  asm("v_cmp_ge_u32_sdwa %0, %1, %2 src0_sel:WORD_1 src1_sel:DWORD" : "=s"(reaches) : "v"(packed), "v"(x));
+  asm("v_cmp_ge_u32_sdwa %0, %1, %2 src0_sel:WORD_1 src1_sel:DWORD" : "=s"(reaches) : "v"(packed), "v"(y));
   return below & reaches;
 }
+// it covers position x
+__device__ __forceinline__ lanemask covers_lanes(uint32_t packed, uint32_t x) { return spans_lanes(packed, x, x); }
 template <typename F>
 __device__ __forceinline__ lanemask byte_ne_k(F a, int i, uint32_t b) {
   return i == 0 ? byte0_ne_k(a, b) : i == 1 ? byte1_ne_k(a, b) : i == 2 ? byte2_ne_k(a, b) : byte3_ne_k(a, b);

@@ -837,7 +837,7 @@ NbKernel pick_kernel(int nt, bool adj_lds, int C, int R) {
 // short passes over T positions: a small base does not feed 16 waves, and several bases on a compute
 // unit hide each other's latencies, as long as the batch has several per unit.  R = 8, C = 2, 1024 bases,
 // microseconds by 256 / 512 / 1024 threads: n = 442 90 / 99 / 112, n = 1000 191 / 178 / 208, n = 2000 577 / 376 / 346.  At most
-// one base to a compute unit: n = 60, 250 bases 28 / 30 / 32; n = 128, R = 4, 191 bases 23.5 / 21.1 / 23.9; n = 250, 250 bases 42 / 33 / 32; n =
+// one base to a compute unit: n = 60, 250 bases 28 / 30 / 32, R = 32, 100 bases 46 / - / 51; n = 128, R = 4, 191 bases 23.5 / 21.1 / 23.9; n = 250, 250 bases 42 / 33 / 32; n =
 // 442, 60 bases 60 / 39 / 33.  (C = 4, n = 40, 16 bases 37 with 256, which read C at run time, 33 with 1024.)
 int nb_threads(int T, int C, int64_t B, int num_cu) {
   const bool own = C == 2 || C == 3;   // C as a constant with any number of threads

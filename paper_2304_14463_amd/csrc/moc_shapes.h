@@ -215,15 +215,17 @@ inline BmLayout bm_layout(int T, int nt) {
 
 // Threads per base: a chain of short passes, which more waves shorten as long as a base feeds them and the bases
 // of a compute unit do not compete.  C = 2, R = 8, microseconds by 256 / 512 / 1024 threads
-// (before, with every field that could win scored: 256 to 1024 threads): n = 50, 1024 bases 19 / 28 / 53 (27); n = 442, 16 bases
-// 16.5 / 15.2 / 15.7 (26), 512 bases 22.5 / 20.2 / 29.6 (28), 1024 bases 22.7 / 28.4 / 50.4 (45), 4096 bases, R = 4 56 / 80 / 185 (114); n =
-// 1000, 300 bases 27.5 / 22.7 / 31.3 (43), 1024 bases 35.9 / 35.6 / 56.4 (72); n = 2000, 512 bases 50 / 34 / 41 (72); n = 2500, C = 3, 100
-// bases 79 / 51 / 38 (135), 600 bases 215 / 134 / 98 (342).
+// (before, with every field that could win scored: 256 to 1024 threads): n = 50, 1024 bases 18 / 26 / 49 (27); n = 442, 16 bases
+// 16.0 / 14.5 / 14.7 (25), 512 bases 19.4 / 17.5 / 26.1 (30), 1024 bases 20.2 / 26.7 / 47.4 (43), 4096 bases, R = 4 49 / 73 / 178 (114); n =
+// 1000, 300 bases - / 18.5 / 28.0 (48), 1024 bases - / 33.7 / 53.2 (72); n = 2000, 512 bases - / 27.9 / 37.4 (70).  C = 3: n = 300, 300
+// bases 17.0 / 15.4 / 23.9 (32), 1024 bases 19.2 / 27.9 / 45.0 (42); n = 600, 100 bases - / 17.6 / 16.3 (32); n = 2500, 100 bases - / 37.1 /
+// 28.5 (84), 600 bases - / 109 / 81 (223).  C = 4: n = 250, 300 bases 17.2 / 15.8 / 25.5 (40), 1024 bases 22.7 / 32.2 / 50.6 (57); n =
+// 1200, 300 bases - / 35.4 / 45.9 (87); n = 1500, 300 bases, two of which fit no compute unit, - / 63.7 / 52.2 (101).
 inline int best_threads(int T, int64_t B, int num_cu, int max_lds) {
   const int64_t share = (B + num_cu - 1) / num_cu;
   if (T <= 1024 && (share > 2 || T <= 256)) return 256;
   if (T <= 2048) return 512;
-  // two workgroups of 1024 do not fit a compute unit (80 registers a thread)
+  // two workgroups of 1024 do not fit a compute unit (80 to 92 registers a thread)
   return share > 1 && T <= 5000 && 2 * bm_layout(T, 512).bytes <= max_lds ? 512 : 1024;
 }
 
