@@ -271,7 +271,7 @@ __global__ __launch_bounds__(kNT) void eval_staged_general_kernel(GraphView g, c
 // stage's recomputed nodes up to its slot.  cur[j] holds, in the high bits, first the number of
 // distinct recomputed starts of stage j, then the offset of its bucket, then the end of the bucket;
 // bit 0 says whether the stage's own node starts there (it comes behind the bucket).
-// Bound by the vector ALU (68 %) and by the barriers between the passes.  n = 1000, C = 2, 16384 candidates: 208 us
+// Bound by the vector ALU (77 %) and by the barriers between the passes.  n = 1000, C = 2, 16384 candidates: 208 us
 // with every copy put into a bucket and searched for, correctly rounded square roots and the whole delta array
 // scanned; 131 us without these; 103 us with the wave scans and sums by lane shifts instead of the LDS crossbar; 98
 // us with predicates as lane masks and violations counted by the scalar unit, the further copies of a lane's nodes
